@@ -1,332 +1,235 @@
-// WHERE with stream compaction, single pass.
+// WHERE with stream compaction, in two kernels and no hand-off between
+// workgroups.
 //
-// Each workgroup takes a 4096-row tile (256 threads x 16 consecutive rows),
-// evaluates the predicate conjunction with wide vector loads and counts its
-// kept rows with a block scan.  A sparse tile stages its kept row ids in LDS
-// in ascending order; its output offset comes from a decoupled look-back over
-// the tiles before it, resolved while the workgroup's next tile is loading,
-// and the staged row ids, with the payload columns read through them, are
-// written at that offset by consecutive threads.  A dense tile resolves its
-// offset at once and writes each column through LDS.  Every predicate byte is
-// read once, payload only where rows are kept; output is written once, in
-// ascending row id order.
-#include "tqp_internal.hpp"
+// k_filter_mask streams the predicate columns: 8 consecutive rows per thread,
+// every column's loads issued before the first test, one keep bit per row
+// written (1/8 byte) and one kept count per block of rows.  k_filter_write
+// takes the blocks again: a block's output offset is the sum of the counts
+// before it (a few kilobytes, read from the caches), its kept rows are expanded
+// from the keep bits into a row list in LDS, in ascending order, and consecutive
+// threads write consecutive slots, reading the payload columns through the list.
+//
+// What bounds it: the read of the predicate columns, then the payload lines that
+// hold kept rows.  The version before this one was a single pass with a
+// decoupled look-back per 4096-row tile: every tile waited for a ticket, a
+// block scan and the look-back before its writes, and the next tile's loads
+// behind them.  20M int32 rows keeping 57%, row ids and one byte of payload:
+// 92 -> 20 + 45 us.  60M int64 rows keeping one in 84 with 13 bytes of payload
+// (beside another stream's work): 244 -> 112 + 64 us.
+#include "rowtest.hpp"
 
 namespace tqp {
 
 constexpr int kFilterNT = 256;
-constexpr int kFilterIPT = 16;
-constexpr int kFilterTile = kFilterNT * kFilterIPT;
+constexpr int kFilterIPT = 8;                            // rows per thread and step
+constexpr int kFilterTile = kFilterNT * kFilterIPT;      // rows per workgroup and step
+constexpr int kFilterMaxSteps = 8;                       // steps per block
 constexpr int kMaxPred = 8;
 constexpr int kMaxPay = 8;
 
-struct FilterArgs {
-    const void *pcol[kMaxPred];
-    int64_t plit[kMaxPred];
-    int32_t pdt[kMaxPred];
-    int32_t pop[kMaxPred];
-    int32_t pcolid[kMaxPred];
+// Steps (tiles) per block: the widest of 8, 4, 2, 1 that still gives sixteen
+// blocks per compute unit, so that both kernels have enough workgroups to hide
+// their memory latency and large tables keep the list of block counts short.
+static int filter_steps(int64_t n) {
+    int st = kFilterMaxSteps;
+    while (st > 1 && n < int64_t(kFilterTile) * st * 16 * kComputeUnits) st >>= 1;
+    return st;
+}
+
+// The kept-row masks of ND columns loaded together (ND = 0: one column after
+// another, for more than kMaxTogether).
+constexpr int kMaxTogether = 4;
+template <int ND>
+__device__ __forceinline__ void load_tile(const RowTests &t, int64_t row0, int64_t n, bool vec,
+                                          RawRows<kFilterIPT> (&v)[ND > 0 ? ND : 1]) {
+#pragma unroll
+    for (int c = 0; c < ND; c++) load_rawrows<kFilterIPT>(t.col[c], t.dt[c], row0, n, vec, v[c]);
+}
+template <int ND>
+__device__ __forceinline__ uint32_t test_tile(const RowTests &t, uint32_t mask,
+                                              const RawRows<kFilterIPT> (&v)[ND > 0 ? ND : 1]) {
+#pragma unroll
+    for (int c = 0; c < ND; c++) mask &= test_rows<kFilterIPT>(t, t.beg[c], t.beg[c + 1], t.dt[c], v[c]);
+    return mask;
+}
+template <int ND>
+__device__ __forceinline__ uint32_t keep_rows(const RowTests &t, int64_t row0, int64_t n, bool vec,
+                                              RawRows<kFilterIPT> (&v)[ND > 0 ? ND : 1]) {
+    uint32_t mask = row0 + kFilterIPT <= n ? 0xffu : row0 < n ? (1u << int(n - row0)) - 1u : 0u;
+    if constexpr (ND > 0) {
+        load_tile<ND>(t, row0, n, vec, v);
+        return test_tile<ND>(t, mask, v);
+    } else {
+        for (int c = 0; c < t.ncol; c++) {
+            load_rawrows<kFilterIPT>(t.col[c], t.dt[c], row0, n, vec, v[0]);
+            mask &= test_rows<kFilterIPT>(t, t.beg[c], t.beg[c + 1], t.dt[c], v[0]);
+        }
+        return mask;
+    }
+}
+
+// keep[row / 8] bit row % 8 and bcnt[block]; a block is `steps` tiles.  Rows
+// past n clear their bits, so every byte of a block is written.
+template <int ND>
+__global__ __launch_bounds__(kFilterNT) void k_filter_mask(RowTests t, int64_t n, int steps, int vec,
+                                                           int64_t nblocks, uint8_t *__restrict__ keep,
+                                                           int32_t *__restrict__ bcnt) {
+    constexpr int U = ND == 1 ? 2 : 1;          // tiles in flight per step
+    __shared__ int32_t s_cnt[kFilterNT / kWave];
+    for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        int32_t kept = 0;
+        for (int st = 0; st < steps; st += U) {
+            const int64_t unit = (b * steps + st) * kFilterNT + threadIdx.x;   // 8 rows each
+            RawRows<kFilterIPT> v[U][ND > 0 ? ND : 1];
+            if (U == 2 && st + 1 < steps && vec && (b * steps + st + 2) * kFilterTile <= n) {
+                // two whole tiles: both tiles' loads go out before the first test
+                uint32_t m[U];
+                load_tile<ND>(t, unit * kFilterIPT, n, true, v[0]);
+                load_tile<ND>(t, (unit + kFilterNT) * kFilterIPT, n, true, v[U - 1]);
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    m[u] = test_tile<ND>(t, 0xffu, v[u]);
+                    keep[unit + u * kFilterNT] = uint8_t(m[u]);
+                    kept += __popc(m[u]);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < U; u++) {
+                    if (st + u >= steps) break;
+                    const int64_t x = unit + u * kFilterNT;
+                    const uint32_t m = keep_rows<ND>(t, x * kFilterIPT, n, vec != 0, v[u]);
+                    keep[x] = uint8_t(m);
+                    kept += __popc(m);
+                }
+            }
+        }
+        kept = wave_sum(kept);
+        if (lane_id() == 0) s_cnt[wave_id()] = kept;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int32_t tot = 0;
+#pragma unroll
+            for (int w = 0; w < kFilterNT / kWave; w++) tot += s_cnt[w];
+            bcnt[b] = tot;
+        }
+        __syncthreads();
+    }
+}
+
+struct FilterOut {
     const void *pin[kMaxPay];
     void *pout[kMaxPay];
     int32_t paydt[kMaxPay];
-    int32_t npred;
     int32_t npay;
-    int32_t vec;          // every column base is 16-byte aligned
     int32_t *out_rows;
     int64_t *d_count;
-    int64_t n;
-    uint32_t *ticket;
-    uint64_t *status;
 };
 
-// Loads 16 consecutive elements starting at row0 (sign-extended to int64).
-__device__ __forceinline__ void load16(const void *p, int dt, int64_t row0, int64_t n,
-                                       bool vec, int64_t (&v)[16]) {
-    if (vec && row0 + 16 <= n) {
-        if (dt == TQP_INT8) {
-            int4 x = *reinterpret_cast<const int4 *>(static_cast<const int8_t *>(p) + row0);
-            const int w[4] = {x.x, x.y, x.z, x.w};
+// Each thread expands steps * 8 keep bits; then kWriteU list entries per thread
+// and pass.  The payload goes out in groups of NP columns (all of them when
+// there are at most four): a group's loads, aligned words whatever the dtype, are
+// all issued before its first store.
+constexpr int kWriteU = 4;
+template <class T, int NP>
+__device__ __forceinline__ void write_col(void *out, const void *in, int lg, int64_t slot, int c,
+                                          const int32_t (&row)[kWriteU],
+                                          const uint64_t (&w)[kWriteU][NP > 0 ? NP : 1]) {
+    T *o = static_cast<T *>(out) + slot;
 #pragma unroll
-            for (int r = 0; r < 16; r++)
-                v[r] = static_cast<int8_t>(static_cast<uint32_t>(w[r >> 2]) >> (8 * (r & 3)));
-        } else if (dt == TQP_INT32) {
-            const int4 *q = reinterpret_cast<const int4 *>(static_cast<const int32_t *>(p) + row0);
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                int4 x = q[k];
-                v[4 * k + 0] = x.x;
-                v[4 * k + 1] = x.y;
-                v[4 * k + 2] = x.z;
-                v[4 * k + 3] = x.w;
-            }
-        } else {
-            const longlong2 *q =
-                reinterpret_cast<const longlong2 *>(static_cast<const int64_t *>(p) + row0);
-#pragma unroll
-            for (int k = 0; k < 8; k++) {
-                longlong2 x = q[k];
-                v[2 * k + 0] = x.x;
-                v[2 * k + 1] = x.y;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < 16; r++)
-            v[r] = (row0 + r < n) ? load_any(p, dt, row0 + r) : 0;
-    }
+    for (int u = 0; u < kWriteU; u++)
+        if (row[u] >= 0) o[u * kFilterNT] = T(from_word(w[u][c], in, lg, row[u]));
 }
 
-// Loads 8 consecutive elements starting at row0 (sign-extended to int64).
-__device__ __forceinline__ void load8(const void *p, int dt, int64_t row0, int64_t n, bool vec,
-                                      int64_t (&v)[8]) {
-    if (vec && row0 + 8 <= n) {
-        if (dt == TQP_INT8) {
-            int2 x = *reinterpret_cast<const int2 *>(static_cast<const int8_t *>(p) + row0);
-            const int w[2] = {x.x, x.y};
-#pragma unroll
-            for (int r = 0; r < 8; r++)
-                v[r] = static_cast<int8_t>(static_cast<uint32_t>(w[r >> 2]) >> (8 * (r & 3)));
-        } else if (dt == TQP_INT32) {
-            const int4 *q = reinterpret_cast<const int4 *>(static_cast<const int32_t *>(p) + row0);
-#pragma unroll
-            for (int k = 0; k < 2; k++) {
-                int4 x = q[k];
-                v[4 * k + 0] = x.x;
-                v[4 * k + 1] = x.y;
-                v[4 * k + 2] = x.z;
-                v[4 * k + 3] = x.w;
-            }
-        } else {
-            const longlong2 *q =
-                reinterpret_cast<const longlong2 *>(static_cast<const int64_t *>(p) + row0);
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                longlong2 x = q[k];
-                v[2 * k + 0] = x.x;
-                v[2 * k + 1] = x.y;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < 8; r++)
-            v[r] = (row0 + r < n) ? load_any(p, dt, row0 + r) : 0;
-    }
-}
-
-// Element v (zero-extended) of a column of element size 1 << lg, stored at i.
-__device__ __forceinline__ void store_lg(void *out, int lg, int64_t i, uint64_t v) {
-    if (lg == 0) static_cast<uint8_t *>(out)[i] = uint8_t(v);
-    else if (lg == 2) static_cast<uint32_t *>(out)[i] = uint32_t(v);
-    else static_cast<uint64_t *>(out)[i] = v;
-}
-
-// Writes a staged tile's kept rows from slot base on: the row ids, then
-// every payload column read through them, consecutive threads taking
-// consecutive slots (so the writes are coalesced, and so are the payload
-// reads where the kept rows are dense).  Each thread takes kWriteU slots per
-// pass with every column's loads issued before the first store, so a dense
-// tile costs few memory round trips.  The staging writes and the prefix in
-// LDS must be visible: callers come here after a barrier that follows both.
-constexpr int kWriteU = 2;
-__device__ __forceinline__ void filter_write_staged(const FilterArgs &a, const int32_t *srow,
-                                                    int64_t base, int cnt, bool last_tile) {
-    if (last_tile && threadIdx.x == 0) *a.d_count = base + cnt;
-    int lg[kMaxPay];
-#pragma unroll
-    for (int c = 0; c < kMaxPay; c++) lg[c] = c < a.npay ? dtype_lg(a.paydt[c]) : 0;
-    for (int i0 = threadIdx.x; i0 < cnt; i0 += kWriteU * kFilterNT) {
-        int32_t row[kWriteU];
-#pragma unroll
-        for (int u = 0; u < kWriteU; u++) {
-            const int i = i0 + u * kFilterNT;
-            row[u] = i < cnt ? srow[i] : -1;
-        }
-        uint64_t w[kWriteU][kMaxPay];
-#pragma unroll
-        for (int c = 0; c < kMaxPay; c++)
-#pragma unroll
-            for (int u = 0; u < kWriteU; u++)
-                if (c < a.npay && row[u] >= 0) w[u][c] = word_of(a.pin[c], lg[c], row[u]);
-#pragma unroll
-        for (int u = 0; u < kWriteU; u++) {
-            if (row[u] < 0) continue;
-            const int64_t slot = base + i0 + u * kFilterNT;
-            if (a.out_rows) a.out_rows[slot] = row[u];
-#pragma unroll
-            for (int c = 0; c < kMaxPay; c++)
-                if (c < a.npay) store_lg(a.pout[c], lg[c], slot, from_word(w[u][c], a.pin[c], lg[c], row[u]));
-        }
-    }
-}
-
-// A tile keeping at most this many rows defers its look-back and writes
-// (its row ids wait in LDS); a denser one resolves its offset at once and
-// writes each column from LDS, where a column's values are staged straight
-// from its vector loads.
-constexpr int kFilterDefer = 1024;
-
-__global__ __launch_bounds__(kFilterNT) void k_filter(FilterArgs a) {
-    __shared__ int64_t s_tile;
-    __shared__ int64_t s_prefix, s_pprefix;
+template <int NP>
+__global__ __launch_bounds__(kFilterNT) void k_filter_write(FilterOut a, int steps, int64_t nblocks,
+                                                            const uint8_t *__restrict__ keep,
+                                                            const int32_t *__restrict__ bcnt) {
+    extern __shared__ uint16_t s_list[];         // steps * kFilterTile entries
     __shared__ int32_t s_scan[kFilterNT / kWave];
-    // Two buffers of a tile's kept row ids (ascending): one filled by the
-    // current tile while the previous tile's rows are written from the
-    // other.  A dense tile uses the whole array for one column at a time.
-    __shared__ int64_t s_stage[kFilterTile];
-    int32_t *const s_rows = reinterpret_cast<int32_t *>(s_stage);
-
-    const int64_t n = a.n;
-    const int64_t ntiles = ceil_div(n, kFilterTile);
-    const bool vec = a.vec != 0;
-    int64_t pend_tile = -1;      // the tile whose kept rows wait in LDS
-    int pend_total = 0, pb = 0;
-    // Persistent workgroups: each takes tiles in ticket order until none are
-    // left.  A sparse tile publishes its count as soon as it is known; its
-    // prefix is resolved while the workgroup's next tile is being loaded, and
-    // its rows are written after that tile's scan.
-    for (;;) {
-        const int64_t tile = take_tile(a.ticket, &s_tile);
-        const bool last = tile >= ntiles;
-        if (last && tile == 0 && threadIdx.x == 0) *a.d_count = 0;   // empty input
-        const int64_t row0 = tile * kFilterTile + int64_t(threadIdx.x) * kFilterIPT;
-        int64_t v[16];
-        if (!last) load16(a.pcol[0], a.pdt[0], row0, n, vec, v);
-        if (pend_tile >= 0 && wave_id() == 0) {
-            const int64_t pre = lookback_resolve(a.status, pend_tile, pend_total);
-            if (lane_id() == 0) s_pprefix = pre;
-        }
-        uint32_t mask = 0;
-        int32_t total = 0, excl = 0;
-        bool defer = true;
-        int cb = pb;
-        if (!last) {       // (uniform across the workgroup)
+    __shared__ int64_t s_sum[kFilterNT / kWave];
+    if (nblocks == 0 && threadIdx.x == 0) *a.d_count = 0;
+    int64_t base = 0, from = 0;                  // kept rows of the blocks before `from`
+    for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        const int64_t unit = b * kFilterNT + threadIdx.x;
+        uint64_t bits;
+        if (steps == 8) bits = reinterpret_cast<const uint64_t *>(keep)[unit];
+        else if (steps == 4) bits = reinterpret_cast<const uint32_t *>(keep)[unit];
+        else if (steps == 2) bits = reinterpret_cast<const uint16_t *>(keep)[unit];
+        else bits = keep[unit];
+        int64_t part = 0;
+#pragma unroll 4
+        for (int64_t i = from + threadIdx.x; i < b; i += kFilterNT) part += bcnt[i];
+        part = wave_sum(part);
+        if (lane_id() == 0) s_sum[wave_id()] = part;
+        int32_t total;
+        int q = block_excl_scan<kFilterNT>(int32_t(__popcll(bits)), &total, s_scan);
 #pragma unroll
-            for (int r = 0; r < 16; r++)
-                if (row0 + r < n) mask |= 1u << r;
-            int loaded = a.pcolid[0];
-            for (int p = 0; p < a.npred; p++) {
-                if (a.pcolid[p] != loaded) {
-                    load16(a.pcol[p], a.pdt[p], row0, n, vec, v);
-                    loaded = a.pcolid[p];
-                }
-                const int op = a.pop[p];
-                const int64_t lit = a.plit[p];
-                uint32_t m = 0;
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    if (cmp_holds(v[r], op, lit)) m |= 1u << r;
-                mask &= m;
-            }
-            excl = block_excl_scan<kFilterNT>(int32_t(__popc(mask)), &total, s_scan);
-            defer = total <= kFilterDefer;
-            if (defer) {
-                if (wave_id() == 0) lookback_publish(a.status, tile, total);
-                cb = pend_tile >= 0 ? pb ^ 1 : pb;
-                int32_t *st = s_rows + cb * kFilterTile;
-                int q = excl;
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    if (mask & (1u << r)) st[q++] = static_cast<int32_t>(row0 + r);
-            } else if (wave_id() == 0) {
-                // dense tile: its offset now
-                const int64_t pre = lookback_count(a.status, tile, total);
-                if (lane_id() == 0) s_prefix = pre;
-            }
-        } else {
-            __syncthreads();     // s_pprefix
+        for (int w = 0; w < kFilterNT / kWave; w++) base += s_sum[w];
+        from = b;
+        if (b == nblocks - 1 && threadIdx.x == 0) *a.d_count = base + total;
+        const int first = int(threadIdx.x) * steps * kFilterIPT;
+        while (bits) {
+            s_list[q++] = uint16_t(first + __builtin_ctzll(bits));
+            bits &= bits - 1;
         }
-        if (pend_tile >= 0)
-            filter_write_staged(a, s_rows + pb * kFilterTile, s_pprefix, pend_total,
-                                pend_tile == ntiles - 1);
-        if (last) break;
-        if (defer) {
-            pend_tile = tile;
-            pend_total = total;
-            pb = cb;
-            continue;
-        }
-
-        // dense tile, with the pending tile's rows out: every column through LDS
-        pend_tile = -1;
         __syncthreads();
-        const int64_t base = s_prefix;
-        if (tile == ntiles - 1 && threadIdx.x == 0) *a.d_count = base + total;
-        // each output column goes through LDS in kept order, then out with
-        // consecutive threads on consecutive addresses
-        if (a.out_rows) {
-            int q = excl;
+        const int64_t row0 = b * steps * kFilterTile;
+        for (int i0 = threadIdx.x; i0 < total; i0 += kWriteU * kFilterNT) {
+            const int64_t slot = base + i0;
+            int32_t row[kWriteU];
 #pragma unroll
-            for (int r = 0; r < 16; r++)
-                if (mask & (1u << r)) s_rows[q++] = static_cast<int32_t>(row0 + r);
-            __syncthreads();
-            for (int i = threadIdx.x; i < total; i += kFilterNT) a.out_rows[base + i] = s_rows[i];
-            __syncthreads();
-        }
-        for (int c = 0; c < a.npay; c++) {
-            const int dt = a.paydt[c];
-            // only threads with kept rows read the column (v is overwritten
-            // either way, so the predicate values are dead by now)
-            if (mask) {
-                load16(a.pin[c], dt, row0, n, vec, v);
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; r++) v[r] = 0;
+            for (int u = 0; u < kWriteU; u++) {
+                const int i = i0 + u * kFilterNT;
+                row[u] = i < total ? int32_t(row0 + s_list[i]) : -1;
             }
-            int q = excl;
-            if (dt == TQP_INT8) {
-                int8_t *st = reinterpret_cast<int8_t *>(s_stage);
+            if (a.out_rows) {
 #pragma unroll
-                for (int r = 0; r < 16; r++)
-                    if (mask & (1u << r)) st[q++] = static_cast<int8_t>(v[r]);
-                __syncthreads();
-                int8_t *out = static_cast<int8_t *>(a.pout[c]);
-                for (int i = threadIdx.x; i < total; i += kFilterNT) out[base + i] = st[i];
-            } else if (dt == TQP_INT32) {
-                int32_t *st = reinterpret_cast<int32_t *>(s_stage);
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    if (mask & (1u << r)) st[q++] = static_cast<int32_t>(v[r]);
-                __syncthreads();
-                int32_t *out = static_cast<int32_t *>(a.pout[c]);
-                for (int i = threadIdx.x; i < total; i += kFilterNT) out[base + i] = st[i];
-            } else {
-                int64_t *st = s_stage;
-#pragma unroll
-                for (int r = 0; r < 16; r++)
-                    if (mask & (1u << r)) st[q++] = v[r];
-                __syncthreads();
-                int64_t *out = static_cast<int64_t *>(a.pout[c]);
-                for (int i = threadIdx.x; i < total; i += kFilterNT) out[base + i] = st[i];
+                for (int u = 0; u < kWriteU; u++)
+                    if (row[u] >= 0) a.out_rows[slot + u * kFilterNT] = row[u];
             }
-            __syncthreads();
+            if constexpr (NP > 0) {
+                for (int g = 0; g < a.npay; g += NP) {
+                    uint64_t w[kWriteU][NP];
+#pragma unroll
+                    for (int c = 0; c < NP; c++) {
+                        if (g + c >= a.npay) break;
+                        const int lg = dtype_lg(a.paydt[g + c]);
+#pragma unroll
+                        for (int u = 0; u < kWriteU; u++)
+                            w[u][c] = word_of(a.pin[g + c], lg, row[u] >= 0 ? row[u] : row[0]);
+                    }
+#pragma unroll
+                    for (int c = 0; c < NP; c++) {
+                        if (g + c >= a.npay) break;
+                        const int lg = dtype_lg(a.paydt[g + c]);
+                        void *out = a.pout[g + c];
+                        const void *in = a.pin[g + c];
+                        if (lg == 0) write_col<uint8_t, NP>(out, in, 0, slot, c, row, w);
+                        else if (lg == 2) write_col<uint32_t, NP>(out, in, 2, slot, c, row, w);
+                        else write_col<uint64_t, NP>(out, in, 3, slot, c, row, w);
+                    }
+                }
+            }
         }
+        __syncthreads();                         // the list is reused
     }
 }
 
-// WHERE + aggregate without compaction: the predicate pass of k_filter (8
-// consecutive rows per thread here, which halves the registers a column
-// takes and doubles the loads in flight), then SUM(a * b) and COUNT over the
-// kept rows.  The predicates come grouped by column; with at most
-// kSumMaxCols distinct columns, every column of a tile is loaded before the
-// first test (one memory round trip per tile instead of one per column), and
-// a value operand that is also a predicate column is taken from those loads.
-// Other value columns are read only by threads holding a kept row, so at low
+// WHERE + aggregate without compaction: the predicate pass of k_filter_mask, then
+// SUM(a * b) and COUNT over the kept rows.  A value operand that is also one of
+// the (at most kMaxTogether) columns loaded together is taken from those loads;
+// other value columns are read only by threads holding a kept row, so at low
 // selectivity most of their cache lines are never fetched.  Partial sums are
-// reduced per workgroup and added with one device atomic each; int64
-// addition wraps modulo 2^64, so every order gives the same bytes.
-constexpr int kSumMaxCols = 4;
+// reduced per workgroup and added with one device atomic each; int64 addition
+// wraps modulo 2^64, so every order gives the same bytes.
+//
+// What bounds it: the read of the predicate columns.  60M rows of 8 + 4 + 1 bytes
+// keeping 1.8%: 241 -> 168 us (4.7 TB/s of those bytes; a plain read of them takes
+// 125 us) against the version that converted each column to 64 bits as it was
+// loaded, which made every column wait for the one before it.
 struct FilterSumArgs {
-    const void *pcol[kMaxPred];      // per predicate, grouped by column
-    int64_t plit[kMaxPred];
-    int32_t pdt[kMaxPred];
-    int32_t pop[kMaxPred];
-    int32_t pcolid[kMaxPred];
-    int32_t npred;
+    RowTests t;
     int32_t vec;
-    const void *dcol[kMaxPred];      // the distinct predicate columns
-    int32_t ddt[kMaxPred];
-    int32_t pbeg[kMaxPred + 1];      // column d's predicates: pbeg[d] .. pbeg[d + 1] - 1
-    int32_t nd;
     int32_t aslot, bslot;            // the distinct column that a / b is, or -1
     const void *a;        // null: the sum is 0
     const void *b;        // null: SUM(a)
@@ -343,103 +246,47 @@ __global__ void k_zero2(unsigned long long *p, unsigned long long *q) {
     }
 }
 
-constexpr int kSumIPT = 8;
-constexpr int kSumTile = kFilterNT * kSumIPT;
+// ND distinct predicate columns (1 .. kMaxTogether) loaded together; ND = 0:
+// one after another (or none).
+template <int ND>
+__device__ __forceinline__ void sum_operand(const FilterSumArgs &f, int slot, const void *p, int dt,
+                                            int64_t row0, const RawRows<kFilterIPT> (&v)[ND > 0 ? ND : 1],
+                                            int64_t (&x)[kFilterIPT]) {
+    if constexpr (ND > 0) {
+        if (slot >= 0) {
+#pragma unroll
+            for (int c = 0; c < ND; c++)
+                if (c == slot) raw_values<kFilterIPT>(v[c], dt, x);
+            return;
+        }
+    }
+    RawRows<kFilterIPT> r;
+    load_rawrows<kFilterIPT>(p, dt, row0, f.n, f.vec != 0, r);
+    raw_values<kFilterIPT>(r, dt, x);
+}
 
-// ND distinct predicate columns (1 .. kSumMaxCols) loaded together; ND = 0:
-// each column loaded when its first predicate is reached.
 template <int ND>
 __global__ __launch_bounds__(kFilterNT) void k_filter_sum(FilterSumArgs f) {
     __shared__ unsigned long long s_red[2][kFilterNT / kWave];
-    const int64_t n = f.n;
-    const int64_t ntiles = ceil_div(n, kSumTile);
-    const bool vec = f.vec != 0;
+    const int64_t ntiles = ceil_div(f.n, kFilterTile);
     uint64_t sum = 0, cnt = 0;
     for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int64_t row0 = tile * kSumTile + int64_t(threadIdx.x) * kSumIPT;
-        uint32_t mask = 0;
-#pragma unroll
-        for (int r = 0; r < kSumIPT; r++)
-            if (row0 + r < n) mask |= 1u << r;
-        if constexpr (ND > 0) {
-            int64_t d[ND][kSumIPT];
-#pragma unroll
-            for (int c = 0; c < ND; c++) load8(f.dcol[c], f.ddt[c], row0, n, vec, d[c]);
-#pragma unroll
-            for (int c = 0; c < ND; c++) {
-                for (int p = f.pbeg[c]; p < f.pbeg[c + 1]; p++) {
-                    const int op = f.pop[p];
-                    const int64_t lit = f.plit[p];
-                    uint32_t m = 0;
-#pragma unroll
-                    for (int r = 0; r < kSumIPT; r++)
-                        if (cmp_holds(d[c][r], op, lit)) m |= 1u << r;
-                    mask &= m;
-                }
-            }
-            cnt += __popc(mask);
-            if (mask && f.a) {
-                int64_t x[kSumIPT], y[kSumIPT];
-                if (f.aslot >= 0) {
-#pragma unroll
-                    for (int c = 0; c < ND; c++)
-                        if (c == f.aslot) {
-#pragma unroll
-                            for (int r = 0; r < kSumIPT; r++) x[r] = d[c][r];
-                        }
-                } else {
-                    load8(f.a, f.adt, row0, n, vec, x);
-                }
-                if (f.b) {
-                    if (f.bslot >= 0) {
-#pragma unroll
-                        for (int c = 0; c < ND; c++)
-                            if (c == f.bslot) {
-#pragma unroll
-                                for (int r = 0; r < kSumIPT; r++) y[r] = d[c][r];
-                            }
-                    } else {
-                        load8(f.b, f.bdt, row0, n, vec, y);
-                    }
-#pragma unroll
-                    for (int r = 0; r < kSumIPT; r++)
-                        if (mask & (1u << r)) sum += uint64_t(x[r]) * uint64_t(y[r]);
-                } else {
-#pragma unroll
-                    for (int r = 0; r < kSumIPT; r++)
-                        if (mask & (1u << r)) sum += uint64_t(x[r]);
-                }
-            }
-            continue;
-        }
-        int64_t v[kSumIPT];
-        int loaded = -1;
-        for (int p = 0; p < f.npred; p++) {
-            if (f.pcolid[p] != loaded) {
-                load8(f.pcol[p], f.pdt[p], row0, n, vec, v);
-                loaded = f.pcolid[p];
-            }
-            const int op = f.pop[p];
-            const int64_t lit = f.plit[p];
-            uint32_t m = 0;
-#pragma unroll
-            for (int r = 0; r < kSumIPT; r++)
-                if (cmp_holds(v[r], op, lit)) m |= 1u << r;
-            mask &= m;
-        }
+        const int64_t row0 = tile * kFilterTile + int64_t(threadIdx.x) * kFilterIPT;
+        RawRows<kFilterIPT> v[ND > 0 ? ND : 1];
+        const uint32_t mask = keep_rows<ND>(f.t, row0, f.n, f.vec != 0, v);
         cnt += __popc(mask);
         if (mask && f.a) {
-            int64_t x[kSumIPT];
-            load8(f.a, f.adt, row0, n, vec, x);
+            int64_t x[kFilterIPT];
+            sum_operand<ND>(f, f.aslot, f.a, f.adt, row0, v, x);
             if (f.b) {
-                load8(f.b, f.bdt, row0, n, vec, v);
+                int64_t y[kFilterIPT];
+                sum_operand<ND>(f, f.bslot, f.b, f.bdt, row0, v, y);
 #pragma unroll
-                for (int r = 0; r < kSumIPT; r++)
-                    if (mask & (1u << r)) sum += uint64_t(x[r]) * uint64_t(v[r]);
+                for (int r = 0; r < kFilterIPT; r++)
+                    sum += mask & (1u << r) ? uint64_t(x[r]) * uint64_t(y[r]) : 0;
             } else {
 #pragma unroll
-                for (int r = 0; r < kSumIPT; r++)
-                    if (mask & (1u << r)) sum += uint64_t(x[r]);
+                for (int r = 0; r < kFilterIPT; r++) sum += mask & (1u << r) ? uint64_t(x[r]) : 0;
             }
         }
     }
@@ -468,7 +315,7 @@ __global__ __launch_bounds__(kFilterNT) void k_filter_sum(FilterSumArgs f) {
 // late-starting workgroups would each still take a full share of tiles.
 template <class Kern>
 static int launch_filter_sum(Kern kern, int nd, int64_t n, hipStream_t s, const FilterSumArgs &f) {
-    static int resident[kSumMaxCols + 1] = {};
+    static int resident[kMaxTogether + 1] = {};
     if (resident[nd] == 0) {
         int per_cu = 0;
         if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kern),
@@ -478,22 +325,48 @@ static int launch_filter_sum(Kern kern, int nd, int64_t n, hipStream_t s, const 
     }
     int per_cu = 2 * tune(kTuneFilterPerCu);
     if (per_cu > resident[nd]) per_cu = resident[nd];
-    const unsigned grid = persistent_grid(ceil_div(n, kSumTile), per_cu);
+    const unsigned grid = persistent_grid(ceil_div(n, kFilterTile), per_cu);
     TQP_LAUNCH("filter_sum", kern, dim3(grid), dim3(kFilterNT), 0, s, f);
     return check_launch("tqp_filter_sum");
 }
 
-static size_t filter_ws(int64_t n) {
-    Carver c(nullptr);
-    c.take<uint64_t>(1 + (n > 0 ? ceil_div(n, kFilterTile) : 1));
-    return c.bytes();
+struct FilterLayout {
+    int steps;
+    int64_t nblocks;
+    uint8_t *keep;
+    int32_t *bcnt;
+    size_t bytes;
+};
+
+static FilterLayout filter_layout(void *ws, int64_t n) {
+    FilterLayout L = {};
+    Carver c(ws);
+    L.steps = filter_steps(n);
+    L.nblocks = ceil_div(n, int64_t(kFilterTile) * L.steps);
+    L.keep = c.take<uint8_t>(size_t(L.nblocks) * kFilterNT * L.steps);
+    L.bcnt = c.take<int32_t>(size_t(L.nblocks > 0 ? L.nblocks : 1));
+    L.bytes = c.bytes();
+    return L;
+}
+
+template <int ND>
+static void launch_filter_mask(unsigned grid, hipStream_t s, const RowTests &t, int64_t n, bool vec,
+                               const FilterLayout &L) {
+    TQP_LAUNCH("filter_mask", k_filter_mask<ND>, dim3(grid), dim3(kFilterNT), 0, s, t, n, L.steps,
+               vec ? 1 : 0, L.nblocks, L.keep, L.bcnt);
+}
+
+template <int NP>
+static void launch_filter_write(unsigned grid, hipStream_t s, const FilterOut &a, const FilterLayout &L) {
+    TQP_LAUNCH("filter", k_filter_write<NP>, dim3(grid), dim3(kFilterNT),
+               size_t(L.steps) * kFilterTile * sizeof(uint16_t), s, a, L.steps, L.nblocks, L.keep, L.bcnt);
 }
 
 }  // namespace tqp
 
 using namespace tqp;
 
-TQP_API size_t tqp_filter_workspace_bytes(int64_t n) { return filter_ws(n < 0 ? 0 : n); }
+TQP_API size_t tqp_filter_workspace_bytes(int64_t n) { return filter_layout(nullptr, n < 0 ? 0 : n).bytes; }
 
 TQP_API int tqp_filter(const tqp_col *cols, int ncols, const tqp_pred *preds, int npred,
                        const tqp_col *pay_in, const tqp_col *pay_out, int npay,
@@ -509,7 +382,7 @@ TQP_API int tqp_filter(const tqp_col *cols, int ncols, const tqp_pred *preds, in
     if (!d_count) return set_error(TQP_EINVAL, "tqp_filter: d_count is required");
     const int64_t n = cols[0].len;
     if (n < 0 || n > INT32_MAX) return set_error(TQP_EINVAL, "tqp_filter: bad row count %lld", (long long)n);
-    FilterArgs a = {};
+    FilterOut a = {};
     bool vec = true;
     for (int c = 0; c < ncols; c++) {
         if (!dtype_ok(cols[c].dtype) || cols[c].len != n || (n > 0 && !cols[c].data))
@@ -518,15 +391,9 @@ TQP_API int tqp_filter(const tqp_col *cols, int ncols, const tqp_pred *preds, in
             return set_error(TQP_EINVAL, "tqp_filter: column %d is unaligned", c);
         vec = vec && (reinterpret_cast<uintptr_t>(cols[c].data) % 16 == 0);
     }
-    for (int p = 0; p < npred; p++) {
+    for (int p = 0; p < npred; p++)
         if (preds[p].col < 0 || preds[p].col >= ncols || preds[p].op < TQP_LT || preds[p].op > TQP_NE)
             return set_error(TQP_EINVAL, "tqp_filter: predicate %d is invalid", p);
-        a.pcol[p] = cols[preds[p].col].data;
-        a.pdt[p] = cols[preds[p].col].dtype;
-        a.pcolid[p] = preds[p].col;
-        a.pop[p] = preds[p].op;
-        a.plit[p] = preds[p].literal;
-    }
     for (int c = 0; c < npay; c++) {
         if (!dtype_ok(pay_in[c].dtype) || pay_in[c].dtype != pay_out[c].dtype ||
             pay_in[c].len != n || pay_out[c].len < n || (n > 0 && (!pay_in[c].data || !pay_out[c].data)))
@@ -534,30 +401,40 @@ TQP_API int tqp_filter(const tqp_col *cols, int ncols, const tqp_pred *preds, in
         // (kept rows' payload is read as the aligned 8-byte word holding it)
         if (!col_aligned(pay_in[c].data, pay_in[c].dtype) || !col_aligned(pay_out[c].data, pay_out[c].dtype))
             return set_error(TQP_EINVAL, "tqp_filter: payload %d is unaligned", c);
-        vec = vec && (reinterpret_cast<uintptr_t>(pay_in[c].data) % 16 == 0);
         a.pin[c] = pay_in[c].data;
         a.pout[c] = pay_out[c].data;
         a.paydt[c] = pay_in[c].dtype;
     }
-    const size_t need = filter_ws(n);
-    if (!ws || ws_bytes < need)
-        return set_error(TQP_ECAPACITY, "tqp_filter: workspace needs %zu bytes", need);
-    hipStream_t s = as_stream(stream);
-    Carver cv(ws);
-    const int64_t ntiles = ceil_div(n, kFilterTile);
-    uint64_t *words = cv.take<uint64_t>(1 + (ntiles > 0 ? ntiles : 1));
-    int rc = fill_u64(words, 0, 1 + (ntiles > 0 ? ntiles : 1), s);
-    if (rc) return rc;
-    a.npred = npred;
+    FilterLayout L = filter_layout(nullptr, n);
+    if (!ws || ws_bytes < L.bytes)
+        return set_error(TQP_ECAPACITY, "tqp_filter: workspace needs %zu bytes", L.bytes);
+    L = filter_layout(ws, n);
+    RowTests t;
+    build_tests(cols, preds, npred, &t);
     a.npay = npay;
-    a.vec = vec ? 1 : 0;
     a.out_rows = out_rows;
     a.d_count = d_count;
-    a.n = n;
-    a.ticket = reinterpret_cast<uint32_t *>(words);
-    a.status = words + 1;
-    const unsigned grid = persistent_grid(ntiles, tune(kTuneFilterPerCu));
-    TQP_LAUNCH("filter", k_filter, dim3(grid), dim3(kFilterNT), 0, s, a);
+    hipStream_t s = as_stream(stream);
+    if (n > 0) {
+        const unsigned grid = persistent_grid(L.nblocks, 2 * tune(kTuneFilterPerCu));
+        switch (t.ncol <= kMaxTogether ? t.ncol : 0) {
+        case 1: launch_filter_mask<1>(grid, s, t, n, vec, L); break;
+        case 2: launch_filter_mask<2>(grid, s, t, n, vec, L); break;
+        case 3: launch_filter_mask<3>(grid, s, t, n, vec, L); break;
+        case 4: launch_filter_mask<4>(grid, s, t, n, vec, L); break;
+        default: launch_filter_mask<0>(grid, s, t, n, vec, L); break;
+        }
+        const int rc = check_launch("tqp_filter");
+        if (rc) return rc;
+    }
+    const unsigned grid = persistent_grid(L.nblocks, 8);
+    switch (npay < 4 ? npay : 4) {
+    case 0: launch_filter_write<0>(grid, s, a, L); break;
+    case 1: launch_filter_write<1>(grid, s, a, L); break;
+    case 2: launch_filter_write<2>(grid, s, a, L); break;
+    case 3: launch_filter_write<3>(grid, s, a, L); break;
+    default: launch_filter_write<4>(grid, s, a, L); break;
+    }
     return check_launch("tqp_filter");
 }
 
@@ -584,30 +461,7 @@ TQP_API int tqp_filter_sum(const tqp_col *cols, int ncols, const tqp_pred *preds
     for (int p = 0; p < npred; p++)
         if (preds[p].col < 0 || preds[p].col >= ncols || preds[p].op < TQP_LT || preds[p].op > TQP_NE)
             return set_error(TQP_EINVAL, "tqp_filter_sum: predicate %d is invalid", p);
-    // predicates grouped by column, columns in order of first use (a
-    // conjunction does not depend on the order of its terms)
-    int np = 0;
-    f.nd = 0;
-    for (int p = 0; p < npred; p++) {
-        const int col = preds[p].col;
-        bool seen = false;
-        for (int q = 0; q < p; q++) seen = seen || preds[q].col == col;
-        if (seen) continue;
-        f.dcol[f.nd] = cols[col].data;
-        f.ddt[f.nd] = cols[col].dtype;
-        f.pbeg[f.nd] = np;
-        f.nd++;
-        for (int q = p; q < npred; q++) {
-            if (preds[q].col != col) continue;
-            f.pcol[np] = cols[col].data;
-            f.pdt[np] = cols[col].dtype;
-            f.pcolid[np] = col;
-            f.pop[np] = preds[q].op;
-            f.plit[np] = preds[q].literal;
-            np++;
-        }
-    }
-    f.pbeg[f.nd] = np;
+    build_tests(cols, preds, npred, &f.t);
     const tqp_col *vals[2] = {a, b};
     for (int k = 0; k < 2; k++) {
         const tqp_col *v = vals[k];
@@ -617,7 +471,6 @@ TQP_API int tqp_filter_sum(const tqp_col *cols, int ncols, const tqp_pred *preds
                              k ? 'b' : 'a');
         vec = vec && (reinterpret_cast<uintptr_t>(v->data) % 16 == 0);
     }
-    f.npred = npred;
     f.vec = vec ? 1 : 0;
     f.a = a ? a->data : nullptr;
     f.b = b ? b->data : nullptr;
@@ -625,9 +478,9 @@ TQP_API int tqp_filter_sum(const tqp_col *cols, int ncols, const tqp_pred *preds
     f.bdt = b ? b->dtype : 0;
     // a value operand that is one of the loaded predicate columns
     f.aslot = f.bslot = -1;
-    for (int c = 0; c < f.nd; c++) {
-        if (a && f.aslot < 0 && f.dcol[c] == a->data && f.ddt[c] == a->dtype) f.aslot = c;
-        if (b && f.bslot < 0 && f.dcol[c] == b->data && f.ddt[c] == b->dtype) f.bslot = c;
+    for (int c = 0; c < f.t.ncol; c++) {
+        if (a && f.aslot < 0 && f.t.col[c] == a->data && f.t.dt[c] == a->dtype) f.aslot = c;
+        if (b && f.bslot < 0 && f.t.col[c] == b->data && f.t.dt[c] == b->dtype) f.bslot = c;
     }
     f.n = n;
     f.d_sum = reinterpret_cast<unsigned long long *>(d_sum);
@@ -636,7 +489,7 @@ TQP_API int tqp_filter_sum(const tqp_col *cols, int ncols, const tqp_pred *preds
     TQP_LAUNCH("filter_sum_init", k_zero2, dim3(1), dim3(64), 0, s, f.d_sum, f.d_count);
     int rc = check_launch("tqp_filter_sum");
     if (rc || n == 0) return rc;
-    const int nd = f.nd <= kSumMaxCols ? f.nd : 0;
+    const int nd = f.t.ncol <= kMaxTogether ? f.t.ncol : 0;
     switch (nd) {
     case 1: return launch_filter_sum(k_filter_sum<1>, nd, n, s, f);
     case 2: return launch_filter_sum(k_filter_sum<2>, nd, n, s, f);
