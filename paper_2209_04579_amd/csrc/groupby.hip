@@ -1,13 +1,14 @@
 // GROUP BY with SUM / COUNT / SUM of products, int64 exact modulo 2^64.
 //
 // Sort-based path (general).  After the keys are sorted, every group is a run.
-// Because int64 addition modulo 2^64 is a group operation, the sum of a run
-// equals the difference of the running prefix sum at its last row and at the
-// last row of the run before it.  One single-pass scan over the sorted rows
-// (block scan + decoupled look-back carrying the head count and one running
-// sum per aggregate) writes, at every run end, the running sums and the
-// unique key; a second, small kernel over the groups takes adjacent
-// differences.  No atomics, so the output is the same bytes on every run.
+// A first kernel counts the run heads of every block of rows; a second one takes
+// the blocks again, starts at the sum of the counts before its block (so no
+// block waits for another), and writes each run that begins in the block:
+// key and aggregates, summed by a segmented scan.  A run that goes on past its
+// block leaves a partial sum in its slot, and every later block it covers
+// leaves its part in an edge record; a third, small kernel adds the edges.
+// Integer addition modulo 2^64 is exact in any order, so the output is the
+// same bytes on every run.
 //
 // Dense path.  When the caller bounds the key to a small domain
 // [key_lo, key_lo + span), each workgroup accumulates into LDS counters
@@ -19,230 +20,141 @@
 namespace tqp {
 
 constexpr int kGbNT = 512;
-constexpr int kGbIPT = 8;
+constexpr int kGbIPT = 4;
 constexpr int kGbTile = kGbNT * kGbIPT;
+constexpr int kGbNW = kGbNT / kWave;
+constexpr int kGbMaxSteps = 8;          // tiles per block
 constexpr int kMaxAgg = 4;
 constexpr int kMaxVals = 8;
-constexpr int kNV = kMaxAgg + 1;        // head count + one running sum per aggregate
 
+// The aggregates as the kernels take them: `nsum` sums (COUNT needs none: it
+// is a count of rows either way) over the `nv` distinct value columns they
+// name; sum g is column sa[g], times column sb[g] (or ic[g] minus it) when
+// sb[g] >= 0.  src[agg] is the agg's sum, -1 for COUNT.
 struct AggArgs {
     const void *val[kMaxVals];
-    int64_t vlen[kMaxVals];
+    uint32_t vlen[kMaxVals];            // rows in [0, vlen) exist (at most 2^31: row ids are int32)
     int32_t vdt[kMaxVals];
+    int32_t nv;
     int32_t op[kMaxAgg];
-    int32_t ia[kMaxAgg];
-    int32_t ib[kMaxAgg];
+    int32_t sa[kMaxAgg];
+    int32_t sb[kMaxAgg];
     int64_t ic[kMaxAgg];
+    int32_t nsum;
+    int32_t src[kMaxAgg];
     int32_t nagg;
     const int32_t *val_rows;
 };
+// Value columns loaded together, before any is used; aggregates over more
+// distinct columns load each one when its sum is formed.
+constexpr int kTogether = 2;
 
-// The second factor of a product aggregate: vals[b] itself (SUM_PRODUCT) or
-// c - vals[b] (SUM_DIFF_PRODUCT), in wrapping int64 arithmetic, so the product
-// is the exact one modulo 2^64.
-__device__ __forceinline__ int64_t agg_second(const AggArgs &a, int g, int64_t y) {
-    return a.op[g] == TQP_AGG_SUM_PRODUCT ? y : int64_t(uint64_t(a.ic[g]) - uint64_t(y));
-}
-
-__device__ __forceinline__ int64_t agg_term(const AggArgs &a, int g, int64_t row) {
-    if (a.op[g] == TQP_AGG_COUNT) return 1;
-    const int x = a.ia[g];
-    const int64_t vx = (row >= 0 && row < a.vlen[x]) ? load_any(a.val[x], a.vdt[x], row) : 0;
-    if (a.op[g] == TQP_AGG_SUM) return vx;
-    const int y = a.ib[g];
-    const int64_t vy = (row >= 0 && row < a.vlen[y]) ? load_any(a.val[y], a.vdt[y], row) : 0;
-    return int64_t(uint64_t(vx) * uint64_t(agg_second(a, g, vy)));
-}
-
-// Look-back over kNV int64 values.  Each tile owns 2 * kNV status words; word
-// 2k holds the low 32 bits of value k and word 2k+1 the high 32 bits, each
-// tagged in its top bits with 1 (tile aggregate) or 2 (inclusive prefix); 0
-// means not written yet.  Every word is a single relaxed agent-scope atomic,
-// so no fence orders one against another: a reader accepts a tile's record
-// only when all the words it needs carry the same non-zero tag, and otherwise
-// reads again.  An aggregate, once written, never changes until the same
-// words are rewritten as the inclusive prefix.
-__device__ __forceinline__ uint64_t tag_word(uint64_t tag, uint32_t half) {
-    return (tag << 62) | half;
-}
-
-template <int NV>
-__device__ __forceinline__ void publish_multi(uint64_t *rec, uint64_t tag, const int64_t (&v)[NV]) {
+// The elements of R rows of a column, as loaded: 8-byte elements whole,
+// narrower ones sign-extended to 32 bits by the load.  One branch on the type
+// for all R, with nothing but loads in it, so that the loads of several
+// columns stay in flight together; typed_value finishes the conversion.
+template <int R>
+__device__ __forceinline__ void load_typed(const void *p, int dt, const uint32_t (&row)[R],
+                                           uint64_t (&out)[R]) {
+    if (dt == TQP_INT64) {
 #pragma unroll
-    for (int k = 0; k < NV; k++) {
-        st_relaxed(&rec[2 * k], tag_word(tag, uint32_t(uint64_t(v[k]))));
-        st_relaxed(&rec[2 * k + 1], tag_word(tag, uint32_t(uint64_t(v[k]) >> 32)));
-    }
-}
-
-// Look-back over NV values (records of 2 * kNV words per tile; the first
-// 2 * NV are used), one predecessor per lane per round trip.
-template <int NV>
-__device__ __forceinline__ void lookback_multi(uint64_t *status, int64_t tile,
-                                               const int64_t (&agg)[NV], int64_t (&excl)[NV]) {
+        for (int r = 0; r < R; r++) out[r] = static_cast<const uint64_t *>(p)[row[r]];
+    } else if (dt == TQP_INT32) {
 #pragma unroll
-    for (int k = 0; k < NV; k++) excl[k] = 0;
-    if (tile == 0) {
-        if (lane_id() == 0) publish_multi<NV>(status, 2, agg);
-        return;
-    }
-    if (lane_id() == 0) publish_multi<NV>(status + tile * 2 * kNV, 1, agg);
-    int64_t base = tile - 1;
-    while (true) {
-        const int64_t idx = base - lane_id();
-        uint64_t tag = 2;
-        int64_t v[NV];
-#pragma unroll
-        for (int k = 0; k < NV; k++) v[k] = 0;
-        if (idx >= 0) {
-            const uint64_t *rec = status + idx * 2 * kNV;
-            while (true) {
-                // all words are read independently (no early exit), then checked
-                uint64_t w[2 * NV];
-#pragma unroll
-                for (int k = 0; k < 2 * NV; k++) w[k] = ld_relaxed(&rec[k]);
-                const uint64_t first = w[0] >> 62;
-                bool ok = first != 0;
-#pragma unroll
-                for (int k = 0; k < NV; k++) {
-                    ok = ok && (w[2 * k] >> 62) == first && (w[2 * k + 1] >> 62) == first;
-                    v[k] = int64_t((w[2 * k + 1] << 32) | (w[2 * k] & 0xffffffffu));
-                }
-                if (ok) {
-                    tag = first;
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
-            }
-        }
-        const uint64_t inc = ballot(tag == 2);
-        const int stop = inc ? (__ffsll(static_cast<long long>(inc)) - 1) : (kWave - 1);
-#pragma unroll
-        for (int k = 0; k < NV; k++) {
-            const int64_t x = lane_id() <= stop ? v[k] : 0;
-            excl[k] += wave_sum(x);
-        }
-        if (inc) break;
-        base -= kWave;
-    }
-    if (lane_id() == 0) {
-        int64_t incl[NV];
-#pragma unroll
-        for (int k = 0; k < NV; k++) incl[k] = int64_t(uint64_t(excl[k]) + uint64_t(agg[k]));
-        publish_multi<NV>(status + tile * 2 * kNV, 2, incl);
-    }
-}
-
-// Reads the value column of N rows (row ids in rows[]; 0 where the bit of
-// valid is clear or the row is outside the column).  One dtype test for all
-// N and no predicated loads (such rows read element 0), so the N loads issue
-// back to back and the sign extension waits for all of them at once.
-template <int N>
-__device__ __forceinline__ void load_vals(const void *col, int dt, int64_t len,
-                                          const int32_t (&rows)[N], uint32_t valid,
-                                          int64_t (&out)[N]) {
-    if (len <= 0) {
-#pragma unroll
-        for (int r = 0; r < N; r++) out[r] = 0;
-        return;
-    }
-    bool ok[N];
-    int32_t li[N];
-    uint64_t raw[N];
-#pragma unroll
-    for (int r = 0; r < N; r++) {
-        ok[r] = ((valid >> r) & 1) && rows[r] >= 0 && rows[r] < len;
-        li[r] = ok[r] ? rows[r] : 0;
-    }
-    load_raw<N>(col, dt, li, raw);
-#pragma unroll
-    for (int r = 0; r < N; r++) out[r] = ok[r] ? sext_of(raw[r], dt) : 0;
-}
-
-// Value-row ids of positions idx[] (position i itself without val_rows; 0
-// past cnt), all loads issued together; needs cnt >= 1.
-template <int N>
-__device__ __forceinline__ void load_rows(const int32_t *val_rows, const int64_t (&idx)[N], int64_t cnt,
-                                          int32_t (&row)[N]) {
-    if (val_rows) {
-        int64_t li[N];
-        uint64_t rr[N];
-#pragma unroll
-        for (int r = 0; r < N; r++) li[r] = idx[r] < cnt ? idx[r] : 0;
-#pragma unroll
-        for (int r = 0; r < N; r++) rr[r] = uint32_t(val_rows[li[r]]);
-#pragma unroll
-        for (int r = 0; r < N; r++) row[r] = idx[r] < cnt ? int32_t(uint32_t(rr[r])) : 0;
+        for (int r = 0; r < R; r++) out[r] = static_cast<const uint32_t *>(p)[row[r]];
     } else {
 #pragma unroll
-        for (int r = 0; r < N; r++) row[r] = idx[r] < cnt ? int32_t(idx[r]) : 0;
+        for (int r = 0; r < R; r++) out[r] = uint32_t(int32_t(static_cast<const int8_t *>(p)[row[r]]));
     }
 }
+__device__ __forceinline__ int64_t typed_value(uint64_t raw, int dt) {
+    return dt == TQP_INT64 ? int64_t(raw) : int64_t(int32_t(uint32_t(raw)));
+}
 
-// Exclusive prefix sums of N values per thread across the block, with one
-// pair of barriers for all N.  lds holds (NT / 64) * N entries.
-template <int NT, int N>
-__device__ __forceinline__ void block_excl_scan_n(const int64_t (&v)[N], int64_t (&ex)[N],
-                                                  int64_t (&tot)[N], int64_t *lds) {
-    constexpr int NW = NT / kWave;
-    int64_t inc[N];
+// Value column c of R rows; rows outside it (or with a clear bit of valid)
+// read row 0 here and count as 0 in take_value.  An empty column reads nothing.
+template <int R>
+__device__ __forceinline__ void load_value(const AggArgs &a, int c, const int32_t (&row)[R],
+                                           uint32_t valid, uint64_t (&out)[R]) {
+    uint32_t at[R];
+    if (a.vlen[c] == 0) {
 #pragma unroll
-    for (int k = 0; k < N; k++) inc[k] = wave_incl_scan(v[k]);
-    const int w = wave_id();
-    if (lane_id() == kWave - 1) {
-#pragma unroll
-        for (int k = 0; k < N; k++) lds[w * N + k] = inc[k];
+        for (int r = 0; r < R; r++) out[r] = 0;
+        return;
     }
-    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < N; k++) {
-        int64_t pre = 0, t = 0;
+    for (int r = 0; r < R; r++)
+        at[r] = ((valid >> r) & 1) && uint32_t(row[r]) < a.vlen[c] ? uint32_t(row[r]) : 0u;
+    load_typed<R>(a.val[c], a.vdt[c], at, out);
+}
+template <int R>
+__device__ __forceinline__ void take_value(const AggArgs &a, int c, const int32_t (&row)[R],
+                                           uint32_t valid, const uint64_t (&raw)[R], int64_t (&v)[R]) {
+    const int dt = a.vdt[c];
 #pragma unroll
-        for (int i = 0; i < NW; i++) {
-            const int64_t x = lds[i * N + k];
-            if (i < w) pre += x;
-            t += x;
+    for (int r = 0; r < R; r++)
+        v[r] = ((valid >> r) & 1) && uint32_t(row[r]) < a.vlen[c] ? typed_value(raw[r], dt) : 0;
+}
+
+// The term of sum g for R rows (0 where valid is clear): its first column, or
+// the product with its second (int64, wrapping, so exact modulo 2^64).
+// TOG: the columns are already loaded in raw.
+template <int R, bool TOG>
+__device__ __forceinline__ void sum_terms(const AggArgs &a, int g, const int32_t (&row)[R], uint32_t valid,
+                                          const uint64_t (&raw)[kTogether][R], int64_t (&t)[R]) {
+    auto column = [&](int c, int64_t (&v)[R]) {
+        if constexpr (TOG) {
+#pragma unroll
+            for (int k = 0; k < kTogether; k++)
+                if (c == k) take_value<R>(a, k, row, valid, raw[k], v);
+        } else {
+            uint64_t w[R];
+            load_value<R>(a, c, row, valid, w);
+            take_value<R>(a, c, row, valid, w, v);
         }
-        ex[k] = pre + inc[k] - v[k];
-        tot[k] = t;
+    };
+    column(a.sa[g], t);
+    if (a.sb[g] >= 0) {
+        int64_t y[R];
+        column(a.sb[g], y);
+        const bool diff = a.op[g] == TQP_AGG_SUM_DIFF_PRODUCT;
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const uint64_t f = diff ? uint64_t(a.ic[g]) - uint64_t(y[r]) : uint64_t(y[r]);
+            t[r] = ((valid >> r) & 1) ? int64_t(uint64_t(t[r]) * f) : 0;
+        }
     }
-    __syncthreads();
 }
 
-// One single-pass scan over sorted keys for NAGG aggregates: head count and
-// running sums carried across tiles by look-back; run ends write the running
-// sums, run heads write the key.  Every value is loaded once, into registers.
-template <class K, int NAGG>
-__global__ __launch_bounds__(kGbNT, 4) void k_gb_scan(const K *__restrict__ keys, int64_t n,
-                                                   const int64_t *d_n, AggArgs a,
-                                                   K *__restrict__ out_key, int64_t key_cap,
-                                                   int64_t *__restrict__ ends /* [NAGG][n] */,
-                                                   int64_t ends_stride, int64_t *d_ngroups,
-                                                   uint32_t *ticket, uint64_t *status) {
-    __shared__ int64_t s_tile;
-    __shared__ int64_t s_scan[(kGbNT / kWave) * (NAGG + 1)];
-    __shared__ int64_t s_term[NAGG * kGbIPT * kGbNT];   // [NAGG][kGbIPT][kGbNT]
-    __shared__ int64_t s_excl[kNV];
-    const int64_t cnt = count_of(d_n, n);
-    const int64_t ntiles = ceil_div(cnt, kGbTile);
-    const bool kvec = reinterpret_cast<uintptr_t>(keys) % 16 == 0;
-    const bool rvec = a.val_rows && reinterpret_cast<uintptr_t>(a.val_rows) % 16 == 0;
-    for (;;) {
-    const int64_t tile = take_tile(ticket, &s_tile);
-    if (tile >= ntiles) {
-        if (tile == 0 && threadIdx.x == 0) *d_ngroups = 0;
-        break;
-    }
-    const int64_t row0 = tile * kGbTile + int64_t(threadIdx.x) * kGbIPT;
+// Tiles per block for cnt rows, the same on the device in every kernel: the
+// widest of 8, 4, 2, 1 that still gives sixteen blocks per compute unit.
+__host__ __device__ inline int gb_steps(int64_t cnt) {
+    int st = kGbMaxSteps;
+    while (st > 1 && cnt < int64_t(kGbTile) * st * 16 * kComputeUnits) st >>= 1;
+    return st;
+}
+// Blocks any count up to n can take (one tile each up to twice sixteen per
+// CU, then at most that many until the blocks are at their longest).
+static int64_t gb_max_blocks(int64_t n) {
+    const int64_t few = int64_t(2) * 16 * kComputeUnits;
+    const int64_t tiles = ceil_div(n > 0 ? n : 1, kGbTile);
+    const int64_t longest = ceil_div(n > 0 ? n : 1, int64_t(kGbTile) * kGbMaxSteps);
+    const int64_t most = longest > few ? longest : few;
+    return tiles < most ? tiles : most;
+}
+
+// This thread's kGbIPT keys and the ones before and after them, and the bits
+// of the rows that exist.
+template <class K>
+__device__ __forceinline__ void load_run_keys(const K *keys, int64_t row0, int64_t cnt, bool vec,
+                                              K (&v)[kGbIPT], K &before, K &after) {
     constexpr int R = kGbIPT;
-    const bool full = row0 + R <= cnt;
-    K v[R];
-    if (kvec && full) {
+    if (vec && row0 + R <= cnt) {
         constexpr int kPer = 16 / sizeof(K);
         const int4 *q = reinterpret_cast<const int4 *>(keys + row0);
 #pragma unroll
         for (int j = 0; j < R / kPer; j++) {
-            int4 x = q[j];
+            const int4 x = q[j];
             const K *e = reinterpret_cast<const K *>(&x);
 #pragma unroll
             for (int t = 0; t < kPer; t++) v[j * kPer + t] = e[t];
@@ -251,302 +163,431 @@ __global__ __launch_bounds__(kGbNT, 4) void k_gb_scan(const K *__restrict__ keys
 #pragma unroll
         for (int r = 0; r < R; r++) v[r] = row0 + r < cnt ? keys[row0 + r] : K(0);
     }
-    int32_t rows[R];
-    if (rvec && full) {
-        const int4 *q = reinterpret_cast<const int4 *>(a.val_rows + row0);
-#pragma unroll
-        for (int j = 0; j < R / 4; j++) {
-            int4 x = q[j];
-            rows[4 * j + 0] = x.x;
-            rows[4 * j + 1] = x.y;
-            rows[4 * j + 2] = x.z;
-            rows[4 * j + 3] = x.w;
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < R; r++)
-            rows[r] = row0 + r < cnt ? (a.val_rows ? a.val_rows[row0 + r] : int32_t(row0 + r)) : 0;
-    }
-    const K before = row0 > 0 && row0 <= cnt ? keys[row0 - 1] : K(0);
-    const K after = row0 + R < cnt ? keys[row0 + R] : K(0);
-    uint32_t head = 0, end = 0, valid = 0;
+    before = row0 > 0 && row0 <= cnt ? keys[row0 - 1] : K(0);
+    after = row0 + R < cnt ? keys[row0 + R] : K(0);
+}
+// Bit r of head: row r starts a run; of end: row r ends one.
+template <class K>
+__device__ __forceinline__ void run_bits(const K (&v)[kGbIPT], K before, K after, int64_t row0,
+                                         int64_t cnt, uint32_t &head, uint32_t &end) {
+    constexpr int R = kGbIPT;
+    head = end = 0;
 #pragma unroll
     for (int r = 0; r < R; r++) {
         const int64_t i = row0 + r;
-        if (i < cnt) {
-            valid |= 1u << r;
-            const K prv = r == 0 ? before : v[r - 1];
-            const K nxt = r == R - 1 ? after : v[r + 1];
-            if (i == 0 || v[r] != prv) head |= 1u << r;
-            if (i == cnt - 1 || v[r] != nxt) end |= 1u << r;
-        }
-    }
-    // per-row aggregate terms, loaded once
-    int64_t term[NAGG][R];
-#pragma unroll
-    for (int g = 0; g < NAGG; g++) {
-        if (a.op[g] == TQP_AGG_COUNT) {
-#pragma unroll
-            for (int r = 0; r < R; r++) term[g][r] = (valid >> r) & 1;
-        } else {
-            const int x = a.ia[g];
-            load_vals<R>(a.val[x], a.vdt[x], a.vlen[x], rows, valid, term[g]);
-            if (a.op[g] >= TQP_AGG_SUM_PRODUCT) {
-                int64_t other[R];
-                const int y = a.ib[g];
-                load_vals<R>(a.val[y], a.vdt[y], a.vlen[y], rows, valid, other);
-#pragma unroll
-                for (int r = 0; r < R; r++)
-                    term[g][r] = int64_t(uint64_t(term[g][r]) * uint64_t(agg_second(a, g, other[r])));
-            }
-        }
-    }
-    // the terms wait in LDS (conflict-free: row r of thread t at r * kGbNT + t)
-    // while the block scan and the look-back run, so they hold no registers
-#pragma unroll
-    for (int g = 0; g < NAGG; g++) {
-#pragma unroll
-        for (int r = 0; r < R; r++) s_term[(g * R + r) * kGbNT + threadIdx.x] = term[g][r];
-    }
-    int64_t agg[NAGG + 1], excl[NAGG + 1], tot[NAGG + 1];
-    agg[0] = __popc(head);
-#pragma unroll
-    for (int g = 0; g < NAGG; g++) {
-        uint64_t s = 0;
-#pragma unroll
-        for (int r = 0; r < R; r++) s += uint64_t(term[g][r]);
-        agg[g + 1] = int64_t(s);
-    }
-    block_excl_scan_n<kGbNT, NAGG + 1>(agg, excl, tot, s_scan);
-    if (wave_id() == 0) {
-        int64_t pre[NAGG + 1];
-        lookback_multi<NAGG + 1>(status, tile, tot, pre);
-        if (lane_id() == 0)
-            for (int k = 0; k <= NAGG; k++) s_excl[k] = pre[k];
-    }
-    __syncthreads();
-    if (tile == ntiles - 1 && threadIdx.x == 0) *d_ngroups = s_excl[0] + tot[0];
-    int64_t hc = s_excl[0] + excl[0];
-    uint64_t run[NAGG];
-#pragma unroll
-    for (int g = 0; g < NAGG; g++) run[g] = uint64_t(s_excl[g + 1]) + uint64_t(excl[g + 1]);
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        if ((valid >> r) & 1) {
-            if (head & (1u << r)) {
-                if (hc < key_cap) out_key[hc] = v[r];
-                hc++;
-            }
-#pragma unroll
-            for (int g = 0; g < NAGG; g++) run[g] += uint64_t(s_term[(g * R + r) * kGbNT + threadIdx.x]);
-            if (end & (1u << r)) {
-#pragma unroll
-                for (int g = 0; g < NAGG; g++) ends[g * ends_stride + (hc - 1)] = int64_t(run[g]);
-            }
-        }
-    }
-    __syncthreads();
+        const K prv = r == 0 ? before : v[r - 1];
+        const K nxt = r == R - 1 ? after : v[r + 1];
+        head |= (i < cnt && (i == 0 || v[r] != prv) ? 1u : 0u) << r;
+        end |= (i < cnt && (i == cnt - 1 || v[r] != nxt) ? 1u : 0u) << r;
     }
 }
 
-__global__ __launch_bounds__(256) void k_gb_diff(const int64_t *__restrict__ ends,
-                                                 int64_t ends_stride, int nagg,
-                                                 const int64_t *d_ngroups, int64_t cap,
-                                                 int64_t *o0, int64_t *o1, int64_t *o2,
-                                                 int64_t *o3) {
-    const int64_t ng0 = *d_ngroups;
-    const int64_t ng = ng0 < cap ? ng0 : cap;
-    int64_t *outs[4] = {o0, o1, o2, o3};
-    for (int64_t g = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; g < ng;
-         g += int64_t(gridDim.x) * blockDim.x) {
+// Run heads of every block.
+template <class K>
+__global__ __launch_bounds__(kGbNT) void k_gb_heads(const K *__restrict__ keys, int64_t n,
+                                                    const int64_t *d_n, int32_t *__restrict__ bcnt) {
+    __shared__ int32_t s_cnt[kGbNW];
+    const int64_t cnt = count_of(d_n, n);
+    const int steps = gb_steps(cnt);
+    const int64_t nblocks = ceil_div(cnt, int64_t(kGbTile) * steps);
+    const bool vec = reinterpret_cast<uintptr_t>(keys) % 16 == 0;
+    for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        int32_t heads = 0;
+        for (int st = 0; st < steps; st++) {
+            const int64_t row0 = (b * steps + st) * kGbTile + int64_t(threadIdx.x) * kGbIPT;
+            K v[kGbIPT], before, after;
+            uint32_t head, end;
+            load_run_keys(keys, row0, cnt, vec, v, before, after);
+            run_bits(v, before, after, row0, cnt, head, end);
+            heads += __popc(head);
+        }
+        heads = wave_sum(heads);
+        if (lane_id() == 0) s_cnt[wave_id()] = heads;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int32_t tot = 0;
+#pragma unroll
+            for (int w = 0; w < kGbNW; w++) tot += s_cnt[w];
+            bcnt[b] = tot;
+        }
+        __syncthreads();
+    }
+}
+
+// The part of a run that lies in a block it did not begin in: the run's slot
+// (-1: the block begins with a run of its own) and the block's share of
+// each aggregate.
+struct GbEdges {
+    int64_t *slot;                 // [blocks]
+    int64_t *part;                 // [nagg][blocks]
+    int64_t stride;
+};
+struct GbOut {
+    int64_t *agg[kMaxAgg];
+    int64_t cap;
+};
+
+// The runs of every block.  Per tile: each thread's sums since its last run
+// head, a segmented scan of those over the workgroup (NSUM sums, the number of
+// heads, and the last head's position, which gives COUNT), then each thread walks
+// its rows from the sum carried into it.  The open run is carried from tile to
+// tile of a block.
+//
+// What bounds it: keys, row ids and values (16 B per row for one 8-byte sum).
+// The version before this carried running sums through a look-back, every tile
+// waiting for the one before it, and wrote them per group for a later
+// difference.  30M sorted int32 keys in 1.5M groups, SUM of an int64 column
+// through row ids and COUNT: 265 + 11 us (scan, differences) -> 23 + 158 + 5 us
+// (heads, runs, edges).  512 threads of 4 rows: with 256 of 8 the rows' terms
+// spill.
+template <class K, int NSUM, bool TOG>
+__global__ __launch_bounds__(kGbNT, 4) void k_gb_runs(const K *__restrict__ keys, int64_t n,
+                                                      const int64_t *d_n, AggArgs a,
+                                                      K *__restrict__ out_key, GbOut o,
+                                                      int64_t *d_ngroups,
+                                                      const int32_t *__restrict__ bcnt, GbEdges e) {
+    constexpr int R = kGbIPT;
+    constexpr int NS = NSUM > 0 ? NSUM : 1;
+    struct Wave {
+        uint64_t sum[NS];
+        int32_t heads, last;
+    };
+    __shared__ Wave s_wave[2][kGbNW];
+    __shared__ int64_t s_base[kGbNW];
+    const int64_t cnt = count_of(d_n, n);
+    const int steps = gb_steps(cnt);
+    const int64_t brows = int64_t(kGbTile) * steps;
+    const int64_t nblocks = ceil_div(cnt, brows);
+    const bool vec = reinterpret_cast<uintptr_t>(keys) % 16 == 0;
+    const bool rvec = a.val_rows && reinterpret_cast<uintptr_t>(a.val_rows) % 16 == 0;
+    const int w = wave_id(), lane = lane_id();
+    if (cnt == 0 && blockIdx.x == 0 && threadIdx.x == 0) *d_ngroups = 0;
+    int64_t base = 0, from = 0;
+    for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        int64_t part = 0;
+#pragma unroll 4
+        for (int64_t i = from + threadIdx.x; i < b; i += kGbNT) part += bcnt[i];
+        part = wave_sum(part);
+        __syncthreads();                               // s_base and s_wave of the block before
+        if (lane == 0) s_base[w] = part;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kGbNW; i++) base += s_base[i];
+        from = b;
+        const int64_t blk0 = b * brows;
+        const int64_t blk1 = blk0 + brows < cnt ? blk0 + brows : cnt;
+        int64_t hc = base;                             // heads before the tile
+        int32_t open_at = -1;                          // the open run's head in the block (-1: before it)
+        uint64_t open[NS];                             // and its sums so far
+#pragma unroll
+        for (int g = 0; g < NS; g++) open[g] = 0;
+        for (int st = 0; st < steps; st++) {
+            const int64_t tile0 = blk0 + int64_t(st) * kGbTile;
+            if (tile0 >= blk1) break;
+            const int64_t row0 = tile0 + int64_t(threadIdx.x) * R;
+            K v[R], before, after;
+            load_run_keys(keys, row0, cnt, vec, v, before, after);
+            int32_t rows[R];
+            if (rvec && row0 + R <= cnt) {
+                const int4 *q = reinterpret_cast<const int4 *>(a.val_rows + row0);
+#pragma unroll
+                for (int j = 0; j < R / 4; j++) {
+                    const int4 x = q[j];
+                    rows[4 * j] = x.x; rows[4 * j + 1] = x.y; rows[4 * j + 2] = x.z; rows[4 * j + 3] = x.w;
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; r++)
+                    rows[r] = row0 + r < cnt ? (a.val_rows ? a.val_rows[row0 + r] : int32_t(row0 + r)) : 0;
+            }
+            const uint32_t valid = row0 >= cnt ? 0u : row0 + R <= cnt ? (1u << R) - 1u : (1u << int(cnt - row0)) - 1u;
+            uint64_t raw[kTogether][R];
+            if constexpr (TOG && NSUM > 0) {
+#pragma unroll
+                for (int c = 0; c < kTogether; c++)
+                    if (c < a.nv) load_value<R>(a, c, rows, valid, raw[c]);
+            }
+            uint32_t head, end;
+            run_bits(v, before, after, row0, cnt, head, end);
+            int64_t term[NS][R];
+            uint64_t sum[NS];                          // since the thread's last head
+#pragma unroll
+            for (int g = 0; g < NSUM; g++) {
+                sum_terms<R, TOG>(a, g, rows, valid, raw, term[g]);
+                sum[g] = 0;
+#pragma unroll
+                for (int r = 0; r < R; r++) sum[g] = (head >> r & 1 ? 0 : sum[g]) + uint64_t(term[g][r]);
+            }
+            const int32_t local0 = int32_t(row0 - blk0);
+            int32_t last = head ? local0 + 31 - __builtin_clz(head) : -1;
+            int32_t heads = __popc(head);
+            const int32_t my_heads = heads;
+            // segmented inclusive scan over the wave (a thread's flag is last >= 0)
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const int32_t uh = shfl_up(heads, d), ul = shfl_up(last, d);
+#pragma unroll
+                for (int g = 0; g < NSUM; g++) {
+                    const uint64_t us = shfl_up(sum[g], d);
+                    if (lane >= d && last < 0) sum[g] += us;
+                }
+                if (lane >= d) {
+                    heads += uh;
+                    last = last > ul ? last : ul;
+                }
+            }
+            Wave *sw = s_wave[st & 1];
+            if (lane == kWave - 1) {
+#pragma unroll
+                for (int g = 0; g < NSUM; g++) sw[w].sum[g] = sum[g];
+                sw[w].heads = heads;
+                sw[w].last = last;
+            }
+            __syncthreads();
+            // what is carried into this wave, and out of the tile
+            int32_t in_at = open_at, wheads = 0;
+            uint64_t in[NS];
+#pragma unroll
+            for (int g = 0; g < NSUM; g++) in[g] = open[g];
+            int32_t theads = 0;
+#pragma unroll
+            for (int i = 0; i < kGbNW; i++) {
+                if (i == w) {
+                    in_at = open_at;
+                    wheads = theads;
+#pragma unroll
+                    for (int g = 0; g < NSUM; g++) in[g] = open[g];
+                }
+                const int32_t l = sw[i].last;
+#pragma unroll
+                for (int g = 0; g < NSUM; g++) open[g] = (l >= 0 ? 0 : open[g]) + sw[i].sum[g];
+                if (l >= 0) open_at = l;
+                theads += sw[i].heads;
+            }
+            // carried into this thread
+            int32_t at = shfl_up(last, 1);
+            uint64_t acc[NS];
+#pragma unroll
+            for (int g = 0; g < NSUM; g++) {
+                const uint64_t u = shfl_up(sum[g], 1);
+                acc[g] = lane == 0 ? in[g] : u + (at < 0 ? in[g] : 0);
+            }
+            at = lane == 0 || at < 0 ? in_at : at;
+            int64_t slot = hc + wheads + (heads - my_heads);       // heads before the row
+            hc += theads;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                if (!((valid >> r) & 1)) continue;
+                if (head >> r & 1) {
+                    if (slot < o.cap) out_key[slot] = v[r];
+                    slot++;
+                    at = local0 + r;
+#pragma unroll
+                    for (int g = 0; g < NSUM; g++) acc[g] = 0;
+                }
+#pragma unroll
+                for (int g = 0; g < NSUM; g++) acc[g] += uint64_t(term[g][r]);
+                const bool close = (end >> r & 1) || row0 + r == blk1 - 1;
+                if (!close) continue;
+#pragma unroll
+                for (int k = 0; k < kMaxAgg; k++) {
+                    if (k >= a.nagg) break;
+                    int64_t x = local0 + r + 1 - (at < 0 ? 0 : at);          // COUNT
+#pragma unroll
+                    for (int g = 0; g < NSUM; g++)
+                        if (a.src[k] == g) x = int64_t(acc[g]);
+                    if (at < 0) e.part[k * e.stride + b] = x;
+                    else if (slot - 1 < o.cap) o.agg[k][slot - 1] = x;
+                }
+            }
+        }
+        if (threadIdx.x == 0) {
+            // the block's first row continues a run exactly when its head
+            // lies before the block
+            e.slot[b] = blk0 > 0 && keys[blk0] == keys[blk0 - 1] ? base - 1 : -1;
+            if (b == nblocks - 1) *d_ngroups = hc;
+        }
+    }
+}
+
+// Adds the edges, a wave combining those of neighbouring blocks that belong to
+// one run (a run can cover thousands of blocks).
+__global__ __launch_bounds__(256) void k_gb_edges(int64_t n, const int64_t *d_n, int nagg, GbOut o, GbEdges e) {
+    const int64_t cnt = count_of(d_n, n);
+    const int64_t nblocks = ceil_div(cnt, int64_t(kGbTile) * gb_steps(cnt));
+    const int lane = lane_id();
+    for (int64_t b0 = blockIdx.x * int64_t(blockDim.x); b0 < nblocks; b0 += int64_t(gridDim.x) * blockDim.x) {
+        const int64_t b = b0 + threadIdx.x;
+        const int64_t slot = b < nblocks ? e.slot[b] : -1;
+        const int64_t prev = shfl_up(slot, 1);
+        const bool leader = slot >= 0 && slot < o.cap && (lane == 0 || prev != slot);
         for (int k = 0; k < nagg; k++) {
-            const int64_t *e = ends + k * ends_stride;
-            const uint64_t hi = uint64_t(e[g]);
-            const uint64_t lo = g > 0 ? uint64_t(e[g - 1]) : 0;
-            outs[k][g] = int64_t(hi - lo);
+            uint64_t x = slot >= 0 ? uint64_t(e.part[k * e.stride + b]) : 0;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const uint64_t ux = uint64_t(__shfl_down((unsigned long long)x, d, kWave));
+                const int64_t us = __shfl_down((long long)slot, d, kWave);
+                if (lane + d < kWave && us == slot) x += ux;
+            }
+            if (leader) atomicAdd(reinterpret_cast<unsigned long long *>(&o.agg[k][slot]), (unsigned long long)x);
         }
     }
 }
 
 // ---- dense key domain ------------------------------------------------------
+//
+// Each workgroup accumulates into LDS: one 64-bit cell per sum and key, and one
+// 32-bit row count per key.  LDS atomics on one address serialize, so every
+// cell has up to 32 copies (as many as fit), one per lane modulo 32: with 32 the
+// lanes of a wave's half never meet, whatever the keys.  A thread takes kDenseR
+// rows per step in three rounds of loads: row ids, then the key terms' and the
+// value columns' elements, then the additions.
+//
+// What bounds it: the bytes of the row ids and values (or, gathered from a
+// table, their cache lines).  A domain of at most 8 keys used to keep every
+// group's accumulators in registers, adding each row to all of them under a
+// mask: that was bound by vector arithmetic.  30M rows of 29 bytes in 6 groups:
+// 290 -> 184 us; 11.4M rows of 2 bytes in 5 groups: 72 -> 34 us.  A larger domain
+// had one copy of each cell, and a grid with 64 rows per thread: 500K rows in 25
+// groups 43 -> 12 us.
+constexpr int kDenseNT = 512;
+constexpr int kDenseR = 4;
+constexpr int kDenseMaxCopies = 32;
+constexpr int kDenseLds = 40 * 1024;        // LDS the copies may fill (four workgroups per CU)
+constexpr int kDenseRows = kDenseNT * kDenseR;
 
-constexpr int kDenseR = 4;                  // rows per thread per step (loads issued together)
-
-// Where a dense group-by reads its keys: a key column, or a packed key built
-// from other columns on the fly (never written to memory).
-template <class K> struct ColKeys {
-    const K *keys;
-    template <int R>
-    __device__ __forceinline__ void get(const int64_t (&idx)[R], int64_t cnt, int64_t (&v)[R]) const {
-        K k[R];
-#pragma unroll
-        for (int r = 0; r < R; r++) k[r] = keys[idx[r] < cnt ? idx[r] : 0];   // cnt >= 1 here
-#pragma unroll
-        for (int r = 0; r < R; r++) v[r] = idx[r] < cnt ? int64_t(k[r]) : 0;
-    }
-};
-struct TermKeys {
-    PackArgs a;
-    template <int R>
-    __device__ __forceinline__ void get(const int64_t (&idx)[R], int64_t cnt, int64_t (&v)[R]) const {
-        uint64_t acc[R];
-        pack_keys<R>(a, idx, cnt, acc);
-#pragma unroll
-        for (int r = 0; r < R; r++) v[r] = int64_t(acc[r]);
-    }
-};
-
-template <class KS>
-__global__ __launch_bounds__(kGbNT) void k_gb_dense(KS ks, int64_t n,
-                                                    const int64_t *d_n, int64_t key_lo,
-                                                    int64_t span, AggArgs a,
-                                                    unsigned long long *__restrict__ gacc) {
-    extern __shared__ unsigned long long s_acc[];   // [(nagg + 1)][span], count last
-    const int nagg = a.nagg;
-    const int64_t cells = int64_t(nagg + 1) * span;
-    for (int64_t i = threadIdx.x; i < cells; i += kGbNT) s_acc[i] = 0;
-    __syncthreads();
-    const int64_t cnt = count_of(d_n, n);
+// NT: at least the number of key terms (1, 2 or 4).  key(i) is as pack_keys
+// gives it.  Cell of sum g, key b, copy c: s_acc[((g * span + b) << lgc) + c];
+// the counts follow.
+template <int NT, bool TOG>
+__global__ __launch_bounds__(kDenseNT) void k_gb_dense(PackArgs k, int64_t n, const int64_t *d_n,
+                                                       int64_t key_lo, int span, int lgc, AggArgs a,
+                                                       unsigned long long *__restrict__ gacc) {
     constexpr int R = kDenseR;
-    const int64_t stride = int64_t(gridDim.x) * kGbNT * R;
-    for (int64_t base = blockIdx.x * int64_t(kGbNT) * R; base < cnt; base += stride) {
-        uint32_t ok = 0;
-        uint64_t b[R];
-        int32_t row[R];
-        int64_t idx[R], kv[R];
-#pragma unroll
-        for (int r = 0; r < R; r++) idx[r] = base + r * kGbNT + threadIdx.x;
-        load_rows<R>(a.val_rows, idx, cnt, row);
-        ks.template get<R>(idx, cnt, kv);
-#pragma unroll
-        for (int r = 0; r < R; r++)
-            b[r] = idx[r] < cnt ? uint64_t(kv[r]) - uint64_t(key_lo) : uint64_t(span);
+    extern __shared__ unsigned long long s_acc[];
+    const int cells = span << lgc;
+    const int nsum = a.nsum;
+    uint32_t *s_cnt = reinterpret_cast<uint32_t *>(s_acc + nsum * cells);
+    const int64_t cnt = count_of(d_n, n);
+    // only as many workgroups take part as the actual row count feeds: each
+    // one costs an addition per cell at the end
+    int64_t active = ceil_div(cnt, kDenseRows);
+    if (active > int64_t(gridDim.x)) active = gridDim.x;
+    if (int64_t(blockIdx.x) >= active) return;
+    for (int i = threadIdx.x; i < nsum * cells; i += kDenseNT) s_acc[i] = 0;
+    for (int i = threadIdx.x; i < cells; i += kDenseNT) s_cnt[i] = 0;
+    __syncthreads();
+    const int copy = int(threadIdx.x) & ((1 << lgc) - 1);
+    for (int64_t base = int64_t(blockIdx.x) * kDenseRows; base < cnt; base += active * kDenseRows) {
+        uint32_t in = 0;
+        int32_t at[R], row[R], trow[NT][R];
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            if (b[r] < uint64_t(span)) {
-                ok |= 1u << r;
-                atomicAdd(&s_acc[nagg * span + b[r]], 1ull);
+            const int64_t i = base + r * kDenseNT + threadIdx.x;
+            in |= (i < cnt ? 1u : 0u) << r;
+            at[r] = int32_t(i < cnt ? i : 0);               // cnt >= 1 here
+        }
+        if (a.val_rows) {
+#pragma unroll
+            for (int r = 0; r < R; r++) row[r] = a.val_rows[at[r]];
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; r++) row[r] = at[r];
+        }
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+            if (t < k.nterms && k.rows[t]) {
+#pragma unroll
+                for (int r = 0; r < R; r++) trow[t][r] = k.rows[t][at[r]];
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; r++) trow[t][r] = at[r];
             }
         }
-        for (int g = 0; g < nagg; g++) {
-            if (a.op[g] == TQP_AGG_COUNT) {
+        uint64_t traw[NT][R], raw[kTogether][R];
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+            if (t < k.nterms && k.col[t] && k.len[t] > 0) {
+                uint32_t p[R];
 #pragma unroll
                 for (int r = 0; r < R; r++)
-                    if ((ok >> r) & 1) atomicAdd(&s_acc[g * span + b[r]], 1ull);
+                    p[r] = trow[t][r] >= 0 && trow[t][r] < k.len[t] ? uint32_t(trow[t][r]) : 0u;
+                load_typed<R>(k.col[t], k.dt[t], p, traw[t]);
+            }
+        }
+        if constexpr (TOG) {
+#pragma unroll
+            for (int c = 0; c < kTogether; c++)
+                if (c < a.nv) load_value<R>(a, c, row, in, raw[c]);
+        }
+        uint64_t b[R];
+#pragma unroll
+        for (int r = 0; r < R; r++) b[r] = 0 - uint64_t(key_lo);
+#pragma unroll
+        for (int t = 0; t < NT; t++) {
+            if (t >= k.nterms) break;
+            const uint64_t mul = uint64_t(k.mul[t]);
+            if (!k.col[t]) {                                 // constant term
+#pragma unroll
+                for (int r = 0; r < R; r++) b[r] += mul;
                 continue;
             }
             int64_t v[R];
-            load_vals<R>(a.val[a.ia[g]], a.vdt[a.ia[g]], a.vlen[a.ia[g]], row, ok, v);
-            if (a.op[g] >= TQP_AGG_SUM_PRODUCT) {
-                int64_t vy[R];
-                load_vals<R>(a.val[a.ib[g]], a.vdt[a.ib[g]], a.vlen[a.ib[g]], row, ok, vy);
-#pragma unroll
-                for (int r = 0; r < R; r++) v[r] = int64_t(uint64_t(v[r]) * uint64_t(agg_second(a, g, vy[r])));
-            }
 #pragma unroll
             for (int r = 0; r < R; r++)
-                if ((ok >> r) & 1) atomicAdd(&s_acc[g * span + b[r]], (unsigned long long)v[r]);
+                v[r] = trow[t][r] >= 0 && trow[t][r] < k.len[t] ? typed_value(traw[t][r], k.dt[t]) : 0;
+            const int64_t m = k.mod[t];
+            if (m > 0 && (m & (m - 1)) == 0) {
+#pragma unroll
+                for (int r = 0; r < R; r++) v[r] &= m - 1;
+            } else if (m > 0) {
+#pragma unroll
+                for (int r = 0; r < R; r++) {
+                    v[r] %= m;
+                    if (v[r] < 0) v[r] += m;
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < R; r++) b[r] += mul * uint64_t(v[r]);
         }
-    }
-    __syncthreads();
-    for (int64_t c = threadIdx.x; c < span; c += kGbNT) {
-        if (s_acc[nagg * span + c] == 0) continue;
-        for (int g = 0; g <= nagg; g++) atomicAdd(&gacc[g * span + c], s_acc[g * span + c]);
-    }
-}
-
-// Domains of at most kTinySpan keys: every thread keeps all the groups'
-// accumulators in registers (selecting, not indexing, the group), so no two
-// lanes ever contend for one counter; waves then reduce with shuffles.  Each
-// thread takes kTinyR rows per step and issues all their loads (keys, row ids,
-// then values) before using any, so a wave has kTinyR dependent gathers in
-// flight instead of one.
-constexpr int kTinySpan = 8;
-constexpr int kTinyR = 4;
-
-template <class KS, int NAGG>
-__global__ __launch_bounds__(kGbNT) void k_gb_tiny(KS ks, int64_t n,
-                                                   const int64_t *d_n, int64_t key_lo, int span,
-                                                   AggArgs a, unsigned long long *__restrict__ gacc) {
-    constexpr int R = kTinyR;
-    __shared__ int64_t s_red[kGbNT / kWave][kTinySpan][NAGG + 1];
-    int64_t acc[kTinySpan][NAGG];
-    int64_t cnt_b[kTinySpan];
-#pragma unroll
-    for (int b = 0; b < kTinySpan; b++) {
-        cnt_b[b] = 0;
-#pragma unroll
-        for (int g = 0; g < NAGG; g++) acc[b][g] = 0;
-    }
-    const int64_t cnt = count_of(d_n, n);
-    const int64_t stride = int64_t(gridDim.x) * kGbNT * R;
-    for (int64_t base = blockIdx.x * int64_t(kGbNT) * R; base < cnt; base += stride) {
         uint32_t ok = 0;
-        uint64_t b[R];
-        int32_t row[R];
-        int64_t idx[R], kv[R];
-#pragma unroll
-        for (int r = 0; r < R; r++) idx[r] = base + r * kGbNT + threadIdx.x;
-        load_rows<R>(a.val_rows, idx, cnt, row);
-        ks.template get<R>(idx, cnt, kv);
-#pragma unroll
-        for (int r = 0; r < R; r++)
-            b[r] = idx[r] < cnt ? uint64_t(kv[r]) - uint64_t(key_lo) : uint64_t(span);
-#pragma unroll
-        for (int r = 0; r < R; r++) ok |= (b[r] < uint64_t(span) ? 1u : 0u) << r;
-        int64_t t[NAGG][R];
-#pragma unroll
-        for (int g = 0; g < NAGG; g++) {
-            if (a.op[g] == TQP_AGG_COUNT) {
-#pragma unroll
-                for (int r = 0; r < R; r++) t[g][r] = 1;
-                continue;
-            }
-            const int x = a.ia[g];
-            load_vals<R>(a.val[x], a.vdt[x], a.vlen[x], row, ok, t[g]);
-            if (a.op[g] >= TQP_AGG_SUM_PRODUCT) {
-                const int y = a.ib[g];
-                int64_t vy[R];
-                load_vals<R>(a.val[y], a.vdt[y], a.vlen[y], row, ok, vy);
-#pragma unroll
-                for (int r = 0; r < R; r++) t[g][r] = int64_t(uint64_t(t[g][r]) * uint64_t(agg_second(a, g, vy[r])));
-            }
-        }
+        int cell[R];
 #pragma unroll
         for (int r = 0; r < R; r++) {
-#pragma unroll
-            for (int bb = 0; bb < kTinySpan; bb++) {
-                const bool hit = ((ok >> r) & 1) && uint64_t(bb) == b[r];
-                cnt_b[bb] += hit ? 1 : 0;
-#pragma unroll
-                for (int g = 0; g < NAGG; g++) acc[bb][g] += hit ? t[g][r] : 0;
-            }
+            const bool hit = ((in >> r) & 1) && b[r] < uint64_t(span);
+            ok |= (hit ? 1u : 0u) << r;
+            cell[r] = ((hit ? int(b[r]) : 0) << lgc) + copy;
+            if (hit) atomicAdd(&s_cnt[cell[r]], 1u);
         }
-    }
-    const int w = wave_id();
+        for (int g = 0; g < nsum; g++) {
+            int64_t t[R];
+            sum_terms<R, TOG>(a, g, row, in, raw, t);
 #pragma unroll
-    for (int bb = 0; bb < kTinySpan; bb++) {
-#pragma unroll
-        for (int g = 0; g < NAGG; g++) {
-            const int64_t sv = wave_sum(acc[bb][g]);
-            if (lane_id() == 0) s_red[w][bb][g] = sv;
+            for (int r = 0; r < R; r++)
+                if ((ok >> r) & 1) atomicAdd(&s_acc[g * cells + cell[r]], (unsigned long long)t[r]);
         }
-        const int64_t c = wave_sum(cnt_b[bb]);
-        if (lane_id() == 0) s_red[w][bb][NAGG] = c;
     }
     __syncthreads();
-    if (threadIdx.x < kTinySpan * (NAGG + 1)) {
-        const int bb = threadIdx.x / (NAGG + 1), g = threadIdx.x % (NAGG + 1);
-        int64_t sv = 0;
-#pragma unroll
-        for (int ww = 0; ww < kGbNT / kWave; ww++) sv += s_red[ww][bb][g];
-        if (bb < span && sv != 0) atomicAdd(&gacc[g * span + bb], (unsigned long long)sv);
+    // one thread per key and sum (the counts as the last row), its copies read
+    // from a different one per lane so that they do not share a bank
+    const int ncopy = 1 << lgc;
+    for (int i = threadIdx.x; i < (nsum + 1) * span; i += kDenseNT) {
+        const int g = i / span, key = i - g * span;
+        unsigned long long x = 0;
+        if (g < nsum) {
+            for (int c = 0; c < ncopy; c++)
+                x += s_acc[g * cells + (key << lgc) + ((c + threadIdx.x) & (ncopy - 1))];
+        } else {
+            for (int c = 0; c < ncopy; c++) x += s_cnt[(key << lgc) + ((c + threadIdx.x) & (ncopy - 1))];
+        }
+        if (x) atomicAdd(&gacc[i], x);
     }
 }
 
+// The groups that occur, from the accumulators [(nsum sums, then counts)][span].
 template <class K>
 __global__ __launch_bounds__(1024) void k_gb_dense_emit(const unsigned long long *__restrict__ gacc,
-                                                        int64_t key_lo, int64_t span, int nagg,
+                                                        int64_t key_lo, int64_t span, AggArgs a,
                                                         K *out_key, int64_t cap, int64_t *o0,
                                                         int64_t *o1, int64_t *o2, int64_t *o3,
                                                         int64_t *d_ngroups) {
@@ -556,14 +597,15 @@ __global__ __launch_bounds__(1024) void k_gb_dense_emit(const unsigned long long
     const int64_t c0 = int64_t(threadIdx.x) * 4;
     uint32_t live = 0;
     for (int r = 0; r < 4; r++)
-        if (c0 + r < span && gacc[nagg * span + c0 + r] != 0) live |= 1u << r;
+        if (c0 + r < span && gacc[a.nsum * span + c0 + r] != 0) live |= 1u << r;
     int64_t total;
     int64_t q = block_excl_scan<1024>(int64_t(__popc(live)), &total, s_scan);
     for (int r = 0; r < 4; r++) {
         if (!(live & (1u << r))) continue;
         if (q < cap) {
             out_key[q] = K(key_lo + c0 + r);
-            for (int g = 0; g < nagg; g++) outs[g][q] = int64_t(gacc[g * span + c0 + r]);
+            for (int g = 0; g < a.nagg; g++)
+                outs[g][q] = int64_t(gacc[(a.src[g] < 0 ? a.nsum : a.src[g]) * span + c0 + r]);
         }
         q++;
     }
@@ -576,10 +618,9 @@ struct GbLayout {
     int32_t *srows;
     void *sort_ws;
     size_t sort_ws_bytes;
-    int64_t *ends;
-    uint64_t *words;          // ticket word, then 2 * kNV status words per tile
-    int64_t nwords;
-    int64_t ntiles;
+    int32_t *bcnt;            // run heads per block
+    GbEdges edges;
+    int64_t nblocks;          // at most
     unsigned long long *gacc;
     size_t bytes;
 };
@@ -606,59 +647,46 @@ static GbLayout gb_layout(void *ws, int64_t n, int dtype, int nagg, uint32_t fla
         L.sort_ws_bytes = sort_ws_bytes(nn, dtype, ks * 8);
         L.sort_ws = c.take<char>(L.sort_ws_bytes);
     }
-    L.ends = c.take<int64_t>(size_t(kMaxAgg) * nn);
-    L.ntiles = ceil_div(nn, kGbTile);
-    L.nwords = 1 + L.ntiles * 2 * kNV;
-    L.words = c.take<uint64_t>(size_t(L.nwords));
+    L.nblocks = gb_max_blocks(nn);
+    L.bcnt = c.take<int32_t>(size_t(L.nblocks));
+    L.edges.slot = c.take<int64_t>(size_t(L.nblocks));
+    L.edges.part = c.take<int64_t>(size_t(L.nblocks) * kMaxAgg);
+    L.edges.stride = L.nblocks;
     L.bytes = c.bytes();
     return L;
 }
 
-// Dense domains: zero the accumulators, aggregate (registers for at most
-// kTinySpan keys, LDS otherwise), emit the groups that occur.  KS gives the
-// keys (a column, or a packed key built on the fly); OK is the output key type.
-template <class OK, class KS>
-static int dense_groupby(const KS &ks, int64_t n, const int64_t *d_n, int64_t key_lo,
+// Dense domains: zero the accumulators, aggregate, emit the groups that occur.
+// The key is packed from terms as the rows are read (a key column is one term).
+template <class OK>
+static int dense_groupby(const PackArgs &k, int64_t n, const int64_t *d_n, int64_t key_lo,
                          int64_t key_span, const AggArgs &args, unsigned long long *gacc,
                          OK *out_key, int64_t out_cap, int64_t *const *o, int64_t *d_ngroups,
                          hipStream_t s) {
-    const int nagg = args.nagg;
-    int rc = fill_u64(gacc, 0, int64_t(nagg + 1) * key_span, s);
+    int rc = fill_u64(gacc, 0, int64_t(args.nsum + 1) * key_span, s);
     if (rc) return rc;
-    if (n > 0 && key_span <= kTinySpan) {
-        // no more workgroups than are resident at once (4 per CU at this
-        // kernel's register count): measured 4% faster than twice as many
-        int64_t g = ceil_div(n, int64_t(kGbNT) * kTinyR * 8);
-        if (g > int64_t(kComputeUnits) * 4) g = int64_t(kComputeUnits) * 4;
-        switch (nagg) {
-        case 1:
-            TQP_LAUNCH("gb_tiny", (k_gb_tiny<KS, 1>), dim3(unsigned(g)), dim3(kGbNT), 0, s, ks, n,
-                       d_n, key_lo, int(key_span), args, gacc);
-            break;
-        case 2:
-            TQP_LAUNCH("gb_tiny", (k_gb_tiny<KS, 2>), dim3(unsigned(g)), dim3(kGbNT), 0, s, ks, n,
-                       d_n, key_lo, int(key_span), args, gacc);
-            break;
-        case 3:
-            TQP_LAUNCH("gb_tiny", (k_gb_tiny<KS, 3>), dim3(unsigned(g)), dim3(kGbNT), 0, s, ks, n,
-                       d_n, key_lo, int(key_span), args, gacc);
-            break;
-        default:
-            TQP_LAUNCH("gb_tiny", (k_gb_tiny<KS, 4>), dim3(unsigned(g)), dim3(kGbNT), 0, s, ks, n,
-                       d_n, key_lo, int(key_span), args, gacc);
-            break;
-        }
-        if ((rc = check_launch("group-by tiny"))) return rc;
-    } else if (n > 0) {
-        int64_t g = ceil_div(n, int64_t(kGbNT) * 64);
-        if (g > 2048) g = 2048;
-        const size_t lds = size_t(nagg + 1) * key_span * 8;
-        TQP_LAUNCH("gb_dense", k_gb_dense<KS>, dim3(unsigned(g)), dim3(kGbNT), lds, s, ks, n, d_n,
-                   key_lo, key_span, args, gacc);
+    if (n > 0) {
+        const size_t one = size_t(key_span) * (8 * size_t(args.nsum) + 4);
+        int lgc = 0;
+        while ((2 << lgc) <= kDenseMaxCopies && (one << (lgc + 1)) <= kDenseLds) lgc++;
+        // as many workgroups as are resident; the kernel lets as many of them
+        // work as there are rows for
+        const unsigned grid = persistent_grid(ceil_div(n, kDenseRows), 2);
+        const bool tog = args.nv <= kTogether;
+        const int nt = k.nterms;
+#define TQP_DENSE(NT, TOG)                                                                          \
+        TQP_LAUNCH("gb_dense", (k_gb_dense<NT, TOG>), dim3(grid), dim3(kDenseNT), one << lgc, s, k, n,   \
+                   d_n, key_lo, int(key_span), lgc, args, gacc)
+        if (tog && nt == 1) TQP_DENSE(1, true);
+        else if (tog && nt == 2) TQP_DENSE(2, true);
+        else if (tog) TQP_DENSE(4, true);
+        else if (nt <= 2) TQP_DENSE(2, false);
+        else TQP_DENSE(4, false);
+#undef TQP_DENSE
         if ((rc = check_launch("group-by dense"))) return rc;
     }
     TQP_LAUNCH("gb_dense_emit", k_gb_dense_emit<OK>, dim3(1), dim3(1024), 0, s, gacc, key_lo,
-               key_span, nagg, out_key, out_cap, o[0], o[1], o[2], o[3], d_ngroups);
+               key_span, args, out_key, out_cap, o[0], o[1], o[2], o[3], d_ngroups);
     return check_launch("group-by dense emit");
 }
 
@@ -672,10 +700,16 @@ static int groupby_typed(const tqp_col *key, const int64_t *d_n, uint32_t flags,
     int64_t *o[4] = {nullptr, nullptr, nullptr, nullptr};
     for (int g = 0; g < nagg; g++) o[g] = out_aggs[g];
     int rc;
-    if (dense_ok(flags, key_span, nagg))
-        return dense_groupby<K>(ColKeys<K>{static_cast<const K *>(key->data)}, n, d_n, key_lo,
-                                key_span, args, L.gacc, static_cast<K *>(out_key->data),
-                                out_key->len, o, d_ngroups, s);
+    if (dense_ok(flags, key_span, nagg)) {
+        PackArgs p = {};
+        p.col[0] = key->data;
+        p.len[0] = n;
+        p.mul[0] = 1;
+        p.dt[0] = key->dtype;
+        p.nterms = 1;
+        return dense_groupby<K>(p, n, d_n, key_lo, key_span, args, L.gacc,
+                                static_cast<K *>(out_key->data), out_key->len, o, d_ngroups, s);
+    }
     const K *k = static_cast<const K *>(key->data);
     AggArgs a = args;
     if (!(flags & TQP_GB_SORTED)) {
@@ -693,37 +727,31 @@ static int groupby_typed(const tqp_col *key, const int64_t *d_n, uint32_t flags,
         k = static_cast<const K *>(L.skey);
         a.val_rows = L.srows;
     }
-    rc = fill_u64(L.words, 0, L.nwords, s);
-    if (rc) return rc;
-    const unsigned grid = persistent_grid(L.ntiles, tune(kTuneGbScanPerCu));
     K *ok = static_cast<K *>(out_key->data);
-    const int64_t es = n > 0 ? n : int64_t(1);
-    uint32_t *tk = reinterpret_cast<uint32_t *>(L.words);
-    switch (nagg) {
-    case 1:
-        TQP_LAUNCH("gb_scan", (k_gb_scan<K, 1>), dim3(grid), dim3(kGbNT), 0, s, k, n, d_n, a, ok,
-                   out_key->len, L.ends, es, d_ngroups, tk, L.words + 1);
-        break;
-    case 2:
-        TQP_LAUNCH("gb_scan", (k_gb_scan<K, 2>), dim3(grid), dim3(kGbNT), 0, s, k, n, d_n, a, ok,
-                   out_key->len, L.ends, es, d_ngroups, tk, L.words + 1);
-        break;
-    case 3:
-        TQP_LAUNCH("gb_scan", (k_gb_scan<K, 3>), dim3(grid), dim3(kGbNT), 0, s, k, n, d_n, a, ok,
-                   out_key->len, L.ends, es, d_ngroups, tk, L.words + 1);
-        break;
-    default:
-        TQP_LAUNCH("gb_scan", (k_gb_scan<K, 4>), dim3(grid), dim3(kGbNT), 0, s, k, n, d_n, a, ok,
-                   out_key->len, L.ends, es, d_ngroups, tk, L.words + 1);
-        break;
+    GbOut out = {};
+    out.cap = out_key->len;
+    for (int g = 0; g < nagg; g++) out.agg[g] = o[g];
+    TQP_LAUNCH("gb_heads", k_gb_heads<K>, dim3(persistent_grid(L.nblocks, 4)), dim3(kGbNT), 0, s, k, n, d_n,
+               L.bcnt);
+    if ((rc = check_launch("group-by heads"))) return rc;
+    const unsigned grid = persistent_grid(L.nblocks, tune(kTuneGbScanPerCu));
+#define TQP_SCAN(NSUM, TOG)                                                                         \
+    TQP_LAUNCH("gb_scan", (k_gb_runs<K, NSUM, TOG>), dim3(grid), dim3(kGbNT), 0, s, k, n, d_n, a, ok, out, \
+               d_ngroups, L.bcnt, L.edges)
+    const bool tog = a.nv <= kTogether;
+    switch (a.nsum) {
+    case 0: TQP_SCAN(0, true); break;
+    case 1: TQP_SCAN(1, true); break;                    // one sum names at most two columns
+    case 2: if (tog) TQP_SCAN(2, true); else TQP_SCAN(2, false); break;
+    case 3: if (tog) TQP_SCAN(3, true); else TQP_SCAN(3, false); break;
+    default: if (tog) TQP_SCAN(4, true); else TQP_SCAN(4, false); break;
     }
-    if ((rc = check_launch("group-by scan"))) return rc;
-    int64_t g = ceil_div(out_key->len > 0 ? out_key->len : 1, 256);
-    if (g > 4096) g = 4096;
-    TQP_LAUNCH("gb_diff", k_gb_diff, dim3(unsigned(g)), dim3(256), 0, s, L.ends,
-                       n > 0 ? n : int64_t(1), nagg, d_ngroups, out_key->len, o[0], o[1], o[2],
-                       o[3]);
-    return check_launch("group-by diff");
+#undef TQP_SCAN
+    if ((rc = check_launch("group-by runs"))) return rc;
+    if (L.nblocks == 1) return TQP_OK;                   // one block has no edges
+    TQP_LAUNCH("gb_edges", k_gb_edges, dim3(unsigned(ceil_div(L.nblocks, 256))), dim3(256), 0, s, n, d_n, nagg,
+               out, L.edges);
+    return check_launch("group-by edges");
 }
 
 }  // namespace tqp
@@ -742,10 +770,19 @@ static int agg_args(const tqp_col *vals, int nvals, const int32_t *val_rows, con
             return set_error(TQP_EINVAL, "%s: value column %d is invalid or unaligned", who, c);
         if (!val_rows && vals[c].len < n)
             return set_error(TQP_EINVAL, "%s: value column %d is shorter than keys", who, c);
-        a->val[c] = vals[c].data;
-        a->vlen[c] = vals[c].len;
-        a->vdt[c] = vals[c].dtype;
     }
+    // the distinct columns the sums name, in order of first use
+    const int64_t most = int64_t(1) << 31;
+    auto slot = [&](int c) {
+        const int64_t l = vals[c].len;
+        const uint32_t len = uint32_t(l < 0 ? 0 : l < most ? l : most);
+        for (int v = 0; v < a->nv; v++)
+            if (a->val[v] == vals[c].data && a->vdt[v] == vals[c].dtype && a->vlen[v] == len) return v;
+        a->val[a->nv] = vals[c].data;
+        a->vdt[a->nv] = vals[c].dtype;
+        a->vlen[a->nv] = len;
+        return int(a->nv++);
+    };
     for (int g = 0; g < nagg; g++) {
         const tqp_agg &x = aggs[g];
         if (x.op < TQP_AGG_SUM || x.op > TQP_AGG_SUM_DIFF_PRODUCT)
@@ -755,10 +792,14 @@ static int agg_args(const tqp_col *vals, int nvals, const int32_t *val_rows, con
         if (x.op >= TQP_AGG_SUM_PRODUCT && (x.b < 0 || x.b >= nvals))
             return set_error(TQP_EINVAL, "%s: aggregate %d names a missing column", who, g);
         if (out_cap > 0 && !out_aggs[g]) return set_error(TQP_EINVAL, "%s: output %d is null", who, g);
-        a->op[g] = x.op;
-        a->ia[g] = x.a;
-        a->ib[g] = x.b;
-        a->ic[g] = x.c;
+        a->src[g] = -1;
+        if (x.op == TQP_AGG_COUNT) continue;
+        const int t = a->nsum++;
+        a->src[g] = t;
+        a->op[t] = x.op;
+        a->sa[t] = slot(x.a);
+        a->sb[t] = x.op >= TQP_AGG_SUM_PRODUCT ? slot(x.b) : -1;
+        a->ic[t] = x.c;
     }
     if (val_rows && !col_aligned(val_rows, TQP_INT32))
         return set_error(TQP_EINVAL, "%s: val_rows must be 4-byte aligned", who);
@@ -865,10 +906,10 @@ TQP_API int tqp_groupby_agg_terms(const tqp_keyterm *terms, int nterms, int64_t 
     hipStream_t s = as_stream(stream);
     unsigned long long *gacc = static_cast<unsigned long long *>(ws);
     if (out_key->dtype == TQP_INT32)
-        return dense_groupby<int32_t>(TermKeys{p}, n, d_n, key_lo, key_span, a, gacc,
+        return dense_groupby<int32_t>(p, n, d_n, key_lo, key_span, a, gacc,
                                       static_cast<int32_t *>(out_key->data), out_key->len, o,
                                       d_ngroups, s);
-    return dense_groupby<int64_t>(TermKeys{p}, n, d_n, key_lo, key_span, a, gacc,
+    return dense_groupby<int64_t>(p, n, d_n, key_lo, key_span, a, gacc,
                                   static_cast<int64_t *>(out_key->data), out_key->len, o,
                                   d_ngroups, s);
 }
