@@ -121,12 +121,10 @@ void tqp_profile_reset(void);
 /* Launch knobs, the control surface of the autotuner (an extension of this
  * library; the paper tunes nothing at this level).  Each knob is an integer in a
  * fixed range with a default: "filter.per_cu", "sort.per_cu", "rle.per_cu",
- * "match.per_cu", "gbscan.per_cu" are workgroups per compute unit of one
- * persistent kernel's grid; "part.ovf_cap" is how many overflowing buckets
+ * "match.per_cu", "gbscan.per_cu" scale one kernel's grid per compute unit; "part.ovf_cap" is how many overflowing buckets
  * tqp_partition_sort re-sorts before it sorts the whole input instead;
- * "sort.mode" picks how a radix pass finds where each tile's digit runs go:
- * 0 = decoupled look-back over earlier tiles, 1 = every tile's digit counts
- * first, then a scan per digit (one more read of the keys, no waiting);
+ * "sort.mode" is accepted for settings saved earlier and changes nothing
+ * (its two ways of finding where a tile's digit runs go are one now);
  * "semijoin.wg" is tqp_semijoin's workgroup size in units of 256 threads
  * (1, 2 or 4; a larger workgroup takes a larger tile) and "semijoin.per_cu"
  * its threads per compute unit in the same units.

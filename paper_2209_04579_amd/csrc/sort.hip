@@ -18,7 +18,7 @@ size_t sort_ws_bytes(int64_t n, int dtype, int key_bits) { return sort_ws_bytes(
 
 static int sort_cols_impl(const void *key_in, int dtype, int64_t n, const int64_t *d_n, int key_bits,
                           int64_t key_min, void *key_out, const SortCols &sc, void *ws,
-                          size_t ws_bytes, hipStream_t s, const PassPred *pred = nullptr,
+                          size_t ws_bytes, hipStream_t s, const RowTests *pred = nullptr,
                           int64_t *d_kept = nullptr) {
     const int width = dtype == TQP_INT32 ? 32 : 64;
     if (key_bits > width) key_bits = width;
@@ -138,16 +138,11 @@ TQP_API int tqp_filter_sort(const tqp_col *cols, int ncols, const tqp_pred *pred
         if (!dtype_ok(cols[c].dtype) || cols[c].len < n || (n > 0 && !cols[c].data) ||
             !col_aligned(cols[c].data, cols[c].dtype))
             return set_error(TQP_EINVAL, "tqp_filter_sort: column %d has a bad dtype, length or pointer", c);
-    PassPred f = {};
-    for (int q = 0; q < npred; q++) {
+    for (int q = 0; q < npred; q++)
         if (preds[q].col < 0 || preds[q].col >= ncols || preds[q].op < TQP_LT || preds[q].op > TQP_NE)
             return set_error(TQP_EINVAL, "tqp_filter_sort: predicate %d is invalid", q);
-        f.col[q] = cols[preds[q].col].data;
-        f.dt[q] = cols[preds[q].col].dtype;
-        f.op[q] = preds[q].op;
-        f.lit[q] = preds[q].literal;
-    }
-    f.npred = npred;
+    RowTests f;
+    build_tests(cols, preds, npred, &f);
     if (npay < 0 || npay > kMaxSortPay || (npay > 0 && (!pay_in || !pay_out)))
         return set_error(TQP_EINVAL, "tqp_filter_sort: npay must be in [0, %d] with both arrays",
                          kMaxSortPay);

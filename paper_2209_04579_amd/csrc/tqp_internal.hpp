@@ -55,13 +55,13 @@ constexpr int kComputeUnits = 256;
 // Tuning knobs (set through tqp_tune_set, read at launch time on the host).
 enum TuneKnob {
     kTuneFilterPerCu = 0,   // workgroups per CU of the filter's persistent grid
-    kTuneSortPerCu,         // ... of each radix pass
+    kTuneSortPerCu,         // eighths of the grid per CU of a radix pass whose count is on the device
     kTuneRlePerCu,          // ... of run-length encoding
     kTuneMatchPerCu,        // ... of the join match
     kTuneGbScanPerCu,       // ... of the sorted group-by scan
     kTunePartOvfCap,        // overflowing buckets a partition sort re-sorts before it
                             // sorts the whole input instead
-    kTuneSortMode,          // radix pass: 0 = decoupled look-back, 1 = tile counts + scan
+    kTuneSortMode,          // no effect (kept for saved settings)
     kTuneSemiPerCu,         // 256-thread units per CU of the semi-join scan
     kTuneSemiWg,            // its workgroup size, in 256-thread units (1, 2, 4)
     kTuneCount
@@ -171,19 +171,43 @@ template <> __device__ __forceinline__ int64_t shfl<int64_t>(int64_t v, int src)
 }
 
 // Inclusive prefix sum across the 64 lanes of a wave (wrapping arithmetic).
-template <class T> __device__ __forceinline__ T wave_incl_scan(T v) {
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        T u = shfl_up(v, d);
-        if (lane_id() >= d) v += u;
-    }
+// 32-bit values stay in the vector unit: shifts inside rows of 16 lanes, then
+// the last lane of row 0 (2) added to row 1 (3) and lane 31 to the upper half.
+// (A shuffle through LDS per step takes about ten times as long.)
+template <int Ctrl, int RowMask> __device__ __forceinline__ uint32_t dpp_add(uint32_t v) {
+    return v + uint32_t(__builtin_amdgcn_update_dpp(0, int(v), Ctrl, RowMask, 0xf, false));
+}
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
+    v = dpp_add<0x111, 0xf>(v);          // row_shr:1, 2, 4, 8
+    v = dpp_add<0x112, 0xf>(v);
+    v = dpp_add<0x114, 0xf>(v);
+    v = dpp_add<0x118, 0xf>(v);
+    v = dpp_add<0x142, 0xa>(v);          // row_bcast:15 into rows 1 and 3
+    v = dpp_add<0x143, 0xc>(v);          // row_bcast:31 into rows 2 and 3
     return v;
 }
-
-template <class T> __device__ __forceinline__ T wave_sum(T v) {
+template <class T> __device__ __forceinline__ T wave_incl_scan(T v) {
+    if constexpr (sizeof(T) == 4) {
+        return T(wave_incl_scan_u32(uint32_t(v)));
+    } else {
 #pragma unroll
-    for (int m = 1; m < kWave; m <<= 1) v += shfl_xor(v, m);
-    return v;
+        for (int d = 1; d < kWave; d <<= 1) {
+            T u = shfl_up(v, d);
+            if (lane_id() >= d) v += u;
+        }
+        return v;
+    }
+}
+
+// Sum over the 64 lanes, in every lane.
+template <class T> __device__ __forceinline__ T wave_sum(T v) {
+    if constexpr (sizeof(T) == 4) {
+        return T(__builtin_amdgcn_readlane(int(wave_incl_scan_u32(uint32_t(v))), kWave - 1));
+    } else {
+#pragma unroll
+        for (int m = 1; m < kWave; m <<= 1) v += shfl_xor(v, m);
+        return v;
+    }
 }
 
 // Exclusive prefix sum across a block of NT threads.  `lds` holds NT/64
