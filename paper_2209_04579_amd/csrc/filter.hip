@@ -416,7 +416,7 @@ TQP_API int tqp_filter(const tqp_col *cols, int ncols, const tqp_pred *preds, in
     a.d_count = d_count;
     hipStream_t s = as_stream(stream);
     if (n > 0) {
-        const unsigned grid = persistent_grid(L.nblocks, 2 * tune(kTuneFilterPerCu));
+        const unsigned grid = block_grid(L.nblocks);
         switch (t.ncol <= kMaxTogether ? t.ncol : 0) {
         case 1: launch_filter_mask<1>(grid, s, t, n, vec, L); break;
         case 2: launch_filter_mask<2>(grid, s, t, n, vec, L); break;
@@ -427,7 +427,7 @@ TQP_API int tqp_filter(const tqp_col *cols, int ncols, const tqp_pred *preds, in
         const int rc = check_launch("tqp_filter");
         if (rc) return rc;
     }
-    const unsigned grid = persistent_grid(L.nblocks, 8);
+    const unsigned grid = block_grid(L.nblocks);
     switch (npay < 4 ? npay : 4) {
     case 0: launch_filter_write<0>(grid, s, a, L); break;
     case 1: launch_filter_write<1>(grid, s, a, L); break;

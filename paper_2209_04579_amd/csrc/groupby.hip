@@ -731,7 +731,7 @@ static int groupby_typed(const tqp_col *key, const int64_t *d_n, uint32_t flags,
     GbOut out = {};
     out.cap = out_key->len;
     for (int g = 0; g < nagg; g++) out.agg[g] = o[g];
-    TQP_LAUNCH("gb_heads", k_gb_heads<K>, dim3(persistent_grid(L.nblocks, 4)), dim3(kGbNT), 0, s, k, n, d_n,
+    TQP_LAUNCH("gb_heads", k_gb_heads<K>, dim3(block_grid(L.nblocks, d_n)), dim3(kGbNT), 0, s, k, n, d_n,
                L.bcnt);
     if ((rc = check_launch("group-by heads"))) return rc;
     const unsigned grid = persistent_grid(L.nblocks, tune(kTuneGbScanPerCu));

@@ -1,5 +1,15 @@
 // Sort-merge inner equi-join over two ascending key columns.
 //
+// Pairs.  In the canonical order (key, i, j) the pairs of one left row are
+// consecutive and left rows follow each other, so the pairs of a tile of left
+// rows are one run of the output.  A first kernel finds each tile's window of
+// right rows and counts its pairs; a second one takes the tiles again, starts at
+// the sum of the counts before its tile, finds every left row's right rows in the
+// window (staged in LDS) and writes the pairs.  A tile with very many pairs is
+// left to a third kernel, which spreads its pairs over the chip.
+//
+// Ranges (one per matched key).
+//
 //  1. Run-length encode each sorted side: one single-pass compaction of the
 //     run heads gives (unique key, run start) and the number of runs.
 //  2. Match: for each left run, find the right run with the same key
@@ -424,6 +434,495 @@ __global__ __launch_bounds__(kJoinNT) void k_join_expand(
     }
 }
 
+// ---- pairs ---------------------------------------------------------------------
+//
+// What bounds it: reading the left keys (twice) and writing the pairs.  The
+// version before this went through the runs of both sides (run-length encoding,
+// a match of the runs with two look-backs, an expansion that searched each
+// output's range): 30M left rows against 2M unique right ones 365 -> 257 us,
+// 500K against 10K 60 -> 24, 1.5M against 400K in runs of two 86 -> 57.  The
+// searches are chains of LDS reads, so many small workgroups are kept resident.
+constexpr int kPjNT = 256;
+constexpr int kPjIPT = 8;
+constexpr int kPjTile = kPjNT * kPjIPT;            // left rows per tile
+constexpr int kPjNW = kPjNT / kWave;
+constexpr int kPjWinBytes = 15360;                 // right keys of a tile's window staged in LDS (five workgroups per CU)
+constexpr int kPjMaxSteps = 8;
+constexpr int64_t kPjDirect = 8 * kPjTile;         // pairs a tile's own workgroup writes
+constexpr int64_t kPjChunk = 32768;                // pairs per step of a larger tile
+
+// Tiles per block for nl left rows: the widest of 8, 4, 2, 1 that still gives
+// eight blocks per compute unit.  (A block's tiles share one search of the right
+// side; the same rule on the device in every kernel.)
+__host__ __device__ inline int pj_steps(int64_t nl) {
+    int st = kPjMaxSteps;
+    while (st > 1 && nl < int64_t(kPjTile) * st * 8 * kComputeUnits) st >>= 1;
+    return st;
+}
+
+struct PairArgs {
+    const void *lkey;
+    const int64_t *d_nl;
+    int64_t nl;
+    const void *rkey;
+    const int64_t *d_nr;
+    int64_t nr;
+    const int32_t *lrows, *rrows;
+    int32_t *out_l, *out_r;
+    void *out_key;
+    int64_t cap;
+    int64_t *d_count;
+    int32_t *win;            // per tile: its window [win[2t], win[2t + 1]) of right rows
+    int64_t *tpairs;         // per tile: its pairs
+    int64_t *bpairs;         // per block: its pairs
+    int64_t *toff;           // first pair of each tile on the list
+    int32_t *list;           // tiles with more than kPjDirect pairs
+    uint32_t *nlist;
+};
+
+// The first position in [lo, n) whose key is not below k (not above k: UPPER),
+// found by a whole wave: 64 probes per round trip, spread over [lo, n), then over
+// ever narrower stretches.  NEAR: the position is likely close to lo, so the
+// first stretches are short ones from lo, ever wider.
+template <bool UPPER, class K>
+__device__ __forceinline__ int64_t wave_bound(const K *p, int64_t lo, int64_t n, K k, bool near) {
+    const int lane = lane_id();
+    auto before = [&](int64_t i) { return UPPER ? !(k < p[i]) : p[i] < k; };
+    int64_t at = lo, step = kWave, hi = n;
+    while (near) {
+        const int64_t i = at + (int64_t(lane) + 1) * step - 1;
+        const bool b = i < n && before(i);
+        const uint64_t m = ballot(b);                 // ones, then zeros
+        const int c = __popcll(m);
+        at += int64_t(c) * step;
+        if (c < kWave) {
+            hi = at + step - 1 < n ? at + step - 1 : n;
+            break;
+        }
+        step *= kWave;
+    }
+    // the bound lies in [at, hi]
+    while (at < hi) {
+        const int64_t s = (hi - at + kWave - 1) / kWave;
+        const int64_t i = at + (int64_t(lane) + 1) * s - 1;
+        const bool b = i < hi && before(i);
+        const int c = __popcll(ballot(b));
+        at += int64_t(c) * s;
+        const int64_t h = at + s - 1;
+        hi = h < hi ? h : hi;
+    }
+    return at;
+}
+
+// The first position in p[0, n) that is not below k (above k: UPPER), at or after
+// lo: steps of 1, 2, 4, ... from lo, then a binary search inside the last one.
+template <bool UPPER, class K, class P>
+__device__ __forceinline__ uint32_t gallop(P p, uint32_t lo, uint32_t n, K k) {
+    uint32_t hi = lo, step = 1;
+    while (hi < n && (UPPER ? !(k < p[hi]) : p[hi] < k)) {
+        lo = hi + 1;
+        hi = lo + step;
+        step <<= 1;
+    }
+    if (hi > n) hi = n;
+    while (lo < hi) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (UPPER ? !(k < p[mid]) : p[mid] < k) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// For a thread's ascending keys: the first position in p[0, n) not below each,
+// and how many positions hold it.  The first key takes a binary search, each
+// further one starts from the one before (most are equal to it or next to it).
+// Returns how many positions hold the last key (valid or not).
+template <class K, class P>
+__device__ __forceinline__ uint32_t match_rows(P p, uint32_t n, const K (&key)[kPjIPT], uint32_t valid,
+                                           uint32_t (&pos)[kPjIPT], uint32_t (&cnt)[kPjIPT]) {
+    uint32_t at = 0, c = 0;
+    for (uint32_t hi = n; at < hi;) {
+        const uint32_t mid = (at + hi) >> 1;
+        if (p[mid] < key[0]) at = mid + 1;
+        else hi = mid;
+    }
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) {
+        if (r == 0 || key[r] != key[r > 0 ? r - 1 : 0]) {
+            if (r > 0) at = gallop<false>(p, at, n, key[r]);
+            c = 0;
+            if (at < n && p[at] == key[r])
+                c = at + 1 < n && p[at + 1] == key[r] ? gallop<true>(p, at + 2, n, key[r]) - at : 1;
+        }
+        pos[r] = at;
+        cnt[r] = (valid >> r) & 1 ? c : 0;
+    }
+    return c;
+}
+
+// A thread's rows: kPjIPT consecutive ones of the tile (past the end: the last
+// row again, its valid bit clear).
+template <class K>
+__device__ __forceinline__ uint32_t load_left(const K *lk, int64_t tile0, int64_t nl, bool vec, K (&key)[kPjIPT]) {
+    const int64_t row0 = tile0 + threadIdx.x * kPjIPT;
+    if (vec && row0 + kPjIPT <= nl) {
+        constexpr int kPer = 16 / sizeof(K);
+        const int4 *q = reinterpret_cast<const int4 *>(lk + row0);
+#pragma unroll
+        for (int j = 0; j < kPjIPT / kPer; j++) {
+            const int4 x = q[j];
+            const K *e = reinterpret_cast<const K *>(&x);
+#pragma unroll
+            for (int t = 0; t < kPer; t++) key[j * kPer + t] = e[t];
+        }
+        return (1u << kPjIPT) - 1u;
+    }
+    uint32_t valid = 0;
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) {
+        key[r] = lk[row0 + r < nl ? row0 + r : nl - 1];
+        valid |= (row0 + r < nl ? 1u : 0u) << r;
+    }
+    return valid;
+}
+
+// match_rows over a window p[0, n) too long to stage: every stride-th of its keys
+// is staged instead (nc of them), and a key's search ends in one stretch of the
+// window.  A thread's searches advance together, so a step is one round trip to
+// memory for all of them, and there are log2(stride) steps.
+template <class K>
+__device__ __forceinline__ uint32_t match_rows_far(const K *p, uint32_t n, const K *s_win, uint32_t nc,
+                                                   uint32_t stride, const K (&key)[kPjIPT], uint32_t valid,
+                                                   uint32_t (&pos)[kPjIPT], uint32_t (&cnt)[kPjIPT]) {
+    constexpr int R = kPjIPT;
+    uint32_t len[R];                                   // the position lies in [pos, pos + len]
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        pos[r] = 0;
+        len[r] = nc;
+    }
+    for (uint32_t left = nc; left > 0; left >>= 1) {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const uint32_t half = (len[r] + 1) >> 1;
+            const bool up = len[r] > 0 && s_win[pos[r] + half - 1] < key[r];
+            pos[r] += up ? half : 0;
+            len[r] = up ? len[r] - half : len[r] > 0 ? half - 1 : 0;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const bool in = pos[r] < nc;
+        pos[r] *= stride;
+        len[r] = in ? stride - 1 : n - pos[r];
+    }
+    for (uint32_t left = stride; left > 0; left >>= 1) {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const uint32_t half = (len[r] + 1) >> 1;
+            const bool up = len[r] > 0 && p[pos[r] + half - 1] < key[r];
+            pos[r] += up ? half : 0;
+            len[r] = up ? len[r] - half : len[r] > 0 ? half - 1 : 0;
+        }
+    }
+    uint32_t c = 0;
+    bool hit[R], more[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        hit[r] = pos[r] < n && p[pos[r]] == key[r];
+        more[r] = hit[r] && pos[r] + 1 < n && p[pos[r] + 1] == key[r];
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        if (r == 0 || key[r] != key[r > 0 ? r - 1 : 0])
+            c = more[r] ? gallop<true>(p, pos[r] + 2, n, key[r]) - pos[r] : hit[r] ? 1 : 0;
+        cnt[r] = (valid >> r) & 1 ? c : 0;
+    }
+    return c;
+}
+
+// The right rows of a tile's left rows in the window [wlo, wlo + wn), staged in
+// s_win whole or in part (the caller's barrier must have freed s_win).
+template <class K>
+__device__ __forceinline__ uint32_t match_tile(const K *rk, int64_t wlo, uint32_t wn, K *s_win,
+                                           const K (&key)[kPjIPT], uint32_t valid,
+                                           uint32_t (&pos)[kPjIPT], uint32_t (&cnt)[kPjIPT]) {
+    constexpr uint32_t kWin = kPjWinBytes / sizeof(K);
+    const uint32_t stride = (wn + kWin - 1) / kWin;
+    if (stride <= 1) {
+        for (uint32_t i = threadIdx.x; i < wn; i += kPjNT) s_win[i] = rk[wlo + i];
+        __syncthreads();
+        return match_rows(static_cast<const K *>(s_win), wn, key, valid, pos, cnt);
+    }
+    const uint32_t nc = wn / stride;
+    for (uint32_t i = threadIdx.x; i < nc; i += kPjNT) s_win[i] = rk[wlo + int64_t(i + 1) * stride - 1];
+    __syncthreads();
+    return match_rows_far(rk + wlo, wn, static_cast<const K *>(s_win), nc, stride, key, valid, pos, cnt);
+}
+
+// Windows and pair counts.  The tiles of a block are taken in order, the next
+// one's keys loading meanwhile; a tile's window starts where the one before found
+// its last key (a block's first tile searches the right side), and kPjAhead right
+// keys from there are staged at once: only a tile whose keys reach further
+// searches for its window's end.
+template <class K> constexpr uint32_t pj_ahead() { return 4096 / sizeof(K); }
+template <class K>
+__global__ __launch_bounds__(kPjNT) void k_pair_count(PairArgs a) {
+    __shared__ K s_win[kPjWinBytes / sizeof(K)];
+    __shared__ K s_last;
+    __shared__ int64_t s_bound;
+    __shared__ uint32_t s_end[2];                      // the last row's position and count
+    __shared__ int64_t s_sum[kPjNW];
+    const int64_t nl = count_of(a.d_nl, a.nl), nr = count_of(a.d_nr, a.nr);
+    const K *lk = static_cast<const K *>(a.lkey), *rk = static_cast<const K *>(a.rkey);
+    const bool vec = reinterpret_cast<uintptr_t>(lk) % 16 == 0;
+    const int steps = pj_steps(nl);
+    const int64_t ntiles = ceil_div(nl, kPjTile), nblocks = ceil_div(ntiles, steps);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.nlist = 0;
+    for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        const int64_t t0 = b * steps, t1 = t0 + steps < ntiles ? t0 + steps : ntiles;
+        K key[kPjIPT];
+        uint32_t valid = load_left(lk, t0 * kPjTile, nl, vec, key);
+        if (wave_id() == 0) {
+            const int64_t x = wave_bound<false>(rk, 0, nr, shfl(key[0], 0), false);
+            if (lane_id() == 0) s_bound = x;
+        }
+        __syncthreads();
+        int64_t from = s_bound, bsum = 0;
+        for (int64_t t = t0; t < t1; t++) {
+            const uint32_t left = uint32_t(nr - from);
+            uint32_t wn = left < pj_ahead<K>() ? left : pj_ahead<K>();
+            for (uint32_t i = threadIdx.x; i < wn; i += kPjNT) s_win[i] = rk[from + i];
+            if (threadIdx.x == kPjNT - 1) s_last = key[kPjIPT - 1];
+            K next[kPjIPT];
+            uint32_t nvalid = 0;
+            if (t + 1 < t1) nvalid = load_left(lk, (t + 1) * kPjTile, nl, vec, next);
+            __syncthreads();
+            uint32_t pos[kPjIPT], cnt[kPjIPT], after;  // after: positions holding the thread's last key
+            if (wn == left || s_last < s_win[wn - 1]) {
+                after = match_rows(static_cast<const K *>(s_win), wn, key, valid, pos, cnt);
+            } else {
+                if (wave_id() == 0) {
+                    const int64_t x = wave_bound<true>(rk, from + wn, nr, s_last, true);
+                    if (lane_id() == 0) s_bound = x;
+                }
+                __syncthreads();
+                wn = uint32_t(s_bound - from);
+                after = match_tile(rk, from, wn, s_win, key, valid, pos, cnt);
+            }
+            if (threadIdx.x == kPjNT - 1) {
+                s_end[0] = pos[kPjIPT - 1];
+                s_end[1] = after;
+            }
+            int64_t sum = 0;
+#pragma unroll
+            for (int r = 0; r < kPjIPT; r++) sum += cnt[r];
+            sum = wave_sum(sum);
+            if (lane_id() == 0) s_sum[wave_id()] = sum;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                int64_t x = 0;
+#pragma unroll
+                for (int w = 0; w < kPjNW; w++) x += s_sum[w];
+                a.tpairs[t] = x;
+                a.win[2 * t] = int32_t(from);
+                a.win[2 * t + 1] = int32_t(from + s_end[0] + s_end[1]);
+                bsum += x;
+            }
+            from += s_end[0];
+#pragma unroll
+            for (int r = 0; r < kPjIPT; r++) key[r] = next[r];
+            valid = nvalid;
+        }
+        if (threadIdx.x == 0) a.bpairs[b] = bsum;
+        __syncthreads();
+    }
+}
+
+struct PairOut {
+    int64_t base;            // the tile's first pair
+    int64_t row0, wlo;
+};
+
+// Writes pairs [o0, o1) of a tile, whose rows' first pairs are s_off[]: consecutive threads take consecutive pairs, each finding
+// its left row by a binary search.
+template <class K, class O>
+__device__ __forceinline__ void expand_tile(const PairArgs &a, const PairOut &t, const uint32_t *s_pos,
+                                            const O *s_off, int64_t o0, int64_t o1) {
+    const K *lk = static_cast<const K *>(a.lkey);
+    for (int64_t o = o0 + threadIdx.x; o < o1; o += kPjNT) {
+        if (t.base + o >= a.cap) return;
+        int row = 0;                                   // the last row with s_off[row] <= o
+#pragma unroll
+        for (int st = kPjTile / 2; st > 0; st >>= 1) row += int64_t(s_off[row + st]) <= o ? st : 0;
+        const int64_t i = t.row0 + row, j = t.wlo + s_pos[row] + (o - int64_t(s_off[row]));
+        if (a.out_l) a.out_l[t.base + o] = a.lrows ? a.lrows[i] : int32_t(i);
+        if (a.out_r) a.out_r[t.base + o] = a.rrows ? a.rrows[j] : int32_t(j);
+        if (a.out_key) static_cast<K *>(a.out_key)[t.base + o] = lk[i];
+    }
+}
+
+// Fills s_pos and s_off (the exclusive sums of the counts) for a tile.
+template <class O>
+__device__ __forceinline__ void tile_offsets(const uint32_t (&pos)[kPjIPT], const uint32_t (&cnt)[kPjIPT],
+                                             uint32_t *s_pos, O *s_off, O *s_scan) {
+    O sum = 0, tot;
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) {
+        s_pos[threadIdx.x * kPjIPT + r] = pos[r];
+        sum += cnt[r];
+    }
+    O ex = block_excl_scan<kPjNT>(sum, &tot, s_scan);
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) {
+        s_off[threadIdx.x * kPjIPT + r] = ex;
+        ex += cnt[r];
+    }
+    __syncthreads();
+}
+
+template <class K>
+__global__ __launch_bounds__(kPjNT, 5) void k_pair_write(PairArgs a) {
+    __shared__ K s_win[kPjWinBytes / sizeof(K)];
+    __shared__ uint32_t s_pos[kPjTile];
+    __shared__ uint32_t s_off[kPjTile];          // at most kPjDirect pairs here
+    __shared__ uint32_t s_scan[kPjNW];
+    __shared__ int64_t s_sum[kPjNW];
+    const int64_t nl = count_of(a.d_nl, a.nl);
+    const K *lk = static_cast<const K *>(a.lkey), *rk = static_cast<const K *>(a.rkey);
+    const bool vec = reinterpret_cast<uintptr_t>(lk) % 16 == 0;
+    const int steps = pj_steps(nl);
+    const int64_t ntiles = ceil_div(nl, kPjTile), nblocks = ceil_div(ntiles, steps);
+    const bool want = a.out_l || a.out_r || a.out_key;
+    const int w = wave_id(), lane = lane_id();
+    if (nblocks == 0 && blockIdx.x == 0 && threadIdx.x == 0) *a.d_count = 0;
+    int64_t base = 0, from = 0;                        // pairs of the blocks before `from`
+    for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+        int64_t part = 0;
+#pragma unroll 4
+        for (int64_t i = from + threadIdx.x; i < b; i += kPjNT) part += a.bpairs[i];
+        part = wave_sum(part);
+        __syncthreads();
+        if (lane == 0) s_sum[w] = part;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kPjNW; i++) base += s_sum[i];
+        from = b;
+        const int64_t t0 = b * steps, t1 = t0 + steps < ntiles ? t0 + steps : ntiles;
+        // the block's tiles, one per lane: pairs, window
+        int64_t tp = 0;
+        int32_t tlo = 0, thi = 0;
+        if (lane < t1 - t0) {
+            tp = a.tpairs[t0 + lane];
+            tlo = a.win[2 * (t0 + lane)];
+            thi = a.win[2 * (t0 + lane) + 1];
+        }
+        int64_t first = base;                          // the tile's first pair
+        for (int64_t t = t0; t < t1; t++) {
+            const int l = int(t - t0);
+            const int64_t total = shfl(tp, l);
+            const PairOut po = {first, t * kPjTile, shfl(tlo, l)};
+            const uint32_t wn = uint32_t(shfl(thi, l) - int32_t(po.wlo));
+            first += total;
+            if (total == 0 || !want || po.base >= a.cap) continue;
+            if (total > kPjDirect) {
+                if (threadIdx.x == 0) {
+                    a.toff[t] = po.base;
+                    a.list[atomicAdd(a.nlist, 1u)] = int32_t(t);
+                }
+                continue;
+            }
+            K key[kPjIPT];
+            const uint32_t valid = load_left(lk, po.row0, nl, vec, key);
+            uint32_t pos[kPjIPT], cnt[kPjIPT];
+            match_tile(rk, po.wlo, wn, s_win, key, valid, pos, cnt);
+            bool single = true;
+            uint32_t hits = 0;
+#pragma unroll
+            for (int r = 0; r < kPjIPT; r++) {
+                single = single && cnt[r] <= 1;
+                hits += cnt[r] ? 1 : 0;
+            }
+            if (__syncthreads_and(single)) {
+                // at most one right row each: the matched rows and their right
+                // rows are listed in LDS, consecutive threads write them
+                uint32_t tot;
+                uint32_t q = block_excl_scan<kPjNT>(hits, &tot, s_scan);
+#pragma unroll
+                for (int r = 0; r < kPjIPT; r++) {
+                    if (cnt[r]) {
+                        s_off[q] = threadIdx.x * kPjIPT + r;
+                        s_pos[q++] = pos[r];
+                    }
+                }
+                __syncthreads();
+                const uint32_t lim = uint32_t(a.cap - po.base < total ? a.cap - po.base : total);
+                const bool staged = wn <= kPjWinBytes / sizeof(K);
+#pragma unroll 4
+                for (uint32_t o = threadIdx.x; o < lim; o += kPjNT) {
+                    const int64_t i = po.row0 + s_off[o], j = po.wlo + s_pos[o];
+                    if (a.out_l) a.out_l[po.base + o] = a.lrows ? a.lrows[i] : int32_t(i);
+                    if (a.out_r) a.out_r[po.base + o] = a.rrows ? a.rrows[j] : int32_t(j);
+                    if (a.out_key)
+                        static_cast<K *>(a.out_key)[po.base + o] = staged ? s_win[s_pos[o]] : rk[j];
+                }
+            } else {
+                tile_offsets(pos, cnt, s_pos, s_off, s_scan);
+                expand_tile<K>(a, po, s_pos, s_off, 0, total);
+            }
+            __syncthreads();                           // LDS is reused by the next tile
+        }
+        if (b == nblocks - 1 && threadIdx.x == 0) *a.d_count = first;
+    }
+}
+
+// The tiles on the list, their pairs cut into chunks that are dealt to all the
+// workgroups in turn.
+template <class K>
+__global__ __launch_bounds__(kPjNT) void k_pair_large(PairArgs a) {
+    __shared__ K s_win[kPjWinBytes / sizeof(K)];
+    __shared__ uint32_t s_pos[kPjTile];
+    __shared__ int64_t s_off[kPjTile];
+    __shared__ int64_t s_scan[kPjNW];
+    __shared__ int64_t s_chunk[kPjNT + 1];             // first chunk of each of kPjNT list entries
+    const uint32_t nlist = *a.nlist;
+    if (nlist == 0) return;
+    const int64_t nl = count_of(a.d_nl, a.nl);
+    const K *lk = static_cast<const K *>(a.lkey), *rk = static_cast<const K *>(a.rkey);
+    const bool vec = reinterpret_cast<uintptr_t>(lk) % 16 == 0;
+    int64_t carry = 0;                                 // chunks of the entries before
+    for (uint32_t e0 = 0; e0 < nlist; e0 += kPjNT) {
+        const uint32_t e = e0 + threadIdx.x;
+        const int64_t n = e < nlist ? ceil_div(a.tpairs[a.list[e]], kPjChunk) : 0;
+        int64_t tot;
+        const int64_t ex = block_excl_scan<kPjNT>(n, &tot, s_scan);
+        s_chunk[threadIdx.x] = ex;
+        if (threadIdx.x == 0) s_chunk[kPjNT] = tot;
+        __syncthreads();
+        // this workgroup's chunks: those with (carry + c) % gridDim.x == blockIdx.x
+        int64_t c = int64_t(blockIdx.x) - carry % gridDim.x;
+        if (c < 0) c += gridDim.x;
+        for (; c < tot; c += gridDim.x) {
+            int x = 0;                                 // the last entry with s_chunk[x] <= c
+#pragma unroll
+            for (int st = kPjNT / 2; st > 0; st >>= 1) x += s_chunk[x + st] <= c ? st : 0;
+            const int64_t t = a.list[e0 + x];
+            const int64_t o0 = (c - s_chunk[x]) * kPjChunk, total = a.tpairs[t];
+            const PairOut po = {a.toff[t], t * kPjTile, a.win[2 * t]};
+            if (po.base + o0 >= a.cap) continue;       // (the same for the workgroup)
+            K key[kPjIPT];
+            const uint32_t valid = load_left(lk, po.row0, nl, vec, key);
+            uint32_t pos[kPjIPT], cnt[kPjIPT];
+            match_tile(rk, po.wlo, uint32_t(a.win[2 * t + 1] - po.wlo), s_win, key, valid, pos, cnt);
+            tile_offsets(pos, cnt, s_pos, s_off, s_scan);
+            expand_tile<K>(a, po, s_pos, s_off, o0, o0 + kPjChunk < total ? o0 + kPjChunk : total);
+            __syncthreads();
+        }
+        carry += tot;
+        __syncthreads();
+    }
+}
+
 struct JoinLayout {
     void *sl_key, *sr_key;
     int32_t *sl_rows, *sr_rows;
@@ -441,6 +940,11 @@ struct JoinLayout {
     uint64_t *words;         // tickets + statuses
     int64_t nwords;
     uint64_t *stL, *stR, *stM, *stP;
+    // pairs without ranges
+    int32_t *win;
+    int64_t *tpairs, *bpairs, *toff;
+    int32_t *list;
+    uint32_t *nlist;
     size_t bytes;
 };
 
@@ -457,6 +961,17 @@ static JoinLayout join_layout(void *ws, int64_t nl, int64_t nr, int dtype, uint3
         const int64_t nmax = nl > nr ? nl : nr;
         L.sort_ws_bytes = sort_ws_bytes(nmax, dtype, ks * 8);
         L.sort_ws = c.take<char>(L.sort_ws_bytes);
+    }
+    if (!(flags & TQP_JOIN_RANGES)) {
+        const size_t nt = size_t(ceil_div(nl > 0 ? nl : 1, kPjTile));
+        L.win = c.take<int32_t>(2 * nt);
+        L.tpairs = c.take<int64_t>(nt);
+        L.bpairs = c.take<int64_t>(nt);
+        L.toff = c.take<int64_t>(nt);
+        L.list = c.take<int32_t>(nt);
+        L.nlist = c.take<uint32_t>(1);
+        L.bytes = c.bytes();
+        return L;
     }
     L.uL = c.take<char>(size_t(nl > 0 ? nl : 1) * ks);
     L.sL = c.take<int32_t>(size_t(nl > 0 ? nl : 1));
@@ -514,6 +1029,39 @@ static int join_typed(const tqp_col *lkey, const int32_t *lrows, const int64_t *
         rk = static_cast<const K *>(L.sr_key);
         lrows = L.sl_rows;
         rrows = L.sr_rows;
+    }
+    if (!(flags & TQP_JOIN_RANGES)) {
+        PairArgs p = {};
+        p.lkey = lk;
+        p.d_nl = d_nl;
+        p.nl = nl;
+        p.rkey = rk;
+        p.d_nr = d_nr;
+        p.nr = nr;
+        p.lrows = lrows;
+        p.rrows = rrows;
+        p.cap = cap;
+        if (want_pairs) {
+            p.out_l = out_l;
+            p.out_r = out_r;
+            p.out_key = out_pair_key;
+        }
+        p.d_count = d_count;
+        p.win = L.win;
+        p.tpairs = L.tpairs;
+        p.bpairs = L.bpairs;
+        p.toff = L.toff;
+        p.list = L.list;
+        p.nlist = L.nlist;
+        const int64_t nt = ceil_div(nl, kPjTile);
+        TQP_LAUNCH("pair_count", k_pair_count<K>, dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
+        if ((rc = check_launch("join pair counts"))) return rc;
+        TQP_LAUNCH("pair_write", k_pair_write<K>, dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
+        if ((rc = check_launch("join pairs"))) return rc;
+        // a tile of nl rows has at most nl * nr pairs
+        if (!want_pairs || (nl < kPjTile ? nl : kPjTile) * nr <= kPjDirect) return TQP_OK;
+        TQP_LAUNCH("pair_large", k_pair_large<K>, dim3(unsigned(kComputeUnits * 4)), dim3(kPjNT), 0, s, p);
+        return check_launch("join large tiles");
     }
     rc = fill_u64(L.words, 0, L.nwords, s);
     if (rc) return rc;

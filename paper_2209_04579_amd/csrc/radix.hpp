@@ -568,7 +568,6 @@ int run_radix(const K *key_in, int64_t n, const int64_t *d_n, int bits, Ord ord,
     const int64_t ntiles = ceil_div(n > 0 ? n : 1, kSortTile);
     // every XCD's tiles have their workgroups
     const int64_t turns = ceil_div(ntiles, int64_t(kXcds) * kTileGroup) * kXcds * kTileGroup;
-    const unsigned grid_count = persistent_grid(ntiles, 4);
     PassCols pc = {};
     for (int p = 0; p < sc.npay; p++) {
         pc.pin[p] = sc.pin[p];
@@ -613,6 +612,7 @@ int run_radix(const K *key_in, int64_t n, const int64_t *d_n, int bits, Ord ord,
         const int shift = p * dbits;
         const bool filt = pred && p == 0;
         const int64_t *cn = filt ? nullptr : pass_n;
+        const unsigned grid_count = block_grid(max_tile_groups(ntiles), cn);
 #define TQP_COUNT(ND, T, VEC, KEEP)                                                                  \
         TQP_LAUNCH("radix_count", (k_radix_count<K, Ord, ND>), dim3(grid_count), dim3(kCountNT), 0, s, src_k, n, \
                    cn, ord, shift, dbits, counts, csum, T, VEC, KEEP)

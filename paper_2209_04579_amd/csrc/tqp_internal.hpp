@@ -74,6 +74,16 @@ inline unsigned persistent_grid(int64_t tiles, int per_cu) {
     return unsigned(g > 0 ? g : 1);
 }
 
+// Grid of a kernel over independent blocks of work: a workgroup per block, so
+// that the hardware deals them out as compute units become free (a grid a little
+// above what is resident at once would leave a second, nearly empty wave of
+// workgroups).  Fewer, each looping, when there are very many blocks, or when
+// the actual count is on the device and may need far fewer than the capacity.
+inline unsigned block_grid(int64_t blocks, const void *d_n = nullptr) {
+    const int64_t most = d_n ? 4096 : 8192;
+    return unsigned(blocks < 1 ? 1 : blocks < most ? blocks : most);
+}
+
 // Per-kernel timing (see profile.hip).  A scope records one event before and
 // one after the launches it encloses, on the launch stream, when enabled.
 bool profile_on();
