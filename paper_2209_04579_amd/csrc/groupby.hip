@@ -613,7 +613,6 @@ __global__ __launch_bounds__(1024) void k_gb_dense_emit(const unsigned long long
 }
 
 struct GbLayout {
-    int64_t *scratch;
     void *skey;
     int32_t *srows;
     void *sort_ws;
@@ -634,7 +633,6 @@ static GbLayout gb_layout(void *ws, int64_t n, int dtype, int nagg, uint32_t fla
     GbLayout L = {};
     Carver c(ws);
     const int ks = dtype_size(dtype);
-    L.scratch = c.take<int64_t>(2);
     if (dense_ok(flags, span, nagg)) {
         L.gacc = c.take<unsigned long long>(size_t(nagg + 1) * span);
         L.bytes = c.bytes();
@@ -718,7 +716,8 @@ static int groupby_typed(const tqp_col *key, const int64_t *d_n, uint32_t flags,
         if (key_span > 0) {
             while (kbits < 64 && (uint64_t(key_span - 1) >> kbits) != 0) kbits++;
         } else {
-            rc = derive_key_range(k, key->dtype, n, d_n, L.scratch, s, &kmin, &kbits);
+            rc = derive_key_range(k, key->dtype, n, d_n, L.sort_ws, L.sort_ws_bytes, s, &kmin,
+                                  &kbits);
             if (rc) return rc;
         }
         rc = sort_impl(k, key->dtype, args.val_rows, n, d_n, kbits, kmin, L.skey, L.srows,

@@ -1013,16 +1013,18 @@ static int join_typed(const tqp_col *lkey, const int32_t *lrows, const int64_t *
     const K *rk = static_cast<const K *>(rkey->data);
     int rc;
     if (!(flags & TQP_JOIN_SORTED)) {
-        int64_t kmin;
-        int kbits;
-        rc = derive_key_range(lk, lkey->dtype, nl, d_nl, L.sort_ws, s, &kmin, &kbits);
+        int64_t kmin[2];
+        int kbits[2];
+        const void *keys[2] = {lk, rk};
+        const int64_t ns[2] = {nl, nr};
+        const int64_t *const d_ns[2] = {d_nl, d_nr};
+        rc = derive_key_ranges(keys, lkey->dtype, ns, d_ns, L.sort_ws, L.sort_ws_bytes, s, kmin,
+                               kbits);
         if (rc) return rc;
-        rc = sort_impl(lk, lkey->dtype, lrows, nl, d_nl, kbits, kmin, L.sl_key, L.sl_rows,
+        rc = sort_impl(lk, lkey->dtype, lrows, nl, d_nl, kbits[0], kmin[0], L.sl_key, L.sl_rows,
                        L.sort_ws, L.sort_ws_bytes, s);
         if (rc) return rc;
-        rc = derive_key_range(rk, rkey->dtype, nr, d_nr, L.sort_ws, s, &kmin, &kbits);
-        if (rc) return rc;
-        rc = sort_impl(rk, rkey->dtype, rrows, nr, d_nr, kbits, kmin, L.sr_key, L.sr_rows,
+        rc = sort_impl(rk, rkey->dtype, rrows, nr, d_nr, kbits[1], kmin[1], L.sr_key, L.sr_rows,
                        L.sort_ws, L.sort_ws_bytes, s);
         if (rc) return rc;
         lk = static_cast<const K *>(L.sl_key);

@@ -1550,7 +1550,6 @@ TQP_API size_t tqp_partition_sort_workspace_bytes(int64_t n, int dtype, int buck
     if (n < 0 || (dtype != TQP_INT32 && dtype != TQP_INT64) || bucket_bits < 1 || bucket_bits > 24)
         return 0;
     Carver c(nullptr);
-    c.take<int64_t>(2);
     c.take<char>(part_layout(nullptr, n, dtype_size(dtype), bucket_bits).bytes);
     return c.bytes();
 }
@@ -1582,10 +1581,10 @@ TQP_API int tqp_partition_sort(const tqp_col *key, const int32_t *in_rows, uint3
     }
     hipStream_t s = as_stream(stream);
     Carver c(ws);
-    void *scratch = c.take<int64_t>(2);
     void *pws = c.take<char>(part_layout(nullptr, n, dtype_size(key->dtype), bucket_bits).bytes);
     if (mode == TQP_PART_RADIX && key_bits == 0) {
-        int rc = derive_key_range(key->data, key->dtype, n, nullptr, scratch, s, &key_min, &key_bits);
+        int rc = derive_key_range(key->data, key->dtype, n, nullptr, ws, ws_bytes, s, &key_min,
+                                  &key_bits);
         if (rc) return rc;
     }
     const int shift = key_bits > bucket_bits ? key_bits - bucket_bits : 0;

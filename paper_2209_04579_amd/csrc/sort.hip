@@ -9,7 +9,6 @@ namespace tqp {
 
 size_t sort_ws_bytes(int64_t n, int dtype, int key_bits, int pay_bytes) {
     Carver c(nullptr);
-    c.take<int64_t>(2);                                   // key-range scratch
     c.take<char>(radix_ws_bytes(n, dtype_size(dtype), npass_for(key_bits), pay_bytes));
     return c.bytes();
 }
@@ -28,15 +27,12 @@ static int sort_cols_impl(const void *key_in, int dtype, int64_t n, const int64_
     const size_t need = sort_ws_bytes(n, dtype, key_bits, pay_bytes);
     if (!ws || ws_bytes < need)
         return set_error(TQP_ECAPACITY, "sort: workspace needs %zu bytes", need);
-    Carver cv(ws);
-    cv.take<int64_t>(2);
-    void *rws = cv.take<char>(radix_ws_bytes(n, dtype_size(dtype), npass_for(key_bits), pay_bytes));
     if (dtype == TQP_INT32)
         return run_radix<int32_t>(static_cast<const int32_t *>(key_in), n, d_n, key_bits,
                                   KeyOrd<int32_t>{int32_t(key_min)},
-                                  static_cast<int32_t *>(key_out), sc, rws, s, pred, d_kept);
+                                  static_cast<int32_t *>(key_out), sc, ws, s, pred, d_kept);
     return run_radix<int64_t>(static_cast<const int64_t *>(key_in), n, d_n, key_bits,
-                              KeyOrd<int64_t>{key_min}, static_cast<int64_t *>(key_out), sc, rws, s,
+                              KeyOrd<int64_t>{key_min}, static_cast<int64_t *>(key_out), sc, ws, s,
                               pred, d_kept);
 }
 
@@ -101,7 +97,8 @@ TQP_API int tqp_sort(const tqp_col *key, const int32_t *in_rows, int64_t n, cons
     if (n == 0) return TQP_OK;
     hipStream_t s = as_stream(stream);
     if (key_bits == 0) {
-        int rc = derive_key_range(key->data, key->dtype, n, d_n, ws, s, &key_min, &key_bits);
+        int rc = derive_key_range(key->data, key->dtype, n, d_n, ws, ws_bytes, s, &key_min,
+                                  &key_bits);
         if (rc) return rc;
     }
     return sort_cols_impl(key->data, key->dtype, n, d_n, key_bits, key_min, out_key->data, sc, ws,
@@ -168,7 +165,8 @@ TQP_API int tqp_filter_sort(const tqp_col *cols, int ncols, const tqp_pred *pred
     if (n == 0) return fill_u64(d_count, 0, 1, s);
     if (key_bits == 0) {
         // the range of all n keys bounds the range of the kept ones
-        int rc = derive_key_range(key->data, key->dtype, n, nullptr, ws, s, &key_min, &key_bits);
+        int rc = derive_key_range(key->data, key->dtype, n, nullptr, ws, ws_bytes, s, &key_min,
+                                  &key_bits);
         if (rc) return rc;
     }
     if (key_bits < 1) key_bits = 1;       // the first pass also compacts, so one always runs

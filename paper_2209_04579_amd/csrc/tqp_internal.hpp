@@ -131,9 +131,14 @@ int sort_impl(const void *key_in, int dtype, const int32_t *rows_in, int64_t n,
               int32_t *rows_out, void *ws, size_t ws_bytes, hipStream_t s);
 size_t sort_ws_bytes(int64_t n, int dtype, int key_bits);
 size_t sort_ws_bytes(int64_t n, int dtype, int key_bits, int pay_bytes);
-// Host-synchronizing derivation of (key_min, key_bits) for a column.
-int derive_key_range(const void *key, int dtype, int64_t n, const int64_t *d_n,
-                     void *scratch16, hipStream_t s, int64_t *key_min, int *key_bits);
+// Host-synchronizing derivation of (key_min, key_bits) for a column.  Faster with
+// more scratch, to 8 KiB per column; 16 bytes per column are enough.
+int derive_key_range(const void *key, int dtype, int64_t n, const int64_t *d_n, void *scratch,
+                     size_t scratch_bytes, hipStream_t s, int64_t *key_min, int *key_bits);
+// The same for two columns of one type, with one launch and one read-back.
+int derive_key_ranges(const void *const key[2], int dtype, const int64_t n[2],
+                      const int64_t *const d_n[2], void *scratch, size_t scratch_bytes,
+                      hipStream_t s, int64_t key_min[2], int key_bits[2]);
 
 // ---- device side --------------------------------------------------------
 
