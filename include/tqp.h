@@ -126,7 +126,7 @@ void tqp_profile_reset(void);
  * "sort.mode" is accepted for settings saved earlier and changes nothing
  * (its two ways of finding where a tile's digit runs go are one now);
  * "semijoin.wg" is tqp_semijoin's workgroup size in units of 256 threads
- * (1, 2 or 4; a larger workgroup takes a larger tile) and "semijoin.per_cu"
+ * (1, 2 or 4) and "semijoin.per_cu"
  * its threads per compute unit in the same units.
  * Knobs change how the work is done, never results.  They are process-wide
  * and read when a call enqueues its kernels; setting them concurrently with
@@ -345,7 +345,9 @@ int tqp_join(const tqp_col *lkey, const int32_t *lrows, const int64_t *d_nl,
  * Sets are staged in on-chip memory while they fit (up to 36864 words in all
  * with 1024-thread workgroups, a quarter of that per 256 threads with
  * smaller ones); the others are read from device memory.  Workspace:
- * tqp_semijoin_workspace_bytes(n, key dtype).  Nothing is synchronized.
+ * tqp_semijoin_workspace_bytes(n, key dtype), about one key per row (keep
+ * bits, and the kept rows' keys where at most a quarter is kept).  Nothing is
+ * synchronized.
  * ---------------------------------------------------------------------- */
 #define TQP_KEYSET_MAX_BITS (1ll << 36)
 typedef struct {
@@ -365,11 +367,10 @@ int tqp_semijoin(const tqp_col *keys, const tqp_keyset *sets, int nsets,
  * tqp_semijoin_noalloc -- tqp_semijoin without a workspace argument, for
  * callers that cannot allocate device memory (code under HIP graph capture,
  * serving loops, harnesses that forbid allocation).  Same arguments, results
- * and errors as tqp_semijoin; its tickets and look-back statuses live in a
- * static 8 MiB device array of the library (one per device, held until the
- * process ends, located on the first call on each device), cleared by a
- * kernel at the start of every call.  It allocates nothing and calls no
- * allocating routine.  Tables of more than
+ * and errors as tqp_semijoin; the table is taken in parts of 2^25 rows, whose
+ * keep bits and counts live in a static 8 MiB device array of the library
+ * (one per device, held until the process ends, located on the first call on
+ * each device).  It allocates nothing and calls no allocating routine.  Tables of more than
  * tqp_semijoin_noalloc_max_rows(dtype) rows (every int32 table up to
  * 2^31 - 1 rows; about 1.6e9 rows of int64 keys) are rejected with
  * TQP_ECAPACITY.  All calls on one device share the array: calls that

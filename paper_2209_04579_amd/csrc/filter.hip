@@ -16,14 +16,11 @@
 // behind them.  20M int32 rows keeping 57%, row ids and one byte of payload:
 // 92 -> 20 + 45 us.  60M int64 rows keeping one in 84 with 13 bytes of payload
 // (beside another stream's work): 244 -> 112 + 64 us.
+#include "keepbits.hpp"
 #include "rowtest.hpp"
 
 namespace tqp {
 
-constexpr int kFilterNT = 256;
-constexpr int kFilterIPT = 8;                            // rows per thread and step
-constexpr int kFilterTile = kFilterNT * kFilterIPT;      // rows per workgroup and step
-constexpr int kFilterMaxSteps = 8;                       // steps per block
 constexpr int kMaxPred = 8;
 constexpr int kMaxPay = 8;
 
@@ -151,11 +148,7 @@ __global__ __launch_bounds__(kFilterNT) void k_filter_write(FilterOut a, int ste
     int64_t base = 0, from = 0;                  // kept rows of the blocks before `from`
     for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
         const int64_t unit = b * kFilterNT + threadIdx.x;
-        uint64_t bits;
-        if (steps == 8) bits = reinterpret_cast<const uint64_t *>(keep)[unit];
-        else if (steps == 4) bits = reinterpret_cast<const uint32_t *>(keep)[unit];
-        else if (steps == 2) bits = reinterpret_cast<const uint16_t *>(keep)[unit];
-        else bits = keep[unit];
+        uint64_t bits = keep_word(keep, unit, steps);
         int64_t part = 0;
 #pragma unroll 4
         for (int64_t i = from + threadIdx.x; i < b; i += kFilterNT) part += bcnt[i];
@@ -330,16 +323,8 @@ static int launch_filter_sum(Kern kern, int nd, int64_t n, hipStream_t s, const 
     return check_launch("tqp_filter_sum");
 }
 
-struct FilterLayout {
-    int steps;
-    int64_t nblocks;
-    uint8_t *keep;
-    int32_t *bcnt;
-    size_t bytes;
-};
-
-static FilterLayout filter_layout(void *ws, int64_t n) {
-    FilterLayout L = {};
+KeepLayout keep_layout(void *ws, int64_t n) {
+    KeepLayout L = {};
     Carver c(ws);
     L.steps = filter_steps(n);
     L.nblocks = ceil_div(n, int64_t(kFilterTile) * L.steps);
@@ -351,13 +336,13 @@ static FilterLayout filter_layout(void *ws, int64_t n) {
 
 template <int ND>
 static void launch_filter_mask(unsigned grid, hipStream_t s, const RowTests &t, int64_t n, bool vec,
-                               const FilterLayout &L) {
+                               const KeepLayout &L) {
     TQP_LAUNCH("filter_mask", k_filter_mask<ND>, dim3(grid), dim3(kFilterNT), 0, s, t, n, L.steps,
                vec ? 1 : 0, L.nblocks, L.keep, L.bcnt);
 }
 
 template <int NP>
-static void launch_filter_write(unsigned grid, hipStream_t s, const FilterOut &a, const FilterLayout &L) {
+static void launch_filter_write(unsigned grid, hipStream_t s, const FilterOut &a, const KeepLayout &L) {
     TQP_LAUNCH("filter", k_filter_write<NP>, dim3(grid), dim3(kFilterNT),
                size_t(L.steps) * kFilterTile * sizeof(uint16_t), s, a, L.steps, L.nblocks, L.keep, L.bcnt);
 }
@@ -366,7 +351,7 @@ static void launch_filter_write(unsigned grid, hipStream_t s, const FilterOut &a
 
 using namespace tqp;
 
-TQP_API size_t tqp_filter_workspace_bytes(int64_t n) { return filter_layout(nullptr, n < 0 ? 0 : n).bytes; }
+TQP_API size_t tqp_filter_workspace_bytes(int64_t n) { return keep_layout(nullptr, n < 0 ? 0 : n).bytes; }
 
 TQP_API int tqp_filter(const tqp_col *cols, int ncols, const tqp_pred *preds, int npred,
                        const tqp_col *pay_in, const tqp_col *pay_out, int npay,
@@ -405,10 +390,10 @@ TQP_API int tqp_filter(const tqp_col *cols, int ncols, const tqp_pred *preds, in
         a.pout[c] = pay_out[c].data;
         a.paydt[c] = pay_in[c].dtype;
     }
-    FilterLayout L = filter_layout(nullptr, n);
+    KeepLayout L = keep_layout(nullptr, n);
     if (!ws || ws_bytes < L.bytes)
         return set_error(TQP_ECAPACITY, "tqp_filter: workspace needs %zu bytes", L.bytes);
-    L = filter_layout(ws, n);
+    L = keep_layout(ws, n);
     RowTests t;
     build_tests(cols, preds, npred, &t);
     a.npay = npay;

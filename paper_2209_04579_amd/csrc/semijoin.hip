@@ -7,39 +7,49 @@
 // of the fact table with each dimension side).
 //
 // A dimension side is reduced to a key set: a bitmap over its key range
-// (tqp_keyset_build).  The fact table is then scanned once.  Each workgroup
-// takes a tile of rows; every key column is read with 16-byte loads that are
-// consecutive across the lanes of the workgroup (each load instruction of a
-// wave covers 1 KiB of one column), all of them issued before the first
-// test.  Sets small enough are staged in LDS once per workgroup; larger ones
-// are read from memory (they stay in L2) for the rows still alive after the
-// LDS tests.  The surviving rows are compacted in ascending order: a block
-// scan inside the tile and a decoupled look-back across tiles give each its
-// output slot, where it is written straight from registers.
+// (tqp_keyset_build).  Two kernels then take the fact table.  k_semi_mask streams the
+// key columns and writes one keep bit per row, a kept count per block and, where few
+// are kept, the kept rows' keys; k_semi_write writes the kept rows out.
+//
+// k_semi_mask: a workgroup stages the sets that fit in LDS once.  Each wave then takes
+// chunks of 512 rows by itself, 8 consecutive rows per lane: the next chunk's keys are
+// loaded before this one's are tested, and the only barrier is where a block's
+// count is written.  Sets that do not fit are read from memory (they stay in L2) for
+// the rows still alive after the LDS tests.
+//
+// What bounds it: the read of the key columns (4.7 TB/s with the slabs' writes
+// between them, 5.5 without), and close behind it the instructions per key: so a
+// position is 32-bit for int32 keys, and one past the set is moved to a zero bit
+// beside it instead of tested.
+//
+// The version before this one was a single pass: tiles handed out by tickets, a
+// decoupled look-back for each tile's slots, and rows written straight from
+// registers.  us, before / now, int32 keys, all sets in LDS:
+//   kept of 300M rows, 3 sets   0.05%    0.8%      2%       5%       9%      14%      22%
+//                             877/760  893/865 1100/933 1177/994 1222/1143 1312/1315 1416/1539
+//   60M rows, 1 set 15% kept 168/110, 2 sets 2% 223/139, 4 sets 13% 471/355
+// (int64 keys: 338/306 at 0.3% of 60M rows and 3 sets, 491/533 at 22%: what the second
+// kernel reads again then shows.)
 #include <mutex>
+#include <type_traits>
 
-#include "tqp_internal.hpp"
+#include "keepbits.hpp"
 
 namespace tqp {
 
 constexpr int kSjNT = 256;
 constexpr int kSjMaxSets = 4;
 constexpr int kSjMaxPay = 4;
+constexpr int kSjIPT = kFilterIPT;               // rows per lane and chunk
+constexpr int kSjChunk = kWave * kSjIPT;         // rows per wave and chunk
 // Words of key sets staged in LDS per 256 threads of workgroup (36 KiB): a
 // 1024-thread workgroup, alone on its compute unit, stages up to 144 KiB.
 constexpr int kSjLdsWordsPer256 = 9216;
-// Kept rows of a tile staged in LDS (row ids and keys) so that the tile's
-// look-back and writes can wait until the next tile's loads are in flight;
-// a tile keeping more is written at once from registers instead.
-constexpr int kSjStage = 256;
-template <class K> constexpr int sj_stage_words(int ns) {
-    return 2 * kSjStage * (1 + ns * int(sizeof(K) / 4));     // two buffers, in 4-byte words
-}
-// Tiles are handed out in groups of kSjGroup consecutive tiles per XCD
-// counter (workgroup b draws from counter b % kSjXcds), so that no single
-// ticket address takes every workgroup's atomic.
-constexpr int kSjXcds = 8;
-constexpr int kSjGroup = 8;
+// A chunk that keeps at most this many rows leaves their keys, row by row, in
+// its slab of the workspace.  The columns would be read again a 128-byte line per
+// kept row and set: at 0.8% kept of 300M rows, three int32 sets, 202 us
+// against SLAB_AFTER; above a quarter kept every line is used anyway.
+constexpr int kSjSlab = 128;
 
 struct SemiArgs {
     const void *key[kSjMaxSets];
@@ -48,34 +58,246 @@ struct SemiArgs {
     uint64_t nbits[kSjMaxSets];
     int32_t lds_off[kSjMaxSets];     // word offset of a set staged in LDS; -1: read from memory
     int32_t lds_len[kSjMaxSets];
+    uint32_t sh[kSjMaxSets];         // int32 keys: position 0 is bit sh of the first word
+    int64_t n;
+    int32_t lg_block;                // log2 of the chunks per block
+    int32_t lg_group;                // log2 of the chunks that a workgroup takes together: at
+                                     // least a block, and at least one per wave
+    int64_t nchunks;                 // chunks of all blocks
+    uint8_t *keep;                   // one byte per lane
+    int32_t *bcnt;
+    void *slab;                      // kSjSlab kept rows' keys per chunk (null: none)
+};
+
+// The keys of a whole chunk of aligned columns, 8 consecutive rows per lane; of the first
+// one where `row0` starts no whole chunk.  There is no second way to load them here: a
+// register that another branch had written would make the compiler wait for every
+// load in flight before this one's are issued.
+template <class K, int NS>
+__device__ __forceinline__ void sj_load(const SemiArgs &a, int64_t row0, K (&v)[NS][kSjIPT]) {
+    constexpr int V = 16 / int(sizeof(K));     // keys per 16-byte load
+    if (row0 + kSjChunk > a.n) row0 = 0;
+#pragma unroll
+    for (int s = 0; s < NS; s++) {
+        const K *p = static_cast<const K *>(a.key[s]) + row0;
+#pragma unroll
+        for (int k = 0; k < kSjIPT / V; k++) {
+            const uint32_t q = uint32_t(threadIdx.x % kWave) * (kSjIPT / V) + k;
+            if constexpr (sizeof(K) == 4) {
+                const int4 x = reinterpret_cast<const int4 *>(p)[q];
+                v[s][k * V + 0] = x.x; v[s][k * V + 1] = x.y;
+                v[s][k * V + 2] = x.z; v[s][k * V + 3] = x.w;
+            } else {
+                const longlong2 x = reinterpret_cast<const longlong2 *>(p)[q];
+                v[s][k * V + 0] = x.x; v[s][k * V + 1] = x.y;
+            }
+        }
+    }
+}
+
+// The keys of any chunk that begins inside the table; past its end, the last row's again.
+template <class K, int NS>
+__device__ __forceinline__ void sj_load_any(const SemiArgs &a, int64_t row0, K (&v)[NS][kSjIPT]) {
+    const uint32_t left = uint32_t(a.n - 1 - row0 < kSjChunk ? a.n - 1 - row0 : kSjChunk - 1);
+#pragma unroll
+    for (int s = 0; s < NS; s++) {
+        const K *p = static_cast<const K *>(a.key[s]) + row0;
+#pragma unroll
+        for (int r = 0; r < kSjIPT; r++) {
+            const uint32_t i = uint32_t(lane_id()) * kSjIPT + r;
+            v[s][r] = p[i < left ? i : left];
+        }
+    }
+}
+
+// The position of a key in a set that starts at lo, 2^32 - 1 if it does not fit 32
+// bits.  int32 keys: modulo 2^32.
+__device__ __forceinline__ uint32_t sj_pos(int32_t v, int64_t lo) { return uint32_t(v) - uint32_t(lo); }
+__device__ __forceinline__ uint32_t sj_pos(int64_t v, int64_t lo) {
+    const uint64_t i = uint64_t(v) - uint64_t(lo);
+    return i >> 32 ? ~0u : uint32_t(i);
+}
+
+// A set in LDS: every row is tested, without a branch.  The set's words lie there in
+// descending order between two zero words, so that with d = 31 - position
+// (plus 32 times where word 0 lies) d >> 5 is the word, a shift by d (modulo
+// 32) brings the bit to the top, and a d on either side of the set is moved to
+// a zero bit: six instructions and a read per key.
+template <class K>
+__device__ __forceinline__ uint32_t sj_test_lds(const SemiArgs &a, int s, const uint32_t *sets,
+                                                const K (&v)[kSjIPT]) {
+    const uint32_t off = uint32_t(a.lds_off[s]), len = uint32_t(a.lds_len[s]);
+    const uint32_t zero = 32 * (off + len) + 31, least = 32 * off + 31, most = zero + 1;
+    uint32_t m = 0;
+#pragma unroll
+    for (int r = kSjIPT - 1; r >= 0; r--) {
+        uint32_t d = zero - sj_pos(v[r], a.lo[s]);
+        d = d < least ? least : d;
+        d = d > most ? most : d;
+        m = __builtin_amdgcn_alignbit(m, sets[d >> 5] << (d & 31), 31);
+    }
+    return m;
+}
+// A set of less than 32 positions, its bits in a scalar register.
+template <class K>
+__device__ __forceinline__ uint32_t sj_test_reg(const SemiArgs &a, int s, uint32_t bits,
+                                                const K (&v)[kSjIPT]) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int r = kSjIPT - 1; r >= 0; r--) {
+        uint32_t d = ~sj_pos(v[r], a.lo[s]);
+        d = d > ~31u ? d : ~31u;
+        m = __builtin_amdgcn_alignbit(m, bits << (d & 31), 31);
+    }
+    return m;
+}
+
+// A set in memory: only the rows still alive read their word.
+template <class K>
+__device__ __forceinline__ uint32_t sj_test_mem(const SemiArgs &a, int s, const K (&v)[kSjIPT],
+                                                uint32_t alive) {
+    using Pos = std::conditional_t<sizeof(K) == 4, uint32_t, uint64_t>;
+    if (a.nbits[s] == 0) return 0;
+    const uint32_t *w = a.bits[s];
+    const Pos lo = Pos(a.lo[s]), last = Pos(a.nbits[s] - 1);
+    const uint32_t sh = sizeof(K) == 4 ? a.sh[s] : 0;
+    uint32_t word[kSjIPT];
+#pragma unroll
+    for (int r = 0; r < kSjIPT; r++) {
+        const Pos idx = Pos(v[r]) - lo;
+        const bool in = ((alive >> r) & 1u) && idx <= last;
+        word[r] = in ? w[(idx >> 5) + ((uint32_t(idx & 31) + sh) >> 5)] : 0u;
+    }
+    uint32_t m = 0;
+#pragma unroll
+    for (int r = 0; r < kSjIPT; r++)
+        m |= ((word[r] >> ((uint32_t(Pos(v[r]) - lo) + sh) & 31)) & 1u) << r;
+    return m;
+}
+
+// VEC: every key column is 16-byte aligned.
+template <class K, int NS, bool VEC>
+__global__ __launch_bounds__(4 * kSjNT) void k_semi_mask(SemiArgs a) {
+    // two chunks' keys in registers, where they take at most half of them
+    constexpr bool kAhead = VEC && NS * int(sizeof(K)) * kSjIPT * 2 <= 64 * 4;
+    extern __shared__ uint32_t s_sets[];
+    __shared__ uint32_t s_cnt[2][4 * kSjNT / kWave];         // by turn: one may still be read
+    const int nw = blockDim.x / kWave;
+    const int wave = __builtin_amdgcn_readfirstlane(wave_id());
+    for (int s = 0; s < NS; s++) {
+        if (a.lds_off[s] < 0) continue;
+        uint32_t *dst = s_sets + a.lds_off[s];
+        const int len = a.lds_len[s];
+        for (int i = threadIdx.x; i <= len + 1; i += blockDim.x) {
+            uint32_t x = i > 0 && i <= len ? a.bits[s][len - i] : 0u;
+            if (i == 1 && (a.nbits[s] & 31)) x &= (1u << (a.nbits[s] & 31)) - 1u;
+            dst[i] = x;
+        }
+    }
+    if (threadIdx.x < 2 * 4 * kSjNT / kWave) (&s_cnt[0][0])[threadIdx.x] = 0;
+    __syncthreads();
+    uint32_t small[NS];
+#pragma unroll
+    for (int s = 0; s < NS; s++)
+        small[s] = a.lds_off[s] >= 0 && a.nbits[s] < 32 ? __builtin_amdgcn_readfirstlane(s_sets[a.lds_off[s] + 1]) : 0u;
+
+    const int ngroups = int((a.nchunks + (1 << a.lg_group) - 1) >> a.lg_group);
+    const int last_j = (1 << a.lg_group) / nw - 1;           // a wave takes every nw-th chunk of a group
+    int g = blockIdx.x, j = 0, turn = 0;
+    K va[NS][kSjIPT], vb[NS][kSjIPT];
+    if constexpr (VEC) sj_load<K, NS>(a, ((int64_t(g) << a.lg_group) + wave) * kSjChunk, va);
+    auto step = [&](K (&v)[NS][kSjIPT], K (&next)[NS][kSjIPT]) {
+        const int in_group = j * nw + wave;
+        const int64_t chunk = (int64_t(g) << a.lg_group) + in_group;
+        const int64_t row0 = chunk * kSjChunk;
+        const bool ends = j == last_j;
+        const int g0 = g;
+        j = ends ? 0 : j + 1;
+        if (ends) g += gridDim.x;
+        const int64_t next_row = ((int64_t(g) << a.lg_group) + j * nw + wave) * kSjChunk;
+        // v has arrived once only the loads of `next` are still out.  Waiting for it here, on
+        // every path, lets its registers be written again without another wait.
+        if constexpr (kAhead) {
+            sj_load<K, NS>(a, next_row, next);
+            __builtin_amdgcn_s_waitcnt(0x0f70 | NS * kSjIPT * int(sizeof(K)) / 16);
+        } else if constexpr (VEC) {
+            __builtin_amdgcn_s_waitcnt(0x0f70);
+        }
+        uint32_t alive = 0xff;
+        if (!VEC || row0 + kSjChunk > a.n) {
+            const int64_t left = a.n - row0 - lane_id() * kSjIPT;    // rows from this lane's on
+            alive = left >= kSjIPT ? 0xffu : left > 0 ? (1u << int(left)) - 1u : 0u;
+            if (row0 < a.n) {
+                sj_load_any<K, NS>(a, row0, v);
+                __builtin_amdgcn_s_waitcnt(0x0f70);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < NS; s++) {
+            if (a.lds_off[s] < 0) continue;
+            alive &= a.nbits[s] < 32 ? sj_test_reg(a, s, small[s], v[s]) : sj_test_lds(a, s, s_sets, v[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < NS; s++)
+            if (a.lds_off[s] < 0) alive &= sj_test_mem(a, s, v[s], alive);
+        if (chunk < a.nchunks) a.keep[chunk * kWave + lane_id()] = uint8_t(alive);
+        const uint32_t upto = wave_incl_scan(uint32_t(__popc(alive)));
+        const int kept = __builtin_amdgcn_readlane(int(upto), kWave - 1);
+        if (a.slab && kept && kept <= kSjSlab) {
+            K *slab = static_cast<K *>(a.slab) + chunk * (kSjSlab * NS);
+            uint32_t at = (upto - __popc(alive)) * NS;
+#pragma unroll
+            for (int r = 0; r < kSjIPT; r++) {
+                if (!((alive >> r) & 1u)) continue;
+#pragma unroll
+                for (int s = 0; s < NS; s++) slab[at + s] = v[s][r];
+                at += NS;
+            }
+        }
+        if constexpr (VEC && !kAhead) sj_load<K, NS>(a, next_row, next);
+        if (lane_id() == 0 && kept) atomicAdd(&s_cnt[turn][in_group >> a.lg_block], uint32_t(kept));
+        if (ends) {
+            __syncthreads();
+            if (int(threadIdx.x) < 1 << (a.lg_group - a.lg_block)) {
+                const int64_t b = (int64_t(g0) << (a.lg_group - a.lg_block)) + threadIdx.x;
+                if (b << a.lg_block < a.nchunks) a.bcnt[b] = int32_t(s_cnt[turn][threadIdx.x]);
+                s_cnt[turn][threadIdx.x] = 0;                // in use again after the next barrier
+            }
+            turn ^= 1;
+        }
+    };
+    if (g >= ngroups) return;
+    if constexpr (kAhead) {
+        for (;;) {
+            step(va, vb);
+            if (g >= ngroups) break;
+            step(vb, va);
+            if (g >= ngroups) break;
+        }
+    } else {
+        while (g < ngroups) step(va, va);
+    }
+}
+
+// The rows that the keep bits name, in ascending order: the block's offset is the sum of the
+// counts before it, its rows become a list in LDS, and consecutive threads write
+// consecutive slots.  (k_filter_write with the keys out of the slabs.)
+struct SemiOut {
     void *key_out[kSjMaxSets];
     const void *pin[kSjMaxPay];
     void *pout[kSjMaxPay];
     int32_t paylg[kSjMaxPay];
     int32_t npay;
-    int32_t lds_words;
-    int32_t vec;                     // every key column is 16-byte aligned
+    int32_t steps;
+    int64_t nblocks;
     int32_t *out_rows;
     int64_t *d_count;
-    int64_t n;
-    uint32_t *ticket;                // kSjXcds counters
-    uint64_t *status;                // one look-back status per tile
+    // a table taken in parts: the id of this part's first row, the kept rows of the
+    // parts before (null: none) and where the next part finds its own (null: nowhere)
+    int32_t row0;
+    const int64_t *d_prev;
+    int64_t *d_next;
 };
-
-// Rows per thread per tile: up to 16, fewer with more sets or wider keys
-// (three steps of 16-byte loads per set with three or four sets), so that a
-// tile's keys and the staging of the previous tile's kept rows fit the
-// registers.  Each step is one 16-byte load per set.
-template <class K, int NS> struct SjShape {
-    static constexpr int V = 16 / int(sizeof(K));     // keys per 16-byte load
-    static constexpr int Steps = (16 / V) < (NS >= 3 ? 3 : 12 / NS) ? (16 / V) : (NS >= 3 ? 3 : 12 / NS);
-    static constexpr int R = V * Steps;               // rows per thread per tile
-};
-// the smallest tile of any set count and workgroup size (sizes the
-// look-back statuses)
-template <class K> constexpr int64_t sj_min_tile() {
-    return int64_t(kSjNT) * SjShape<K, kSjMaxSets>::R;
-}
 
 // Stores element value v of a payload column of element size 1 << lg.
 __device__ __forceinline__ void sj_store(void *out, int lg, int64_t i, uint64_t v) {
@@ -84,276 +306,92 @@ __device__ __forceinline__ void sj_store(void *out, int lg, int64_t i, uint64_t 
     else static_cast<uint64_t *>(out)[i] = v;
 }
 
-// Tiles of one XCD counter come in groups of kSjGroup consecutive tiles.
-__device__ __forceinline__ int64_t sj_tile_of(int64_t ticket, int xcd) {
-    return ((ticket / kSjGroup) * kSjXcds + xcd) * kSjGroup + ticket % kSjGroup;
-}
-
-// Writes a staged tile's kept rows (row ids, keys, then the payload read
-// through the row ids) to their slots from base, consecutive threads taking
-// consecutive slots.  The staging writes and the prefix in LDS must be
-// visible: callers come here after a barrier that follows both.
-template <class K, int NS, int NT>
-__device__ __forceinline__ void sj_write_staged(const SemiArgs &a, const int32_t *srow,
-                                                int64_t base, int cnt, bool last_tile) {
-    const K *skey = reinterpret_cast<const K *>(srow + kSjStage);
-    if (last_tile && threadIdx.x == 0) *a.d_count = base + cnt;
-    for (int i = threadIdx.x; i < cnt; i += NT) {
-        const int32_t row = srow[i];
-        if (a.out_rows) a.out_rows[base + i] = row;
+template <class K, int NS>
+__global__ __launch_bounds__(kFilterNT) void k_semi_write(SemiArgs a, SemiOut o) {
+    constexpr int kU = 4;                        // rows per thread and pass
+    extern __shared__ uint16_t s_list[];         // steps * kFilterTile entries
+    __shared__ int32_t s_scan[kFilterNT / kWave];
+    __shared__ int64_t s_sum[kFilterNT / kWave];
+    __shared__ int32_t s_chunk[kFilterMaxSteps * kFilterTile / kSjChunk + 1];   // first list entry
+    if (o.nblocks == 0 && threadIdx.x == 0) *o.d_count = 0;
+    const int steps = o.steps;
+    int64_t base = o.d_prev ? *o.d_prev : 0;     // kept rows of the blocks before `from`
+    int64_t from = 0;
+    for (int64_t b = blockIdx.x; b < o.nblocks; b += gridDim.x) {
+        uint64_t bits = keep_word(a.keep, b * kFilterNT + threadIdx.x, steps);
+        int64_t part = 0;
+#pragma unroll 4
+        for (int64_t i = from + threadIdx.x; i < b; i += kFilterNT) part += a.bcnt[i];
+        part = wave_sum(part);
+        if (lane_id() == 0) s_sum[wave_id()] = part;
+        int32_t total;
+        int q = block_excl_scan<kFilterNT>(int32_t(__popcll(bits)), &total, s_scan);
 #pragma unroll
-        for (int s = 0; s < NS; s++)
-            if (a.key_out[s]) static_cast<K *>(a.key_out[s])[base + i] = skey[s * kSjStage + i];
-#pragma unroll 1
-        for (int c = 0; c < a.npay; c++) {
-            const int lg = a.paylg[c];
-            sj_store(a.pout[c], lg, base + i, from_word(word_of(a.pin[c], lg, row), a.pin[c], lg, row));
+        for (int w = 0; w < kFilterNT / kWave; w++) base += s_sum[w];
+        from = b;
+        if (b == o.nblocks - 1 && threadIdx.x == 0) {
+            *o.d_count = base + total;
+            if (o.d_next) *o.d_next = base + total;
         }
-    }
-}
-
-// NT threads per workgroup; a tile is NT * R rows.  Larger workgroups take
-// larger tiles, so the per-tile ticket, scan and look-back are paid over
-// more rows.
-template <class K, int NS, int NT>
-__global__ __launch_bounds__(NT) void k_semijoin(SemiArgs a) {
-    using S = SjShape<K, NS>;
-    constexpr int V = S::V;
-    constexpr int R = S::R;
-    constexpr int64_t Tile = int64_t(NT) * R;
-    constexpr int64_t Step = int64_t(NT) * V;
-    constexpr int NW = S::Steps > 4 ? 2 : 1;       // words of packed step counts
-    static_assert(R <= 32, "keep bits of a thread fit one word");
-    __shared__ int64_t s_tile;
-    __shared__ int64_t s_prefix, s_pprefix;
-    __shared__ uint64_t s_scan[NT / kWave];
-    extern __shared__ uint32_t s_sets[];
-
-    const int64_t n = a.n;
-    const int64_t ntiles = ceil_div(n, Tile);
-    const bool vec = a.vec != 0;
-    const int tid = threadIdx.x;
-    const int xcd = int(blockIdx.x % kSjXcds);
-    const uint32_t full = R == 32 ? ~0u : (1u << R) - 1u;
-
-    // stage the small sets once per workgroup
-    for (int s = 0; s < NS; s++) {
-        if (a.lds_off[s] < 0) continue;
-        uint32_t *dst = s_sets + a.lds_off[s];
-        for (int i = tid; i < a.lds_len[s]; i += NT) dst[i] = a.bits[s][i];
-    }
-    __syncthreads();
-    // the kept rows waiting to be written, after the sets: two buffers, each
-    // row ids then each set's keys.  A tile stages into one while the
-    // previous tile's rows are written from the other.
-    int32_t *s_stage = reinterpret_cast<int32_t *>(s_sets + ((a.lds_words + 3) & ~3));
-    const int stage_half = sj_stage_words<K>(NS) / 2;
-    int64_t pend_tile = -1;              // the tile whose kept rows wait in LDS
-    int pend_total = 0, pb = 0;
-    // A tile's ticket is drawn only when the workgroup is ready to work on
-    // it: every tile handed out is in progress, so the look-backs of later
-    // tiles never wait on a tile that is merely reserved.
-    for (;;) {
-        const int64_t tile = sj_tile_of(take_tile(a.ticket + xcd, &s_tile), xcd);
-        const bool last = tile >= ntiles;
-        if (last && tile == 0 && tid == 0) *a.d_count = 0;    // empty input
-        const int64_t row0 = tile * Tile;
-        // item r = k * V + jj of this thread is row trow + k * Step + jj
-        const int64_t trow = row0 + int64_t(tid) * V;
-        K v[NS][R];
-        uint32_t alive = full;
-        if (vec && row0 + Tile <= n) {
-            // a whole tile (the same branch for the workgroup): every load is
-            // one 16-byte vector, all issued before the first test
+        const int per_chunk = kWave / steps;     // threads whose bits are one chunk
+        if (threadIdx.x % per_chunk == 0) s_chunk[threadIdx.x / per_chunk] = q;
+        if (threadIdx.x == 0) s_chunk[(1 << a.lg_block)] = total;
+        const int first = int(threadIdx.x) * steps * kFilterIPT;
+        while (bits) {
+            s_list[q++] = uint16_t(first + __builtin_ctzll(bits));
+            bits &= bits - 1;
+        }
+        __syncthreads();
+        const int64_t row0 = b * steps * kFilterTile;
+        for (int i0 = threadIdx.x; i0 < total; i0 += kU * kFilterNT) {
+            const int64_t slot = base + i0;
+            int32_t row[kU];
+            const K *at[kU];                     // in a slab, or null
 #pragma unroll
-            for (int s = 0; s < NS; s++) {
-                const K *p = static_cast<const K *>(a.key[s]);
-#pragma unroll
-                for (int k = 0; k < S::Steps; k++) {
-                    if constexpr (sizeof(K) == 4) {
-                        const int4 x = *reinterpret_cast<const int4 *>(p + trow + k * Step);
-                        v[s][k * V + 0] = x.x; v[s][k * V + 1] = x.y;
-                        v[s][k * V + 2] = x.z; v[s][k * V + 3] = x.w;
-                    } else {
-                        const longlong2 x = *reinterpret_cast<const longlong2 *>(p + trow + k * Step);
-                        v[s][k * V + 0] = x.x; v[s][k * V + 1] = x.y;
-                    }
-                }
+            for (int u = 0; u < kU; u++) {
+                const int i = i0 + u * kFilterNT;
+                const int r = s_list[i < total ? i : i0];
+                const int c = r / kSjChunk;
+                const int beg = s_chunk[c], cnt = s_chunk[c + 1] - beg;
+                row[u] = int32_t(row0 + r);
+                at[u] = a.slab && cnt <= kSjSlab ? static_cast<const K *>(a.slab) +
+                            ((b * (1 << a.lg_block) + c) * kSjSlab + (i < total ? i : i0) - beg) * NS
+                                                 : nullptr;
             }
-        } else {
-            alive = 0;
+            K key[kU][NS];
 #pragma unroll
-            for (int s = 0; s < NS; s++) {
-                const K *p = static_cast<const K *>(a.key[s]);
+            for (int u = 0; u < kU; u++) {
+                if (at[u]) {
 #pragma unroll
-                for (int r = 0; r < R; r++) {
-                    const int64_t row = trow + (r / V) * Step + (r % V);
-                    v[s][r] = row < n ? p[row] : K(0);
+                    for (int s = 0; s < NS; s++)
+                        if (o.key_out[s]) key[u][s] = at[u][s];
+                } else {
+#pragma unroll
+                    for (int s = 0; s < NS; s++)
+                        if (o.key_out[s]) key[u][s] = static_cast<const K *>(a.key[s])[row[u]];
                 }
             }
 #pragma unroll
-            for (int r = 0; r < R; r++)
-                if (trow + (r / V) * Step + (r % V) < n) alive |= 1u << r;
-        }
-        // the previous tile's look-back while these loads are in flight (its
-        // predecessors have long posted their counts); its rows are written
-        // at the end of this tile, once this tile's keys are no longer held
-        if (pend_tile >= 0 && wave_id() == 0) {
-            const int64_t pre = lookback_resolve(a.status, pend_tile, pend_total);
-            if (lane_id() == 0) s_pprefix = pre;
-        }
-        if (last) {
-            if (pend_tile >= 0) {
-                __syncthreads();
-                sj_write_staged<K, NS, NT>(a, s_stage + pb * stage_half, s_pprefix, pend_total,
-                                           pend_tile == ntiles - 1);
-            }
-            break;
-        }
-        // sets in LDS: every row tested (LDS reads are cheap); a set of at
-        // most 64 keys is held in a register instead
-#pragma unroll
-        for (int s = 0; s < NS; s++) {
-            if (a.lds_off[s] < 0) continue;
-            const uint32_t *w = s_sets + a.lds_off[s];
-            const uint64_t lo = uint64_t(a.lo[s]);
-            const uint64_t nb = a.nbits[s];
-            uint32_t m = 0;
-            if (nb <= 64) {
-                const uint64_t bits = uint64_t(w[0]) | (nb > 32 ? uint64_t(w[1]) << 32 : 0);
-#pragma unroll
-                for (int r = 0; r < R; r++) {
-                    const uint64_t idx = uint64_t(int64_t(v[s][r])) - lo;
-                    if (idx < nb && ((bits >> idx) & 1u)) m |= 1u << r;
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; r++) {
-                    const uint64_t idx = uint64_t(int64_t(v[s][r])) - lo;
-                    const bool in = idx < nb;
-                    const uint32_t word = w[in ? uint32_t(idx >> 5) : 0u];
-                    if (in && ((word >> (idx & 31)) & 1u)) m |= 1u << r;
-                }
-            }
-            alive &= m;
-        }
-        // sets in memory: only the rows still alive read their word
-#pragma unroll
-        for (int s = 0; s < NS; s++) {
-            if (a.lds_off[s] >= 0) continue;
-            const uint32_t *w = a.bits[s];
-            const uint64_t lo = uint64_t(a.lo[s]);
-            const uint64_t nb = a.nbits[s];
-            uint32_t word[R];
-            uint32_t need = 0;
-#pragma unroll
-            for (int r = 0; r < R; r++) {
-                const uint64_t idx = uint64_t(int64_t(v[s][r])) - lo;
-                const bool in = ((alive >> r) & 1u) && idx < nb;
-                if (in) need |= 1u << r;
-                word[r] = in ? w[idx >> 5] : 0u;
-            }
-            uint32_t m = 0;
-#pragma unroll
-            for (int r = 0; r < R; r++) {
-                const uint64_t idx = uint64_t(int64_t(v[s][r])) - lo;
-                if (((need >> r) & 1u) && ((word[r] >> (idx & 31)) & 1u)) m |= 1u << r;
-            }
-            alive &= m;
-        }
-
-        // slots: kept items are ordered by (step k, thread, jj) = by row.
-        // Per-step counts are packed 16 bits apiece, four steps per word
-        // (a step keeps at most NT * V <= 4096 rows).
-        uint64_t packed[NW], excl[NW], tot[NW];
-#pragma unroll
-        for (int w = 0; w < NW; w++) packed[w] = 0;
-#pragma unroll
-        for (int k = 0; k < S::Steps; k++) {
-            const uint32_t mk = (alive >> (k * V)) & ((1u << V) - 1u);
-            packed[k / 4] += uint64_t(__popc(mk)) << (16 * (k % 4));
-        }
-#pragma unroll
-        for (int w = 0; w < NW; w++) excl[w] = block_excl_scan<NT>(packed[w], &tot[w], s_scan);
-        int total = 0;
-        int first[S::Steps];                     // slot of the thread's first kept item of step k
-#pragma unroll
-        for (int k = 0; k < S::Steps; k++) {
-            first[k] = total + int((excl[k / 4] >> (16 * (k % 4))) & 0xffff);
-            total += int((tot[k / 4] >> (16 * (k % 4))) & 0xffff);
-        }
-        if (wave_id() == 0) lookback_publish(a.status, tile, total);
-        const bool stage = total <= kSjStage;
-        const int cb = pend_tile >= 0 ? pb ^ 1 : pb;
-        if (stage) {
-            // stage the kept rows in slot order; written during the next tile
-            int32_t *srow = s_stage + cb * stage_half;
-            K *skey = reinterpret_cast<K *>(srow + kSjStage);
-#pragma unroll
-            for (int r = 0; r < R; r++) {
-                const int k = r / V, jj = r % V;
-                const uint32_t mk = (alive >> (k * V)) & ((1u << V) - 1u);
-                if (!((mk >> jj) & 1u)) continue;
-                const int local = first[k] + __popc(mk & ((1u << jj) - 1u));
-                srow[local] = int32_t(trow + k * Step + jj);
-#pragma unroll
-                for (int s = 0; s < NS; s++) skey[s * kSjStage + local] = v[s][r];
-            }
-        } else {
-            // too many kept rows to stage: this tile's prefix now, its rows
-            // straight from registers (each column's writes of a tile cover
-            // one contiguous run, which the L2 merges into whole lines)
-            if (wave_id() == 0) {
-                const int64_t pre = lookback_resolve(a.status, tile, total);
-                if (lane_id() == 0) s_prefix = pre;
-            }
-            __syncthreads();
-            const int64_t base = s_prefix;
-            if (tile == ntiles - 1 && tid == 0) *a.d_count = base + total;
-#pragma unroll
-            for (int r = 0; r < R; r++) {
-                const int k = r / V, jj = r % V;
-                const uint32_t mk = (alive >> (k * V)) & ((1u << V) - 1u);
-                if (!((mk >> jj) & 1u)) continue;
-                const int64_t slot = base + first[k] + __popc(mk & ((1u << jj) - 1u));
-                if (a.out_rows) a.out_rows[slot] = int32_t(trow + k * Step + jj);
+            for (int u = 0; u < kU; u++) {
+                if (i0 + u * kFilterNT >= total) break;
+                if (o.out_rows) o.out_rows[slot + u * kFilterNT] = o.row0 + row[u];
 #pragma unroll
                 for (int s = 0; s < NS; s++)
-                    if (a.key_out[s]) static_cast<K *>(a.key_out[s])[slot] = v[s][r];
+                    if (o.key_out[s]) static_cast<K *>(o.key_out[s])[slot + u * kFilterNT] = key[u][s];
             }
-            // payload: only kept rows are read, four loads in flight at a time
-            for (int c = 0; c < a.npay; c++) {
-                const int lg = a.paylg[c];
-                const void *src = a.pin[c];
+            for (int c = 0; c < o.npay; c++) {
+                const int lg = o.paylg[c];
+                const void *in = o.pin[c];
+                uint64_t w[kU];
 #pragma unroll
-                for (int r0 = 0; r0 < R; r0 += 4) {
-                    uint64_t val[4];
+                for (int u = 0; u < kU; u++) w[u] = word_of(in, lg, row[u]);
 #pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        const int r = r0 + q;
-                        const int64_t row = trow + (r / V) * Step + (r % V);
-                        val[q] = ((alive >> r) & 1u) ? word_of(src, lg, row) : 0;
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; q++) {
-                        const int r = r0 + q, k = r / V, jj = r % V;
-                        if (!((alive >> r) & 1u)) continue;
-                        const uint32_t mk = (alive >> (k * V)) & ((1u << V) - 1u);
-                        const int64_t row = trow + k * Step + jj;
-                        const int64_t slot = base + first[k] + __popc(mk & ((1u << jj) - 1u));
-                        sj_store(a.pout[c], lg, slot, from_word(val[q], src, lg, row));
-                    }
-                }
+                for (int u = 0; u < kU; u++)
+                    if (i0 + u * kFilterNT < total)
+                        sj_store(o.pout[c], lg, slot + u * kFilterNT, from_word(w[u], in, lg, row[u]));
             }
         }
-        // the previous tile's rows, now that this tile's keys are no longer
-        // needed (its prefix was posted before this tile's block scan)
-        if (pend_tile >= 0)
-            sj_write_staged<K, NS, NT>(a, s_stage + pb * stage_half, s_pprefix, pend_total,
-                                       pend_tile == ntiles - 1);
-        pend_tile = stage ? tile : -1;
-        pend_total = total;
-        pb = cb;
+        __syncthreads();                         // the lists are reused
     }
 }
 
@@ -372,59 +410,54 @@ __global__ __launch_bounds__(256) void k_keyset_set(const void *key, int dt, int
     }
 }
 
-static size_t semijoin_ws(int64_t n, int dtype) {
-    const int64_t tile = dtype == TQP_INT32 ? sj_min_tile<int32_t>() : sj_min_tile<int64_t>();
-    Carver c(nullptr);
-    c.take<uint64_t>(kSjXcds / 2 + (n > 0 ? ceil_div(n, tile) : 1));
-    return c.bytes();
-}
-
-// Dynamic LDS beyond 64 KiB has to be allowed per kernel.
-template <class F> static int sj_allow_lds(F kern, size_t lds) {
-    if (lds <= 65536) return TQP_OK;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    return e == hipSuccess ? TQP_OK
-                           : set_error(TQP_EHIP, "tqp_semijoin: LDS of %zu bytes: %s", lds,
-                                       hipGetErrorString(e));
-}
-
-template <class K, int NT>
-static int launch_semijoin_nt(int ns, unsigned grid, size_t lds, hipStream_t s, const SemiArgs &a) {
-    int rc = TQP_OK;
-    switch (ns) {
-    case 1: rc = sj_allow_lds(k_semijoin<K, 1, NT>, lds); break;
-    case 2: rc = sj_allow_lds(k_semijoin<K, 2, NT>, lds); break;
-    case 3: rc = sj_allow_lds(k_semijoin<K, 3, NT>, lds); break;
-    default: rc = sj_allow_lds(k_semijoin<K, 4, NT>, lds); break;
+template <class K, int NS, bool VEC>
+static int launch_semijoin(SemiArgs a, const SemiOut &o, int per_cu, int nt, size_t lds, hipStream_t s) {
+    if (a.n > 0) {
+        if (lds > 65536) {                       // has to be allowed per kernel
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_semi_mask<K, NS, VEC>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+            if (e != hipSuccess)
+                return set_error(TQP_EHIP, "tqp_semijoin: LDS of %zu bytes: %s", lds, hipGetErrorString(e));
+        }
+        const unsigned grid = persistent_grid(ceil_div(a.nchunks, int64_t(1) << a.lg_group), per_cu);
+        TQP_LAUNCH("semijoin", (k_semi_mask<K, NS, VEC>), dim3(grid), dim3(unsigned(nt)), lds, s, a);
+        const int rc = check_launch("tqp_semijoin");
+        if (rc) return rc;
     }
-    if (rc) return rc;
+    TQP_LAUNCH("semijoin_write", (k_semi_write<K, NS>), dim3(block_grid(o.nblocks)), dim3(kFilterNT),
+               size_t(o.steps) * kFilterTile * sizeof(uint16_t), s, a, o);
+    return check_launch("tqp_semijoin");
+}
+
+template <class K, bool VEC>
+static int launch_semijoin(int ns, const SemiArgs &a, const SemiOut &o, int per_cu, int nt, size_t lds,
+                           hipStream_t s) {
     switch (ns) {
-    case 1: TQP_LAUNCH("semijoin", (k_semijoin<K, 1, NT>), dim3(grid), dim3(NT), lds, s, a); break;
-    case 2: TQP_LAUNCH("semijoin", (k_semijoin<K, 2, NT>), dim3(grid), dim3(NT), lds, s, a); break;
-    case 3: TQP_LAUNCH("semijoin", (k_semijoin<K, 3, NT>), dim3(grid), dim3(NT), lds, s, a); break;
-    default: TQP_LAUNCH("semijoin", (k_semijoin<K, 4, NT>), dim3(grid), dim3(NT), lds, s, a); break;
+    case 1: return launch_semijoin<K, 1, VEC>(a, o, per_cu, nt, lds, s);
+    case 2: return launch_semijoin<K, 2, VEC>(a, o, per_cu, nt, lds, s);
+    case 3: return launch_semijoin<K, 3, VEC>(a, o, per_cu, nt, lds, s);
+    default: return launch_semijoin<K, 4, VEC>(a, o, per_cu, nt, lds, s);
     }
-    return TQP_OK;
 }
 
-// The workgroup size in units of kSjNT threads (1, 2 or 4) from the
-// "semijoin.wg" knob.  A 1024-thread workgroup allows 128 registers per
-// thread; only three 4-byte key sets and three or four 8-byte ones (12 and
-// 6 rows per thread) fit it without spilling, the other shapes stop at 512.
-static int sj_wg(int dtype, int ns) {
-    const int wg = tune(kTuneSemiWg);
-    const bool fits = dtype == TQP_INT32 ? ns == 3 : ns >= 3;
-    if (wg >= 4) return fits ? 4 : 2;
-    return wg >= 2 ? 2 : 1;
-}
+struct SemiLayout {
+    KeepLayout keep;
+    void *slab;
+    int64_t *d_sum;                  // two, for a table taken in parts
+    size_t bytes;
+};
 
-template <class K>
-static int launch_semijoin(int ns, int wg, unsigned grid, size_t lds, hipStream_t s,
-                           const SemiArgs &a) {
-    if (wg >= 4) return launch_semijoin_nt<K, 4 * kSjNT>(ns, grid, lds, s, a);
-    if (wg >= 2) return launch_semijoin_nt<K, 2 * kSjNT>(ns, grid, lds, s, a);
-    return launch_semijoin_nt<K, kSjNT>(ns, grid, lds, s, a);
+static SemiLayout semi_layout(void *ws, int64_t n, int dtype, bool slabs) {
+    SemiLayout L = {};
+    Carver c(ws);
+    L.d_sum = c.take<int64_t>(2);
+    const size_t bits = keep_layout(nullptr, n).bytes;
+    char *at = c.take<char>(bits);
+    L.keep = keep_layout(at, n);
+    if (slabs)
+        L.slab = c.take<char>(size_t(ceil_div(n, kSjChunk)) * kSjSlab * kSjMaxSets * dtype_size(dtype));
+    L.bytes = c.bytes();
+    return L;
 }
 
 }  // namespace tqp
@@ -454,16 +487,15 @@ TQP_API int tqp_keyset_build(const tqp_col *key, const int64_t *d_n, int64_t lo,
 }
 
 TQP_API size_t tqp_semijoin_workspace_bytes(int64_t n, int dtype) {
-    return semijoin_ws(n < 0 ? 0 : n, dtype);
+    return semi_layout(nullptr, n < 0 ? 0 : n, dtype, true).bytes;
 }
 
-// Validates the arguments, then clears the tickets and look-back statuses in
-// `words` (the caller's workspace, or the library's static scratch) and
-// launches the scan.  words_cap: uint64 words available at `words`.
+// Validates the arguments and runs both kernels, over the whole table with slabs or,
+// with `part` rows > 0, over parts of that many rows one after another without.
 static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *sets, int nsets,
                         const tqp_col *keys_out, const tqp_col *pay_in, const tqp_col *pay_out,
-                        int npay, int32_t *out_rows, int64_t *d_count, uint64_t *words,
-                        int64_t words_cap, void *stream) {
+                        int npay, int32_t *out_rows, int64_t *d_count, void *ws, size_t ws_bytes,
+                        int64_t part, void *stream) {
     if (!keys || !sets || nsets < 1 || nsets > kSjMaxSets)
         return set_error(TQP_EINVAL, "%s: nsets must be in [1, %d] with keys and sets", who,
                          kSjMaxSets);
@@ -478,9 +510,11 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
     if (dt != TQP_INT32 && dt != TQP_INT64)
         return set_error(TQP_EINVAL, "%s: key columns must be int32 or int64", who);
     SemiArgs a = {};
+    SemiOut out = {};
     bool vec = true;
     int lds_words = 0;
-    const int wg = sj_wg(dt, nsets);
+    const int knob = tune(kTuneSemiWg);
+    const int wg = knob >= 4 ? 4 : knob >= 2 ? 2 : 1;
     const int lds_budget = kSjLdsWordsPer256 * wg;
     for (int s = 0; s < nsets; s++) {
         if (keys[s].dtype != dt || keys[s].len != n || (n > 0 && !keys[s].data) ||
@@ -495,11 +529,29 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
         a.bits[s] = sets[s].bits;
         a.lo[s] = sets[s].lo;
         a.nbits[s] = uint64_t(sets[s].nbits);
-        const int64_t words_s = ceil_div(sets[s].nbits, 32);
-        if (words_s > 0 && lds_words + words_s <= lds_budget) {
+        // int32 keys: positions are computed modulo 2^32, over the part of the
+        // range that int32 can hold
+        if (dt == TQP_INT32 && sets[s].nbits > 0) {
+            int64_t lo = sets[s].lo, hi = lo + (sets[s].nbits - 1);
+            if (hi < INT32_MIN || lo > INT32_MAX) {
+                a.nbits[s] = 0;
+            } else {
+                if (hi > INT32_MAX) hi = INT32_MAX;
+                if (lo < INT32_MIN) {
+                    const uint64_t skip = uint64_t(INT32_MIN) - uint64_t(lo);
+                    a.bits[s] += skip / 32;
+                    a.sh[s] = uint32_t(skip % 32);
+                    lo = INT32_MIN;
+                }
+                a.lo[s] = lo;
+                a.nbits[s] = uint64_t(hi - lo) + 1;
+            }
+        }
+        const int64_t words_s = ceil_div(int64_t(a.nbits[s]), 32);
+        if (words_s > 0 && a.sh[s] == 0 && lds_words + words_s <= lds_budget) {
             a.lds_off[s] = lds_words;
             a.lds_len[s] = int32_t(words_s);
-            lds_words += int(words_s);
+            lds_words += int(words_s) + 2;       // between two zero words
         } else {
             a.lds_off[s] = -1;
             a.lds_len[s] = 0;
@@ -507,7 +559,7 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
         if (keys_out && keys_out[s].data) {
             if (keys_out[s].dtype != dt || keys_out[s].len < n)
                 return set_error(TQP_EINVAL, "%s: keys_out[%d] has a bad dtype or length", who, s);
-            a.key_out[s] = keys_out[s].data;
+            out.key_out[s] = keys_out[s].data;
         }
     }
     for (int c = 0; c < npay; c++) {
@@ -517,38 +569,49 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
             !col_aligned(pay_in[c].data, pay_in[c].dtype) ||
             !col_aligned(pay_out[c].data, pay_out[c].dtype))
             return set_error(TQP_EINVAL, "%s: payload %d has a bad dtype, length or pointer", who, c);
-        a.pin[c] = pay_in[c].data;
-        a.pout[c] = pay_out[c].data;
-        a.paylg[c] = pay_in[c].dtype == TQP_INT8 ? 0 : pay_in[c].dtype == TQP_INT32 ? 2 : 3;
+        out.pin[c] = pay_in[c].data;
+        out.pout[c] = pay_out[c].data;
+        out.paylg[c] = pay_in[c].dtype == TQP_INT8 ? 0 : pay_in[c].dtype == TQP_INT32 ? 2 : 3;
     }
-    const int64_t tile = dt == TQP_INT32 ? sj_min_tile<int32_t>() : sj_min_tile<int64_t>();
-    const int64_t ntiles = ceil_div(n, tile);        // an upper bound for every set count
-    const int64_t nwords = kSjXcds / 2 + (ntiles > 0 ? ntiles : 1);
-    if (!words || words_cap < nwords)
-        return set_error(TQP_ECAPACITY, "%s: scratch needs %lld bytes", who,
-                         (long long)(nwords * 8));
+    out.npay = npay;
+    const int64_t most = part > 0 && part < n ? part : n;
+    const size_t need = semi_layout(nullptr, most, dt, part == 0).bytes;
+    if (!ws || ws_bytes < need)
+        return set_error(TQP_ECAPACITY, "%s: scratch needs %zu bytes", who, need);
     hipStream_t s = as_stream(stream);
-    int rc = fill_u64(words, 0, nwords, s);
-    if (rc) return rc;
-    a.npay = npay;
-    a.lds_words = lds_words;
-    a.vec = vec ? 1 : 0;
-    a.out_rows = out_rows;
-    a.d_count = d_count;
-    a.n = n;
-    a.ticket = reinterpret_cast<uint32_t *>(words);
-    a.status = words + kSjXcds / 2;
+    out.out_rows = out_rows;
+    out.d_count = d_count;
     // workgroups per CU count 256-thread units: a 1024-thread workgroup takes four
     const int per_cu = tune(kTuneSemiPerCu) / wg > 0 ? tune(kTuneSemiPerCu) / wg : 1;
-    const unsigned grid = persistent_grid(ntiles, per_cu);
-    // the sets, then (16-byte aligned) the staging of kept rows
-    const int stage_words = dt == TQP_INT32 ? sj_stage_words<int32_t>(nsets)
-                                            : sj_stage_words<int64_t>(nsets);
-    const size_t lds = size_t(((lds_words + 3) & ~3) + stage_words) * 4;
-    rc = dt == TQP_INT32 ? launch_semijoin<int32_t>(nsets, wg, grid, lds, s, a)
-                         : launch_semijoin<int64_t>(nsets, wg, grid, lds, s, a);
-    if (rc) return rc;
-    return check_launch(who);
+    const int ks = dtype_size(dt), nw = kSjNT * wg / kWave;
+    int64_t row0 = 0;
+    for (int turn = 0; row0 < n || row0 == 0; turn ^= 1) {
+        const int64_t rows = n - row0 < most ? n - row0 : most;
+        const SemiLayout L = semi_layout(ws, rows, dt, part == 0);
+        a.n = rows;
+        const int per_block = L.keep.steps * kFilterTile / kSjChunk;        // powers of two
+        a.lg_block = __builtin_ctz(per_block);
+        a.lg_group = __builtin_ctz(per_block > nw ? per_block : nw);
+        a.nchunks = L.keep.nblocks << a.lg_block;
+        a.keep = L.keep.keep;
+        a.bcnt = L.keep.bcnt;
+        a.slab = L.slab;
+        out.steps = L.keep.steps;
+        out.nblocks = L.keep.nblocks;
+        out.row0 = int32_t(row0);
+        out.d_prev = row0 > 0 ? L.d_sum + turn : nullptr;
+        out.d_next = row0 + rows < n ? L.d_sum + (turn ^ 1) : nullptr;
+        const size_t lds = size_t(lds_words) * 4;
+        const auto run = dt == TQP_INT32 ? (vec ? launch_semijoin<int32_t, true> : launch_semijoin<int32_t, false>)
+                                         : (vec ? launch_semijoin<int64_t, true> : launch_semijoin<int64_t, false>);
+        const int rc = run(nsets, a, out, per_cu, kSjNT * wg, lds, s);
+        if (rc || n == 0) return rc;
+        row0 += rows;
+        for (int k = 0; k < nsets; k++) a.key[k] = static_cast<const char *>(a.key[k]) + rows * ks;
+        for (int c = 0; c < npay; c++)
+            out.pin[c] = static_cast<const char *>(out.pin[c]) + (rows << out.paylg[c]);
+    }
+    return TQP_OK;
 }
 
 TQP_API int tqp_semijoin(const tqp_col *keys, const tqp_keyset *sets, int nsets,
@@ -559,18 +622,20 @@ TQP_API int tqp_semijoin(const tqp_col *keys, const tqp_keyset *sets, int nsets,
     if (reinterpret_cast<uintptr_t>(ws) % 8 != 0)
         return set_error(TQP_EINVAL, "tqp_semijoin: the workspace must be 8-byte aligned");
     return semijoin_run("tqp_semijoin", keys, sets, nsets, keys_out, pay_in, pay_out, npay,
-                        out_rows, d_count, static_cast<uint64_t *>(ws), int64_t(ws_bytes / 8),
-                        stream);
+                        out_rows, d_count, ws, ws_bytes, 0, stream);
 }
 
-// ---- the same scan with library-held scratch ------------------------------
+// ---- the same with library-held scratch -----------------------------------
 // For callers that cannot allocate device memory (code under graph capture,
-// serving loops, harnesses that forbid allocation): the tickets and
-// look-back statuses live in a file-scope device array instead of a
-// caller's workspace.  Each device the library runs on holds its own copy
-// until the process ends.
-constexpr int64_t kSjScratchWords = int64_t(1) << 20;       // 8 MiB
-static __device__ __align__(256) uint64_t scratch[kSjScratchWords];
+// serving loops, harnesses that forbid allocation): the keep bits and counts
+// live in a file-scope device array instead of a caller's workspace, of one part of
+// the table at a time.  Each device the library runs on holds its own copy until
+// the process ends.
+constexpr size_t kSjScratchBytes = size_t(8) << 20;
+constexpr int64_t kSjPartRows = int64_t(1) << 25;       // 4 MiB of keep bits
+// the longest table with int64 keys (of int32: any)
+constexpr int64_t kSjMaxRows64 = ((int64_t(1) << 20) - 4) * 1536;
+static __device__ __align__(256) uint64_t scratch[kSjScratchBytes / 8];
 constexpr int kSjMaxDevices = 64;
 static std::mutex g_scratch_mu;
 static uint64_t *g_scratch_ptr[kSjMaxDevices];
@@ -600,9 +665,7 @@ static int sj_scratch(uint64_t **out) {
 
 TQP_API int64_t tqp_semijoin_noalloc_max_rows(int dtype) {
     if (dtype != TQP_INT32 && dtype != TQP_INT64) return 0;
-    const int64_t tile = dtype == TQP_INT32 ? sj_min_tile<int32_t>() : sj_min_tile<int64_t>();
-    const int64_t rows = (kSjScratchWords - kSjXcds / 2) * tile;
-    return rows < INT32_MAX ? rows : INT32_MAX;
+    return dtype == TQP_INT32 ? INT32_MAX : kSjMaxRows64;
 }
 
 TQP_API int tqp_semijoin_noalloc(const tqp_col *keys, const tqp_keyset *sets, int nsets,
@@ -620,5 +683,5 @@ TQP_API int tqp_semijoin_noalloc(const tqp_col *keys, const tqp_keyset *sets, in
     int rc = sj_scratch(&words);
     if (rc) return rc;
     return semijoin_run("tqp_semijoin_noalloc", keys, sets, nsets, keys_out, pay_in, pay_out,
-                        npay, out_rows, d_count, words, kSjScratchWords, stream);
+                        npay, out_rows, d_count, words, kSjScratchBytes, kSjPartRows, stream);
 }
