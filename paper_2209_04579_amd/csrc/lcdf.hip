@@ -734,6 +734,7 @@ __global__ __launch_bounds__(kFillNT) void k_lcdf_leaf_fill(LcdfModel *mod) {
 struct BucketStats {
     unsigned long long max_bucket;
     unsigned long long nbig;            // entries of the big-bucket list
+    unsigned long long nwide;           // windows of a span beyond 51 bits
 };
 
 struct Overflow {
@@ -865,13 +866,15 @@ __device__ __forceinline__ int64_t run_end(const int32_t *rs, int64_t nruns, int
 // The grouped keys are cut into windows of whole buckets: slot w holds the
 // buckets that start in [w * kWin, (w + 1) * kWin).  All of them but the
 // last lie inside that range, so they span fewer than kWin positions; when
-// the last one makes the slot wider than kWinCap = 2 kWin, the slot becomes
-// two windows, the buckets before the last and the last one alone, and a
+// the last one makes the slot wider than kWinCap, the slot becomes two windows, the buckets before the last and the last one alone, and a
 // last bucket of more than kWinCap keys goes to the big-bucket path instead.
 // Buckets are disjoint key ranges in key order, so sorting a window's keys
 // as one sequence sorts each of its buckets.
-constexpr int kWin = 4096;
-constexpr int kWinCap = 2 * kWin;
+// (A window's cost is mostly its barriers and latencies, so slots are as long as few
+// enough of them split: with buckets of 3052 keys on average 62.5M keys took 991 us
+// at 4096, 874 at 5120, 871 at 6144.)
+constexpr int kWin = 5120;
+constexpr int kWinCap = 8192;
 constexpr int kWinNT = 1024;
 constexpr int kWinPer = kWinCap / kWinNT;        // elements per thread
 constexpr int kWinIdxBits = 13;                  // local index in a packed value
@@ -911,7 +914,7 @@ __global__ __launch_bounds__(256) void k_window_plan(const int32_t *__restrict__
             win[nwin + w] = make_int2(0, 0);
             continue;
         }
-        const int64_t sl = rs[b - 1];            // the last bucket: [sl, e0), longer than kWin
+        const int64_t sl = rs[b - 1];            // the last bucket: [sl, e0)
         win[w] = make_int2(int(s0), int(sl));
         if (e0 - sl <= kWinCap) {
             win[nwin + w] = make_int2(int(sl), int(e0));
@@ -952,16 +955,41 @@ __device__ __forceinline__ void cx(uint64_t &a, uint64_t &b) {
 // same banks as its neighbours'.
 __device__ __forceinline__ int wphys(int i) { return i + (i >> 3); }
 constexpr int kWinPhys = kWinCap + kWinCap / 8;
+// Bins of a window spread by value, and the most keys of a bin that are still put in
+// order one by one (see k_window_sort).
+constexpr int kWinBins = kWinCap;
+constexpr int kWinMaxBin = 16;
+constexpr int kWinBinsPer = kWinBins / kWinNT;
 
-// Persistent workgroups over the windows.  A window of m keys whose key span
-// (max - min) is below 2^51 is sorted as packed values
-// ((key - min) << 13 | local index), all distinct, by a merge sort in LDS:
+// Persistent workgroups over the windows.  The keys of a window are sorted as
+// packed values ((key - min) << 13 | local index), all distinct; that holds a span
+// (max - min) of up to 51 bits.
+//
+// A window is a short stretch of the key range, where keys mostly lie evenly: they
+// are spread over kWinBins equal parts of the span by a counting pass (a bin's own
+// keys in any order), and a thread then puts the keys of its kWinBinsPer bins in
+// order one by one, usually none to one step each.  A window where some bin has
+// more than kWinMaxBin keys (runs of equal keys, a gap beside a cluster) is merged
+// instead:
 // runs of 8 sorted in registers, then merge levels 8, 16, ... where each
 // thread finds its 8 outputs by a merge-path search (the last run of a level
 // may be short: nothing is padded beyond a multiple of 8).  Ties cannot
-// occur, so the order is (key, position), the stable one.  A wider window is
-// sorted by a bitonic network on (key, local index) in LDS.  Row ids are read
-// through the local indices and written back in place.
+// occur, so the order is (key, position), the stable one.
+//
+// A wider window (few keys in a large part of the range) drops the low bits of its
+// keys from the packed values, and fetches the whole keys through the local
+// indices afterwards.  Only if two of them then stand the wrong way round, having
+// differed in those bits alone, is the window merged over, by those bits and then
+// by the others.  Row ids are read through the local indices and written back in
+// place.
+//
+// What bounds it: latency (a window's dozen barriers, and the LDS chains of a merge
+// or of a thread's bins), with one workgroup per compute unit for its two 64 KiB
+// buffers; so the next window's keys are loaded while the spread one is put in order.
+// Wide windows are left for a launch of their own, whose registers would spill in
+// this one.  50M and 12.5M int64 keys (lognormal, clusters, Zipf): 2236 us when
+// every narrow window was merged and every wide one went through the network;
+// 723 + 467 us now (all of the bytes take 300).
 template <class K>
 __device__ __forceinline__ void window_load(const K *keys, const int32_t *rows, const int2 *win,
                                             int64_t w, int64_t nwin, int2 &se, K (&k)[kWinPer],
@@ -976,20 +1004,28 @@ __device__ __forceinline__ void window_load(const K *keys, const int32_t *rows, 
     }
 }
 
-template <class K>
+// WIDE: the windows of the list, of a span beyond 51 bits; otherwise all windows, of which
+// those go into the list.
+template <class K, bool WIDE>
 __global__ __launch_bounds__(kWinNT) void k_window_sort(K *keys, int32_t *rows,
-                                                        const int2 *__restrict__ win, int64_t nwin) {
+                                                        const int2 *__restrict__ win, int64_t nwin,
+                                                        int2 *wide, BucketStats *stats) {
     __shared__ uint64_t s_a[kWinPhys], s_b[kWinPhys];
     __shared__ int64_t s_lo[kWinNT / kWave], s_hi[kWinNT / kWave];
-    const int tid = threadIdx.x;
+    __shared__ uint32_t s_scan[kWinNT / kWave], s_most[kWinNT / kWave];
+    if constexpr (WIDE) nwin = int64_t(stats->nwide);
+    int2 se;
+    K k[kWinPer];
+    int32_t rw[kWinPer];
+    bool loaded = false;                 // the next window's keys are on their way
     for (int64_t w = blockIdx.x; w < nwin; w += gridDim.x) {
-        int2 se;
-        K k[kWinPer];
-        int32_t rw[kWinPer];
-        window_load(keys, rows, win, w, nwin, se, k, rw);
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));        // keeps LDS addresses out of registers between windows
+        if (!loaded) window_load(keys, rows, WIDE ? wide : win, w, nwin, se, k, rw);
+        loaded = false;
         const int64_t s0 = se.x;
         const int m = se.y - se.x;
-        if (m > 1) {
+        if (m <= 1) continue;
         int64_t lo = INT64_MAX, hi = INT64_MIN;
 #pragma unroll
         for (int i = 0; i < kWinPer; i++) {
@@ -1016,126 +1052,221 @@ __global__ __launch_bounds__(kWinNT) void k_window_sort(K *keys, int32_t *rows,
             hi = s_hi[ww] > hi ? s_hi[ww] : hi;
         }
         const int m8 = (m + 7) & ~7;
-        const bool packed = (uint64_t(hi) - uint64_t(lo)) < (uint64_t(1) << (64 - kWinIdxBits));
+        const uint64_t span = uint64_t(hi) - uint64_t(lo);
+        // the low bits that packing drops
+        const int drop = WIDE ? kWinIdxBits - __builtin_clzll(span) : 0;
+        const auto pack = [&](K key, int j) {
+            return ((uint64_t(int64_t(key)) - uint64_t(lo)) >> drop) << kWinIdxBits | uint64_t(j);
+        };
         uint64_t *res = nullptr;
-        if (packed) {
+        bool spread = false;
+        if constexpr (!WIDE) {
+            if (sizeof(K) == 8 && span >> (64 - kWinIdxBits)) {
+                if (threadIdx.x == 0) wide[atomicAdd(&stats->nwide, 1ull)] = se;
+                __syncthreads();                         // s_lo is reused
+                continue;
+            }
+            // the bins' counts, their prefix sums, and each key's rank in its bin as
+            // the counting found it
+            uint32_t *cnt = reinterpret_cast<uint32_t *>(s_b);
+            const int sh = span >> 32 ? 32 - __builtin_clz(uint32_t(span >> 32)) : 0;
+            const uint32_t span32 = uint32_t(span >> sh);
+            const bool fine = span32 < uint32_t(kWinBins);          // a bin per value
+            const uint32_t scale = fine ? 0 : uint32_t(double(kWinBins) * 4294967296.0 / (double(span32) + 1.0));
+            uint32_t at[kWinPer];                    // bin << kWinIdxBits | rank
+#pragma unroll
+            for (int i = 0; i < kWinBinsPer; i++) cnt[tid + i * kWinNT] = 0;
+            __syncthreads();
 #pragma unroll
             for (int i = 0; i < kWinPer; i++) {
                 const int j = tid + i * kWinNT;
-                if (j < m8)
-                    s_a[wphys(j)] = j < m ? ((uint64_t(int64_t(k[i])) - uint64_t(lo)) << kWinIdxBits) |
-                                                uint64_t(j)
-                                          : ~uint64_t(0);
+                const uint32_t d = uint32_t((uint64_t(int64_t(k[i])) - uint64_t(lo)) >> sh);
+                const uint32_t b = fine ? d : __umulhi(d, scale);
+                at[i] = b < uint32_t(kWinBins) ? b : uint32_t(kWinBins - 1);
+                if (j < m) at[i] = at[i] << kWinIdxBits | atomicAdd(&cnt[at[i]], 1u);
+            }
+            if (lane_id() == 0) s_most[wave_id()] = 0;
+            __syncthreads();
+            uint32_t c[kWinBinsPer], mine = 0, most = 0;
+#pragma unroll
+            for (int i = 0; i < kWinBinsPer; i++) {
+                c[i] = cnt[tid * kWinBinsPer + i];
+                mine += c[i];
+                most = c[i] > most ? c[i] : most;
+            }
+            uint32_t all;
+            const uint32_t beg = block_excl_scan<kWinNT>(mine, &all, s_scan);
+            if (most > uint32_t(kWinMaxBin)) s_most[wave_id()] = 1;
+            {
+                uint32_t first = beg;
+#pragma unroll
+                for (int i = 0; i < kWinBinsPer; i++) {
+                    cnt[tid * kWinBinsPer + i] = first;
+                    first += c[i];
+                }
             }
             __syncthreads();
-            // runs of 8 in registers
-            if (tid * 8 < m8) {
-                uint64_t v[8];
+            uint32_t crowded = 0;
 #pragma unroll
-                for (int i = 0; i < 8; i++) v[i] = s_a[wphys(tid * 8 + i)];
+            for (int i = 0; i < kWinNT / kWave; i++) crowded |= s_most[i];
+            spread = crowded == 0;
+            if (spread) {
+                int32_t *srow = reinterpret_cast<int32_t *>(s_b) + kWinBins;
 #pragma unroll
-                for (int r = 0; r < 8; r++)
-#pragma unroll
-                    for (int i = r & 1; i + 1 < 8; i += 2) cx(v[i], v[i + 1]);
-#pragma unroll
-                for (int i = 0; i < 8; i++) s_a[wphys(tid * 8 + i)] = v[i];
-            }
-            __syncthreads();
-            uint64_t *src = s_a, *dst = s_b;
-            for (int L = 8; L < m8; L <<= 1) {
-                if (tid * 8 < m8) {
-                    const int out0 = tid * 8;
-                    const int base = (out0 / (2 * L)) * (2 * L);
-                    const int d = out0 - base;
-                    const int la = m8 - base < L ? m8 - base : L;
-                    const int lb = m8 - base - L < 0 ? 0 : (m8 - base - L < L ? m8 - base - L : L);
-                    const int pa = base, pb = base + L;          // run starts (logical)
-                    int a = d - lb > 0 ? d - lb : 0, hb = d < la ? d : la;
-                    while (a < hb) {
-                        const int mid = (a + hb) >> 1;
-                        if (src[wphys(pa + mid)] <= src[wphys(pb + d - 1 - mid)]) a = mid + 1;
-                        else hb = mid;
-                    }
-                    int b = d - a;
-#pragma unroll
-                    for (int i = 0; i < 8; i++) {
-                        const uint64_t va = a < la ? src[wphys(pa + a)] : ~uint64_t(0);
-                        const uint64_t vb = b < lb ? src[wphys(pb + b)] : ~uint64_t(0);
-                        const bool takeA = a < la && (b >= lb || va <= vb);
-                        dst[wphys(out0 + i)] = takeA ? va : vb;
-                        a += takeA ? 1 : 0;
-                        b += takeA ? 0 : 1;
+                for (int i = 0; i < kWinPer; i++) {
+                    const int j = tid + i * kWinNT;
+                    if (j < m) {
+                        s_a[wphys(int(cnt[at[i] >> kWinIdxBits] + (at[i] & (kWinCap - 1))))] = pack(k[i], j);
+                        srow[j] = rw[i];
                     }
                 }
                 __syncthreads();
-                uint64_t *t = src;
-                src = dst;
-                dst = t;
-            }
-            res = src;
-        } else {
-            // bitonic on (key, local index): keys in s_a, indices in s_b
-            int P = 8;
-            while (P < m) P <<= 1;
-            K *sk = reinterpret_cast<K *>(s_a);
-            uint16_t *sx = reinterpret_cast<uint16_t *>(s_b);
-#pragma unroll
-            for (int i = 0; i < kWinPer; i++) {
-                const int j = tid + i * kWinNT;
-                if (j < P) {
-                    sk[j] = j < m ? k[i] : (sizeof(K) == 4 ? K(INT32_MAX) : K(INT64_MAX));
-                    sx[j] = j < m ? uint16_t(j) : uint16_t(0xffff);
+                // k and rw have been copied out
+                window_load(keys, rows, win, w + gridDim.x, nwin, se, k, rw);
+                loaded = true;
+                const int end = int(beg + mine);
+                uint64_t last = 0;
+                for (int p = int(beg); p < end; p++) {
+                    const uint64_t x = s_a[wphys(p)];
+                    if (x >= last) {
+                        last = x;
+                        continue;
+                    }
+                    int q = p;
+                    do {
+                        s_a[wphys(q)] = s_a[wphys(q - 1)];
+                        q--;
+                    } while (q > int(beg) && s_a[wphys(q - 1)] > x);
+                    s_a[wphys(q)] = x;
                 }
+                res = s_a;
             }
             __syncthreads();
-            for (int kk = 2; kk <= P; kk <<= 1) {
-                for (int jj = kk >> 1; jj > 0; jj >>= 1) {
-                    for (int i = tid; i < P; i += kWinNT) {
-                        const int l = i ^ jj;
-                        if (l > i) {
-                            const K ki = sk[i], kl = sk[l];
-                            const uint16_t xi = sx[i], xl = sx[l];
-                            const bool gt = ki > kl || (ki == kl && xi > xl);
-                            if (gt == ((i & kk) == 0)) {
-                                sk[i] = kl;
-                                sk[l] = ki;
-                                sx[i] = xl;
-                                sx[l] = xi;
-                            }
+        }
+        // Turn 0 merges the packed keys.  Where two keys that differ in the dropped bits
+        // alone then stand the wrong way round, turn 1 puts the window in the order of
+        // those bits, and turn 2 merges the packed keys again.
+        K ok[kWinPer];
+        int idx[kWinPer];
+        for (int turn = 0;; turn++) {
+            if (WIDE || !spread) {
+#pragma unroll
+                for (int i = 0; i < kWinPer; i++) {
+                    const int j = tid + i * kWinNT;
+                    if (j < m8)
+                        s_a[wphys(j)] = j >= m ? ~uint64_t(0)
+                                        : !WIDE || turn != 1 ? pack(k[i], j)
+                                        : ((uint64_t(int64_t(k[i])) - uint64_t(lo)) &
+                                           ((uint64_t(1) << drop) - 1)) << kWinIdxBits | uint64_t(j);
+                }
+                __syncthreads();
+                // runs of 8 in registers
+                if (tid * 8 < m8) {
+                    uint64_t v[8];
+#pragma unroll
+                    for (int i = 0; i < 8; i++) v[i] = s_a[wphys(tid * 8 + i)];
+#pragma unroll
+                    for (int r = 0; r < 8; r++)
+#pragma unroll
+                        for (int i = r & 1; i + 1 < 8; i += 2) cx(v[i], v[i + 1]);
+#pragma unroll
+                    for (int i = 0; i < 8; i++) s_a[wphys(tid * 8 + i)] = v[i];
+                }
+                __syncthreads();
+                uint64_t *src = s_a, *dst = s_b;
+                for (int L = 8; L < m8; L <<= 1) {
+                    if (tid * 8 < m8) {
+                        const int out0 = tid * 8;
+                        const int base = (out0 / (2 * L)) * (2 * L);
+                        const int d = out0 - base;
+                        const int la = m8 - base < L ? m8 - base : L;
+                        const int lb = m8 - base - L < 0 ? 0 : (m8 - base - L < L ? m8 - base - L : L);
+                        const int pa = base, pb = base + L;          // run starts (logical)
+                        int a = d - lb > 0 ? d - lb : 0, hb = d < la ? d : la;
+                        while (a < hb) {
+                            const int mid = (a + hb) >> 1;
+                            if (src[wphys(pa + mid)] <= src[wphys(pb + d - 1 - mid)]) a = mid + 1;
+                            else hb = mid;
+                        }
+                        int b = d - a;
+#pragma unroll
+                        for (int i = 0; i < 8; i++) {
+                            const uint64_t va = a < la ? src[wphys(pa + a)] : ~uint64_t(0);
+                            const uint64_t vb = b < lb ? src[wphys(pb + b)] : ~uint64_t(0);
+                            const bool takeA = a < la && (b >= lb || va <= vb);
+                            dst[wphys(out0 + i)] = takeA ? va : vb;
+                            a += takeA ? 1 : 0;
+                            b += takeA ? 0 : 1;
                         }
                     }
                     __syncthreads();
+                    uint64_t *t = src;
+                    src = dst;
+                    dst = t;
                 }
+                res = src;
             }
-        }
-        // sorted keys and local indices into registers, then the row ids
-        // permuted through LDS (the buffer the sort no longer uses)
-        K ok[kWinPer];
-        int idx[kWinPer];
+            // sorted keys and local indices into registers
 #pragma unroll
-        for (int i = 0; i < kWinPer; i++) {
-            const int j = tid + i * kWinNT;
-            idx[i] = 0;
-            if (j < m) {
-                if (packed) {
+            for (int i = 0; i < kWinPer; i++) {
+                const int j = tid + i * kWinNT;
+                idx[i] = 0;
+                if (j < m) {
                     const uint64_t v = res[wphys(j)];
                     idx[i] = int(v & uint64_t(kWinCap - 1));
                     ok[i] = K(int64_t(uint64_t(lo) + (v >> kWinIdxBits)));
-                } else {
-                    idx[i] = reinterpret_cast<uint16_t *>(s_b)[j];
-                    ok[i] = reinterpret_cast<K *>(s_a)[j];
                 }
             }
-        }
-        __syncthreads();
-        int32_t *srow = reinterpret_cast<int32_t *>(packed && res == s_a ? s_b : s_a);
-        if (!packed) srow = reinterpret_cast<int32_t *>(s_b) + kWinCap;   // past the indices
+            if constexpr (!WIDE) break;
+            // whole keys through the local indices
+            K *whole = reinterpret_cast<K *>(res == s_a ? s_b : s_a);
 #pragma unroll
-        for (int i = 0; i < kWinPer; i++) {
-            const int j = tid + i * kWinNT;
-            if (j < m) srow[j] = rw[i];
+            for (int i = 0; i < kWinPer; i++) {
+                const int j = tid + i * kWinNT;
+                if (j < m) whole[j] = k[i];
+            }
+            __syncthreads();
+            int wrong = 0;
+#pragma unroll
+            for (int i = 0; i < kWinPer; i++) {
+                const int j = tid + i * kWinNT;
+                if (j < m) {
+                    ok[i] = whole[idx[i]];
+                    if (turn == 0 && j + 1 < m) wrong |= whole[res[wphys(j + 1)] & uint64_t(kWinCap - 1)] < ok[i];
+                }
+            }
+            if (turn == 2 || (turn == 0 && !__syncthreads_or(wrong))) break;
+            if (turn == 1) {
+                __syncthreads();
+                int32_t *row = reinterpret_cast<int32_t *>(whole);
+#pragma unroll
+                for (int i = 0; i < kWinPer; i++) {
+                    const int j = tid + i * kWinNT;
+                    if (j < m) row[j] = rw[i];
+                }
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < kWinPer; i++) {
+                    const int j = tid + i * kWinNT;
+                    if (j < m) {
+                        k[i] = ok[i];
+                        rw[i] = row[idx[i]];
+                    }
+                }
+                __syncthreads();
+            }
         }
-        __syncthreads();
+        // the row ids permuted through LDS
+        int32_t *srow = reinterpret_cast<int32_t *>(s_b) + kWinBins;
+        if (WIDE || !spread) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < kWinPer; i++) {
+                const int j = tid + i * kWinNT;
+                if (j < m) srow[j] = rw[i];
+            }
+            __syncthreads();
+        }
 #pragma unroll
         for (int i = 0; i < kWinPer; i++) {
             const int j = tid + i * kWinNT;
@@ -1145,26 +1276,35 @@ __global__ __launch_bounds__(kWinNT) void k_window_sort(K *keys, int32_t *rows,
             }
         }
         __syncthreads();                 // LDS is reused by the next window
-        }
     }
 }
 
 // Min and max key of the big buckets, in chunks of at most kChunk keys per
 // workgroup: chunk c covers keys [cs[c].start, cs[c].start + cs[c].len) of big
-// bucket cs[c].kmin (its index); one atomic min and max per chunk.
+// bucket cs[c].kmin (its index); one atomic min and max per chunk.  Eight loads in
+// flight per thread (past the end: the last key again); with 256 threads and one load
+// each a chunk took 116 us.
 constexpr int64_t kChunk = 65536;
-
+constexpr int kBigNT = 1024;
 template <class K>
-__global__ __launch_bounds__(256) void k_big_minmax(const K *__restrict__ keys,
-                                                    const Overflow *__restrict__ cs,
-                                                    long long *__restrict__ mm) {
-    __shared__ long long s_lo[256 / kWave], s_hi[256 / kWave];
+__global__ __launch_bounds__(kBigNT) void k_big_minmax(const K *__restrict__ keys,
+                                                       const Overflow *__restrict__ cs,
+                                                       long long *__restrict__ mm) {
+    constexpr int kU = 8;
+    __shared__ long long s_lo[kBigNT / kWave], s_hi[kBigNT / kWave];
     const Overflow c = cs[blockIdx.x];
-    long long lo = LLONG_MAX, hi = LLONG_MIN;
-    for (int64_t i = c.start + threadIdx.x; i < c.start + c.len; i += blockDim.x) {
-        const long long x = keys[i];
-        lo = x < lo ? x : lo;
-        hi = x > hi ? x : hi;
+    const K *key = keys + c.start;
+    const int len = int(c.len);
+    long long lo = key[0], hi = lo;
+    for (int base = threadIdx.x; base < len; base += kBigNT * kU) {
+        K x[kU];
+#pragma unroll
+        for (int u = 0; u < kU; u++) x[u] = key[base + u * kBigNT < len ? base + u * kBigNT : len - 1];
+#pragma unroll
+        for (int u = 0; u < kU; u++) {
+            lo = x[u] < lo ? x[u] : lo;
+            hi = x[u] > hi ? x[u] : hi;
+        }
     }
     for (int o = 1; o < kWave; o <<= 1) {
         const long long ol = __shfl_xor(lo, o, kWave), oh = __shfl_xor(hi, o, kWave);
@@ -1177,7 +1317,7 @@ __global__ __launch_bounds__(256) void k_big_minmax(const K *__restrict__ keys,
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 256 / kWave; w++) {
+        for (int w = 1; w < kBigNT / kWave; w++) {
             lo = s_lo[w] < lo ? s_lo[w] : lo;
             hi = s_hi[w] > hi ? s_hi[w] : hi;
         }
@@ -1354,8 +1494,12 @@ static int partition_sort_typed(const K *key, const int32_t *in_rows, int64_t n,
         TQP_LAUNCH("window_plan", k_window_plan, dim3(unsigned(g)), dim3(256), 0, s, L.rus,
                    L.d_nruns, n, nwin, L.win, L.stats, L.ovf, L.ovf_cap);
         if ((rc = check_launch("window plan"))) return rc;
-        TQP_LAUNCH("window_sort", k_window_sort<K>, dim3(unsigned(kComputeUnits)), dim3(kWinNT), 0,
-                   s, out_key, out_rows, L.win, 2 * nwin);
+        int2 *wide = reinterpret_cast<int2 *>(L.ids);        // the bucket numbers are no longer needed
+        TQP_LAUNCH("window_sort", (k_window_sort<K, false>), dim3(unsigned(kComputeUnits)), dim3(kWinNT), 0,
+                   s, out_key, out_rows, L.win, 2 * nwin, wide, L.stats);
+        if constexpr (sizeof(K) == 8)
+            TQP_LAUNCH("window_sort", (k_window_sort<K, true>), dim3(unsigned(kComputeUnits)), dim3(kWinNT), 0,
+                       s, out_key, out_rows, L.win, 2 * nwin, wide, L.stats);
         if ((rc = check_launch("window sort"))) return rc;
     }
     BucketStats hs;
@@ -1397,7 +1541,7 @@ static int partition_sort_typed(const K *key, const int32_t *in_rows, int64_t n,
         if ((rc = upload(L.chunks, chunks.data(), sizeof(Overflow) * chunks.size(), s, "chunks")))
             return rc;
         if ((rc = upload(L.mm, mm.data(), sizeof(long long) * mm.size(), s, "min/max"))) return rc;
-        TQP_LAUNCH("big_minmax", k_big_minmax<K>, dim3(unsigned(chunks.size())), dim3(256), 0, s,
+        TQP_LAUNCH("big_minmax", k_big_minmax<K>, dim3(unsigned(chunks.size())), dim3(kBigNT), 0, s,
                    out_key, L.chunks, L.mm);
         if ((rc = check_launch("big bucket min/max"))) return rc;
         if ((rc = download(mm.data(), L.mm, sizeof(long long) * mm.size(), s, "min/max"))) return rc;
