@@ -277,48 +277,64 @@ __global__ __launch_bounds__(256) void k_lcdf_init(const int64_t *sorted, int64_
 
 // The whole training loop in one launch: one workgroup keeps the parameters,
 // Adam's moments and the training points on chip and runs `steps`
-// full-batch steps.  Each step: the per-ramp constants (inverse width,
-// height, centre) once; a forward pass (thread t: points t + k * 1024) that
-// leaves every point's scaled error in LDS; a backward pass in which thread
-// t accumulates the three gradients of ramp t mod 32 over the points
-// congruent to t / 32 mod 32; reductions in a fixed order (lanes by
-// shuffles, then the waves in turn); one Adam step per parameter (b1 = 0.9,
-// b2 = 0.999, bias-corrected).  The parameters with the lowest loss seen are
-// kept.  The gradient is that of the mean squared error between the root
-// and the sample ranks.
+// full-batch steps.  Each step: a forward pass (thread t: points t + k * 1024) that
+// leaves every point's scaled error in LDS; a backward pass in which a thread
+// accumulates the three gradients of one ramp over the points of one residue
+// modulo 32; reductions in a fixed order (lanes by shuffles, then the waves in
+// turn); one Adam step per parameter (b1 = 0.9, b2 = 0.999, bias-corrected), by
+// the thread that also turns it into the ramp's inverse width, height or
+// centre.  The parameters with the lowest loss seen are kept.  The gradient is
+// that of the mean squared error between the root and the sample ranks.
+//
+// What bounds it: instructions issued on the one compute unit, and the latency
+// between its three barriers per step.  The points ascend, so a ramp is 0 up to
+// some point, inside its slope up to another and 1 after that: its thread skips the
+// first part and only adds errors in the last.  A wave takes two ramps, so that the
+// lengths of those parts are shared by its lanes.  50 steps over 4096 points: 988 us
+// when every thread took every 32nd point through the ramp's formula and seven
+// barriers, 431 now, the model byte for byte the same.
 constexpr int kFitNT = 1024;
 constexpr int kFitNW = kFitNT / kWave;
 constexpr int kFitPer = kTrainPoints / kFitNT;              // forward points per thread
 constexpr int kFitGroups = kFitNT / kHidden;                // threads per ramp in the backward pass
 static_assert(kTrainPoints % kFitNT == 0 && kFitNT % kHidden == 0, "training layout");
+static_assert(kFitGroups == kHidden && 2 * kFitGroups == kWave, "a wave takes two ramps");
+
+// The first point at which a ramp leaves 0 (TOP: reaches 1).
+template <bool TOP>
+__device__ __forceinline__ int ramp_edge(const float *x, int T, float c, float w) {
+    int lo = 0, hi = T;
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        const float z = (x[mid] - c) * w + 0.5f;
+        if (TOP ? z >= 1.f : !(z <= 0.f)) hi = mid;
+        else lo = mid + 1;
+    }
+    return lo;
+}
 
 __global__ __launch_bounds__(kFitNT) void k_lcdf_fit(LcdfModel *mod, const float *tx,
                                                      const float *tq, int T, int steps, float lr) {
-    __shared__ float s_th[kNParam], s_m1[kNParam], s_m2[kNParam], s_best[kNParam];
-    __shared__ float s_w[kHidden], s_v[kHidden], s_c[kHidden], s_c0[kHidden], s_s0[kHidden];
+    __shared__ float4 s_ramp[kHidden];                       // centre, inverse width, height
+    __shared__ float s_bias;
     __shared__ float s_x[kTrainPoints], s_e[kTrainPoints];
     __shared__ float s_red[kFitNW][3 * kHidden];
     __shared__ float s_red1[kFitNW][2];
-    __shared__ float s_g[kNParam + 1];
-    __shared__ float s_lbest, s_lfirst, s_llast;
-    __shared__ int s_step;
+    __shared__ float2 s_corr[kFitNT];                        // 1 - b^step of the next steps
     const int tid = threadIdx.x, w = wave_id(), lane = lane_id();
-    for (int p = tid; p < kNParam; p += kFitNT) {
-        s_th[p] = mod->theta[p];
-        s_m1[p] = mod->m1[p];
-        s_m2[p] = mod->m2[p];
-        s_best[p] = mod->theta[p];
-    }
-    if (tid < kHidden) {
-        s_c0[tid] = mod->c0[tid];
-        s_s0[tid] = mod->s0[tid];
-    }
-    if (tid == 0) {
-        s_lbest = mod->loss_best;
-        s_lfirst = mod->loss_first;
-        s_llast = mod->loss_last;
-        s_step = mod->steps_done;
-    }
+    // thread p keeps parameter p, all of those threads the losses
+    const int p = tid < kNParam ? tid : kNParam - 1;
+    float th = mod->theta[p], m1 = mod->m1[p], m2 = mod->m2[p], best = th;
+    float lbest = mod->loss_best, lfirst = mod->loss_first, llast = mod->loss_last;
+    const int step0 = mod->steps_done;
+    const float c0 = p < kHidden ? mod->c0[p] : 0.f, s0 = p < kHidden ? mod->s0[p] : 0.f;
+    const auto use = [&]() {
+        if (tid < kHidden) s_ramp[p].x = c0 + s0 * th;
+        else if (tid < 2 * kHidden) s_ramp[p - kHidden].y = __expf(-th);
+        else if (tid < 3 * kHidden) s_ramp[p - 2 * kHidden].z = __expf(th);
+        else if (tid == 3 * kHidden) s_bias = th;
+    };
+    use();
     float pq[kFitPer];
 #pragma unroll
     for (int k = 0; k < kFitPer; k++) {
@@ -327,28 +343,38 @@ __global__ __launch_bounds__(kFitNT) void k_lcdf_fit(LcdfModel *mod, const float
         pq[k] = t < T ? tq[t] : 0.f;
     }
     const float inv_t = 2.0f / float(T);
-    const int j = tid % kHidden, q = tid / kHidden;
-    __syncthreads();
+    const int j = 2 * w + lane / kFitGroups, q = lane % kFitGroups;      // backward: ramp, residue
+    const float sj = mod->s0[j];
     for (int it = 0; it < steps; it++) {
-        if (tid < kHidden) {
-            s_w[tid] = __expf(-s_th[kHidden + tid]);
-            s_v[tid] = __expf(s_th[2 * kHidden + tid]);
-            s_c[tid] = s_c0[tid] + s_s0[tid] * s_th[tid];
+        if (it % kFitNT == 0) {
+            __syncthreads();
+            const float step = float(step0 + it + tid + 1);
+            s_corr[tid] = make_float2(1.f - powf(0.9f, step), 1.f - powf(0.999f, step));
         }
         __syncthreads();
         // forward: the root at this thread's points, their scaled errors
         float loss = 0.f, esum = 0.f;
+        {
+            float x[kFitPer], y[kFitPer];
 #pragma unroll
-        for (int k = 0; k < kFitPer; k++) {
-            const int t = tid + k * kFitNT;
-            const float x = s_x[t];
-            float y = s_th[3 * kHidden];
+            for (int k = 0; k < kFitPer; k++) {
+                x[k] = s_x[tid + k * kFitNT];
+                y[k] = s_bias;
+            }
+#pragma unroll 8
+            for (int r = 0; r < kHidden; r++) {
+                const float4 rp = s_ramp[r];
 #pragma unroll
-            for (int r = 0; r < kHidden; r++) y += s_v[r] * ramp((x - s_c[r]) * s_w[r] + 0.5f);
-            const float err = t < T ? y - pq[k] : 0.f;
-            s_e[t] = err * inv_t;
-            loss += err * err / float(T);
-            esum += err * inv_t;
+                for (int k = 0; k < kFitPer; k++) y[k] += rp.z * ramp((x[k] - rp.x) * rp.y + 0.5f);
+            }
+#pragma unroll
+            for (int k = 0; k < kFitPer; k++) {
+                const int t = tid + k * kFitNT;
+                const float err = t < T ? y[k] - pq[k] : 0.f;
+                s_e[t] = err * inv_t;
+                loss += err * err / float(T);
+                esum += err * inv_t;
+            }
         }
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
@@ -359,14 +385,18 @@ __global__ __launch_bounds__(kFitNT) void k_lcdf_fit(LcdfModel *mod, const float
             s_red1[w][0] = loss;
             s_red1[w][1] = esum;
         }
+        // (the points do not change, so the edges need no barrier)
+        const float4 rp = s_ramp[j];
+        const int edge0 = ramp_edge<false>(s_x, T, rp.x, rp.y), edge1 = ramp_edge<true>(s_x, T, rp.x, rp.y);
         __syncthreads();
         // backward: ramp j over the points q, q + 32, ...
         {
-            const float wj = s_w[j], vj = s_v[j], cj = s_c[j], sj = s_s0[j];
+            const float wj = rp.y, vj = rp.z, cj = rp.x;
             float gc = 0.f, gw = 0.f, gv = 0.f;
-            for (int p = q; p < T; p += kFitGroups) {
-                const float z = (s_x[p] - cj) * wj + 0.5f;
-                const float e = s_e[p];
+            int pt = edge0 + ((q - edge0) & (kFitGroups - 1));
+            for (; pt < edge1; pt += kFitGroups) {
+                const float z = (s_x[pt] - cj) * wj + 0.5f;
+                const float e = s_e[pt];
                 const float h = z < 0.f ? 0.f : (z > 1.f ? 1.f : z);
                 if (z > 0.f && z < 1.f) {
                     gc += e * vj * (-wj) * sj;                    // d/du = s0 * d/dcentre
@@ -374,72 +404,66 @@ __global__ __launch_bounds__(kFitNT) void k_lcdf_fit(LcdfModel *mod, const float
                 }
                 gv += e * vj * h;
             }
-            // lanes l and l + 32 of a wave hold the same ramp
-            gc += __shfl_xor(gc, kHidden, kWave);
-            gw += __shfl_xor(gw, kHidden, kWave);
-            gv += __shfl_xor(gv, kHidden, kWave);
-            if (lane < kHidden) {
-                s_red[w][j] = gc;
-                s_red[w][kHidden + j] = gw;
-                s_red[w][2 * kHidden + j] = gv;
+            float one = 1.f;
+            asm("" : "+v"(one));         // the product is rounded before it is added, as above
+#pragma unroll 8
+            for (; pt < T; pt += kFitGroups) gv += s_e[pt] * vj * one;
+            // lanes l and l ^ 1 hold neighbouring residues of one ramp
+            gc += __shfl_xor(gc, 1, kWave);
+            gw += __shfl_xor(gw, 1, kWave);
+            gv += __shfl_xor(gv, 1, kWave);
+            if ((q & 1) == 0) {
+                s_red[q / 2][j] = gc;
+                s_red[q / 2][kHidden + j] = gw;
+                s_red[q / 2][2 * kHidden + j] = gv;
             }
         }
         __syncthreads();
-        if (tid <= kNParam) {
-            float sum = 0.f;
-            if (tid < 3 * kHidden) {
-                for (int ww = 0; ww < kFitNW; ww++) sum += s_red[ww][tid];
-            } else {
-                const int c = tid == 3 * kHidden ? 1 : 0;        // bias gradient, then the loss
-                for (int ww = 0; ww < kFitNW; ww++) sum += s_red1[ww][c];
-            }
-            s_g[tid] = sum;
-        }
-        __syncthreads();
-        const float lossv = s_g[kNParam];
-        const bool better = lossv < s_lbest;
-        const int step = s_step + 1;
         if (tid < kNParam) {
-            const int p = tid;
-            if (better) s_best[p] = s_th[p];
-            const float b1 = 0.9f, b2 = 0.999f, gp = s_g[p];
-            const float m1 = b1 * s_m1[p] + (1.f - b1) * gp;
-            const float m2 = b2 * s_m2[p] + (1.f - b2) * gp * gp;
-            s_m1[p] = m1;
-            s_m2[p] = m2;
-            const float mh = m1 / (1.f - powf(b1, float(step)));
-            const float vh = m2 / (1.f - powf(b2, float(step)));
-            float th = s_th[p] - lr * mh / (sqrtf(vh) + 1e-12f);
+            float gp = 0.f, lossv = 0.f;
+#pragma unroll
+            for (int ww = 0; ww < kFitNW; ww++) {
+                gp += tid < 3 * kHidden ? s_red[ww][p] : s_red1[ww][1];
+                lossv += s_red1[ww][0];
+            }
+            const bool better = lossv < lbest;
+            if (better) best = th;
+            const float b1 = 0.9f, b2 = 0.999f;
+            m1 = __builtin_fmaf(1.f - b1, gp, b1 * m1);
+            m2 = __builtin_fmaf((1.f - b2) * gp, gp, b2 * m2);
+            const float2 corr = s_corr[it % kFitNT];
+            const float mh = m1 / corr.x;
+            const float vh = m2 / corr.y;
+            th = th - lr * mh / (sqrtf(vh) + 1e-12f);
             if (p >= kHidden && p < 2 * kHidden && th < -40.f) th = -40.f;    // width > 0
-            s_th[p] = th;
+            use();
+            if (step0 + it + 1 == 1) lfirst = lossv;
+            llast = lossv;
+            if (better) lbest = lossv;
         }
-        __syncthreads();
-        if (tid == 0) {
-            if (step == 1) s_lfirst = lossv;
-            s_llast = lossv;
-            if (better) s_lbest = lossv;
-            s_step = step;
-        }
-        __syncthreads();
     }
-    for (int p = tid; p < kNParam; p += kFitNT) {
-        mod->theta[p] = s_th[p];
-        mod->m1[p] = s_m1[p];
-        mod->m2[p] = s_m2[p];
-        if (steps > 0) mod->best[p] = s_best[p];
+    if (tid < kNParam) {
+        mod->theta[p] = th;
+        mod->m1[p] = m1;
+        mod->m2[p] = m2;
+        if (steps > 0) mod->best[p] = best;
     }
     if (tid == 0) {
-        mod->loss_best = s_lbest;
-        mod->loss_first = s_lfirst;
-        mod->loss_last = s_llast;
-        mod->steps_done = s_step;
+        mod->loss_best = lbest;
+        mod->loss_first = lfirst;
+        mod->loss_last = llast;
+        mod->steps_done = step0 + steps;
     }
 }
 
 // Effective root parameters from the best parameters seen (the starting ones
 // when no step was taken): w = 1 / width, c = 0.5 - centre * w, v = height;
 // then the root's table, which routing uses.
-__global__ void k_lcdf_finalize(LcdfModel *mod) {
+// One thread per table point: 84 us in the one that did all of it.
+constexpr int kFinNT = 128;
+__global__ __launch_bounds__(kFinNT) void k_lcdf_finalize(LcdfModel *mod) {
+    __shared__ float s_pt[kRootPts], s_at[kRootPts], s_y[kRootPts];
+    __shared__ int s_np, s_n;
     const int j = threadIdx.x;
     const bool trained = mod->loss_best < INFINITY;
     const float *th = trained ? mod->best : mod->theta;
@@ -450,41 +474,51 @@ __global__ void k_lcdf_finalize(LcdfModel *mod) {
         mod->c[j] = 0.5f - centre * w;
         mod->v[j] = expf(th[2 * kHidden + j]);
     }
-    if (j == 0) mod->d = th[3 * kHidden];
+    if (j == 0) {
+        mod->d = th[3 * kHidden];
+        s_np = 2;
+        s_pt[0] = 0.f;
+        s_pt[1] = 1.f;
+    }
     __syncthreads();
-    if (j != 0) return;
     // the root's table: breakpoints inside (0, 1), then 0 and 1, sorted and
     // without repeats; values from the ramp sum, made non-decreasing
-    float pts[kRootPts];
-    int np = 0;
-    pts[np++] = 0.f;
-    pts[np++] = 1.f;
-    for (int q = 0; q < kHidden; q++) {
-        const float a = -mod->c[q] / mod->w[q], b = (1.f - mod->c[q]) / mod->w[q];
-        if (a > 0.f && a < 1.f) pts[np++] = a;
-        if (b > 0.f && b < 1.f) pts[np++] = b;
+    if (j < kHidden) {
+        const float a = -mod->c[j] / mod->w[j], b = (1.f - mod->c[j]) / mod->w[j];
+        if (a > 0.f && a < 1.f) s_pt[atomicAdd(&s_np, 1)] = a;
+        if (b > 0.f && b < 1.f) s_pt[atomicAdd(&s_np, 1)] = b;
     }
-    for (int i = 1; i < np; i++)                  // insertion sort (at most 66 points)
-        for (int t = i; t > 0 && pts[t - 1] > pts[t]; t--) {
-            const float u = pts[t];
-            pts[t] = pts[t - 1];
-            pts[t - 1] = u;
-        }
-    int n = 0;
-    for (int i = 0; i < np; i++)
-        if (n == 0 || pts[i] > mod->px[n - 1]) mod->px[n++] = pts[i];
-    for (int i = n; i < kRootPad; i++) mod->px[i] = INFINITY;
-    float ymax = -INFINITY;
-    for (int i = 0; i < n; i++) {
-        const float y = lcdf_root(mod, mod->px[i]);
-        ymax = y > ymax ? y : ymax;
-        mod->py[i] = ymax;
+    __syncthreads();
+    const int np = s_np;
+    if (j < np) {
+        const float a = s_pt[j];
+        int at = 0;
+        for (int t = 0; t < np; t++) at += s_pt[t] < a || (s_pt[t] == a && t < j);
+        s_at[at] = a;
     }
-    for (int i = 0; i + 1 < n; i++)
-        mod->ps[i] = (mod->py[i + 1] - mod->py[i]) / (mod->px[i + 1] - mod->px[i]);
-    mod->ps[n - 1] = 0.f;
-    mod->npts = n;
+    __syncthreads();
+    const bool keep = j < np && (j == 0 || s_at[j] > s_at[j - 1]);
+    int slot = 0;
+    for (int t = 0; t < j && t < np; t++) slot += t == 0 || s_at[t] > s_at[t - 1];
+    mod->px[j] = INFINITY;                        // kRootPad of them
+    __syncthreads();
+    if (keep) {
+        mod->px[slot] = s_at[j];
+        s_y[slot] = lcdf_root(mod, s_at[j]);
+    }
+    if (j == np - 1) s_n = slot + keep;
+    __syncthreads();
+    const int n = s_n;
+    if (j < n) {
+        float ymax = -INFINITY;
+        for (int i = 0; i <= j; i++) ymax = s_y[i] > ymax ? s_y[i] : ymax;
+        mod->py[j] = ymax;
+    }
+    __syncthreads();
+    if (j < n) mod->ps[j] = j + 1 < n ? (mod->py[j + 1] - mod->py[j]) / (mod->px[j + 1] - mod->px[j]) : 0.f;
+    if (j == 0) mod->npts = n;
 }
+static_assert(kFinNT == kRootPad && kRootPts <= kFinNT, "a thread per table point");
 
 // lstart[l] = the first sorted sample point the root routes to leaf l or
 // later (lstart[nleaf] = m): the routing is monotone along the sorted
@@ -503,12 +537,10 @@ __global__ __launch_bounds__(256) void k_leaf_starts(const LcdfModel *mod, const
     }
 }
 
-// The spline through knots (kx, kr) at a key, in float64: the rank of the
-// last knot at or below the key, moved linearly toward the next one.
-__device__ __forceinline__ double knot_spline(const int64_t *kx, const double *kr, int nk,
+// The spline through knots (kx, kr) at a key with c knots at or below it, in
+// float64: the rank of the last of those, moved linearly toward the next one.
+__device__ __forceinline__ double knot_spline(const int64_t *kx, const double *kr, int nk, int c,
                                               int64_t key) {
-    int c = 0;
-    while (c < nk && kx[c] <= key) c++;
     if (c == 0) return kr[0];
     if (c == nk) return kr[nk - 1];
     const double d = double(uint64_t(key) - uint64_t(kx[c - 1]));
@@ -523,6 +555,12 @@ __device__ __forceinline__ double knot_spline(const int64_t *kx, const double *k
 // knot is the sample point where the spline so far misses the sample rank
 // the most (so knots land on the edges of dense clusters, where a straight
 // segment across a gap would put a whole cluster edge into one bucket).
+//
+// What bounds it: the leaf with the most points, whose workgroup runs alone at the
+// end.  A new knot changes the spline only between its neighbours, so each
+// segment keeps its point of largest error and only the two beside a new knot are
+// looked through again: 625K points in 1688 leaves 224 us when every knot went
+// through all points (and every run of keys was measured), 102 now.
 __global__ __launch_bounds__(256) void k_lcdf_leaf_fit(LcdfModel *mod, const int64_t *sorted,
                                                        int64_t m, const int64_t *lstart) {
     __shared__ int64_t s_run[256 / kWave][2];
@@ -531,23 +569,27 @@ __global__ __launch_bounds__(256) void k_lcdf_leaf_fit(LcdfModel *mod, const int
     __shared__ int s_nk, s_hpos, s_done;
     __shared__ double s_err[256 / kWave];
     __shared__ int64_t s_arg[256 / kWave];
+    // segment c: the points with c knots at or below them, from s_beg[c] on
+    __shared__ int64_t s_beg[kKnots + 2], s_sarg[kKnots + 1];
+    __shared__ double s_serr[kKnots + 1];
+    __shared__ int s_at;
     const int leaf = blockIdx.x, tid = threadIdx.x;
     const int64_t a0 = lstart[leaf], a1 = lstart[leaf + 1];
-    // longest run of equal keys: each run start finds its end by binary search
+    // longest run of equal keys: each start of a run longer than the thread's longest
+    // finds its end by binary search
     int64_t best_len = 0, best_start = 0;
     for (int64_t i = a0 + tid; i < a1; i += blockDim.x) {
         const int64_t v = sorted[i];
         if (i > a0 && sorted[i - 1] == v) continue;
-        int64_t lo = i + 1, hi = a1;
+        if (i + best_len >= a1 || sorted[i + best_len] != v) continue;
+        int64_t lo = i + best_len + 1, hi = a1;
         while (lo < hi) {
             const int64_t mid = (lo + hi) >> 1;
             if (sorted[mid] == v) lo = mid + 1;
             else hi = mid;
         }
-        if (lo - i > best_len) {
-            best_len = lo - i;
-            best_start = i;
-        }
+        best_len = lo - i;
+        best_start = i;
     }
     for (int o = 1; o < kWave; o <<= 1) {
         const int64_t ol = __shfl_xor(best_len, o, kWave);
@@ -591,44 +633,72 @@ __global__ __launch_bounds__(256) void k_lcdf_leaf_fit(LcdfModel *mod, const int
         s_nk = nk;
         s_hpos = hpos;
         s_done = 0;
+        s_at = 0;
     }
     __syncthreads();
     // greedy knots: the point of largest rank error, until the knots run out
-    while (!s_done && s_nk < kKnots) {
+    int first = 0, last = s_nk;                   // segments to look through
+    while (a1 > a0 && !s_done && s_nk < kKnots) {
         const int nk = s_nk;
-        double be = 0.0;
-        int64_t ba = -1;
-        for (int64_t i = a0 + tid; i < a1; i += blockDim.x) {
-            if (heavy && i >= rs && i < rs + rl) continue;      // the pair places these exactly
-            const double e = fabs(knot_spline(s_kx, s_kr, nk, sorted[i]) - (double(i) + 0.5) / double(m));
-            if (e > be) {
-                be = e;
-                ba = i;
+        if (tid >= first && tid <= last + 1) {
+            int64_t lo = a0, hi = a1;
+            if (tid == 0) hi = a0;
+            else if (tid > nk) lo = a1;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (sorted[mid] < s_kx[tid - 1]) lo = mid + 1;
+                else hi = mid;
             }
-        }
-        for (int o = 1; o < kWave; o <<= 1) {
-            const double oe = __shfl_xor(be, o, kWave);
-            const int64_t oa = __shfl_xor(ba, o, kWave);
-            if (oe > be || (oe == be && oa >= 0 && (ba < 0 || oa < ba))) {
-                be = oe;
-                ba = oa;
-            }
-        }
-        if (lane_id() == 0) {
-            s_err[wave_id()] = be;
-            s_arg[wave_id()] = ba;
+            s_beg[tid] = lo;
         }
         __syncthreads();
+        for (int c = first; c <= last; c++) {
+            double be = 0.0;
+            int64_t ba = -1;
+            for (int64_t i = s_beg[c] + tid; i < s_beg[c + 1]; i += blockDim.x) {
+                if (heavy && i >= rs && i < rs + rl) continue;      // the pair places these exactly
+                const double e = fabs(knot_spline(s_kx, s_kr, nk, c, sorted[i]) - (double(i) + 0.5) / double(m));
+                if (e > be) {
+                    be = e;
+                    ba = i;
+                }
+            }
+            for (int o = 1; o < kWave; o <<= 1) {
+                const double oe = __shfl_xor(be, o, kWave);
+                const int64_t oa = __shfl_xor(ba, o, kWave);
+                if (oe > be || (oe == be && oa >= 0 && (ba < 0 || oa < ba))) {
+                    be = oe;
+                    ba = oa;
+                }
+            }
+            if (lane_id() == 0) {
+                s_err[wave_id()] = be;
+                s_arg[wave_id()] = ba;
+            }
+            __syncthreads();
+            if (tid == 0) {
+                double e = 0.0;
+                int64_t arg = -1;
+                for (int ww = 0; ww < 256 / kWave; ww++)
+                    if (s_err[ww] > e || (s_err[ww] == e && s_arg[ww] >= 0 && (arg < 0 || s_arg[ww] < arg))) {
+                        e = s_err[ww];
+                        arg = s_arg[ww];
+                    }
+                s_serr[c] = e;
+                s_sarg[c] = arg;
+            }
+            __syncthreads();
+        }
         if (tid == 0) {
             double e = 0.0;
             int64_t arg = -1;
-            for (int ww = 0; ww < 256 / kWave; ww++)
-                if (s_err[ww] > e || (s_err[ww] == e && s_arg[ww] >= 0 && (arg < 0 || s_arg[ww] < arg))) {
-                    e = s_err[ww];
-                    arg = s_arg[ww];
+            for (int c = 0; c <= nk; c++)
+                if (s_serr[c] > e) {                               // the lowest of equals
+                    e = s_serr[c];
+                    arg = s_sarg[c];
                 }
-            if (arg < 0 || !(e > 0.0)) {
-                s_done = 1;                                    // exact already
+            if (arg < 0) {
+                s_done = 1;                                        // exact already
             } else {
                 // insert (key, rank) in (key, rank) order
                 const int64_t key = sorted[arg];
@@ -642,10 +712,19 @@ __global__ __launch_bounds__(256) void k_lcdf_leaf_fit(LcdfModel *mod, const int
                 s_kx[at] = key;
                 s_kr[at] = rank;
                 if (s_hpos >= at) s_hpos++;
+                // segment `at` becomes two; those behind it move on
+                for (int c = nk; c > at; c--) {
+                    s_serr[c + 1] = s_serr[c];
+                    s_sarg[c + 1] = s_sarg[c];
+                }
+                for (int c = nk + 1; c > at; c--) s_beg[c + 1] = s_beg[c];
                 s_nk = nk + 1;
+                s_at = at;
             }
         }
         __syncthreads();
+        first = s_at;
+        last = first + 1;
     }
     if (tid != 0) return;
     Leaf o;
@@ -1658,7 +1737,7 @@ TQP_API int tqp_lcdf_train(const tqp_col *cols, int ncols, int sample_stride, in
     if (steps > 0)
         TQP_LAUNCH("lcdf_fit", k_lcdf_fit, dim3(1), dim3(kFitNT), 0, s, mod, L.tx, L.tq, T, steps, lr);
     if ((rc = check_launch("lcdf train"))) return rc;
-    TQP_LAUNCH("lcdf_finalize", k_lcdf_finalize, dim3(1), dim3(64), 0, s, mod);
+    TQP_LAUNCH("lcdf_finalize", k_lcdf_finalize, dim3(1), dim3(kFinNT), 0, s, mod);
     {
         int64_t g = ceil_div(m, 256);
         if (g > 4096) g = 4096;
