@@ -32,17 +32,17 @@ constexpr int kJoinIPT = 16;
 constexpr int kJoinTile = kJoinNT * kJoinIPT;
 constexpr int kExpandPer = 8;
 constexpr int kExpandTile = kJoinNT * kExpandPer;   // output pairs per expand tile
-// Consecutive left runs per thread of the match: 4 when either side is
+// Consecutive runs of the match's first side per thread: 4 when either side is
 // below 2^25 rows (each lane's ranges 32 bytes apart, so a store covers few
-// cache lines when most left runs match, as against a dimension), 16 when
-// both sides are large (a quarter of the tiles, tickets and look-backs).  The
+// cache lines when most runs match, as against a dimension), 16 when both
+// sides are large (a quarter of the tiles, tickets and look-backs).  The
 // tile count and the workspace are sized for the smaller tile.
 constexpr int kMatchIPTSmall = 4;
 constexpr int kMatchIPTLarge = 16;
 constexpr int64_t kMatchLargeRows = int64_t(1) << 25;
 constexpr int kMatchTile = kJoinNT * kMatchIPTSmall;
-__host__ __device__ constexpr int match_ipt(int64_t nl) {
-    return nl >= kMatchLargeRows ? kMatchIPTLarge : kMatchIPTSmall;
+static int match_ipt(int64_t first) {
+    return first >= kMatchLargeRows ? kMatchIPTLarge : kMatchIPTSmall;
 }
 constexpr int kMatchWindow = 4096;      // right keys staged in LDS per match tile
 constexpr int kRleNT = 1024;
@@ -326,10 +326,10 @@ __global__ __launch_bounds__(kJoinNT) void k_join_match(MatchArgs a) {
     int64_t tot_p;
     const int32_t ex_m = block_excl_scan<kJoinNT>(int32_t(__popc(hit)), &tot_m, s_scan32);
     const int64_t ex_p = block_excl_scan<kJoinNT>(pairs, &tot_p, s_scan64);
-    if (wave_id() == 0) {
-        int64_t pm = lookback_count(a.status_m, tile, tot_m);
-        int64_t pp = lookback_count(a.status_p, tile, tot_p);
-        if (lane_id() == 0) { s_pm = pm; s_pp = pp; }
+    if (wave_id() < 2) {                 // a wave each
+        const int64_t pre = wave_id() == 0 ? lookback_count(a.status_m, tile, tot_m)
+                                           : lookback_count(a.status_p, tile, tot_p);
+        if (lane_id() == 0) (wave_id() == 0 ? s_pm : s_pp) = pre;
     }
     __syncthreads();
     if (tile == ntiles - 1 && threadIdx.x == 0) {
@@ -1076,29 +1076,37 @@ static int join_typed(const tqp_col *lkey, const int32_t *lrows, const int64_t *
     TQP_LAUNCH("rle", k_rle<K>, dim3(gr), dim3(kRleNT), 0, s, rk, nr, d_nr,
                        static_cast<K *>(L.uR), L.sR, &L.counters[1], tickets + 2, L.stR);
     if ((rc = check_launch("join rle right"))) return rc;
+    // The match searches the other side for each run of its first one, so that is the
+    // shorter side (both give the same ranges).  50M and 12.5M keys, 31M and 8M runs:
+    // 557 us the long way round, 354 this way.
+    const int f = nr < nl ? 1 : 0, o = 1 - f;        // the sides as first and other: 0 left, 1 right
+    const K *uk[2] = {static_cast<const K *>(L.uL), static_cast<const K *>(L.uR)};
+    const int32_t *us[2] = {L.sL, L.sR};
+    const int64_t *const d_len[2] = {d_nl, d_nr};
+    const int64_t len[2] = {nl, nr};
     MatchArgs a = {};
-    a.uL = L.uL;
-    a.sL = L.sL;
-    a.d_nuL = &L.counters[0];
-    a.d_nl = d_nl;
-    a.nl = nl;
-    a.uR = L.uR;
-    a.sR = L.sR;
-    a.d_nuR = &L.counters[1];
-    a.d_nr = d_nr;
-    a.nr = nr;
+    a.uL = uk[f];
+    a.sL = us[f];
+    a.d_nuL = &L.counters[f];
+    a.d_nl = d_len[f];
+    a.nl = len[f];
+    a.uR = uk[o];
+    a.sR = us[o];
+    a.d_nuR = &L.counters[o];
+    a.d_nr = d_len[o];
+    a.nr = len[o];
     a.rkey = L.rng[0];
-    a.rls = L.rng[1];
-    a.rlc = L.rng[2];
-    a.rrs = L.rng[3];
-    a.rrc = L.rng[4];
+    a.rls = L.rng[f ? 3 : 1];
+    a.rlc = L.rng[f ? 4 : 2];
+    a.rrs = L.rng[f ? 1 : 3];
+    a.rrc = L.rng[f ? 2 : 4];
     a.off = L.off;
     if (flags & TQP_JOIN_RANGES) {
         a.ukey = ranges->key;
-        a.uls = ranges->lstart;
-        a.ulc = ranges->lcnt;
-        a.urs = ranges->rstart;
-        a.urc = ranges->rcnt;
+        a.uls = f ? ranges->rstart : ranges->lstart;
+        a.ulc = f ? ranges->rcnt : ranges->lcnt;
+        a.urs = f ? ranges->lstart : ranges->rstart;
+        a.urc = f ? ranges->lcnt : ranges->rcnt;
         a.ucap = range_cap;
         a.d_nranges_user = d_nranges;
     }
@@ -1113,17 +1121,16 @@ static int join_typed(const tqp_col *lkey, const int32_t *lrows, const int64_t *
     a.status_m = L.stM;
     a.status_p = L.stP;
     a.bounds = L.bounds;
+    const int ipt = match_ipt(len[f]);
     {
         int64_t g = ceil_div(L.ntiles_match, 256);
         if (g > 1024) g = 1024;
         TQP_LAUNCH("match_bounds", k_match_bounds<K>, dim3(unsigned(g)), dim3(256), 0, s,
-                   static_cast<const K *>(L.uL), &L.counters[0], static_cast<const K *>(L.uR),
-                   &L.counters[1], int64_t(kJoinNT) * match_ipt(nl < nr ? nl : nr), L.ntiles_match,
+                   uk[f], &L.counters[f], uk[o], &L.counters[o], int64_t(kJoinNT) * ipt, L.ntiles_match,
                    L.bounds);
         if ((rc = check_launch("join match bounds"))) return rc;
     }
-    const int ipt = match_ipt(nl < nr ? nl : nr);
-    const unsigned gm = persistent_grid(ceil_div(nl > 0 ? nl : 1, int64_t(kJoinNT) * ipt),
+    const unsigned gm = persistent_grid(ceil_div(len[f] > 0 ? len[f] : 1, int64_t(kJoinNT) * ipt),
                                         tune(kTuneMatchPerCu));
     if (ipt == kMatchIPTLarge)
         TQP_LAUNCH("join_match", (k_join_match<K, kMatchIPTLarge>), dim3(gm), dim3(kJoinNT), 0, s, a);
