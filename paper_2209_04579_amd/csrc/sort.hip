@@ -45,6 +45,19 @@ int sort_impl(const void *key_in, int dtype, const int32_t *rows_in, int64_t n, 
     return sort_cols_impl(key_in, dtype, n, d_n, key_bits, key_min, key_out, sc, ws, ws_bytes, s);
 }
 
+int sort_columns(const void *key_in, int dtype, int64_t n, const int64_t *d_n, int key_bits,
+                 int64_t key_min, void *key_out, const void *const *pay_in, void *const *pay_out,
+                 const int32_t *pay_dt, int npay, void *ws, size_t ws_bytes, hipStream_t s) {
+    SortCols sc = {};
+    sc.npay = npay;
+    for (int c = 0; c < npay; c++) {
+        sc.pin[c] = pay_in[c];
+        sc.pout[c] = pay_out[c];
+        sc.pdt[c] = pay_dt[c];
+    }
+    return sort_cols_impl(key_in, dtype, n, d_n, key_bits, key_min, key_out, sc, ws, ws_bytes, s);
+}
+
 }  // namespace tqp
 
 using namespace tqp;

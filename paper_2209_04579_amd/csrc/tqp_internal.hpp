@@ -129,6 +129,10 @@ int launch_minmax(const void *key, int dtype, int64_t n, const int64_t *d_n,
 int sort_impl(const void *key_in, int dtype, const int32_t *rows_in, int64_t n,
               const int64_t *d_n, int key_bits, int64_t key_min, void *key_out,
               int32_t *rows_out, void *ws, size_t ws_bytes, hipStream_t s);
+// The same with columns moving along instead of row ids.
+int sort_columns(const void *key_in, int dtype, int64_t n, const int64_t *d_n, int key_bits,
+                 int64_t key_min, void *key_out, const void *const *pay_in, void *const *pay_out,
+                 const int32_t *pay_dt, int npay, void *ws, size_t ws_bytes, hipStream_t s);
 size_t sort_ws_bytes(int64_t n, int dtype, int key_bits);
 size_t sort_ws_bytes(int64_t n, int dtype, int key_bits, int pay_bytes);
 // Host-synchronizing derivation of (key_min, key_bits) for a column.  Faster with
