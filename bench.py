@@ -84,21 +84,22 @@ def parse():
 
 # ------------------------------------------------------- counter traffic ----
 
-KERNEL_FILE = {"semijoin": "semijoin.hip", "filter": "filter.hip", "onesweep": "radix.hpp",
-               "radix_hist": "radix.hpp", "rle": "join.hip", "join_match": "join.hip",
-               "join_expand": "join.hip", "pack_key": "gather.hip", "gather": "gather.hip",
-               "gb_dense": "groupby.hip", "gb_scan": "groupby.hip", "gb_tiny": "groupby.hip",
-               "gb_diff": "groupby.hip", "keyset_set": "semijoin.hip",
-               "filter_sum": "filter.hip", "mlp_predict": "predict.hip"}
-# kernels timed under one name (the filtered histogram of tqp_filter_sort
-# and the plain one both launch as "radix_hist")
-KERNEL_ALIASES = {"radix_hist": ("radix_hist", "radix_hist_filt")}
+KERNEL_FILE = {"semijoin": "semijoin.hip", "semijoin_write": "semijoin.hip", "filter": "filter.hip",
+               "filter_mask": "filter.hip", "filter_sum": "filter.hip", "onesweep": "radix.hpp",
+               "radix_count": "radix.hpp", "rle": "join.hip", "join_match": "join.hip",
+               "pair_count": "join.hip", "pair_write": "join.hip", "pack_key": "gather.hip",
+               "gather": "gather.hip", "gb_dense": "groupby.hip", "gb_heads": "groupby.hip",
+               "gb_scan": "groupby.hip", "keyset_set": "semijoin.hip", "mlp_predict": "predict.hip"}
+# launches whose kernels have other names
+KERNEL_ALIASES = {"semijoin": ("semi_mask",), "semijoin_write": ("semi_write",), "filter": ("filter_write",),
+                  "gb_scan": ("gb_runs",), "mlp_predict": ("mlp_predict", "mlp_predict2")}
 
 
 def source_sha(kernel_file: str) -> str:
     h = hashlib.sha256()
-    for f in (kernel_file, "tqp_internal.hpp"):
-        with open(os.path.join(ROOT, "paper_2209_04579_amd", "csrc", f), "rb") as fh:
+    src = os.path.join(ROOT, "paper_2209_04579_amd", "csrc")
+    for f in sorted({kernel_file, *(f for f in os.listdir(src) if f.endswith(".hpp"))}):
+        with open(os.path.join(src, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
 
@@ -187,26 +188,30 @@ def star3_kernel_bytes(name: str, st: dict) -> float | None:
     nd, kd = st["nd"], st["kd"]
     p = st["passes"]                  # (d1, d2, d3, fk3 sort, fk2 sort, fk1 sort)
     if name == "semijoin":
-        # the three foreign-key columns read once; row id + three keys
-        # written per kept row
-        return 12.0 * n + 16.0 * S
+        # the three foreign-key columns read once; a keep bit written per row,
+        # three keys per kept row
+        return (12.0 + 1 / 8) * n + 12.0 * S
+    if name == "semijoin_write":
+        # those read; row id and three keys written per kept row
+        return n / 8 + 12.0 * S + 16.0 * S
+    if name == "filter_mask":
+        # attr read and a keep bit written per dimension row
+        return sum((4.0 + 1 / 8) * x for x in nd)
     if name == "filter":
-        # attr read per dimension row; pk (and cat) read and written per kept row
-        return sum(4.0 * nd[i] + kd[i] * 2 * (4 + 4 * (i < 2)) for i in range(3))
+        # the keep bits; pk (and cat) read and written per kept row
+        return sum(nd[i] / 8 + kd[i] * 2 * (4 + 4 * (i < 2)) for i in range(3))
     if name == "keyset_set":
         return 4.0 * sum(kd)
-    if name == "radix_hist":
-        return 4.0 * (sum(kd) + S + c0 + c1)
+    if name == "radix_count":
+        return 4.0 * (sum(p[i] * kd[i] for i in range(3)) + p[3] * S + p[4] * c0 + p[5] * c1)
     if name == "onesweep":
         dims = sum(p[i] * kd[i] * 2 * (4 + 4 * (i < 2)) for i in range(3))
         return dims + p[3] * S * 2 * 16 + p[4] * c0 * 2 * 12 + p[5] * c1 * 2 * 12
     joins = ((S, kd[2], c0), (c0, kd[1], c1), (c1, kd[0], c2))
-    if name == "rle":
-        return sum((l + r) * 4.0 + 2 * min(l, r) * 8.0 for l, r, _ in joins)
-    if name == "join_match":
-        return sum(min(l, r) * 64.0 for l, r, _ in joins)
-    if name == "join_expand":
-        return sum(c * 8.0 + min(l, r) * 48.0 for l, r, c in joins)
+    if name == "pair_count":
+        return sum((l + r) * 4.0 for l, r, _ in joins)
+    if name == "pair_write":
+        return sum((l + r) * 4.0 + c * 8.0 for l, r, c in joins)
     if name == "gather":
         return 12.0 * (3 * c0 + 3 * c1 + c2)
     if name == "gb_dense":
@@ -220,13 +225,12 @@ def star_kernel_bytes(name: str, st: dict) -> float | None:
     fact payload the sort moves (fk + qty [+ price + flag]), gbv = bytes the
     low-cardinality group-by reads per joined row."""
     n, kept, nd, pairs = st["n"], st["kept"], st["nd"], st["pairs"]
-    ul, ur, gb, pay = st["uniq_l"], st["uniq_r"], st["groups_b"], st["pay"]
-    if name == "filter":
-        return n * (4 + pay) + kept * pay
-    if name == "radix_hist":
-        # fact side (filtered): fk and day of every row, one keep bit written
-        # per row; dim side: pk
-        return n * (4 + 4 + 1 / 8) + 4.0 * nd
+    gb, pay = st["groups_b"], st["pay"]
+    if name == "radix_count":
+        # fact side: fk and day of every row (filtered), one keep bit written
+        # per row, then the kept keys before every later pass; dim side: pk
+        p = st["passes"]
+        return n * (4 + 4 + 1 / 8) + 4.0 * ((p - 1) * kept + p * nd)
     if name == "onesweep":
         # the first fact pass reads the payload of every row (at this
         # selectivity every cache line holds kept rows) plus the keep bits and
@@ -234,18 +238,16 @@ def star_kernel_bytes(name: str, st: dict) -> float | None:
         # every dim pass reads and writes pk (4) + cat (4)
         p = st["passes"]
         return (n * (pay + 1 / 8) + kept * pay) + (p - 1) * kept * 2.0 * pay + p * nd * 2.0 * 8
-    if name == "rle":
-        return 4.0 * (kept + nd) + 8.0 * (ul + ur)
-    if name == "join_match":
-        return ul * (4 + 4 + 4 + 4 + 6 * 8)
-    if name == "join_expand":
-        return pairs * (4 + 4 + 4) + ul * 6 * 8
-    if name in ("gb_dense", "gb_tiny"):
+    if name == "pair_count":
+        return 4.0 * (kept + nd)
+    if name == "pair_write":
+        return 4.0 * (kept + nd) + pairs * (4 + 4 + 4)
+    if name == "gb_dense":
         return pairs * st["gbv"]
+    if name == "gb_heads":
+        return pairs * 4.0
     if name == "gb_scan":
         return pairs * (4 + 4 + 8) + gb * (4 + 16)
-    if name == "gb_diff":
-        return gb * 32.0
     return None
 
 
@@ -501,8 +503,7 @@ def bench_star60m(args, tqp, stream) -> dict:
     n, nd = fact["fk"].numel(), dim["pk"].numel()
     st = {"n": n, "nd": nd, "kept": res["rows_filtered"], "pairs": res["pairs"],
           "groups_b": len(res["b_key"]), "passes": _passes(q.jk_bits),
-          "uniq_l": len(res["b_key"]), "uniq_r": nd, "pay": 21,
-          "gbv": 4 + 4 + 1 + 4 + 8 + 8}
+          "pay": 21, "gbv": 4 + 4 + 1 + 4 + 8 + 8}
     out = {"workload": "skewed star query: fact 60M rows (fk Zipf s=1 over 2M keys), dim 2M; "
                        "day<1278; join fk=pk; group by (flag, cat mod 2) and by fk",
            "ms": round(ms, 4), "median_ms": round(med, 4),
@@ -555,8 +556,7 @@ def _bench_small(args, tqp, stream) -> dict:
     graph_ok = all(np.array_equal(again[k], got[k]) for k in ("key", "sum_qty", "count"))
     del graph
     st = {"n": 1_000_000, "nd": 10_000, "kept": got["rows_filtered"], "pairs": got["pairs"],
-          "groups_b": 0, "passes": _passes(q.jk_bits), "uniq_l": 10_000, "uniq_r": 10_000,
-          "pay": 12, "gbv": 4 + 4 + 4 + 8}
+          "groups_b": 0, "passes": _passes(q.jk_bits), "pay": 12, "gbv": 4 + 4 + 4 + 8}
     kernels = kernel_table(kernel_profile(q.run, 20), 20, star_kernel_bytes, st)
     return {"workload": "fact 1M rows, dim 10k; day<1278; join; group by cat "
                                      "(16 MB of input: cache-resident, launch-bound)",
@@ -615,9 +615,9 @@ def _bench_q14(args, tqp, stream) -> dict:
     got = q14.result()
     n14 = q14.n
     kern = kernel_profile(q14.run, 20)
-    fl = kern.get("filter", (20, ms * 20))
-    # the filter reads ship (8 B) of every row and the payload lines of kept rows
-    fbytes = n14 * 8 + got["rows_filtered"] * (4 + 8 + 1) * 2
+    fl = kern.get("filter_mask", (20, ms * 20))
+    # the filter's first kernel reads ship (8 B) of every row and writes its keep bit
+    fbytes = n14 * (8 + 1 / 8)
     achieved = fbytes / (fl[1] / fl[0] * 1e-3) / 1e9
     out = {"workload": "60M items (one month of int64 epoch-ns ship dates kept), 2M "
                                    "parts with (n x 24) byte-matrix types; LIKE prefix flag, "
@@ -626,10 +626,10 @@ def _bench_q14(args, tqp, stream) -> dict:
                        "ms": round(ms, 4), "rows_per_s": round(n14 / (ms * 1e-3), 1),
                        "pairs": got["pairs"],
                        "promo_revenue_ratio": [got["promo_rev"], got["total_rev"]],
-                       "roofline": {"kernel": "filter", "bound": "hbm",
+                       "roofline": {"kernel": "filter_mask", "bound": "hbm",
                                     "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
-                                    "traffic": traffic_for("filter", "q14"),
+                                    "traffic": traffic_for("filter_mask", "q14"),
                                     "algo_bytes_per_launch": int(fbytes),
                                     "avg_launch_ms": round(fl[1] / fl[0], 5)},
                        "kernel_ms": {k: round(v[1] / 20, 4) for k, v in kern.items()}}
@@ -913,8 +913,7 @@ def bench_batch(args, tqp, stream) -> dict:
     q = b.q
     kept, pairs = int(q.cnt.item()), int(q.npairs.item())
     st = {"n": q.n, "nd": q.nd, "kept": kept, "pairs": pairs, "groups_b": 0,
-          "passes": _passes(q.jk_bits), "uniq_l": q.nd, "uniq_r": q.nd, "pay": 12,
-          "gbv": 4 + 4 + 4 + 8}
+          "passes": _passes(q.jk_bits), "pay": 12, "gbv": 4 + 4 + 4 + 8}
     kernels = kernel_table(kernel_profile(q.run, 3), 3, star_kernel_bytes, st)
     for k, v in defaults.items():
         tqp.tune_set(k, v)
