@@ -45,6 +45,7 @@
 #include <limits.h>
 #include <stddef.h>
 #include <math.h>
+#include <string.h>
 #include <algorithm>
 #include <vector>
 
@@ -972,7 +973,7 @@ __device__ __forceinline__ int64_t runs_lower_bound(const int32_t *rs, int64_t n
 __device__ __forceinline__ void push_big(BucketStats *stats, Overflow *big, int64_t big_cap,
                                          int64_t start, int64_t len) {
     const unsigned long long slot = atomicAdd(&stats->nbig, 1ull);
-    if (int64_t(slot) < big_cap) big[slot] = Overflow{start, len, 0, 0, 0};
+    if (int64_t(slot) < big_cap) big[slot] = Overflow{start, len, INT64_MAX, INT64_MIN, 0};
 }
 
 // One thread per slot: its one or two windows, win[w] and win[nwin + w], as
@@ -1358,50 +1359,72 @@ __global__ __launch_bounds__(kWinNT) void k_window_sort(K *keys, int32_t *rows,
     }
 }
 
-// Min and max key of the big buckets, in chunks of at most kChunk keys per
-// workgroup: chunk c covers keys [cs[c].start, cs[c].start + cs[c].len) of big
-// bucket cs[c].kmin (its index); one atomic min and max per chunk.  Eight loads in
-// flight per thread (past the end: the last key again); with 256 threads and one load
-// each a chunk took 116 us.
-constexpr int64_t kChunk = 65536;
+// Min and max key of the big buckets, into their entries, in chunks of kChunk keys dealt
+// to the workgroups; one atomic min and max per chunk.  kBigNT entries at a time,
+// the prefix sums of their chunk counts in LDS.  Eight loads in flight per thread
+// (past the end: the last key again); with 256 threads and one load each this took
+// 116 us for the 50M-key side of 50M x 12.5M, 25 now.
+constexpr int64_t kChunk = 16384;
 constexpr int kBigNT = 1024;
 template <class K>
-__global__ __launch_bounds__(kBigNT) void k_big_minmax(const K *__restrict__ keys,
-                                                       const Overflow *__restrict__ cs,
-                                                       long long *__restrict__ mm) {
+__global__ __launch_bounds__(kBigNT) void k_big_minmax(const K *__restrict__ keys, Overflow *big,
+                                                       int64_t big_cap, const BucketStats *stats) {
     constexpr int kU = 8;
-    __shared__ long long s_lo[kBigNT / kWave], s_hi[kBigNT / kWave];
-    const Overflow c = cs[blockIdx.x];
-    const K *key = keys + c.start;
-    const int len = int(c.len);
-    long long lo = key[0], hi = lo;
-    for (int base = threadIdx.x; base < len; base += kBigNT * kU) {
-        K x[kU];
+    __shared__ int64_t s_lo[kBigNT / kWave], s_hi[kBigNT / kWave];
+    __shared__ uint32_t s_first[kBigNT + 1], s_scan[kBigNT / kWave];
+    const int64_t nbig = int64_t(stats->nbig);
+    if (nbig > big_cap) return;                      // the list does not hold them all
+    uint32_t before = 0;                             // chunks of the entries before e0
+    for (int64_t e0 = 0; e0 < nbig; e0 += kBigNT) {
+        const int64_t e = e0 + threadIdx.x;
+        const uint32_t mine = e < nbig ? uint32_t((big[e].len + kChunk - 1) / kChunk) : 0u;
+        uint32_t all;
+        s_first[threadIdx.x] = block_excl_scan<kBigNT>(mine, &all, s_scan);
+        if (threadIdx.x == 0) s_first[kBigNT] = all;
+        __syncthreads();
+        uint32_t c = blockIdx.x + gridDim.x - before % gridDim.x;
+        for (c = c >= gridDim.x ? c - gridDim.x : c; c < all; c += gridDim.x) {
+            int x = 0;                               // the last entry with s_first[x] <= c
 #pragma unroll
-        for (int u = 0; u < kU; u++) x[u] = key[base + u * kBigNT < len ? base + u * kBigNT : len - 1];
+            for (int st = kBigNT / 2; st > 0; st >>= 1) x += s_first[x + st] <= c ? st : 0;
+            Overflow *b = big + e0 + x;
+            const int64_t o = int64_t(c - s_first[x]) * kChunk;
+            const int len = int(b->len - o < kChunk ? b->len - o : kChunk);
+            const K *key = keys + b->start + o;
+            K klo = key[0], khi = klo;
+            for (int base = threadIdx.x; base < len; base += kBigNT * kU) {
+                K v[kU];
 #pragma unroll
-        for (int u = 0; u < kU; u++) {
-            lo = x[u] < lo ? x[u] : lo;
-            hi = x[u] > hi ? x[u] : hi;
+                for (int u = 0; u < kU; u++) v[u] = key[base + u * kBigNT < len ? base + u * kBigNT : len - 1];
+#pragma unroll
+                for (int u = 0; u < kU; u++) {
+                    klo = v[u] < klo ? v[u] : klo;
+                    khi = v[u] > khi ? v[u] : khi;
+                }
+            }
+            int64_t lo = klo, hi = khi;
+            for (int o2 = 1; o2 < kWave; o2 <<= 1) {
+                const int64_t ol = shfl_xor(lo, o2), oh = shfl_xor(hi, o2);
+                lo = ol < lo ? ol : lo;
+                hi = oh > hi ? oh : hi;
+            }
+            if (lane_id() == 0) {
+                s_lo[wave_id()] = lo;
+                s_hi[wave_id()] = hi;
+            }
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                for (int w = 1; w < kBigNT / kWave; w++) {
+                    lo = s_lo[w] < lo ? s_lo[w] : lo;
+                    hi = s_hi[w] > hi ? s_hi[w] : hi;
+                }
+                atomicMin(reinterpret_cast<long long *>(&b->kmin), (long long)lo);
+                atomicMax(reinterpret_cast<long long *>(&b->kmax), (long long)hi);
+            }
+            __syncthreads();
         }
-    }
-    for (int o = 1; o < kWave; o <<= 1) {
-        const long long ol = __shfl_xor(lo, o, kWave), oh = __shfl_xor(hi, o, kWave);
-        lo = ol < lo ? ol : lo;
-        hi = oh > hi ? oh : hi;
-    }
-    if (lane_id() == 0) {
-        s_lo[wave_id()] = lo;
-        s_hi[wave_id()] = hi;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int w = 1; w < kBigNT / kWave; w++) {
-            lo = s_lo[w] < lo ? s_lo[w] : lo;
-            hi = s_hi[w] > hi ? s_hi[w] : hi;
-        }
-        atomicMin(&mm[2 * c.kmin], lo);
-        atomicMax(&mm[2 * c.kmin + 1], hi);
+        before += all;
+        __syncthreads();
     }
 }
 
@@ -1478,9 +1501,6 @@ struct PartLayout {
     BucketStats *stats;
     Overflow *ovf;                      // big buckets, then the overflow list
     int64_t ovf_cap;
-    Overflow *chunks;                   // min/max chunks of the big buckets
-    int64_t chunk_cap;
-    long long *mm;                      // min, max per big bucket
     int32_t *ids, *ids_sorted;          // bucket number of every key, before / after grouping
     int2 *win;                          // windows of whole buckets
     int32_t *ruk, *rus;                 // runs of the grouped bucket numbers: value, start
@@ -1499,12 +1519,9 @@ static PartLayout part_layout(void *ws, int64_t n, int ksize, int bucket_bits) {
     PartLayout L = {};
     Carver c(ws);
     const int64_t nn = n > 0 ? n : 1;
-    L.stats = c.take<BucketStats>(1);
+    L.stats = c.take<BucketStats>(1);                   // read back together with the list
     L.ovf_cap = (int64_t(1) << bucket_bits) < kOvfCap ? (int64_t(1) << bucket_bits) : kOvfCap;
     L.ovf = c.take<Overflow>(size_t(L.ovf_cap));
-    L.chunk_cap = nn / kChunk + 1 + L.ovf_cap;
-    L.chunks = c.take<Overflow>(size_t(L.chunk_cap));
-    L.mm = c.take<long long>(size_t(2 * L.ovf_cap));
     L.ids = c.take<int32_t>(size_t(nn));
     L.ids_sorted = c.take<int32_t>(size_t(nn));
     L.win = c.take<int2>(size_t(2 * ceil_div(nn, kWin)));
@@ -1581,8 +1598,17 @@ static int partition_sort_typed(const K *key, const int32_t *in_rows, int64_t n,
                        s, out_key, out_rows, L.win, 2 * nwin, wide, L.stats);
         if ((rc = check_launch("window sort"))) return rc;
     }
+    TQP_LAUNCH("big_minmax", k_big_minmax<K>, dim3(unsigned(2 * kComputeUnits)), dim3(kBigNT), 0, s,
+               out_key, L.ovf, L.ovf_cap, L.stats);
+    if ((rc = check_launch("big bucket min/max"))) return rc;
+    // the counts and the first entries of the list in one read-back
+    constexpr size_t kPeek = 1024;
+    const size_t at = size_t(reinterpret_cast<char *>(L.ovf) - reinterpret_cast<char *>(L.stats));
+    const size_t peek = size_t(L.ovf_cap) < kPeek ? size_t(L.ovf_cap) : kPeek;
+    std::vector<char> head(at + peek * sizeof(Overflow));
+    if ((rc = download(head.data(), L.stats, head.size(), s, "partition stats"))) return rc;
     BucketStats hs;
-    if ((rc = download(&hs, L.stats, sizeof hs, s, "partition stats"))) return rc;
+    memcpy(&hs, head.data(), sizeof hs);
     int64_t n_ovf = 0, ovf_keys = 0, single = 0;
     const int64_t cap = tune(kTunePartOvfCap) < L.ovf_cap ? tune(kTunePartOvfCap) : L.ovf_cap;
     if (int64_t(hs.nbig) > cap) {
@@ -1598,45 +1624,25 @@ static int partition_sort_typed(const K *key, const int32_t *in_rows, int64_t n,
         n_ovf = int64_t(hs.nbig);
         ovf_keys = n;
     } else if (hs.nbig > 0) {
-        // 3. min and max of each big bucket: equal means one key, already in
+        // 4. big buckets whose min and max are equal hold one key, already in
         // stable order; the others are re-sorted together
-        const size_t nbig = size_t(hs.nbig);
-        std::vector<Overflow> big(nbig);
-        if ((rc = download(big.data(), L.ovf, sizeof(Overflow) * nbig, s, "big buckets"))) return rc;
-        std::vector<Overflow> chunks;
-        for (size_t j = 0; j < nbig; j++)
-            for (int64_t o = 0; o < big[j].len; o += kChunk)
-                chunks.push_back(Overflow{big[j].start + o,
-                                          big[j].len - o < kChunk ? big[j].len - o : kChunk,
-                                          int64_t(j), 0, 0});
-        if (int64_t(chunks.size()) > L.chunk_cap)
-            return set_error(TQP_EHIP, "partition sort: %zu chunks exceed %lld", chunks.size(),
-                             (long long)L.chunk_cap);
-        std::vector<long long> mm(2 * nbig);
-        for (size_t j = 0; j < nbig; j++) {
-            mm[2 * j] = LLONG_MAX;
-            mm[2 * j + 1] = LLONG_MIN;
-        }
-        if ((rc = upload(L.chunks, chunks.data(), sizeof(Overflow) * chunks.size(), s, "chunks")))
+        const size_t nbig = size_t(hs.nbig), seen = nbig < peek ? nbig : peek;
+        std::vector<Overflow> big(nbig), list;
+        memcpy(big.data(), head.data() + at, seen * sizeof(Overflow));
+        if (nbig > seen && (rc = download(big.data() + seen, L.ovf + seen, sizeof(Overflow) * (nbig - seen),
+                                          s, "big buckets")))
             return rc;
-        if ((rc = upload(L.mm, mm.data(), sizeof(long long) * mm.size(), s, "min/max"))) return rc;
-        TQP_LAUNCH("big_minmax", k_big_minmax<K>, dim3(unsigned(chunks.size())), dim3(kBigNT), 0, s,
-                   out_key, L.chunks, L.mm);
-        if ((rc = check_launch("big bucket min/max"))) return rc;
-        if ((rc = download(mm.data(), L.mm, sizeof(long long) * mm.size(), s, "min/max"))) return rc;
-        std::vector<Overflow> list;
-        for (size_t j = 0; j < nbig; j++) {
-            if (mm[2 * j] == mm[2 * j + 1]) {
+        for (const Overflow &b : big) {
+            if (b.kmin == b.kmax) {
                 single++;
                 continue;
             }
-            list.push_back(Overflow{big[j].start, big[j].len, int64_t(mm[2 * j]),
-                                    int64_t(mm[2 * j + 1]), 0});
-            ovf_keys += big[j].len;
+            list.push_back(b);
+            ovf_keys += b.len;
         }
         n_ovf = int64_t(list.size());
         if (!list.empty()) {
-            // 4. gather the overflowing buckets, sort them together, scatter back
+            // 5. gather the overflowing buckets, sort them together, scatter back
             std::sort(list.begin(), list.end(),
                       [](const Overflow &a, const Overflow &b) { return a.start < b.start; });
             int64_t total = 0, kmin = list[0].kmin, kmax = list[0].kmax;
