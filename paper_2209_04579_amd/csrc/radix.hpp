@@ -7,18 +7,17 @@
 // correctly and drops the bits that never vary.  The b significant bits are
 // cut into ceil(b / 8) digits of equal width (at most 8 bits: 21 bits take
 // three 7-bit digits, not 8 + 8 + 5), so each pass has as few bins, and as
-// long runs per bin, as its pass count allows.  One sweep builds the
-// histograms of every digit at once; each digit then takes one pass:
-//   * a workgroup takes a 4096-key tile (dynamic tile id),
+// long runs per bin, as its pass count allows.  A pass first counts each tile's
+// digits; then
+//   * a workgroup takes a 4096-key tile,
 //   * ranks its keys stably: each wave walks its items in input order, finds
 //     the lanes holding the same digit with one ballot per digit bit, and
 //     bumps a per-wave LDS counter once per distinct digit,
-//   * publishes its digit counts, stages its keys in LDS in digit order, and
-//     looks back over earlier tiles (one thread per digit) for the global start
-//     of each digit run,
+//   * adds the counts of the tiles before for the global start of each digit run,
 //   * then, column by column (keys, payloads, row ids), stages the tile in LDS
 //     in digit order and writes each digit run out with consecutive threads on
 //     consecutive addresses.
+// A sort of one tile does all of its passes in LDS, in one launch.
 // Carrying the payload through the passes keeps every later read of it
 // sequential, instead of a random gather through a permutation.
 #include "rowtest.hpp"
@@ -297,7 +296,7 @@ __device__ __forceinline__ void flush_stage(const void *s_stage, const uint32_t 
 //
 // What bounds it: on wide rows the traffic itself (each column read and
 // written once, the writes in runs of about 4096 / bins items); on narrow ones
-// the phases between barriers and the look-back.  So the kernel is kept to 64
+// the phases between barriers.  So the kernel is kept to 64
 // registers and 42 KiB of LDS, and two workgroups of 16 waves (all a CU can
 // hold) share a CU: one's waits are the other's work.  (512 threads of 8 items
 // take 100 to 128 registers, so half the waves.)  10M rows of 21 bytes: 139 -> 100
@@ -305,7 +304,7 @@ __device__ __forceinline__ void flush_stage(const void *s_stage, const uint32_t 
 // half of them kept: 572 -> 466.
 //
 // FILT: items whose bit in keep_bits is clear (bit i % 64 of
-// word i / 64, written by the filtered histogram) are dropped, as items past
+// word i / 64, written by the filtered count) are dropped, as items past
 // the end are, so the pass also compacts: its output holds the kept items,
 // sorted by the digit, in their input order within a digit, and their number
 // (the digits' total) goes to *d_kept.
@@ -497,6 +496,116 @@ __global__ __launch_bounds__(kSortNT, 8) void k_onesweep(
     }
 }
 
+// A whole sort of at most one tile in one launch: every pass in LDS, over keys and
+// local positions, the columns then read through the positions.  Small sorts are
+// bound by their launches, two per pass of about 4 us each, so this is taken
+// whenever the capacity is one tile.  Row ids out, a captured sort in us, one
+// launch per pass with its histograms / this one:
+//   keys                  100       1000       4000
+//   int32, 24 bits      34/7.4     36/11      38/14
+//   int64, 64 bits      82/17      88/24      96/34
+template <class K, class Ord>
+__global__ __launch_bounds__(kSortNT) void k_sort_tile(const K *__restrict__ keys_in, K *__restrict__ keys_out,
+                                                       PassCols c, int64_t n, const int64_t *d_n, Ord ord,
+                                                       int npass, int dbits) {
+    __shared__ K s_key[kSortTile];
+    __shared__ uint16_t s_idx[kSortTile];
+    __shared__ __attribute__((aligned(8))) uint16_t s_hist[kSortNW][kBins];
+    __shared__ uint32_t s_wtot[kBins / kWave];
+    const uint32_t cnt = uint32_t(count_of(d_n, n));
+    if (cnt == 0) return;
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(wave_id());
+    const int lane = lane_id();
+    const uint32_t nbins = 1u << dbits;
+    const uint32_t wave0 = w * (kWave * kSortIPT), at = wave0 + lane;
+    K key[kSortIPT];
+    uint32_t idx[kSortIPT];
+    load_items(keys_in, at, cnt, false, key);
+#pragma unroll
+    for (int k = 0; k < kSortIPT; k++) idx[k] = at + k * kWave;
+    for (int pass = 0; pass < npass; pass++) {
+        const int shift = pass * dbits;
+        reinterpret_cast<uint64_t *>(s_hist)[tid] = 0;
+        __syncthreads();
+        // stable rank of each item among the items of this wave with its digit
+        uint32_t dp[kSortIPT];
+#pragma unroll
+        for (int k = 0; k < kSortIPT; k++) {
+            dp[k] = kNoPos;
+            if (wave0 + k * kWave >= cnt) continue;          // (the same for the wave)
+            const uint32_t d = uint32_t(ord(key[k]) >> shift) & (nbins - 1);
+            const bool valid = at + k * kWave < cnt;
+            uint64_t peers = ballot(valid);
+            for (int b = 0; b < dbits; b++) {
+                const bool set = (d >> b) & 1u;
+                const uint64_t bb = ballot(set);
+                peers &= set ? bb : ~bb;
+            }
+            const uint32_t before = __popcll(peers & lanemask_lt());
+            uint16_t *h = &s_hist[w][d];
+            const uint32_t old = *h;
+            if (valid) dp[k] = (d << 16) | (old + before);
+            if (valid && before == 0) *h = uint16_t(old + __popcll(peers));
+        }
+        __syncthreads();
+        // per digit: its start, then the start of each wave's items of it
+        uint32_t local = 0;
+        if (tid < kBins) {
+            uint32_t tot = 0;
+#pragma unroll
+            for (int ww = 0; ww < kSortNW; ww++) tot += s_hist[ww][tid];
+            local = wave_incl_scan(tot);
+            if (lane == kWave - 1) s_wtot[w] = local;
+            local -= tot;
+        }
+        __syncthreads();
+        if (tid < kBins) {
+            for (int i = 0; i < w; i++) local += s_wtot[i];
+#pragma unroll
+            for (int ww = 0; ww < kSortNW; ww++) {
+                const uint32_t cw = s_hist[ww][tid];
+                s_hist[ww][tid] = uint16_t(local);
+                local += cw;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSortIPT; k++) {
+            if (dp[k] == kNoPos) continue;
+            const uint32_t p = (dp[k] & 0xffffu) + s_hist[w][dp[k] >> 16];
+            s_key[p] = key[k];
+            s_idx[p] = uint16_t(idx[k]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSortIPT; k++) {
+            const uint32_t i = at + k * kWave;
+            key[k] = s_key[i < cnt ? i : 0];
+            idx[k] = s_idx[i < cnt ? i : 0];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kSortIPT; k++)
+        if (at + k * kWave < cnt) keys_out[at + k * kWave] = key[k];
+    for (int p = 0; p < c.ncols; p++) {
+        uint64_t v[kSortIPT];
+        const void *src = c.pin[p];
+        const int dt = c.pdt[p];
+#pragma unroll
+        for (int k = 0; k < kSortIPT; k++) {
+            const uint32_t i = idx[k];
+            if (!src) v[k] = i;
+            else if (dt == TQP_INT64) v[k] = static_cast<const uint64_t *>(src)[i];
+            else if (dt == TQP_INT32) v[k] = static_cast<const uint32_t *>(src)[i];
+            else v[k] = static_cast<const uint8_t *>(src)[i];
+        }
+#pragma unroll
+        for (int k = 0; k < kSortIPT; k++)
+            if (at + k * kWave < cnt) store_any(c.pout[p], dt, at + k * kWave, int64_t(v[k]));
+    }
+}
+
 template <class K>
 __global__ __launch_bounds__(256) void k_copy_sorted(const K *__restrict__ keys_in, K *__restrict__ keys_out,
                                                      PassCols c, int64_t n, const int64_t *d_n) {
@@ -585,6 +694,11 @@ int run_radix(const K *key_in, int64_t n, const int64_t *d_n, int bits, Ord ord,
         const unsigned g = unsigned(ntiles > 4096 ? 4096 : ntiles);
         TQP_LAUNCH("copy_sorted", k_copy_sorted<K>, dim3(g), dim3(256), 0, s, key_in, key_out, pc, n, d_n);
         return check_launch("sort copy");
+    }
+    if (!pred && n <= kSortTile) {
+        TQP_LAUNCH("sort_tile", (k_sort_tile<K, Ord>), dim3(1), dim3(kSortNT), 0, s, key_in, key_out, pc, n, d_n,
+                   ord, npass, dbits);
+        return check_launch("sort of one tile");
     }
     Carver cv(ws);
     K *tmp_keys = nullptr;
