@@ -476,7 +476,8 @@ struct PairArgs {
     int64_t *tpairs;         // per tile: its pairs
     int64_t *bpairs;         // per block: its pairs
     int64_t *toff;           // first pair of each tile on the list
-    int32_t *list;           // tiles with more than kPjDirect pairs
+    int64_t direct;          // pairs up to which a tile's own workgroup writes them
+    int32_t *list;           // tiles with more
     uint32_t *nlist;
 };
 
@@ -785,7 +786,7 @@ template <class K>
 __global__ __launch_bounds__(kPjNT, 5) void k_pair_write(PairArgs a) {
     __shared__ K s_win[kPjWinBytes / sizeof(K)];
     __shared__ uint32_t s_pos[kPjTile];
-    __shared__ uint32_t s_off[kPjTile];          // at most kPjDirect pairs here
+    __shared__ uint32_t s_off[kPjTile];          // at most a.direct pairs here
     __shared__ uint32_t s_scan[kPjNW];
     __shared__ int64_t s_sum[kPjNW];
     const int64_t nl = count_of(a.d_nl, a.nl);
@@ -825,7 +826,7 @@ __global__ __launch_bounds__(kPjNT, 5) void k_pair_write(PairArgs a) {
             const uint32_t wn = uint32_t(shfl(thi, l) - int32_t(po.wlo));
             first += total;
             if (total == 0 || !want || po.base >= a.cap) continue;
-            if (total > kPjDirect) {
+            if (total > a.direct) {
                 if (threadIdx.x == 0) {
                     a.toff[t] = po.base;
                     a.list[atomicAdd(a.nlist, 1u)] = int32_t(t);
@@ -1055,13 +1056,17 @@ static int join_typed(const tqp_col *lkey, const int32_t *lrows, const int64_t *
         p.toff = L.toff;
         p.list = L.list;
         p.nlist = L.nlist;
+        // A tile has at most `most` pairs, and with a capacity of kPjDirect none of them
+        // writes more than that: then every tile is written at once and the third
+        // launch (4 us of a 10,000-row query's 66) is left out.
+        const int64_t most = (nl < kPjTile ? nl : kPjTile) * nr;
+        p.direct = cap <= kPjDirect && most <= INT32_MAX ? most : kPjDirect;
         const int64_t nt = ceil_div(nl, kPjTile);
         TQP_LAUNCH("pair_count", k_pair_count<K>, dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
         if ((rc = check_launch("join pair counts"))) return rc;
         TQP_LAUNCH("pair_write", k_pair_write<K>, dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
         if ((rc = check_launch("join pairs"))) return rc;
-        // a tile of nl rows has at most nl * nr pairs
-        if (!want_pairs || (nl < kPjTile ? nl : kPjTile) * nr <= kPjDirect) return TQP_OK;
+        if (!want_pairs || most <= p.direct) return TQP_OK;
         TQP_LAUNCH("pair_large", k_pair_large<K>, dim3(unsigned(kComputeUnits * 4)), dim3(kPjNT), 0, s, p);
         return check_launch("join large tiles");
     }
