@@ -34,14 +34,14 @@
 #include <type_traits>
 
 #include "keepbits.hpp"
+#include "semirows.hpp"
 
 namespace tqp {
 
 constexpr int kSjNT = 256;
 constexpr int kSjMaxSets = 4;
 constexpr int kSjMaxPay = 4;
-constexpr int kSjIPT = kFilterIPT;               // rows per lane and chunk
-constexpr int kSjChunk = kWave * kSjIPT;         // rows per wave and chunk
+static_assert(kSjIPT == kFilterIPT && kSjChunk == kWave * kSjIPT, "a lane's keep bits are a byte");
 // Words of key sets staged in LDS per 256 threads of workgroup (36 KiB): a
 // 1024-thread workgroup, alone on its compute unit, stages up to 144 KiB.
 constexpr int kSjLdsWordsPer256 = 9216;
@@ -70,25 +70,25 @@ struct SemiArgs {
 };
 
 // The keys of a whole chunk of aligned columns, 8 consecutive rows per lane; of the first
-// one where `row0` starts no whole chunk.  There is no second way to load them here: a
-// register that another branch had written would make the compiler wait for every
-// load in flight before this one's are issued.
+// one where `row0` starts no whole chunk (so a.n >= kSjChunk: sj_whole_chunks).  There is
+// no second way to load them here: a register that another branch had written would
+// make the compiler wait for every load in flight before this one's are issued.
 template <class K, int NS>
 __device__ __forceinline__ void sj_load(const SemiArgs &a, int64_t row0, K (&v)[NS][kSjIPT]) {
     constexpr int V = 16 / int(sizeof(K));     // keys per 16-byte load
-    if (row0 + kSjChunk > a.n) row0 = 0;
+    row0 = sj_chunk_row(row0, a.n);
 #pragma unroll
     for (int s = 0; s < NS; s++) {
         const K *p = static_cast<const K *>(a.key[s]) + row0;
 #pragma unroll
         for (int k = 0; k < kSjIPT / V; k++) {
-            const uint32_t q = uint32_t(threadIdx.x % kWave) * (kSjIPT / V) + k;
+            const uint32_t q = sj_lane_key<V>(threadIdx.x % kWave, k);
             if constexpr (sizeof(K) == 4) {
-                const int4 x = reinterpret_cast<const int4 *>(p)[q];
+                const int4 x = *reinterpret_cast<const int4 *>(p + q);
                 v[s][k * V + 0] = x.x; v[s][k * V + 1] = x.y;
                 v[s][k * V + 2] = x.z; v[s][k * V + 3] = x.w;
             } else {
-                const longlong2 x = reinterpret_cast<const longlong2 *>(p)[q];
+                const longlong2 x = *reinterpret_cast<const longlong2 *>(p + q);
                 v[s][k * V + 0] = x.x; v[s][k * V + 1] = x.y;
             }
         }
@@ -98,15 +98,11 @@ __device__ __forceinline__ void sj_load(const SemiArgs &a, int64_t row0, K (&v)[
 // The keys of any chunk that begins inside the table; past its end, the last row's again.
 template <class K, int NS>
 __device__ __forceinline__ void sj_load_any(const SemiArgs &a, int64_t row0, K (&v)[NS][kSjIPT]) {
-    const uint32_t left = uint32_t(a.n - 1 - row0 < kSjChunk ? a.n - 1 - row0 : kSjChunk - 1);
 #pragma unroll
     for (int s = 0; s < NS; s++) {
         const K *p = static_cast<const K *>(a.key[s]) + row0;
 #pragma unroll
-        for (int r = 0; r < kSjIPT; r++) {
-            const uint32_t i = uint32_t(lane_id()) * kSjIPT + r;
-            v[s][r] = p[i < left ? i : left];
-        }
+        for (int r = 0; r < kSjIPT; r++) v[s][r] = p[sj_any_row(row0, a.n, lane_id(), r)];
     }
 }
 
@@ -175,7 +171,7 @@ __device__ __forceinline__ uint32_t sj_test_mem(const SemiArgs &a, int s, const 
     return m;
 }
 
-// VEC: every key column is 16-byte aligned.
+// VEC: every key column is 16-byte aligned, and there is a whole chunk of rows at least.
 template <class K, int NS, bool VEC>
 __global__ __launch_bounds__(4 * kSjNT) void k_semi_mask(SemiArgs a) {
     // two chunks' keys in registers, where they take at most half of them
@@ -586,7 +582,7 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
     const int ks = dtype_size(dt), nw = kSjNT * wg / kWave;
     int64_t row0 = 0;
     for (int turn = 0; row0 < n || row0 == 0; turn ^= 1) {
-        const int64_t rows = n - row0 < most ? n - row0 : most;
+        const int64_t rows = sj_part_rows(n, row0, most);
         const SemiLayout L = semi_layout(ws, rows, dt, part == 0);
         a.n = rows;
         const int per_block = L.keep.steps * kFilterTile / kSjChunk;        // powers of two
@@ -602,8 +598,9 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
         out.d_prev = row0 > 0 ? L.d_sum + turn : nullptr;
         out.d_next = row0 + rows < n ? L.d_sum + (turn ^ 1) : nullptr;
         const size_t lds = size_t(lds_words) * 4;
-        const auto run = dt == TQP_INT32 ? (vec ? launch_semijoin<int32_t, true> : launch_semijoin<int32_t, false>)
-                                         : (vec ? launch_semijoin<int64_t, true> : launch_semijoin<int64_t, false>);
+        const bool whole = sj_whole_chunks(vec, rows);
+        const auto run = dt == TQP_INT32 ? (whole ? launch_semijoin<int32_t, true> : launch_semijoin<int32_t, false>)
+                                         : (whole ? launch_semijoin<int64_t, true> : launch_semijoin<int64_t, false>);
         const int rc = run(nsets, a, out, per_cu, kSjNT * wg, lds, s);
         if (rc || n == 0) return rc;
         row0 += rows;
@@ -632,7 +629,7 @@ TQP_API int tqp_semijoin(const tqp_col *keys, const tqp_keyset *sets, int nsets,
 // the table at a time.  Each device the library runs on holds its own copy until
 // the process ends.
 constexpr size_t kSjScratchBytes = size_t(8) << 20;
-constexpr int64_t kSjPartRows = int64_t(1) << 25;       // 4 MiB of keep bits
+static_assert(size_t(kSjPartRows) / 8 < kSjScratchBytes, "a part's keep bits");
 // the longest table with int64 keys (of int32: any)
 constexpr int64_t kSjMaxRows64 = ((int64_t(1) << 20) - 4) * 1536;
 static __device__ __align__(256) uint64_t scratch[kSjScratchBytes / 8];
