@@ -5,8 +5,8 @@
 // rows are one run of the output.  A first kernel finds each tile's window of
 // right rows and counts its pairs; a second one takes the tiles again, starts at
 // the sum of the counts before its tile, finds every left row's right rows in the
-// window (staged in LDS) and writes the pairs.  A tile with very many pairs is
-// left to a third kernel, which spreads its pairs over the chip.
+// window (staged in LDS) and writes the pairs.  The pairs of a tile with many of them are
+// left to a third kernel, which spreads them over the chip.
 //
 // Ranges (one per matched key).
 //
@@ -436,20 +436,37 @@ __global__ __launch_bounds__(kJoinNT) void k_join_expand(
 
 // ---- pairs ---------------------------------------------------------------------
 //
-// What bounds it: reading the left keys (twice) and writing the pairs.  The
-// version before this went through the runs of both sides (run-length encoding,
-// a match of the runs with two look-backs, an expansion that searched each
-// output's range): 30M left rows against 2M unique right ones 365 -> 257 us,
-// 500K against 10K 60 -> 24, 1.5M against 400K in runs of two 86 -> 57.  The
-// searches are chains of LDS reads, so many small workgroups are kept resident.
+// What bounds it: reading the left keys (twice) and writing the pairs.  A version of
+// this through the runs of both sides (run-length encoding, a match of the runs with two
+// look-backs, an expansion that searched each output's range) takes 345 us for 30M
+// left rows against 2M right ones, 280 now; 20M against 1M unique ones 232 and 140; 1.5M
+// against 400K in runs of two 86 and 57.  The searches are chains of LDS reads, so
+// many small workgroups are kept resident.
+//
+// Where left rows meet many right ones, the pairs decide, not the rows: tiles with many are
+// listed, and windows that cannot be staged are searched once only, with what the
+// search found kept for the writing (12 bytes per left row).  us through the runs / with
+// every tile's pairs found again and written by its own workgroup up to 16384 of
+// them, in steps of 32768 beyond / now, int32 keys:
+//   500 x 10K, 20 right rows each 41/83/28          10K x 1M, 100 each     54/205/44
+//   3M x 3M, 10 each             200/238/168        2M x 30M, 30 each      450/923/339
+//   30K x 30K, 300 each          66/129/44          20K x 20K, 10K each    4330/720/500
 constexpr int kPjNT = 256;
 constexpr int kPjIPT = 8;
 constexpr int kPjTile = kPjNT * kPjIPT;            // left rows per tile
 constexpr int kPjNW = kPjNT / kWave;
-constexpr int kPjWinBytes = 15360;                 // right keys of a tile's window staged in LDS (five workgroups per CU)
+constexpr int kPjWinBytes = 19456;                 // right keys of a tile's window staged in LDS (five workgroups per CU)
 constexpr int kPjMaxSteps = 8;
-constexpr int64_t kPjDirect = 8 * kPjTile;         // pairs a tile's own workgroup writes
-constexpr int64_t kPjChunk = 32768;                // pairs per step of a larger tile
+constexpr uint32_t kPjSegments = 16;               // staged lengths of window that the count goes through one by one
+constexpr int64_t kPjFewTiles = 2 * kComputeUnits; // ... unless there are fewer tiles
+constexpr int kPjChunk = kPjNT * kPjIPT;           // pairs written at a time
+constexpr int kPjSpread = 2 * kPjChunk;            // ... of listed tiles
+constexpr uint32_t kPjRun = 32;                    // right rows per left one that a tile's own workgroup writes
+constexpr int64_t kPjSmallCap = 8 * kPjChunk;      // capacity up to which it writes all of its pairs
+
+// Pairs that a tile's own workgroup writes, a chunk after the other: where the tiles leave the
+// chip idle, fewer.
+__device__ __forceinline__ int64_t pj_direct(int64_t ntiles) { return (ntiles < kPjFewTiles ? 2 : 4) * kPjChunk; }
 
 // Tiles per block for nl left rows: the widest of 8, 4, 2, 1 that still gives
 // eight blocks per compute unit.  (A block's tiles share one search of the right
@@ -473,13 +490,31 @@ struct PairArgs {
     int64_t cap;
     int64_t *d_count;
     int32_t *win;            // per tile: its window [win[2t], win[2t + 1]) of right rows
-    int64_t *tpairs;         // per tile: its pairs
+    int64_t *tpairs;         // per tile: its pairs, complemented if it is listed
     int64_t *bpairs;         // per block: its pairs
-    int64_t *toff;           // first pair of each tile on the list
-    int64_t direct;          // pairs up to which a tile's own workgroup writes them
-    int32_t *list;           // tiles with more
+    // Where tiles may be listed or have windows that cannot be staged (else null): of
+    // those that are or have, per left row its first pair in the tile and its first right row;
+    // of the listed ones their first pair, and the list of their chunks.
+    int64_t *toff;
+    int64_t *roff;
+    int32_t *rpos;
+    int2 *list;              // tile, chunk in the tile
     uint32_t *nlist;
 };
+// A tile is listed if it has more than pj_direct pairs or a left row with more than kPjRun
+// right rows: its pairs are then spread over the chip by a third launch.  With a capacity of kPjSmallCap (or as many pairs at most) no workgroup
+// writes more than that anyway, so if every window can be staged, every tile is written
+// at once and that launch (4 us of a 10,000-row query's 66) is left out.
+static bool pj_lists(int64_t nl, int64_t nr, int64_t cap, int key_size) {
+    const int64_t most = (nl < kPjTile ? nl : kPjTile) * nr;
+    return nr > kPjWinBytes / key_size || (most > kPjSmallCap && cap > kPjSmallCap);
+}
+
+// Whether the windows are longer on average than can be staged.
+static bool pj_long(int64_t nl, int64_t nr, int key_size) {
+    const int64_t win = kPjWinBytes / key_size;
+    return nr > win && nr * kPjTile > nl * win;
+}
 
 // The first position in [lo, n) whose key is not below k (not above k: UPPER),
 // found by a whole wave: 64 probes per round trip, spread over [lo, n), then over
@@ -642,6 +677,119 @@ __device__ __forceinline__ uint32_t match_rows_far(const K *p, uint32_t n, const
     return c;
 }
 
+// match_rows by binary searches for all the thread's keys, and for both ends of their
+// positions, side by side: one read's latency per step instead of a chain of them, but
+// more reads where the keys lie close together.
+template <class K, class P>
+__device__ __forceinline__ uint32_t search_rows(P p, uint32_t n, const K (&key)[kPjIPT], uint32_t valid,
+                                                uint32_t (&pos)[kPjIPT], uint32_t (&cnt)[kPjIPT]) {
+    uint32_t end[kPjIPT];
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) pos[r] = end[r] = 0;
+    for (uint32_t st = n ? 1u << (31 - __builtin_clz(n)) : 0u; st > 0; st >>= 1) {
+#pragma unroll
+        for (int r = 0; r < kPjIPT; r++) {
+            const uint32_t a = pos[r] + st, b = end[r] + st;
+            const K x = p[a <= n ? a - 1 : 0], y = p[b <= n ? b - 1 : 0];
+            pos[r] = a <= n && x < key[r] ? a : pos[r];
+            end[r] = b <= n && !(key[r] < y) ? b : end[r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) cnt[r] = (valid >> r) & 1 ? end[r] - pos[r] : 0;
+    return end[kPjIPT - 1] - pos[kPjIPT - 1];
+}
+
+// The same over a window p[0, n) too long to stage: every stride-th of its keys is staged in
+// s_win instead (nc of them), and a search there ends in one stretch of the window, so
+// that there are log2(stride) steps of one round trip to memory each.
+template <class K>
+__device__ __forceinline__ uint32_t search_rows_far(const K *p, uint32_t n, const K *s_win, uint32_t nc,
+                                                    uint32_t stride, const K (&key)[kPjIPT], uint32_t valid,
+                                                    uint32_t (&pos)[kPjIPT], uint32_t (&cnt)[kPjIPT]) {
+    search_rows(s_win, nc, key, ~0u, pos, cnt);
+    uint32_t pb[kPjIPT], end[kPjIPT], eb[kPjIPT];      // the stretches, and the positions inside
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) {
+        pb[r] = pos[r] * stride;
+        eb[r] = (pos[r] + cnt[r]) * stride;
+        pos[r] = end[r] = 0;
+    }
+    for (uint32_t st = 1u << (31 - __builtin_clz(stride)); st > 0; st >>= 1) {
+#pragma unroll
+        for (int r = 0; r < kPjIPT; r++) {
+            // (a stretch has stride - 1 unstaged keys, the last one what is left of the window)
+            const uint32_t a = pos[r] + st, b = end[r] + st;
+            const bool ina = a < stride && pb[r] + a <= n, inb = b < stride && eb[r] + b <= n;
+            const K x = p[ina ? pb[r] + a - 1 : 0], y = p[inb ? eb[r] + b - 1 : 0];
+            pos[r] = ina && x < key[r] ? a : pos[r];
+            end[r] = inb && !(key[r] < y) ? b : end[r];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) {
+        pos[r] += pb[r];
+        end[r] += eb[r];
+        cnt[r] = (valid >> r) & 1 ? end[r] - pos[r] : 0;
+    }
+    return end[kPjIPT - 1] - pos[kPjIPT - 1];
+}
+
+// Stages len (at most kWin) right keys, every stride-th from p on, all loads in flight at once.
+template <class K>
+__device__ __forceinline__ void stage_keys(const K *p, uint32_t len, uint32_t stride, K *s_win) {
+    constexpr int kPer = (kPjWinBytes / int(sizeof(K)) + kPjNT - 1) / kPjNT;
+    K x[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; u++) {
+        const uint32_t i = threadIdx.x + u * kPjNT;
+        x[u] = p[int64_t(i < len ? i : len - 1) * stride];
+    }
+#pragma unroll
+    for (int u = 0; u < kPer; u++)
+        if (threadIdx.x + u * kPjNT < len) s_win[threadIdx.x + u * kPjNT] = x[u];
+}
+
+// The right rows of a tile's left rows in a window [wlo, wlo + wn) of any length, by searches:
+// staged in turn, a segment at a time, or, beyond kPjSegments of them, every stride-th
+// key staged.  (The second way has fewer steps in a row, but its reads of the window are
+// scattered: so few tiles, which leave the chip idle, always take it.)
+template <class K>
+__device__ __forceinline__ uint32_t match_long(const K *rk, int64_t wlo, uint32_t wn, int64_t ntiles, K *s_win,
+                                               const K (&key)[kPjIPT], uint32_t valid,
+                                               uint32_t (&pos)[kPjIPT], uint32_t (&cnt)[kPjIPT]) {
+    constexpr uint32_t kWin = kPjWinBytes / sizeof(K);
+    if (wn > (ntiles < kPjFewTiles ? 1 : kPjSegments) * kWin) {
+        const uint32_t stride = (wn + kWin - 1) / kWin, nc = wn / stride;
+        __syncthreads();
+        stage_keys(rk + wlo + stride - 1, nc, stride, s_win);
+        __syncthreads();
+        return search_rows_far(rk + wlo, wn, static_cast<const K *>(s_win), nc, stride, key, valid, pos, cnt);
+    }
+    uint32_t after = 0;
+#pragma unroll
+    for (int r = 0; r < kPjIPT; r++) pos[r] = cnt[r] = 0;
+    for (uint32_t s0 = 0; s0 < wn; s0 += kWin) {
+        const uint32_t len = wn - s0 < kWin ? wn - s0 : kWin;
+        __syncthreads();
+        stage_keys(rk + wlo + s0, len, 1, s_win);
+        __syncthreads();
+        if (s_win[len - 1] < key[0]) {
+#pragma unroll
+            for (int r = 0; r < kPjIPT; r++) pos[r] += len;
+        } else if (!(key[kPjIPT - 1] < s_win[0])) {
+            uint32_t p[kPjIPT], c[kPjIPT];
+            after += search_rows(static_cast<const K *>(s_win), len, key, valid, p, c);
+#pragma unroll
+            for (int r = 0; r < kPjIPT; r++) {
+                pos[r] += p[r];
+                cnt[r] += c[r];
+            }
+        }
+    }
+    return after;
+}
+
 // The right rows of a tile's left rows in the window [wlo, wlo + wn), staged in
 // s_win whole or in part (the caller's barrier must have freed s_win).
 template <class K>
@@ -667,13 +815,14 @@ __device__ __forceinline__ uint32_t match_tile(const K *rk, int64_t wlo, uint32_
 // keys from there are staged at once: only a tile whose keys reach further
 // searches for its window's end.
 template <class K> constexpr uint32_t pj_ahead() { return 4096 / sizeof(K); }
-template <class K>
-__global__ __launch_bounds__(kPjNT) void k_pair_count(PairArgs a) {
+template <class K, bool LONG>
+__global__ __launch_bounds__(kPjNT, LONG ? 3 : sizeof(K) == 4 ? 6 : 5) void k_pair_count(PairArgs a) {
     __shared__ K s_win[kPjWinBytes / sizeof(K)];
     __shared__ K s_last;
-    __shared__ int64_t s_bound;
+    __shared__ int64_t s_bound, s_upper;
     __shared__ uint32_t s_end[2];                      // the last row's position and count
     __shared__ int64_t s_sum[kPjNW];
+    __shared__ uint32_t s_long[kPjNW];                 // whether a row has more than kPjRun right rows
     const int64_t nl = count_of(a.d_nl, a.nl), nr = count_of(a.d_nr, a.nr);
     const K *lk = static_cast<const K *>(a.lkey), *rk = static_cast<const K *>(a.rkey);
     const bool vec = reinterpret_cast<uintptr_t>(lk) % 16 == 0;
@@ -684,51 +833,102 @@ __global__ __launch_bounds__(kPjNT) void k_pair_count(PairArgs a) {
         const int64_t t0 = b * steps, t1 = t0 + steps < ntiles ? t0 + steps : ntiles;
         K key[kPjIPT];
         uint32_t valid = load_left(lk, t0 * kPjTile, nl, vec, key);
+        if constexpr (LONG) {
+            if (threadIdx.x == kPjNT - 1) s_last = key[kPjIPT - 1];
+            __syncthreads();
+        }
         if (wave_id() == 0) {
             const int64_t x = wave_bound<false>(rk, 0, nr, shfl(key[0], 0), false);
             if (lane_id() == 0) s_bound = x;
+        } else if (LONG && wave_id() == 1) {
+            const int64_t x = wave_bound<true>(rk, 0, nr, s_last, false);
+            if (lane_id() == 0) s_upper = x;
         }
         __syncthreads();
         int64_t from = s_bound, bsum = 0;
         for (int64_t t = t0; t < t1; t++) {
-            const uint32_t left = uint32_t(nr - from);
-            uint32_t wn = left < pj_ahead<K>() ? left : pj_ahead<K>();
-            for (uint32_t i = threadIdx.x; i < wn; i += kPjNT) s_win[i] = rk[from + i];
-            if (threadIdx.x == kPjNT - 1) s_last = key[kPjIPT - 1];
             K next[kPjIPT];
             uint32_t nvalid = 0;
-            if (t + 1 < t1) nvalid = load_left(lk, (t + 1) * kPjTile, nl, vec, next);
-            __syncthreads();
             uint32_t pos[kPjIPT], cnt[kPjIPT], after;  // after: positions holding the thread's last key
-            if (wn == left || s_last < s_win[wn - 1]) {
-                after = match_rows(static_cast<const K *>(s_win), wn, key, valid, pos, cnt);
-            } else {
-                if (wave_id() == 0) {
-                    const int64_t x = wave_bound<true>(rk, from + wn, nr, s_last, true);
-                    if (lane_id() == 0) s_bound = x;
+            if constexpr (LONG) {
+                if (t > t0) {
+                    if (threadIdx.x == kPjNT - 1) s_last = key[kPjIPT - 1];
+                    __syncthreads();
+                    if (wave_id() == 0) {
+                        const int64_t x = wave_bound<true>(rk, from, nr, s_last, true);
+                        if (lane_id() == 0) s_upper = x;
+                    }
+                    __syncthreads();
                 }
+                after = match_long(rk, from, uint32_t(s_upper - from), ntiles, s_win, key, valid, pos, cnt);
+                if (t + 1 < t1) nvalid = load_left(lk, (t + 1) * kPjTile, nl, vec, next);
+            } else {
+                const uint32_t left = uint32_t(nr - from);
+                uint32_t wn = left < pj_ahead<K>() ? left : pj_ahead<K>();
+                for (uint32_t i = threadIdx.x; i < wn; i += kPjNT) s_win[i] = rk[from + i];
+                if (threadIdx.x == kPjNT - 1) s_last = key[kPjIPT - 1];
+                if (t + 1 < t1) nvalid = load_left(lk, (t + 1) * kPjTile, nl, vec, next);
                 __syncthreads();
-                wn = uint32_t(s_bound - from);
-                after = match_tile(rk, from, wn, s_win, key, valid, pos, cnt);
+                if (wn == left || s_last < s_win[wn - 1]) {
+                    after = match_rows(static_cast<const K *>(s_win), wn, key, valid, pos, cnt);
+                } else {
+                    if (wave_id() == 0) {
+                        const int64_t x = wave_bound<true>(rk, from + wn, nr, s_last, true);
+                        if (lane_id() == 0) s_bound = x;
+                    }
+                    __syncthreads();
+                    wn = uint32_t(s_bound - from);
+                    after = match_tile(rk, from, wn, s_win, key, valid, pos, cnt);
+                }
             }
             if (threadIdx.x == kPjNT - 1) {
                 s_end[0] = pos[kPjIPT - 1];
                 s_end[1] = after;
             }
             int64_t sum = 0;
+            bool longrun = false;
 #pragma unroll
-            for (int r = 0; r < kPjIPT; r++) sum += cnt[r];
-            sum = wave_sum(sum);
-            if (lane_id() == 0) s_sum[wave_id()] = sum;
+            for (int r = 0; r < kPjIPT; r++) {
+                sum += cnt[r];
+                longrun = longrun || cnt[r] > kPjRun;
+            }
+            longrun = __any(longrun);
+            const int64_t upto = wave_incl_scan(sum);
+            if (lane_id() == kWave - 1) {
+                s_sum[wave_id()] = upto;
+                s_long[wave_id()] = longrun;
+            }
             __syncthreads();
-            if (threadIdx.x == 0) {
-                int64_t x = 0;
+            int64_t ex = upto - sum, total = 0;
+            const bool stored = a.roff && s_end[0] + s_end[1] > kPjWinBytes / sizeof(K);
+            bool listed = false;
 #pragma unroll
-                for (int w = 0; w < kPjNW; w++) x += s_sum[w];
-                a.tpairs[t] = x;
+            for (int w = 0; w < kPjNW; w++) {
+                if (w < wave_id()) ex += s_sum[w];
+                total += s_sum[w];
+                listed = listed || s_long[w];
+            }
+            listed = (listed || total > pj_direct(ntiles)) && a.roff;
+            if (threadIdx.x == 0) {
+                a.tpairs[t] = listed ? ~total : total;
                 a.win[2 * t] = int32_t(from);
                 a.win[2 * t + 1] = int32_t(from + s_end[0] + s_end[1]);
-                bsum += x;
+                bsum += total;
+            }
+            if (listed || stored) {
+                // (the arrays hold whole tiles)
+                const int64_t row0 = t * kPjTile + threadIdx.x * kPjIPT;
+#pragma unroll
+                for (int r = 0; r < kPjIPT; r += 4) {
+                    const int64_t e1 = ex + cnt[r], e2 = e1 + cnt[r + 1], e3 = e2 + cnt[r + 2];
+                    const int32_t f = int32_t(from);
+                    longlong2 *off = reinterpret_cast<longlong2 *>(a.roff + row0 + r);
+                    off[0] = {ex, e1};
+                    off[1] = {e2, e3};
+                    *reinterpret_cast<int4 *>(a.rpos + row0 + r) = {f + int32_t(pos[r]), f + int32_t(pos[r + 1]),
+                                                                    f + int32_t(pos[r + 2]), f + int32_t(pos[r + 3])};
+                    ex = e3 + cnt[r + 3];
+                }
             }
             from += s_end[0];
 #pragma unroll
@@ -740,55 +940,109 @@ __global__ __launch_bounds__(kPjNT) void k_pair_count(PairArgs a) {
     }
 }
 
-struct PairOut {
-    int64_t base;            // the tile's first pair
-    int64_t row0, wlo;
-};
-
-// Writes pairs [o0, o1) of a tile, whose rows' first pairs are s_off[]: consecutive threads take consecutive pairs, each finding
-// its left row by a binary search.
-template <class K, class O>
-__device__ __forceinline__ void expand_tile(const PairArgs &a, const PairOut &t, const uint32_t *s_pos,
-                                            const O *s_off, int64_t o0, int64_t o1) {
-    const K *lk = static_cast<const K *>(a.lkey);
-    for (int64_t o = o0 + threadIdx.x; o < o1; o += kPjNT) {
-        if (t.base + o >= a.cap) return;
-        int row = 0;                                   // the last row with s_off[row] <= o
-#pragma unroll
-        for (int st = kPjTile / 2; st > 0; st >>= 1) row += int64_t(s_off[row + st]) <= o ? st : 0;
-        const int64_t i = t.row0 + row, j = t.wlo + s_pos[row] + (o - int64_t(s_off[row]));
-        if (a.out_l) a.out_l[t.base + o] = a.lrows ? a.lrows[i] : int32_t(i);
-        if (a.out_r) a.out_r[t.base + o] = a.rrows ? a.rrows[j] : int32_t(j);
-        if (a.out_key) static_cast<K *>(a.out_key)[t.base + o] = lk[i];
-    }
+// Inclusive maximum over the lanes of a wave (values >= 0), as wave_incl_scan_u32.
+template <int Ctrl, int RowMask> __device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
+    const uint32_t u = uint32_t(__builtin_amdgcn_update_dpp(0, int(v), Ctrl, RowMask, 0xf, false));
+    return u > v ? u : v;
+}
+__device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
+    v = dpp_max<0x111, 0xf>(v);
+    v = dpp_max<0x112, 0xf>(v);
+    v = dpp_max<0x114, 0xf>(v);
+    v = dpp_max<0x118, 0xf>(v);
+    v = dpp_max<0x142, 0xa>(v);
+    v = dpp_max<0x143, 0xc>(v);
+    return v;
 }
 
-// Fills s_pos and s_off (the exclusive sums of the counts) for a tile.
-template <class O>
-__device__ __forceinline__ void tile_offsets(const uint32_t (&pos)[kPjIPT], const uint32_t (&cnt)[kPjIPT],
-                                             uint32_t *s_pos, O *s_off, O *s_scan) {
-    O sum = 0, tot;
+// The left row of each pair of a chunk, in place: s_mark holds a row at the chunk's first
+// pair and at the first pair of every further row, 0 elsewhere; rows ascend, so that a
+// running maximum fills it.  The marks must be visible; a barrier is left to the caller.
+template <int N>
+__device__ __forceinline__ void fill_marks(uint16_t *s_mark, uint32_t *s_max) {
+    constexpr int R = N / kPjNT;                       // pairs per thread
+    static_assert(R % 8 == 0, "16-byte accesses");
+    uint4 x[R / 8];
+    uint32_t v[R];
 #pragma unroll
-    for (int r = 0; r < kPjIPT; r++) {
-        s_pos[threadIdx.x * kPjIPT + r] = pos[r];
-        sum += cnt[r];
+    for (int q = 0; q < R / 8; q++) {
+        x[q] = reinterpret_cast<const uint4 *>(s_mark)[threadIdx.x * (R / 8) + q];
+        v[8 * q] = x[q].x & 0xffff; v[8 * q + 1] = x[q].x >> 16; v[8 * q + 2] = x[q].y & 0xffff; v[8 * q + 3] = x[q].y >> 16;
+        v[8 * q + 4] = x[q].z & 0xffff; v[8 * q + 5] = x[q].z >> 16; v[8 * q + 6] = x[q].w & 0xffff; v[8 * q + 7] = x[q].w >> 16;
     }
-    O ex = block_excl_scan<kPjNT>(sum, &tot, s_scan);
 #pragma unroll
-    for (int r = 0; r < kPjIPT; r++) {
-        s_off[threadIdx.x * kPjIPT + r] = ex;
-        ex += cnt[r];
-    }
+    for (int k = 1; k < R; k++) v[k] = v[k] > v[k - 1] ? v[k] : v[k - 1];
+    const uint32_t inc = wave_incl_max(v[R - 1]);
+    if (lane_id() == kWave - 1) s_max[wave_id()] = inc;
+    const uint32_t up = uint32_t(__shfl_up(int(inc), 1, kWave));
+    uint32_t pre = lane_id() > 0 ? up : 0;
     __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kPjNW; w++)
+        if (w < wave_id()) pre = s_max[w] > pre ? s_max[w] : pre;
+#pragma unroll
+    for (int k = 0; k < R; k++) v[k] = v[k] > pre ? v[k] : pre;
+#pragma unroll
+    for (int q = 0; q < R / 8; q++)
+        reinterpret_cast<uint4 *>(s_mark)[threadIdx.x * (R / 8) + q] =
+            uint4{v[8 * q] | v[8 * q + 1] << 16, v[8 * q + 2] | v[8 * q + 3] << 16,
+                  v[8 * q + 4] | v[8 * q + 5] << 16, v[8 * q + 6] | v[8 * q + 7] << 16};
 }
 
-template <class K>
-__global__ __launch_bounds__(kPjNT, 5) void k_pair_write(PairArgs a) {
+// Pairs [o0, o0 + n) of a tile whose first pair is slot base, from the filled marks
+// (rows counted from left row row0): consecutive threads take consecutive pairs.  The right
+// row of pair o is s_d[its left row] + o (modulo 2^32).
+template <class K, int N, int R>
+__device__ __forceinline__ void write_chunk(const PairArgs &a, const uint16_t *s_mark, const uint32_t *s_d,
+                                            int64_t row0, int64_t base, int64_t o0, int n) {
+    const K *lk = static_cast<const K *>(a.lkey);
+    const int64_t slot = base + o0;
+    // (past the end: the last pair again, so that no load waits for a branch)
+#pragma unroll 1
+    for (int k0 = 0; k0 < N / kPjNT; k0 += R) {
+        uint32_t row[R];
+        int32_t j[R], left[R];
+        K key[R];
+#pragma unroll
+        for (int k = 0; k < R; k++) {
+            const int o = (k0 + k) * kPjNT + int(threadIdx.x), at = o < n ? o : n - 1;
+            row[k] = s_mark[at];
+            j[k] = int32_t(s_d[row[k]] + uint32_t(o0) + uint32_t(at));
+            left[k] = int32_t(row0) + int32_t(row[k]);
+        }
+        if (a.out_key) {
+#pragma unroll
+            for (int k = 0; k < R; k++) key[k] = lk[row0 + row[k]];
+        }
+        if (a.lrows) {
+#pragma unroll
+            for (int k = 0; k < R; k++) left[k] = a.lrows[row0 + row[k]];
+        }
+        if (a.rrows) {
+#pragma unroll
+            for (int k = 0; k < R; k++) j[k] = a.rrows[j[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < R; k++) {
+            const int o = (k0 + k) * kPjNT + int(threadIdx.x);
+            if (o >= n) break;
+            if (a.out_l) a.out_l[slot + o] = left[k];
+            if (a.out_r) a.out_r[slot + o] = j[k];
+            if (a.out_key) static_cast<K *>(a.out_key)[slot + o] = key[k];
+        }
+    }
+}
+
+// LIST: tiles that are listed are left out.
+template <class K, bool LIST>
+__global__ __launch_bounds__(kPjNT, LIST ? 5 : 3) void k_pair_write(PairArgs a) {
     __shared__ K s_win[kPjWinBytes / sizeof(K)];
+    // the left and right rows of a chunk's pairs (or, of long runs, the chunk's marks)
     __shared__ uint32_t s_pos[kPjTile];
-    __shared__ uint32_t s_off[kPjTile];          // at most a.direct pairs here
+    __shared__ __attribute__((aligned(16))) uint16_t s_off[kPjTile];
     __shared__ uint32_t s_scan[kPjNW];
     __shared__ int64_t s_sum[kPjNW];
+    __shared__ uint32_t s_slot;
     const int64_t nl = count_of(a.d_nl, a.nl);
     const K *lk = static_cast<const K *>(a.lkey), *rk = static_cast<const K *>(a.rkey);
     const bool vec = reinterpret_cast<uintptr_t>(lk) % 16 == 0;
@@ -813,63 +1067,128 @@ __global__ __launch_bounds__(kPjNT, 5) void k_pair_write(PairArgs a) {
         // the block's tiles, one per lane: pairs, window
         int64_t tp = 0;
         int32_t tlo = 0, thi = 0;
+        bool listed = false;
         if (lane < t1 - t0) {
             tp = a.tpairs[t0 + lane];
+            listed = tp < 0;
+            if (listed) tp = ~tp;
             tlo = a.win[2 * (t0 + lane)];
             thi = a.win[2 * (t0 + lane) + 1];
+        }
+        if (LIST && __any(listed)) {                   // (the same for the workgroup)
+            // the chunks, below the capacity, of the listed tiles go on the list
+            const int64_t end = base + wave_incl_scan(tp), tbase = end - tp;
+            const int64_t room = a.cap - tbase < tp ? a.cap - tbase : tp;
+            const uint32_t n = listed && room > 0 ? uint32_t((room + kPjSpread - 1) / kPjSpread) : 0u;
+            const uint32_t upto = wave_incl_scan(n);
+            const uint32_t all = uint32_t(__builtin_amdgcn_readlane(int(upto), kWave - 1));
+            if (all) {
+                if (threadIdx.x == 0) s_slot = atomicAdd(a.nlist, all);
+                if (w == 0 && n) a.toff[t0 + lane] = tbase;
+                __syncthreads();
+                const uint32_t at = s_slot;
+                for (int l = 0; l < int(t1 - t0); l++) {
+                    const uint32_t nt = uint32_t(__builtin_amdgcn_readlane(int(n), l));
+                    const uint32_t to = at + uint32_t(__builtin_amdgcn_readlane(int(upto), l)) - nt;
+                    for (uint32_t c = threadIdx.x; c < nt; c += kPjNT) a.list[to + c] = make_int2(int(t0) + l, int(c));
+                }
+            }
         }
         int64_t first = base;                          // the tile's first pair
         for (int64_t t = t0; t < t1; t++) {
             const int l = int(t - t0);
-            const int64_t total = shfl(tp, l);
-            const PairOut po = {first, t * kPjTile, shfl(tlo, l)};
-            const uint32_t wn = uint32_t(shfl(thi, l) - int32_t(po.wlo));
+            const int64_t total = shfl(tp, l), tbase = first, row0 = t * kPjTile, wlo = shfl(tlo, l);
+            const uint32_t wn = uint32_t(shfl(thi, l) - int32_t(wlo));
             first += total;
-            if (total == 0 || !want || po.base >= a.cap) continue;
-            if (total > a.direct) {
-                if (threadIdx.x == 0) {
-                    a.toff[t] = po.base;
-                    a.list[atomicAdd(a.nlist, 1u)] = int32_t(t);
-                }
-                continue;
-            }
+            if (total == 0 || !want || tbase >= a.cap) continue;
+            if (LIST && shfl(int(listed), l)) continue;
+            const uint32_t lim = uint32_t(a.cap - tbase < total ? a.cap - tbase : total);
             K key[kPjIPT];
-            const uint32_t valid = load_left(lk, po.row0, nl, vec, key);
+            const uint32_t valid = load_left(lk, row0, nl, vec, key);
             uint32_t pos[kPjIPT], cnt[kPjIPT];
-            match_tile(rk, po.wlo, wn, s_win, key, valid, pos, cnt);
-            bool single = true;
-            uint32_t hits = 0;
+            if (LIST && wn > kPjWinBytes / sizeof(K)) {
+                // the count has left the rows' positions and offsets
+                const int64_t at = row0 + threadIdx.x * kPjIPT;
 #pragma unroll
-            for (int r = 0; r < kPjIPT; r++) {
-                single = single && cnt[r] <= 1;
-                hits += cnt[r] ? 1 : 0;
-            }
-            if (__syncthreads_and(single)) {
-                // at most one right row each: the matched rows and their right
-                // rows are listed in LDS, consecutive threads write them
-                uint32_t tot;
-                uint32_t q = block_excl_scan<kPjNT>(hits, &tot, s_scan);
+                for (int r = 0; r < kPjIPT; r++) pos[r] = uint32_t(a.rpos[at + r] - int32_t(wlo));
+                uint32_t off = uint32_t(a.roff[at]);
 #pragma unroll
                 for (int r = 0; r < kPjIPT; r++) {
-                    if (cnt[r]) {
-                        s_off[q] = threadIdx.x * kPjIPT + r;
-                        s_pos[q++] = pos[r];
-                    }
-                }
-                __syncthreads();
-                const uint32_t lim = uint32_t(a.cap - po.base < total ? a.cap - po.base : total);
-                const bool staged = wn <= kPjWinBytes / sizeof(K);
-#pragma unroll 4
-                for (uint32_t o = threadIdx.x; o < lim; o += kPjNT) {
-                    const int64_t i = po.row0 + s_off[o], j = po.wlo + s_pos[o];
-                    if (a.out_l) a.out_l[po.base + o] = a.lrows ? a.lrows[i] : int32_t(i);
-                    if (a.out_r) a.out_r[po.base + o] = a.rrows ? a.rrows[j] : int32_t(j);
-                    if (a.out_key)
-                        static_cast<K *>(a.out_key)[po.base + o] = staged ? s_win[s_pos[o]] : rk[j];
+                    const uint32_t end = r + 1 < kPjIPT || threadIdx.x < kPjNT - 1 ? uint32_t(a.roff[at + r + 1]) : uint32_t(total);
+                    cnt[r] = end - off;
+                    off = end;
                 }
             } else {
-                tile_offsets(pos, cnt, s_pos, s_off, s_scan);
-                expand_tile<K>(a, po, s_pos, s_off, 0, total);
+                for (uint32_t i = threadIdx.x; i < wn; i += kPjNT) s_win[i] = rk[wlo + i];
+                __syncthreads();
+                match_rows(static_cast<const K *>(s_win), wn, key, valid, pos, cnt);
+            }
+            uint32_t sum = 0, tot;
+            bool longrun = false;
+#pragma unroll
+            for (int r = 0; r < kPjIPT; r++) {
+                sum += cnt[r];
+                longrun = longrun || cnt[r] > kPjRun;
+            }
+            uint32_t off = block_excl_scan<kPjNT>(sum, &tot, s_scan);
+            bool marks = false;
+            if constexpr (!LIST) marks = __syncthreads_or(longrun);
+            if (!marks) {
+                // the left and right rows of a chunk's pairs are listed in LDS,
+                // consecutive threads write them
+                for (uint32_t o0 = 0; o0 < lim; o0 += kPjChunk) {
+                    uint32_t at = off;
+#pragma unroll
+                    for (int r = 0; r < kPjIPT; r++) {
+                        const uint32_t end = at + cnt[r];
+                        for (uint32_t q = at > o0 ? at : o0; q < end && q < o0 + kPjChunk; q++) {
+                            s_off[q - o0] = uint16_t(threadIdx.x * kPjIPT + r);
+                            s_pos[q - o0] = pos[r] + (q - at);
+                        }
+                        at = end;
+                    }
+                    __syncthreads();
+                    const uint32_t n = lim - o0 < kPjChunk ? lim - o0 : kPjChunk;
+                    const int64_t slot = tbase + o0;
+                    // (one loop for each place of the keys: a choice inside makes the reads flat)
+                    const auto write = [&](const auto &key_of) {
+#pragma unroll 4
+                        for (uint32_t o = threadIdx.x; o < n; o += kPjNT) {
+                            const int64_t i = row0 + s_off[o], j = wlo + s_pos[o];
+                            if (a.out_l) a.out_l[slot + o] = a.lrows ? a.lrows[i] : int32_t(i);
+                            if (a.out_r) a.out_r[slot + o] = a.rrows ? a.rrows[j] : int32_t(j);
+                            if (a.out_key) static_cast<K *>(a.out_key)[slot + o] = key_of(i, s_pos[o]);
+                        }
+                    };
+                    if (LIST && wn > kPjWinBytes / sizeof(K)) write([&](int64_t i, uint32_t) { return lk[i]; });
+                    else write([&](int64_t, uint32_t x) { return s_win[x]; });
+                    if (o0 + kPjChunk < lim) __syncthreads();
+                }
+            }
+            if constexpr (!LIST) if (marks) {
+                // long runs: the first pair of every left row is marked, chunk by chunk
+#pragma unroll
+                for (int r = 0; r < kPjIPT; r++) {
+                    s_pos[threadIdx.x * kPjIPT + r] = uint32_t(wlo) + pos[r] - off;
+                    off += cnt[r];
+                }
+                off -= sum;
+                for (uint32_t o0 = 0; o0 < lim; o0 += kPjChunk) {
+                    reinterpret_cast<uint4 *>(s_off)[threadIdx.x] = uint4{0, 0, 0, 0};
+                    __syncthreads();
+                    uint32_t at = off;
+#pragma unroll
+                    for (int r = 0; r < kPjIPT; r++) {
+                        if (cnt[r] && at + cnt[r] > o0 && at < o0 + kPjChunk)
+                            s_off[at > o0 ? at - o0 : 0] = uint16_t(threadIdx.x * kPjIPT + r);
+                        at += cnt[r];
+                    }
+                    __syncthreads();
+                    fill_marks<kPjChunk>(s_off, s_scan);
+                    __syncthreads();
+                    write_chunk<K, kPjChunk, 4>(a, s_off, s_pos, row0, tbase, o0, int(lim - o0 < kPjChunk ? lim - o0 : kPjChunk));
+                    __syncthreads();
+                }
             }
             __syncthreads();                           // LDS is reused by the next tile
         }
@@ -877,50 +1196,55 @@ __global__ __launch_bounds__(kPjNT, 5) void k_pair_write(PairArgs a) {
     }
 }
 
-// The tiles on the list, their pairs cut into chunks that are dealt to all the
-// workgroups in turn.
+// The chunks on the list, one per workgroup at a time: the rows that a chunk's pairs
+// belong to are found in the offsets that the count has left, and filled in as above.  What
+// bounds it: the round trips to memory of a chunk, one after another (the next chunk's
+// entry is read ahead).
 template <class K>
-__global__ __launch_bounds__(kPjNT) void k_pair_large(PairArgs a) {
-    __shared__ K s_win[kPjWinBytes / sizeof(K)];
-    __shared__ uint32_t s_pos[kPjTile];
-    __shared__ int64_t s_off[kPjTile];
-    __shared__ int64_t s_scan[kPjNW];
-    __shared__ int64_t s_chunk[kPjNT + 1];             // first chunk of each of kPjNT list entries
-    const uint32_t nlist = *a.nlist;
-    if (nlist == 0) return;
+__global__ __launch_bounds__(kPjNT) void k_pair_spread(PairArgs a) {
+    __shared__ uint32_t s_d[kPjTile];
+    __shared__ __attribute__((aligned(16))) uint16_t s_mark[kPjSpread];
+    __shared__ uint32_t s_max[kPjNW];
+    __shared__ int32_t s_rows[2];
+    const uint32_t n = *a.nlist;
     const int64_t nl = count_of(a.d_nl, a.nl);
-    const K *lk = static_cast<const K *>(a.lkey), *rk = static_cast<const K *>(a.rkey);
-    const bool vec = reinterpret_cast<uintptr_t>(lk) % 16 == 0;
-    int64_t carry = 0;                                 // chunks of the entries before
-    for (uint32_t e0 = 0; e0 < nlist; e0 += kPjNT) {
-        const uint32_t e = e0 + threadIdx.x;
-        const int64_t n = e < nlist ? ceil_div(a.tpairs[a.list[e]], kPjChunk) : 0;
-        int64_t tot;
-        const int64_t ex = block_excl_scan<kPjNT>(n, &tot, s_scan);
-        s_chunk[threadIdx.x] = ex;
-        if (threadIdx.x == 0) s_chunk[kPjNT] = tot;
-        __syncthreads();
-        // this workgroup's chunks: those with (carry + c) % gridDim.x == blockIdx.x
-        int64_t c = int64_t(blockIdx.x) - carry % gridDim.x;
-        if (c < 0) c += gridDim.x;
-        for (; c < tot; c += gridDim.x) {
-            int x = 0;                                 // the last entry with s_chunk[x] <= c
+    if (blockIdx.x >= n) return;
+    int2 e = a.list[blockIdx.x];
+    int64_t base = a.toff[e.x], total = ~a.tpairs[e.x];
+    for (uint32_t c = blockIdx.x; c < n; c += gridDim.x) {
+        const int2 ne = a.list[c + gridDim.x < n ? c + gridDim.x : c];
+        const int64_t row0 = int64_t(e.x) * kPjTile, o0 = int64_t(e.y) * kPjSpread;
+        const int rows = int(nl - row0 < kPjTile ? nl - row0 : kPjTile);
+        int64_t o1 = o0 + kPjSpread < total ? o0 + kPjSpread : total;
+        if (base + o1 > a.cap) o1 = a.cap - base;
+        const int64_t *off = a.roff + row0;
 #pragma unroll
-            for (int st = kPjNT / 2; st > 0; st >>= 1) x += s_chunk[x + st] <= c ? st : 0;
-            const int64_t t = a.list[e0 + x];
-            const int64_t o0 = (c - s_chunk[x]) * kPjChunk, total = a.tpairs[t];
-            const PairOut po = {a.toff[t], t * kPjTile, a.win[2 * t]};
-            if (po.base + o0 >= a.cap) continue;       // (the same for the workgroup)
-            K key[kPjIPT];
-            const uint32_t valid = load_left(lk, po.row0, nl, vec, key);
-            uint32_t pos[kPjIPT], cnt[kPjIPT];
-            match_tile(rk, po.wlo, uint32_t(a.win[2 * t + 1] - po.wlo), s_win, key, valid, pos, cnt);
-            tile_offsets(pos, cnt, s_pos, s_off, s_scan);
-            expand_tile<K>(a, po, s_pos, s_off, o0, o0 + kPjChunk < total ? o0 + kPjChunk : total);
-            __syncthreads();
+        for (int q = 0; q < kPjSpread / kPjChunk; q++)
+            reinterpret_cast<uint4 *>(s_mark)[threadIdx.x + q * kPjNT] = uint4{0, 0, 0, 0};
+        // the last row that begins at or before the first pair, and the first past the last one
+        if (wave_id() == 0) {
+            const int64_t x = wave_bound<true>(off, 0, rows, o0, false) - 1;
+            if (lane_id() == 0) s_rows[0] = int32_t(x);
+        } else if (wave_id() == 1) {
+            const int64_t x = wave_bound<false>(off, 0, rows, o1, false);
+            if (lane_id() == 0) s_rows[1] = int32_t(x);
         }
-        carry += tot;
+        const int64_t nbase = a.toff[ne.x], ntotal = ~a.tpairs[ne.x];
         __syncthreads();
+        const int ra = s_rows[0], rb = s_rows[1];
+        for (int r = ra + int(threadIdx.x); r < rb; r += kPjNT) {
+            const int64_t at = off[r], next = r + 1 < rows ? off[r + 1] : total;
+            s_d[r - ra] = uint32_t(a.rpos[row0 + r]) - uint32_t(at);
+            if (next > at && next > o0) s_mark[at > o0 ? at - o0 : 0] = uint16_t(r - ra);
+        }
+        __syncthreads();
+        fill_marks<kPjSpread>(s_mark, s_max);
+        __syncthreads();
+        write_chunk<K, kPjSpread, 8>(a, s_mark, s_d, row0 + ra, base, o0, int(o1 - o0));
+        __syncthreads();
+        e = ne;
+        base = nbase;
+        total = ntotal;
     }
 }
 
@@ -943,8 +1267,9 @@ struct JoinLayout {
     uint64_t *stL, *stR, *stM, *stP;
     // pairs without ranges
     int32_t *win;
-    int64_t *tpairs, *bpairs, *toff;
-    int32_t *list;
+    int64_t *tpairs, *bpairs, *toff, *roff;
+    int32_t *rpos;
+    int2 *list;
     uint32_t *nlist;
     size_t bytes;
 };
@@ -968,9 +1293,13 @@ static JoinLayout join_layout(void *ws, int64_t nl, int64_t nr, int dtype, uint3
         L.win = c.take<int32_t>(2 * nt);
         L.tpairs = c.take<int64_t>(nt);
         L.bpairs = c.take<int64_t>(nt);
-        L.toff = c.take<int64_t>(nt);
-        L.list = c.take<int32_t>(nt);
         L.nlist = c.take<uint32_t>(1);
+        if (cap > 0 && pj_lists(nl, nr, cap, ks)) {
+            L.toff = c.take<int64_t>(nt);
+            L.roff = c.take<int64_t>(nt * kPjTile);
+            L.rpos = c.take<int32_t>(nt * kPjTile);
+            L.list = c.take<int2>(size_t(cap / kPjSpread) + nt);
+        }
         L.bytes = c.bytes();
         return L;
     }
@@ -1056,19 +1385,21 @@ static int join_typed(const tqp_col *lkey, const int32_t *lrows, const int64_t *
         p.toff = L.toff;
         p.list = L.list;
         p.nlist = L.nlist;
-        // A tile has at most `most` pairs, and with a capacity of kPjDirect none of them
-        // writes more than that: then every tile is written at once and the third
-        // launch (4 us of a 10,000-row query's 66) is left out.
-        const int64_t most = (nl < kPjTile ? nl : kPjTile) * nr;
-        p.direct = cap <= kPjDirect && most <= INT32_MAX ? most : kPjDirect;
+        p.roff = L.roff;
+        p.rpos = L.rpos;
         const int64_t nt = ceil_div(nl, kPjTile);
-        TQP_LAUNCH("pair_count", k_pair_count<K>, dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
+        if (pj_long(nl, nr, sizeof(K)))
+            TQP_LAUNCH("pair_count", (k_pair_count<K, true>), dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
+        else
+            TQP_LAUNCH("pair_count", (k_pair_count<K, false>), dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
         if ((rc = check_launch("join pair counts"))) return rc;
-        TQP_LAUNCH("pair_write", k_pair_write<K>, dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
-        if ((rc = check_launch("join pairs"))) return rc;
-        if (!want_pairs || most <= p.direct) return TQP_OK;
-        TQP_LAUNCH("pair_large", k_pair_large<K>, dim3(unsigned(kComputeUnits * 4)), dim3(kPjNT), 0, s, p);
-        return check_launch("join large tiles");
+        if (L.roff || !want_pairs)
+            TQP_LAUNCH("pair_write", (k_pair_write<K, true>), dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
+        else
+            TQP_LAUNCH("pair_write", (k_pair_write<K, false>), dim3(block_grid(nt, d_nl)), dim3(kPjNT), 0, s, p);
+        if ((rc = check_launch("join pairs")) || !L.roff) return rc;
+        TQP_LAUNCH("pair_spread", k_pair_spread<K>, dim3(unsigned(kComputeUnits * 8)), dim3(kPjNT), 0, s, p);
+        return check_launch("join pairs of large tiles");
     }
     rc = fill_u64(L.words, 0, L.nwords, s);
     if (rc) return rc;
