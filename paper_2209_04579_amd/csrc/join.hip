@@ -161,41 +161,43 @@ int rle_i32(const int32_t *keys, int64_t n, int32_t *ukey, int32_t *ustart, int6
     return check_launch("run-length encoding");
 }
 
+// The two sides (0 left, 1 right), the results by side.
 struct MatchArgs {
-    const void *uL;
-    const int32_t *sL;
-    const int64_t *d_nuL;
-    const int64_t *d_nl;     // left row count (device), or null => nl
-    int64_t nl;
-    const void *uR;
-    const int32_t *sR;
-    const int64_t *d_nuR;
-    const int64_t *d_nr;
-    int64_t nr;
-    int64_t *rkey, *rls, *rlc, *rrs, *rrc;   // ranges (workspace), capacity min(nl, nr)
+    const void *uk[2];       // run keys
+    const int32_t *us[2];    // run starts
+    const int64_t *d_nu[2];  // runs
+    const int64_t *d_n[2];   // rows (device), or null => n
+    int64_t n[2];
+    // ranges (workspace), capacity min(n): key, then start and count on each side
+    int64_t *rkey, *rs[2], *rc[2];
     int64_t *off;                            // first pair of each range
-    int64_t *ukey, *uls, *ulc, *urs, *urc;   // optional user copies
+    int64_t *ukey, *uss[2], *usc[2];         // user copies
     int64_t ucap;
     int64_t *d_nranges_ws;
     int64_t *d_nranges_user;
     int64_t *d_count;
     int64_t *tile_first;     // optional: range holding the first pair of each output tile
     int64_t ntiles_out;
-    const int64_t *bounds;   // per match tile: its window [bounds[2t], bounds[2t + 1]) of right runs
+    int64_t *bounds;         // per match tile: its window [bounds[2t], bounds[2t + 1]) of the other side's runs
     uint32_t *ticket;
     uint64_t *status_m;
     uint64_t *status_p;
 };
 
-// The right runs a match tile can meet lie in [lower_bound of its first left
+// The match searches the other side for each run of its first one, so that is the side
+// with fewer runs (both give the same ranges).  50M and 12.5M keys, 31M and 8M runs: 557 us the
+// long way round, 354 this way; 50M keys in 1000 runs against 20M in 20M: 400 and 220 us
+// with both run-length encodings.
+__device__ __forceinline__ int match_first(const MatchArgs &a) { return *a.d_nu[1] < *a.d_nu[0] ? 1 : 0; }
+
+// The other side's runs a match tile can meet lie in [lower_bound of its first
 // key, upper_bound of its last): one thread per tile, all tiles at once, so no
-// tile waits on a search over the whole right side.
+// tile waits on a search over the whole other side.
 template <class K>
-__global__ __launch_bounds__(256) void k_match_bounds(const K *__restrict__ uL,
-                                                      const int64_t *d_nuL, const K *__restrict__ uR,
-                                                      const int64_t *d_nuR, int64_t tile_runs,
-                                                      int64_t cap_tiles, int64_t *bounds) {
-    const int64_t nuL = *d_nuL, nuR = *d_nuR;
+__global__ __launch_bounds__(256) void k_match_bounds(MatchArgs a, int64_t tile_runs, int64_t cap_tiles) {
+    const int f = match_first(a);
+    const K *uL = static_cast<const K *>(a.uk[f]), *uR = static_cast<const K *>(a.uk[1 - f]);
+    const int64_t nuL = *a.d_nu[f], nuR = *a.d_nu[1 - f];
     const int64_t ntiles = ceil_div(nuL, tile_runs);
     for (int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; t < ntiles && t < cap_tiles;
          t += int64_t(gridDim.x) * blockDim.x) {
@@ -215,8 +217,8 @@ __global__ __launch_bounds__(256) void k_match_bounds(const K *__restrict__ uL,
             if (!(k1 < uR[mid])) lo = mid + 1;
             else hi = mid;
         }
-        bounds[2 * t] = wl;
-        bounds[2 * t + 1] = lo;
+        a.bounds[2 * t] = wl;
+        a.bounds[2 * t + 1] = lo;
     }
 }
 
@@ -240,8 +242,8 @@ __device__ __forceinline__ int64_t gallop_lower(P wkeys, int64_t pos, int64_t wn
     return lo;
 }
 
-// Each thread takes IPT consecutive left runs and finds each one's key
-// among the tile's right window (staged in LDS when it fits) by galloping
+// Each thread takes IPT consecutive runs of the first side (called left here) and finds
+// each one's key among the tile's right window (staged in LDS when it fits) by galloping
 // from the previous key's position.  A first sweep counts the matched runs
 // and their pairs; after the two look-backs, a second sweep writes the
 // ranges of the matched runs from the window positions kept in registers.
@@ -253,13 +255,17 @@ __global__ __launch_bounds__(kJoinNT) void k_join_match(MatchArgs a) {
     __shared__ K s_rkeys[kMatchWindow];
     __shared__ int32_t s_scan32[kJoinNT / kWave];
     __shared__ int64_t s_scan64[kJoinNT / kWave];
-    const int64_t nuL = count_of(a.d_nuL, a.nl);
-    const int64_t nuR = count_of(a.d_nuR, a.nr);
-    const int64_t nl = count_of(a.d_nl, a.nl);
-    const int64_t nr = count_of(a.d_nr, a.nr);
+    const int f = match_first(a), o2 = 1 - f;
+    const int64_t nuL = count_of(a.d_nu[f], a.n[f]);
+    const int64_t nuR = count_of(a.d_nu[o2], a.n[o2]);
+    const int64_t nl = count_of(a.d_n[f], a.n[f]);
+    const int64_t nr = count_of(a.d_n[o2], a.n[o2]);
     const int64_t ntiles = ceil_div(nuL, kTileRuns);
-    const K *uL = static_cast<const K *>(a.uL);
-    const K *uR = static_cast<const K *>(a.uR);
+    const K *uL = static_cast<const K *>(a.uk[f]);
+    const K *uR = static_cast<const K *>(a.uk[o2]);
+    const int32_t *sL = a.us[f], *sR = a.us[o2];
+    int64_t *const rls = a.rs[f], *const rlc = a.rc[f], *const rrs = a.rs[o2], *const rrc = a.rc[o2];
+    int64_t *const uls = a.uss[f], *const ulc = a.usc[f], *const urs = a.uss[o2], *const urc = a.usc[o2];
     for (;;) {
     const int64_t tile = take_tile(a.ticket, &s_tile);
     if (tile >= ntiles) {
@@ -297,7 +303,7 @@ __global__ __launch_bounds__(kJoinNT) void k_join_match(MatchArgs a) {
     }
     int32_t st[IPT + 1];
 #pragma unroll
-    for (int r = 0; r <= IPT; r++) st[r] = u0 + r < nuL ? a.sL[u0 + r] : int32_t(nl);
+    for (int r = 0; r <= IPT; r++) st[r] = u0 + r < nuL ? sL[u0 + r] : int32_t(nl);
     __syncthreads();
     uint32_t hit = 0;
     int32_t widx[IPT];
@@ -316,8 +322,8 @@ __global__ __launch_bounds__(kJoinNT) void k_join_match(MatchArgs a) {
                 hit |= 1u << r;
                 widx[r] = int32_t(lo);
                 const int64_t g = w_lo + lo;
-                const int64_t rs = a.sR[g];
-                const int64_t rc = (g + 1 < nuR ? int64_t(a.sR[g + 1]) : nr) - rs;
+                const int64_t rs = sR[g];
+                const int64_t rc = (g + 1 < nuR ? int64_t(sR[g + 1]) : nr) - rs;
                 pairs += int64_t(st[r + 1] - st[r]) * rc;
             }
         }
@@ -343,23 +349,23 @@ __global__ __launch_bounds__(kJoinNT) void k_join_match(MatchArgs a) {
     for (int r = 0; r < IPT; r++) {
         if (!(hit & (1u << r))) continue;
         const int64_t g = w_lo + widx[r];
-        const int64_t rs = a.sR[g];
-        const int64_t rc = (g + 1 < nuR ? int64_t(a.sR[g + 1]) : nr) - rs;
+        const int64_t rs = sR[g];
+        const int64_t rc = (g + 1 < nuR ? int64_t(sR[g + 1]) : nr) - rs;
         const int64_t ls = st[r], lc = int64_t(st[r + 1]) - ls;
         if (a.rkey) {
             a.rkey[q] = int64_t(key[r]);
-            a.rls[q] = ls;
-            a.rlc[q] = lc;
-            a.rrs[q] = rs;
-            a.rrc[q] = rc;
+            rls[q] = ls;
+            rlc[q] = lc;
+            rrs[q] = rs;
+            rrc[q] = rc;
             a.off[q] = o;
         }
         if (a.ukey && q < a.ucap) {
             a.ukey[q] = int64_t(key[r]);
-            a.uls[q] = ls;
-            a.ulc[q] = lc;
-            a.urs[q] = rs;
-            a.urc[q] = rc;
+            uls[q] = ls;
+            ulc[q] = lc;
+            urs[q] = rs;
+            urc[q] = rc;
         }
         const int64_t p = lc * rc;
         if (a.tile_first) {
@@ -1412,40 +1418,28 @@ static int join_typed(const tqp_col *lkey, const int32_t *lrows, const int64_t *
     TQP_LAUNCH("rle", k_rle<K>, dim3(gr), dim3(kRleNT), 0, s, rk, nr, d_nr,
                        static_cast<K *>(L.uR), L.sR, &L.counters[1], tickets + 2, L.stR);
     if ((rc = check_launch("join rle right"))) return rc;
-    // The match searches the other side for each run of its first one, so that is the
-    // shorter side (both give the same ranges).  50M and 12.5M keys, 31M and 8M runs:
-    // 557 us the long way round, 354 this way.
-    const int f = nr < nl ? 1 : 0, o = 1 - f;        // the sides as first and other: 0 left, 1 right
-    const K *uk[2] = {static_cast<const K *>(L.uL), static_cast<const K *>(L.uR)};
-    const int32_t *us[2] = {L.sL, L.sR};
-    const int64_t *const d_len[2] = {d_nl, d_nr};
-    const int64_t len[2] = {nl, nr};
     MatchArgs a = {};
-    a.uL = uk[f];
-    a.sL = us[f];
-    a.d_nuL = &L.counters[f];
-    a.d_nl = d_len[f];
-    a.nl = len[f];
-    a.uR = uk[o];
-    a.sR = us[o];
-    a.d_nuR = &L.counters[o];
-    a.d_nr = d_len[o];
-    a.nr = len[o];
-    a.rkey = L.rng[0];
-    a.rls = L.rng[f ? 3 : 1];
-    a.rlc = L.rng[f ? 4 : 2];
-    a.rrs = L.rng[f ? 1 : 3];
-    a.rrc = L.rng[f ? 2 : 4];
-    a.off = L.off;
-    if (flags & TQP_JOIN_RANGES) {
-        a.ukey = ranges->key;
-        a.uls = f ? ranges->rstart : ranges->lstart;
-        a.ulc = f ? ranges->rcnt : ranges->lcnt;
-        a.urs = f ? ranges->lstart : ranges->rstart;
-        a.urc = f ? ranges->lcnt : ranges->rcnt;
-        a.ucap = range_cap;
-        a.d_nranges_user = d_nranges;
+    const void *const uk[2] = {L.uL, L.uR};
+    const int32_t *const us[2] = {L.sL, L.sR};
+    const int64_t *const d_n[2] = {d_nl, d_nr};
+    int64_t *const uss[2] = {ranges->lstart, ranges->rstart}, *const usc[2] = {ranges->lcnt, ranges->rcnt};
+    for (int k = 0; k < 2; k++) {
+        a.uk[k] = uk[k];
+        a.us[k] = us[k];
+        a.d_nu[k] = &L.counters[k];
+        a.d_n[k] = d_n[k];
+        a.rs[k] = L.rng[1 + 2 * k];
+        a.rc[k] = L.rng[2 + 2 * k];
+        a.uss[k] = uss[k];
+        a.usc[k] = usc[k];
     }
+    a.n[0] = nl;
+    a.n[1] = nr;
+    a.rkey = L.rng[0];
+    a.off = L.off;
+    a.ukey = ranges->key;
+    a.ucap = range_cap;
+    a.d_nranges_user = d_nranges;
     a.d_nranges_ws = &L.counters[2];
     a.d_count = d_count;
     if (want_pairs) {
@@ -1457,16 +1451,16 @@ static int join_typed(const tqp_col *lkey, const int32_t *lrows, const int64_t *
     a.status_m = L.stM;
     a.status_p = L.stP;
     a.bounds = L.bounds;
-    const int ipt = match_ipt(len[f]);
+    const int64_t most = nl < nr ? nl : nr;          // runs of the first side, whichever it is
+    const int ipt = match_ipt(most);
     {
         int64_t g = ceil_div(L.ntiles_match, 256);
         if (g > 1024) g = 1024;
-        TQP_LAUNCH("match_bounds", k_match_bounds<K>, dim3(unsigned(g)), dim3(256), 0, s,
-                   uk[f], &L.counters[f], uk[o], &L.counters[o], int64_t(kJoinNT) * ipt, L.ntiles_match,
-                   L.bounds);
+        TQP_LAUNCH("match_bounds", k_match_bounds<K>, dim3(unsigned(g)), dim3(256), 0, s, a,
+                   int64_t(kJoinNT) * ipt, L.ntiles_match);
         if ((rc = check_launch("join match bounds"))) return rc;
     }
-    const unsigned gm = persistent_grid(ceil_div(len[f] > 0 ? len[f] : 1, int64_t(kJoinNT) * ipt),
+    const unsigned gm = persistent_grid(ceil_div(most > 0 ? most : 1, int64_t(kJoinNT) * ipt),
                                         tune(kTuneMatchPerCu));
     if (ipt == kMatchIPTLarge)
         TQP_LAUNCH("join_match", (k_join_match<K, kMatchIPTLarge>), dim3(gm), dim3(kJoinNT), 0, s, a);
