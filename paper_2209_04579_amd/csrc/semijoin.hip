@@ -8,28 +8,31 @@
 //
 // A dimension side is reduced to a key set: a bitmap over its key range
 // (tqp_keyset_build).  Two kernels then take the fact table.  k_semi_mask streams the
-// key columns and writes one keep bit per row, a kept count per block and, where few
-// are kept, the kept rows' keys; k_semi_write writes the kept rows out.
+// key columns and writes one keep bit per row, a kept count per block and, of a large
+// table, the kept rows' keys where they are few; k_semi_write writes the kept rows out.
+// Where the sets keep many rows of several columns, k_semi_direct does both in one pass.
 //
-// k_semi_mask: a workgroup stages the sets that fit in LDS once.  Each wave then takes
+// k_semi_mask: a workgroup stages the sets that belong in LDS once.  Each wave then takes
 // chunks of 512 rows by itself, 8 consecutive rows per lane: the next chunk's keys are
 // loaded before this one's are tested, and the only barrier is where a block's
-// count is written.  Sets that do not fit are read from memory (they stay in L2) for
-// the rows still alive after the LDS tests.
+// count is written.  The other sets are read from memory (they stay in L2) for the rows
+// still alive after the LDS tests.
 //
 // What bounds it: the read of the key columns (4.7 TB/s with the slabs' writes
 // between them, 5.5 without), and close behind it the instructions per key: so a
 // position is 32-bit for int32 keys, and one past the set is moved to a zero bit
 // beside it instead of tested.
 //
-// The version before this one was a single pass: tiles handed out by tickets, a
-// decoupled look-back for each tile's slots, and rows written straight from
-// registers.  us, before / now, int32 keys, all sets in LDS:
-//   kept of 300M rows, 3 sets   0.05%    0.8%      2%       5%       9%      14%      22%
-//                             877/760  893/865 1100/933 1177/994 1222/1143 1312/1315 1416/1539
-//   60M rows, 1 set 15% kept 168/110, 2 sets 2% 223/139, 4 sets 13% 471/355
-// (int64 keys: 338/306 at 0.3% of 60M rows and 3 sets, 491/533 at 22%: what the second
-// kernel reads again then shows.)
+// us, k_semi_direct's form of 512-thread workgroups for every table / now:
+//   kept, of 300M rows and 3 int32 sets  1% 903/877   5% 1207/999  14% 1326/1310  22% 1433/1292
+//   of 60M rows and 3 int64 sets         1% 356/347   5% 449/398   14% 473/473    22% 512/491
+//   of 3M rows, sets of 1M, 100K, 25 and 1000 positions   1%       22%       60%
+//     1 int32 set                                      30.3/15.6 33.8/19.7 36.4/24.0
+//     3 int32 sets                                     26.6/19.3 31.6/25.6 38.5/31.9
+//     3 int64 sets                                     36.5/25.9 43.7/37.9 48.7/45.9
+// Slower than that form: three or four int64 sets of tables below 200 MB by up to 16% where most rows are
+// kept (four sets: 200K rows, all kept 22.3/25.4; 4M rows, 14% 59.8/67.9), and four of 60M
+// rows, all kept 925/990.
 #include <mutex>
 #include <type_traits>
 
@@ -45,11 +48,21 @@ static_assert(kSjIPT == kFilterIPT && kSjChunk == kWave * kSjIPT, "a lane's keep
 // Words of key sets staged in LDS per 256 threads of workgroup (36 KiB): a
 // 1024-thread workgroup, alone on its compute unit, stages up to 144 KiB.
 constexpr int kSjLdsWordsPer256 = 9216;
+// Every workgroup stages the sets, so a table of few rows reads a large set from L2 instead.
+// us, staged / from L2, of sets of 1M, 100K, 25 and 1000 positions: one int32 set 13.7/12.6 at 1M
+// rows, 15.6/19.8 at 3M; two int64 sets 17.5/15.1 at 400K, 21.2/14.8 at 1M, 27.9/20.5 at 3M; four
+// 27.9/19.3 at 1M, 43.9/35.3 at 3M (at 60% kept 64.5/59.8).  A set of a few words is staged
+// at once: 10K to 200K rows of three int64 sets of 100K, 30K and 10K positions, all kept, 18.0/20.0.
+static bool sj_staged(int64_t n, int nsets, int64_t words) {
+    return words <= 4096 || n >= (nsets == 1 ? 64 : 128) * words;
+}
 // A chunk that keeps at most this many rows leaves their keys, row by row, in
 // its slab of the workspace.  The columns would be read again a 128-byte line per
-// kept row and set: at 0.8% kept of 300M rows, three int32 sets, 202 us
-// against SLAB_AFTER; above a quarter kept every line is used anyway.
+// kept row and set (three int32 sets, 300M rows, without slabs / with: 0.8% kept 926/882 us, 5%
+// 1345/1004, 14% 1587/1317); above a quarter kept every line is used anyway, and
+// columns of at most kSjCached bytes are still in the last-level cache (256 MiB).
 constexpr int kSjSlab = 128;
+constexpr int64_t kSjCached = 200'000'000;
 
 struct SemiArgs {
     const void *key[kSjMaxSets];
@@ -67,6 +80,10 @@ struct SemiArgs {
     uint8_t *keep;                   // one byte per lane
     int32_t *bcnt;
     void *slab;                      // kSjSlab kept rows' keys per chunk (null: none)
+    // where the device chooses (else null): 1, the single pass, or 0, the two kernels
+    int32_t *pick;
+    uint64_t *words;                 // the single pass's ticket, then a look-back status per tile
+    int64_t nwords;
 };
 
 // The keys of a whole chunk of aligned columns, 8 consecutive rows per lane; of the first
@@ -119,14 +136,13 @@ __device__ __forceinline__ uint32_t sj_pos(int64_t v, int64_t lo) {
 // (plus 32 times where word 0 lies) d >> 5 is the word, a shift by d (modulo
 // 32) brings the bit to the top, and a d on either side of the set is moved to
 // a zero bit: six instructions and a read per key.
-template <class K>
-__device__ __forceinline__ uint32_t sj_test_lds(const SemiArgs &a, int s, const uint32_t *sets,
-                                                const K (&v)[kSjIPT]) {
+template <class K, int R>
+__device__ __forceinline__ uint32_t sj_test_lds(const SemiArgs &a, int s, const uint32_t *sets, const K (&v)[R]) {
     const uint32_t off = uint32_t(a.lds_off[s]), len = uint32_t(a.lds_len[s]);
     const uint32_t zero = 32 * (off + len) + 31, least = 32 * off + 31, most = zero + 1;
     uint32_t m = 0;
 #pragma unroll
-    for (int r = kSjIPT - 1; r >= 0; r--) {
+    for (int r = R - 1; r >= 0; r--) {
         uint32_t d = zero - sj_pos(v[r], a.lo[s]);
         d = d < least ? least : d;
         d = d > most ? most : d;
@@ -135,12 +151,11 @@ __device__ __forceinline__ uint32_t sj_test_lds(const SemiArgs &a, int s, const 
     return m;
 }
 // A set of less than 32 positions, its bits in a scalar register.
-template <class K>
-__device__ __forceinline__ uint32_t sj_test_reg(const SemiArgs &a, int s, uint32_t bits,
-                                                const K (&v)[kSjIPT]) {
+template <class K, int R>
+__device__ __forceinline__ uint32_t sj_test_reg(const SemiArgs &a, int s, uint32_t bits, const K (&v)[R]) {
     uint32_t m = 0;
 #pragma unroll
-    for (int r = kSjIPT - 1; r >= 0; r--) {
+    for (int r = R - 1; r >= 0; r--) {
         uint32_t d = ~sj_pos(v[r], a.lo[s]);
         d = d > ~31u ? d : ~31u;
         m = __builtin_amdgcn_alignbit(m, bits << (d & 31), 31);
@@ -149,27 +164,97 @@ __device__ __forceinline__ uint32_t sj_test_reg(const SemiArgs &a, int s, uint32
 }
 
 // A set in memory: only the rows still alive read their word.
-template <class K>
-__device__ __forceinline__ uint32_t sj_test_mem(const SemiArgs &a, int s, const K (&v)[kSjIPT],
-                                                uint32_t alive) {
+template <class K, int R>
+__device__ __forceinline__ uint32_t sj_test_mem(const SemiArgs &a, int s, const K (&v)[R], uint32_t alive) {
     using Pos = std::conditional_t<sizeof(K) == 4, uint32_t, uint64_t>;
     if (a.nbits[s] == 0) return 0;
     const uint32_t *w = a.bits[s];
     const Pos lo = Pos(a.lo[s]), last = Pos(a.nbits[s] - 1);
     const uint32_t sh = sizeof(K) == 4 ? a.sh[s] : 0;
-    uint32_t word[kSjIPT];
+    uint32_t word[R];
 #pragma unroll
-    for (int r = 0; r < kSjIPT; r++) {
+    for (int r = 0; r < R; r++) {
         const Pos idx = Pos(v[r]) - lo;
         const bool in = ((alive >> r) & 1u) && idx <= last;
         word[r] = in ? w[(idx >> 5) + ((uint32_t(idx & 31) + sh) >> 5)] : 0u;
     }
     uint32_t m = 0;
 #pragma unroll
-    for (int r = 0; r < kSjIPT; r++)
+    for (int r = 0; r < R; r++)
         m |= ((word[r] >> ((uint32_t(Pos(v[r]) - lo) + sh) & 31)) & 1u) << r;
     return m;
 }
+
+// Copies the sets that belong in LDS there (see sj_test_lds), the positions below 32 of the smallest ones to
+// small.  COUNT: returns the product of the sets' shares of members, the share of
+// rows kept if keys were spread evenly; 0 if a set is not in LDS.
+template <int NS, bool COUNT>
+__device__ __forceinline__ float sj_stage(const SemiArgs &a, uint32_t *s_sets, uint32_t (&small)[NS]) {
+    __shared__ uint32_t s_pop[NS];
+    if constexpr (COUNT) {
+        if (threadIdx.x < NS) s_pop[threadIdx.x] = 0;
+        __syncthreads();
+    }
+    for (int s = 0; s < NS; s++) {
+        if (a.lds_off[s] < 0) continue;
+        uint32_t *dst = s_sets + a.lds_off[s];
+        const int len = a.lds_len[s];
+        uint32_t pop = 0;
+        for (int i = threadIdx.x; i <= len + 1; i += blockDim.x) {
+            uint32_t x = i > 0 && i <= len ? a.bits[s][len - i] : 0u;
+            if (i == 1 && (a.nbits[s] & 31)) x &= (1u << (a.nbits[s] & 31)) - 1u;
+            dst[i] = x;
+            pop += __popc(x);
+        }
+        if constexpr (COUNT) {
+            pop = wave_sum(pop);
+            if (lane_id() == 0 && pop) atomicAdd(&s_pop[s], pop);
+        }
+    }
+    __syncthreads();
+    float share = 1.0f;
+#pragma unroll
+    for (int s = 0; s < NS; s++) {
+        small[s] = a.lds_off[s] >= 0 && a.nbits[s] < 32 ? __builtin_amdgcn_readfirstlane(s_sets[a.lds_off[s] + 1]) : 0u;
+        if constexpr (COUNT) share *= a.lds_off[s] >= 0 ? float(s_pop[s]) / float(a.nbits[s]) : 0.0f;
+    }
+    return share;
+}
+
+// The rows of R keys that are in every set, of those in alive.
+template <class K, int NS, int R>
+__device__ __forceinline__ uint32_t sj_test(const SemiArgs &a, const uint32_t *s_sets, const uint32_t (&small)[NS],
+                                            const K (&v)[NS][R], uint32_t alive) {
+#pragma unroll
+    for (int s = 0; s < NS; s++) {
+        if (a.lds_off[s] < 0) continue;
+        alive &= a.nbits[s] < 32 ? sj_test_reg(a, s, small[s], v[s]) : sj_test_lds(a, s, s_sets, v[s]);
+    }
+#pragma unroll
+    for (int s = 0; s < NS; s++)
+        if (a.lds_off[s] < 0) alive &= sj_test_mem(a, s, v[s], alive);
+    return alive;
+}
+
+// The two kernels read the kept rows' keys twice, the single pass of k_semi_direct once; but
+// there each tile waits for the counts of those before it.  So the single pass is taken
+// where many rows are kept: where the sets' shares of members multiply to sj_dense, which is
+// the share kept if keys are spread evenly, known before a key is read, and only for columns
+// wide and long enough (above kSjCached) that the second read counts.  us, two kernels /
+// single pass, by share kept:
+//   rows                1%        5%       14%       22%       30%       50%       100%
+//   60M  2 int64     254/345   279/355   340/366   383/382   489/393   545/437   664/540
+//        3 int64     347/438   404/452   479/473   552/494   681/513   764/565   920/736
+//        4 int64     446/532   537/572   668/587   729/621   896/639   990/711  1190/981
+//   300M 2 int32     615/856   691/874   888/907  1041/978 1181/1060 1332/1274 1837/1833
+//        3 int32    883/1081  996/1139 1309/1197 1549/1301 1730/1407 1943/1721 2448/2495
+//        4 int32   1146/1342 1301/1417 1705/1488 2066/1610 2267/1764 2529/2145 3120/3165
+//   8M   4 int64     78/93 (1%), 115/106 (14%), 132/119 (30%), 167/143 (60%)
+// The choice costs 2-4 us, and the single pass 5-7 more where it follows (the sets are staged
+// twice): at 8M rows of 3 int64 sets, 192 MB, it would be 88/95 at 30%, 110/113 at 60%.
+// Two int32 sets gain too little.
+__host__ __device__ constexpr float sj_dense(int nsets) { return nsets == 2 ? 0.22f : 0.12f; }
+__host__ __device__ constexpr bool sj_picks(int key_bytes, int nsets) { return nsets >= (key_bytes == 8 ? 2 : 3); }
 
 // VEC: every key column is 16-byte aligned, and there is a whole chunk of rows at least.
 template <class K, int NS, bool VEC>
@@ -180,22 +265,18 @@ __global__ __launch_bounds__(4 * kSjNT) void k_semi_mask(SemiArgs a) {
     __shared__ uint32_t s_cnt[2][4 * kSjNT / kWave];         // by turn: one may still be read
     const int nw = blockDim.x / kWave;
     const int wave = __builtin_amdgcn_readfirstlane(wave_id());
-    for (int s = 0; s < NS; s++) {
-        if (a.lds_off[s] < 0) continue;
-        uint32_t *dst = s_sets + a.lds_off[s];
-        const int len = a.lds_len[s];
-        for (int i = threadIdx.x; i <= len + 1; i += blockDim.x) {
-            uint32_t x = i > 0 && i <= len ? a.bits[s][len - i] : 0u;
-            if (i == 1 && (a.nbits[s] & 31)) x &= (1u << (a.nbits[s] & 31)) - 1u;
-            dst[i] = x;
+    if (threadIdx.x < 2 * 4 * kSjNT / kWave) (&s_cnt[0][0])[threadIdx.x] = 0;
+    uint32_t small[NS];
+    const float share = sj_stage<NS, sj_picks(sizeof(K), NS)>(a, s_sets, small);
+    if (sj_picks(sizeof(K), NS) && a.pick) {                       // (the same for every workgroup)
+        const bool dense = share >= sj_dense(NS);
+        if (blockIdx.x == 0 && threadIdx.x == 0) *a.pick = dense ? 1 : 0;
+        if (dense) {
+            for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < a.nwords; i += int64_t(gridDim.x) * blockDim.x)
+                a.words[i] = 0;
+            return;
         }
     }
-    if (threadIdx.x < 2 * 4 * kSjNT / kWave) (&s_cnt[0][0])[threadIdx.x] = 0;
-    __syncthreads();
-    uint32_t small[NS];
-#pragma unroll
-    for (int s = 0; s < NS; s++)
-        small[s] = a.lds_off[s] >= 0 && a.nbits[s] < 32 ? __builtin_amdgcn_readfirstlane(s_sets[a.lds_off[s] + 1]) : 0u;
 
     const int ngroups = int((a.nchunks + (1 << a.lg_group) - 1) >> a.lg_group);
     const int last_j = (1 << a.lg_group) / nw - 1;           // a wave takes every nw-th chunk of a group
@@ -228,14 +309,7 @@ __global__ __launch_bounds__(4 * kSjNT) void k_semi_mask(SemiArgs a) {
                 __builtin_amdgcn_s_waitcnt(0x0f70);
             }
         }
-#pragma unroll
-        for (int s = 0; s < NS; s++) {
-            if (a.lds_off[s] < 0) continue;
-            alive &= a.nbits[s] < 32 ? sj_test_reg(a, s, small[s], v[s]) : sj_test_lds(a, s, s_sets, v[s]);
-        }
-#pragma unroll
-        for (int s = 0; s < NS; s++)
-            if (a.lds_off[s] < 0) alive &= sj_test_mem(a, s, v[s], alive);
+        alive = sj_test(a, s_sets, small, v, alive);
         if (chunk < a.nchunks) a.keep[chunk * kWave + lane_id()] = uint8_t(alive);
         const uint32_t upto = wave_incl_scan(uint32_t(__popc(alive)));
         const int kept = __builtin_amdgcn_readlane(int(upto), kWave - 1);
@@ -309,6 +383,7 @@ __global__ __launch_bounds__(kFilterNT) void k_semi_write(SemiArgs a, SemiOut o)
     __shared__ int32_t s_scan[kFilterNT / kWave];
     __shared__ int64_t s_sum[kFilterNT / kWave];
     __shared__ int32_t s_chunk[kFilterMaxSteps * kFilterTile / kSjChunk + 1];   // first list entry
+    if (sj_picks(sizeof(K), NS) && a.pick && *a.pick) return;
     if (o.nblocks == 0 && threadIdx.x == 0) *o.d_count = 0;
     const int steps = o.steps;
     int64_t base = o.d_prev ? *o.d_prev : 0;     // kept rows of the blocks before `from`
@@ -391,6 +466,111 @@ __global__ __launch_bounds__(kFilterNT) void k_semi_write(SemiArgs a, SemiOut o)
     }
 }
 
+// The single pass (see sj_picks): tiles handed out by a ticket, each tile's first slot from a
+// look-back over the counts of the tiles before it, its rows written straight from registers.
+// Bounded by the same reads and writes, then by what a tile waits for: so a tile is as long as
+// the registers hold (three 16-byte loads per thread and set), and a compute unit's threads
+// are one workgroup.
+constexpr int kSjDirectNT = 1024;
+constexpr int kSjDirectSteps = 3;                // 16-byte loads per set
+template <class K> constexpr int64_t sj_direct_tile() { return int64_t(kSjDirectNT) * (16 / sizeof(K)) * kSjDirectSteps; }
+// (a word or status per tile, in place of its keep bits)
+static_assert(sj_direct_tile<int64_t>() >= 8 * 8 * 2, "the words fit the keep bits");
+
+template <class K, int NS>
+__global__ __launch_bounds__(kSjDirectNT) void k_semi_direct(SemiArgs a, SemiOut o, int vec) {
+    constexpr int V = 16 / int(sizeof(K)), Steps = kSjDirectSteps, R = V * Steps;
+    constexpr int64_t Step = int64_t(kSjDirectNT) * V, Tile = Step * Steps;
+    __shared__ int64_t s_tile, s_prefix;
+    __shared__ uint64_t s_scan[kSjDirectNT / kWave];
+    extern __shared__ uint32_t s_sets[];
+    if (a.pick && !*a.pick) return;
+    const int64_t n = a.n, ntiles = ceil_div(n, Tile);
+    const int64_t before = o.d_prev ? *o.d_prev : 0;
+    const int tid = threadIdx.x;
+    uint32_t small[NS];
+    sj_stage<NS, false>(a, s_sets, small);
+    for (;;) {
+        const int64_t tile = take_tile(reinterpret_cast<uint32_t *>(a.words), &s_tile);
+        if (tile >= ntiles) break;
+        // item r = k * V + j of this thread is row trow + k * Step + j
+        const int64_t trow = tile * Tile + int64_t(tid) * V;
+        K v[NS][R];
+        uint32_t alive = (1u << R) - 1u;
+        if (vec && tile * Tile + Tile <= n) {            // (the same for the workgroup)
+#pragma unroll
+            for (int s = 0; s < NS; s++) {
+                const K *p = static_cast<const K *>(a.key[s]) + trow;
+#pragma unroll
+                for (int k = 0; k < Steps; k++) {
+                    const int4 x = *reinterpret_cast<const int4 *>(p + k * Step);
+                    const K *e = reinterpret_cast<const K *>(&x);
+#pragma unroll
+                    for (int j = 0; j < V; j++) v[s][k * V + j] = e[j];
+                }
+            }
+        } else {
+            alive = 0;
+#pragma unroll
+            for (int r = 0; r < R; r++) {
+                const int64_t row = trow + (r / V) * Step + r % V;
+                alive |= (row < n ? 1u : 0u) << r;
+#pragma unroll
+                for (int s = 0; s < NS; s++) v[s][r] = row < n ? static_cast<const K *>(a.key[s])[row] : K(0);
+            }
+        }
+        alive = sj_test(a, s_sets, small, v, alive);
+        // kept rows are ordered by (step, thread, j): per-step counts, 16 bits apiece (a step
+        // keeps at most 4096 rows)
+        static_assert(Steps <= 4 && kSjDirectNT * V < 1 << 16, "packed counts");
+        uint64_t packed = 0, tot;
+#pragma unroll
+        for (int k = 0; k < Steps; k++) packed |= uint64_t(__popc((alive >> (k * V)) & ((1u << V) - 1u))) << (16 * k);
+        const uint64_t ex = block_excl_scan<kSjDirectNT>(packed, &tot, s_scan);
+        int total = 0, first[Steps];                 // the thread's first kept row of each step
+#pragma unroll
+        for (int k = 0; k < Steps; k++) {
+            first[k] = total + int((ex >> (16 * k)) & 0xffff);
+            total += int((tot >> (16 * k)) & 0xffff);
+        }
+        if (wave_id() == 0) {
+            const int64_t pre = lookback_count(a.words + 1, tile, total);
+            if (lane_id() == 0) s_prefix = pre;
+        }
+        __syncthreads();
+        const int64_t base = before + s_prefix;
+        if (tile == ntiles - 1 && tid == 0) {
+            *o.d_count = base + total;
+            if (o.d_next) *o.d_next = base + total;
+        }
+        const auto slot_of = [&](int r) {
+            const uint32_t mk = (alive >> (r / V * V)) & ((1u << V) - 1u);
+            return base + first[r / V] + __popc(mk & ((1u << (r % V)) - 1u));
+        };
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (!((alive >> r) & 1u)) continue;
+            const int64_t slot = slot_of(r);
+            if (o.out_rows) o.out_rows[slot] = o.row0 + int32_t(trow + (r / V) * Step + r % V);
+#pragma unroll
+            for (int s = 0; s < NS; s++)
+                if (o.key_out[s]) static_cast<K *>(o.key_out[s])[slot] = v[s][r];
+        }
+        for (int c = 0; c < o.npay; c++) {
+            const int lg = o.paylg[c];
+            const void *in = o.pin[c];
+            uint64_t w[R];
+#pragma unroll
+            for (int r = 0; r < R; r++)
+                w[r] = (alive >> r) & 1u ? word_of(in, lg, trow + (r / V) * Step + r % V) : 0;
+#pragma unroll
+            for (int r = 0; r < R; r++)
+                if ((alive >> r) & 1u)
+                    sj_store(o.pout[c], lg, slot_of(r), from_word(w[r], in, lg, trow + (r / V) * Step + r % V));
+        }
+    }
+}
+
 // Sets the bit of every key (of the first count) that falls in the set's
 // range [lo, lo + nbits).
 __global__ __launch_bounds__(256) void k_keyset_set(const void *key, int dt, int64_t n,
@@ -406,33 +586,54 @@ __global__ __launch_bounds__(256) void k_keyset_set(const void *key, int dt, int
     }
 }
 
-template <class K, int NS, bool VEC>
-static int launch_semijoin(SemiArgs a, const SemiOut &o, int per_cu, int nt, size_t lds, hipStream_t s) {
-    if (a.n > 0) {
-        if (lds > 65536) {                       // has to be allowed per kernel
-            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_semi_mask<K, NS, VEC>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-            if (e != hipSuccess)
-                return set_error(TQP_EHIP, "tqp_semijoin: LDS of %zu bytes: %s", lds, hipGetErrorString(e));
-        }
-        const unsigned grid = persistent_grid(ceil_div(a.nchunks, int64_t(1) << a.lg_group), per_cu);
-        TQP_LAUNCH("semijoin", (k_semi_mask<K, NS, VEC>), dim3(grid), dim3(unsigned(nt)), lds, s, a);
-        const int rc = check_launch("tqp_semijoin");
-        if (rc) return rc;
-    }
-    TQP_LAUNCH("semijoin_write", (k_semi_write<K, NS>), dim3(block_grid(o.nblocks)), dim3(kFilterNT),
-               size_t(o.steps) * kFilterTile * sizeof(uint16_t), s, a, o);
+struct SemiLaunch {
+    int per_cu, nt;
+    size_t lds;
+    bool vec;                        // the key columns are 16-byte aligned
+};
+
+template <class F> static int sj_allow_lds(F kern, size_t lds) {
+    if (lds <= 65536) return TQP_OK;             // more has to be allowed per kernel
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    return e == hipSuccess ? TQP_OK
+                           : set_error(TQP_EHIP, "tqp_semijoin: LDS of %zu bytes: %s", lds, hipGetErrorString(e));
+}
+
+template <class K, int NS>
+static int launch_semi_direct(const SemiArgs &a, const SemiOut &o, const SemiLaunch &l, hipStream_t s) {
+    int rc = sj_allow_lds(k_semi_direct<K, NS>, l.lds);
+    if (rc) return rc;
+    const unsigned grid = persistent_grid(ceil_div(a.n, sj_direct_tile<K>()), l.lds > 65536 ? 1 : 2);
+    TQP_LAUNCH("semijoin_direct", (k_semi_direct<K, NS>), dim3(grid), dim3(kSjDirectNT), l.lds, s, a, o, l.vec ? 1 : 0);
     return check_launch("tqp_semijoin");
 }
 
+template <class K, int NS, bool VEC>
+static int launch_semijoin(const SemiArgs &a, const SemiOut &o, const SemiLaunch &l, hipStream_t s) {
+    int rc;
+    if (a.n > 0) {
+        if ((rc = sj_allow_lds(k_semi_mask<K, NS, VEC>, l.lds))) return rc;
+        const unsigned grid = persistent_grid(ceil_div(a.nchunks, int64_t(1) << a.lg_group), l.per_cu);
+        TQP_LAUNCH("semijoin", (k_semi_mask<K, NS, VEC>), dim3(grid), dim3(unsigned(l.nt)), l.lds, s, a);
+        if ((rc = check_launch("tqp_semijoin"))) return rc;
+    }
+    TQP_LAUNCH("semijoin_write", (k_semi_write<K, NS>), dim3(block_grid(o.nblocks)), dim3(kFilterNT),
+               size_t(o.steps) * kFilterTile * sizeof(uint16_t), s, a, o);
+    if ((rc = check_launch("tqp_semijoin"))) return rc;
+    if constexpr (sj_picks(sizeof(K), NS)) {
+        if (a.pick) return launch_semi_direct<K, NS>(a, o, l, s);
+    }
+    return TQP_OK;
+}
+
 template <class K, bool VEC>
-static int launch_semijoin(int ns, const SemiArgs &a, const SemiOut &o, int per_cu, int nt, size_t lds,
-                           hipStream_t s) {
+static int launch_semijoin(int ns, const SemiArgs &a, const SemiOut &o, const SemiLaunch &l, hipStream_t s) {
     switch (ns) {
-    case 1: return launch_semijoin<K, 1, VEC>(a, o, per_cu, nt, lds, s);
-    case 2: return launch_semijoin<K, 2, VEC>(a, o, per_cu, nt, lds, s);
-    case 3: return launch_semijoin<K, 3, VEC>(a, o, per_cu, nt, lds, s);
-    default: return launch_semijoin<K, 4, VEC>(a, o, per_cu, nt, lds, s);
+    case 1: return launch_semijoin<K, 1, VEC>(a, o, l, s);
+    case 2: return launch_semijoin<K, 2, VEC>(a, o, l, s);
+    case 3: return launch_semijoin<K, 3, VEC>(a, o, l, s);
+    default: return launch_semijoin<K, 4, VEC>(a, o, l, s);
     }
 }
 
@@ -440,13 +641,15 @@ struct SemiLayout {
     KeepLayout keep;
     void *slab;
     int64_t *d_sum;                  // two, for a table taken in parts
+    int32_t *pick;
     size_t bytes;
 };
 
 static SemiLayout semi_layout(void *ws, int64_t n, int dtype, bool slabs) {
     SemiLayout L = {};
     Carver c(ws);
-    L.d_sum = c.take<int64_t>(2);
+    L.d_sum = c.take<int64_t>(3);
+    L.pick = reinterpret_cast<int32_t *>(L.d_sum ? L.d_sum + 2 : nullptr);
     const size_t bits = keep_layout(nullptr, n).bytes;
     char *at = c.take<char>(bits);
     L.keep = keep_layout(at, n);
@@ -544,7 +747,7 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
             }
         }
         const int64_t words_s = ceil_div(int64_t(a.nbits[s]), 32);
-        if (words_s > 0 && a.sh[s] == 0 && lds_words + words_s <= lds_budget) {
+        if (words_s > 0 && a.sh[s] == 0 && lds_words + words_s <= lds_budget && sj_staged(n, nsets, words_s)) {
             a.lds_off[s] = lds_words;
             a.lds_len[s] = int32_t(words_s);
             lds_words += int(words_s) + 2;       // between two zero words
@@ -591,17 +794,22 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
         a.nchunks = L.keep.nblocks << a.lg_block;
         a.keep = L.keep.keep;
         a.bcnt = L.keep.bcnt;
-        a.slab = L.slab;
+        const bool large = rows * ks * nsets > kSjCached;
+        a.slab = large ? L.slab : nullptr;
         out.steps = L.keep.steps;
         out.nblocks = L.keep.nblocks;
         out.row0 = int32_t(row0);
         out.d_prev = row0 > 0 ? L.d_sum + turn : nullptr;
         out.d_next = row0 + rows < n ? L.d_sum + (turn ^ 1) : nullptr;
-        const size_t lds = size_t(lds_words) * 4;
+        // the single pass leaves the keep bits unwritten: its words take their place
+        a.pick = sj_picks(ks, nsets) && large ? L.pick : nullptr;
+        a.words = reinterpret_cast<uint64_t *>(L.keep.keep);
+        a.nwords = 1 + ceil_div(rows, ks == 4 ? sj_direct_tile<int32_t>() : sj_direct_tile<int64_t>());
+        const SemiLaunch l = {per_cu, kSjNT * wg, size_t(lds_words) * 4, vec};
         const bool whole = sj_whole_chunks(vec, rows);
         const auto run = dt == TQP_INT32 ? (whole ? launch_semijoin<int32_t, true> : launch_semijoin<int32_t, false>)
                                          : (whole ? launch_semijoin<int64_t, true> : launch_semijoin<int64_t, false>);
-        const int rc = run(nsets, a, out, per_cu, kSjNT * wg, lds, s);
+        const int rc = run(nsets, a, out, l, s);
         if (rc || n == 0) return rc;
         row0 += rows;
         for (int k = 0; k < nsets; k++) a.key[k] = static_cast<const char *>(a.key[k]) + rows * ks;
