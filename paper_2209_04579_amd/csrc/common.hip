@@ -256,7 +256,7 @@ struct KnobDef {
 };
 static const KnobDef kKnobs[kTuneCount] = {
     {"filter.per_cu", 4, 1, 8},
-    {"sort.per_cu", 2, 1, 2},
+    {"sort.per_cu", 1, 1, 2},
     {"rle.per_cu", 1, 1, 2},
     {"match.per_cu", 4, 1, 8},
     {"gbscan.per_cu", 2, 1, 4},
@@ -265,7 +265,7 @@ static const KnobDef kKnobs[kTuneCount] = {
     {"semijoin.per_cu", 4, 1, 8},
     {"semijoin.wg", 4, 1, 4},
 };
-static int g_knob[kTuneCount] = {4, 2, 1, 4, 2, 65536, 0, 4, 4};
+static int g_knob[kTuneCount] = {4, 1, 1, 4, 2, 65536, 0, 4, 4};
 
 int tune(TuneKnob k) { return g_knob[k]; }
 

@@ -750,8 +750,11 @@ int run_radix(const K *key_in, int64_t n, const int64_t *d_n, int bits, Ord ord,
 #define TQP_PASS(FILT)                                                                         \
         TQP_LAUNCH("onesweep", (k_onesweep<K, Ord, FILT>), dim3(grid_pass), dim3(kSortNT), 0, s, src_k, dk, \
                    x, n, cn, ord, shift, dbits, counts, csum, dtot, keep_bits, d_kept)
-        // a workgroup per tile of the capacity; fewer of them, each looping,
-        // when the actual count is on the device and may be far smaller
+        // a workgroup per tile of the capacity; at most eight per compute unit and unit of the
+        // knob, each looping, when the actual count is on the device and may be far smaller: a
+        // workgroup without rows still costs its launch.  us at two units / one, capacity 30M,
+        // int32 keys of 20 bits (and with 9 bytes of payload): 3000 rows 50/39 (51/46), 3M 92/80
+        // (115/104), 15M 243/243 (438/438), 30M 508/499 (908/948).
         const int64_t most = int64_t(8) * kComputeUnits * tune(kTuneSortPerCu);
         const unsigned grid_pass = unsigned(cn && turns > most ? most : turns);
         if (filt) TQP_PASS(true);

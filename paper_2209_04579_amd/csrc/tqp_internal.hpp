@@ -55,7 +55,7 @@ constexpr int kComputeUnits = 256;
 // Tuning knobs (set through tqp_tune_set, read at launch time on the host).
 enum TuneKnob {
     kTuneFilterPerCu = 0,   // workgroups per CU of the filter's persistent grid
-    kTuneSortPerCu,         // eighths of the grid per CU of a radix pass whose count is on the device
+    kTuneSortPerCu,         // 8 workgroups per CU and unit of a radix pass whose count is on the device
     kTuneRlePerCu,          // ... of run-length encoding
     kTuneMatchPerCu,        // ... of the join match
     kTuneGbScanPerCu,       // ... of the sorted group-by scan
