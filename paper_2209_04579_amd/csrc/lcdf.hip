@@ -1040,6 +1040,10 @@ constexpr int kWinPhys = kWinCap + kWinCap / 8;
 constexpr int kWinBins = kWinCap;
 constexpr int kWinMaxBin = 16;
 constexpr int kWinBinsPer = kWinBins / kWinNT;
+// Pairs of a thread's successive keys (of 7/8 of the window's keys) that fall in one bin,
+// from which the window is merged without a count: evenly spread keys have 0.5 on average, runs
+// of 30 equal keys 26, and their additions to one cell wait for one another.
+constexpr uint32_t kWinPairs = 8;
 
 // Persistent workgroups over the windows.  The keys of a window are sorted as
 // packed values ((key - min) << 13 | local index), all distinct; that holds a span
@@ -1050,7 +1054,8 @@ constexpr int kWinBinsPer = kWinBins / kWinNT;
 // keys in any order), and a thread then puts the keys of its kWinBinsPer bins in
 // order one by one, usually none to one step each.  A window where some bin has
 // more than kWinMaxBin keys (runs of equal keys, a gap beside a cluster) is merged
-// instead:
+// instead, at once where kWinPairs show it (30M int64 keys, the whole sort: of 4096 values
+// 2023 -> 1880 us, runs of 200 equal keys 1726 -> 1664, of 15 1710 -> 1665; even keys 1312/1317):
 // runs of 8 sorted in registers, then merge levels 8, 16, ... where each
 // thread finds its 8 outputs by a merge-path search (the last run of a level
 // may be short: nothing is padded beyond a multiple of 8).  Ties cannot
@@ -1156,70 +1161,82 @@ __global__ __launch_bounds__(kWinNT) void k_window_sort(K *keys, int32_t *rows,
             uint32_t at[kWinPer];                    // bin << kWinIdxBits | rank
 #pragma unroll
             for (int i = 0; i < kWinBinsPer; i++) cnt[tid + i * kWinNT] = 0;
-            __syncthreads();
+            uint32_t pairs = 0;                      // the wave's neighbours in one bin
 #pragma unroll
             for (int i = 0; i < kWinPer; i++) {
                 const int j = tid + i * kWinNT;
                 const uint32_t d = uint32_t((uint64_t(int64_t(k[i])) - uint64_t(lo)) >> sh);
                 const uint32_t b = fine ? d : __umulhi(d, scale);
                 at[i] = b < uint32_t(kWinBins) ? b : uint32_t(kWinBins - 1);
-                if (j < m) at[i] = at[i] << kWinIdxBits | atomicAdd(&cnt[at[i]], 1u);
+                if (i > 0) pairs += __popcll(__ballot(j < m && at[i] == at[i - 1]));
             }
-            if (lane_id() == 0) s_most[wave_id()] = 0;
+            if (lane_id() == 0) s_most[wave_id()] = pairs;
             __syncthreads();
-            uint32_t c[kWinBinsPer], mine = 0, most = 0;
+            pairs = 0;
 #pragma unroll
-            for (int i = 0; i < kWinBinsPer; i++) {
-                c[i] = cnt[tid * kWinBinsPer + i];
-                mine += c[i];
-                most = c[i] > most ? c[i] : most;
-            }
-            uint32_t all;
-            const uint32_t beg = block_excl_scan<kWinNT>(mine, &all, s_scan);
-            if (most > uint32_t(kWinMaxBin)) s_most[wave_id()] = 1;
-            {
-                uint32_t first = beg;
-#pragma unroll
-                for (int i = 0; i < kWinBinsPer; i++) {
-                    cnt[tid * kWinBinsPer + i] = first;
-                    first += c[i];
-                }
-            }
-            __syncthreads();
-            uint32_t crowded = 0;
-#pragma unroll
-            for (int i = 0; i < kWinNT / kWave; i++) crowded |= s_most[i];
-            spread = crowded == 0;
-            if (spread) {
-                int32_t *srow = reinterpret_cast<int32_t *>(s_b) + kWinBins;
+            for (int i = 0; i < kWinNT / kWave; i++) pairs += s_most[i];
+            if (pairs < kWinPairs) {
 #pragma unroll
                 for (int i = 0; i < kWinPer; i++) {
                     const int j = tid + i * kWinNT;
-                    if (j < m) {
-                        s_a[wphys(int(cnt[at[i] >> kWinIdxBits] + (at[i] & (kWinCap - 1))))] = pack(k[i], j);
-                        srow[j] = rw[i];
+                    if (j < m) at[i] = at[i] << kWinIdxBits | atomicAdd(&cnt[at[i]], 1u);
+                }
+                __syncthreads();
+                if (lane_id() == 0) s_most[wave_id()] = 0;
+                uint32_t c[kWinBinsPer], mine = 0, most = 0;
+#pragma unroll
+                for (int i = 0; i < kWinBinsPer; i++) {
+                    c[i] = cnt[tid * kWinBinsPer + i];
+                    mine += c[i];
+                    most = c[i] > most ? c[i] : most;
+                }
+                uint32_t all;
+                const uint32_t beg = block_excl_scan<kWinNT>(mine, &all, s_scan);
+                if (most > uint32_t(kWinMaxBin)) s_most[wave_id()] = 1;
+                {
+                    uint32_t first = beg;
+#pragma unroll
+                    for (int i = 0; i < kWinBinsPer; i++) {
+                        cnt[tid * kWinBinsPer + i] = first;
+                        first += c[i];
                     }
                 }
                 __syncthreads();
-                // k and rw have been copied out
-                window_load(keys, rows, win, w + gridDim.x, nwin, se, k, rw);
-                loaded = true;
-                const int end = int(beg + mine);
-                uint64_t last = 0;
-                for (int p = int(beg); p < end; p++) {
-                    const uint64_t x = s_a[wphys(p)];
-                    if (x >= last) {
-                        last = x;
-                        continue;
+                uint32_t crowded = 0;
+#pragma unroll
+                for (int i = 0; i < kWinNT / kWave; i++) crowded |= s_most[i];
+                spread = crowded == 0;
+                if (spread) {
+                    int32_t *srow = reinterpret_cast<int32_t *>(s_b) + kWinBins;
+#pragma unroll
+                    for (int i = 0; i < kWinPer; i++) {
+                        const int j = tid + i * kWinNT;
+                        if (j < m) {
+                            s_a[wphys(int(cnt[at[i] >> kWinIdxBits] + (at[i] & (kWinCap - 1))))] = pack(k[i], j);
+                            srow[j] = rw[i];
+                        }
                     }
-                    int q = p;
-                    do {
-                        s_a[wphys(q)] = s_a[wphys(q - 1)];
-                        q--;
-                    } while (q > int(beg) && s_a[wphys(q - 1)] > x);
-                    s_a[wphys(q)] = x;
+                    __syncthreads();
+                    // k and rw have been copied out
+                    window_load(keys, rows, win, w + gridDim.x, nwin, se, k, rw);
+                    loaded = true;
+                    const int end = int(beg + mine);
+                    uint64_t last = 0;
+                    for (int p = int(beg); p < end; p++) {
+                        const uint64_t x = s_a[wphys(p)];
+                        if (x >= last) {
+                            last = x;
+                            continue;
+                        }
+                        int q = p;
+                        do {
+                            s_a[wphys(q)] = s_a[wphys(q - 1)];
+                            q--;
+                        } while (q > int(beg) && s_a[wphys(q - 1)] > x);
+                        s_a[wphys(q)] = x;
+                    }
+                    res = s_a;
                 }
-                res = s_a;
             }
             __syncthreads();
         }
