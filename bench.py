@@ -888,8 +888,7 @@ def bench_batch(args, tqp, stream) -> dict:
     def plan_for(t):
         b.q.tuning = dict(t)
         return b
-    plan_knobs = ("filter.per_cu", "sort.per_cu", "rle.per_cu", "match.per_cu",
-                  "gbscan.per_cu", "sort.mode")
+    plan_knobs = ("sort.per_cu", "gbscan.per_cu")
     key = autotune.cache_key("batch_star", rows, "zipf0-1.5", "int32")
     timings = {}
 

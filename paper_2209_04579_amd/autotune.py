@@ -7,11 +7,11 @@ setting is cached as JSON under a key of (GPU architecture, operation, key
 dtype, log2 of the row count, skew class), so a later plan of the same class
 starts from it without re-tuning (``tune_cached``).
 
-Knobs: every library knob from ``tune_knobs()`` (persistent-grid workgroups
-per CU of the filter, radix passes, run-length encoding, join match and
-sorted group-by; the radix pass mode; the semi-join's workgroup size, which
-is its tile size) and ``gb.dense_max``, the largest group-key domain the
-star query aggregates directly instead of by sort.  ``tune_params`` sweeps a
+Knobs: the library knobs from ``tune_knobs()`` that change a launch (workgroups
+per CU of the filtered sum, radix passes, run-length encoding, join match,
+sorted group-by and semi-join, and the semi-join's workgroup size, which bounds
+the key sets it holds in LDS) and ``gb.dense_max``, the largest group-key domain
+the star query aggregates directly instead of by sort.  ``tune_params`` sweeps a
 plan's own discrete parameters the same way: for the learned partition sort,
 the bucket count (2^bits), the model's leaf count and its training steps.
 """
@@ -26,6 +26,7 @@ import torch
 from . import tune_knobs
 
 DENSE_MAX_CHOICES = (0, 64, 1024)
+NO_EFFECT = ("sort.mode",)      # accepted for saved settings
 
 
 def cache_key(op: str, rows: int, skew: str = "", dtype: str = "") -> str:
@@ -75,11 +76,11 @@ def tune(make_plan, reps: int = 5, rounds: int = 2, include_dense: bool = True,
     """Coordinate descent over the knobs.
 
     make_plan(tuning) -> plan.  Returns (best tuning, best ms, all timings).
-    Knobs with at most 16 settings are swept (grid sizes, the radix pass
-    mode, workgroup sizes), not capacity limits; ``only`` limits the sweep to
-    the knobs of the kernels the plan runs."""
+    Knobs with at most 16 settings are swept (grid sizes, workgroup sizes), not
+    capacity limits; ``only`` limits the sweep to the knobs of the kernels the
+    plan runs."""
     knobs = {k: v for k, v in tune_knobs().items()
-             if v[2] - v[1] <= 16 and (only is None or k in only)}
+             if v[2] - v[1] <= 16 and k not in NO_EFFECT and (only is None or k in only)}
     best = {k: v[0] for k, v in knobs.items()}
     if include_dense:
         best["gb.dense_max"] = 1024
