@@ -120,14 +120,15 @@ void tqp_profile_reset(void);
 
 /* Launch knobs, the control surface of the autotuner (an extension of this
  * library; the paper tunes nothing at this level).  Each knob is an integer in a
- * fixed range with a default: "filter.per_cu", "sort.per_cu", "rle.per_cu",
- * "match.per_cu", "gbscan.per_cu" scale one kernel's grid per compute unit; "part.ovf_cap" is how many overflowing buckets
+ * fixed range with a default: "filter.per_cu" (tqp_filter_sum), "sort.per_cu",
+ * "rle.per_cu", "match.per_cu" and "gbscan.per_cu" scale one kernel's grid per
+ * compute unit; "part.ovf_cap" is how many overflowing buckets
  * tqp_partition_sort re-sorts before it sorts the whole input instead;
  * "sort.mode" is accepted for settings saved earlier and changes nothing
  * (its two ways of finding where a tile's digit runs go are one now);
  * "semijoin.wg" is tqp_semijoin's workgroup size in units of 256 threads
- * (1, 2 or 4) and "semijoin.per_cu"
- * its threads per compute unit in the same units.
+ * (1, 2 or 4), which bounds the key sets held in LDS, and "semijoin.per_cu" its
+ * threads per compute unit in the same units.
  * Knobs change how the work is done, never results.  They are process-wide
  * and read when a call enqueues its kernels; setting them concurrently with
  * calls on other threads is a race.
@@ -344,10 +345,11 @@ int tqp_join(const tqp_col *lkey, const int32_t *lrows, const int64_t *d_nl,
  *   d_count    : required; receives the number of kept rows.
  * Sets are staged in on-chip memory while they fit (up to 36864 words in all
  * with 1024-thread workgroups, a quarter of that per 256 threads with
- * smaller ones); the others are read from device memory.  Workspace:
- * tqp_semijoin_workspace_bytes(n, key dtype), about one key per row (keep
- * bits, and the kept rows' keys where at most a quarter is kept).  Nothing is
- * synchronized.
+ * smaller ones) and the table has rows enough to pay for it; the others are
+ * read from device memory.  Workspace: tqp_semijoin_workspace_bytes(n, key
+ * dtype), about one key per row whatever nsets is (keep bits, and room for a
+ * quarter of the rows' keys of four sets; 2.4 GB for 600M int32 rows).  Nothing
+ * is synchronized.
  * ---------------------------------------------------------------------- */
 #define TQP_KEYSET_MAX_BITS (1ll << 36)
 typedef struct {
@@ -370,10 +372,10 @@ int tqp_semijoin(const tqp_col *keys, const tqp_keyset *sets, int nsets,
  * and errors as tqp_semijoin; the table is taken in parts of 2^25 rows, whose
  * keep bits and counts live in a static 8 MiB device array of the library
  * (one per device, held until the process ends, located on the first call on
- * each device).  It allocates nothing and calls no allocating routine.  Tables of more than
- * tqp_semijoin_noalloc_max_rows(dtype) rows (every int32 table up to
- * 2^31 - 1 rows; about 1.6e9 rows of int64 keys) are rejected with
- * TQP_ECAPACITY.  All calls on one device share the array: calls that
+ * each device).  It allocates nothing and calls no allocating routine.  Tables
+ * of more than tqp_semijoin_noalloc_max_rows(dtype) rows (2^31 - 1 for int32
+ * keys; about 1.6e9 for int64 keys, a limit that the parts do not need any more
+ * and that is kept as it was) are rejected with TQP_ECAPACITY.  All calls on one device share the array: calls that
  * overlap on one device (other streams, other threads) race and must be
  * serialized by the caller.
  * ---------------------------------------------------------------------- */

@@ -15,7 +15,9 @@
 // block scan and the look-back before its writes, and the next tile's loads
 // behind them.  20M int32 rows keeping 57%, row ids and one byte of payload:
 // 92 -> 20 + 45 us.  60M int64 rows keeping one in 84 with 13 bytes of payload
-// (beside another stream's work): 244 -> 112 + 64 us.
+// (beside another stream's work): 244 -> 112 + 64 us.  Slower than that pass: five and
+// more int8 payload columns of which more than two thirds are kept, whose bytes go out one per
+// store (60M rows, eight columns: 55% kept 448/421 us, 70% 469/498, 100% 506/635).
 #include "keepbits.hpp"
 #include "rowtest.hpp"
 

@@ -239,7 +239,8 @@ struct GbOut {
 // difference.  30M sorted int32 keys in 1.5M groups, SUM of an int64 column
 // through row ids and COUNT: 265 + 11 us (scan, differences) -> 23 + 158 + 5 us
 // (heads, runs, edges).  512 threads of 4 rows: with 256 of 8 the rows' terms
-// spill.
+// spill with one sum already.  (Here two sums of columns loaded together spill 2 registers, of
+// int64 keys 5; three 13 and 17; four 32 and 42, and 20 to 23 loaded one by one.)
 template <class K, int NSUM, bool TOG>
 __global__ __launch_bounds__(kGbNT, 4) void k_gb_runs(const K *__restrict__ keys, int64_t n,
                                                       const int64_t *d_n, AggArgs a,

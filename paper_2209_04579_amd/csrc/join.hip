@@ -29,7 +29,6 @@ namespace tqp {
 
 constexpr int kJoinNT = 256;
 constexpr int kJoinIPT = 16;
-constexpr int kJoinTile = kJoinNT * kJoinIPT;
 constexpr int kExpandPer = 8;
 constexpr int kExpandTile = kJoinNT * kExpandPer;   // output pairs per expand tile
 // Consecutive runs of the match's first side per thread: 4 when either side is
@@ -47,34 +46,6 @@ static int match_ipt(int64_t first) {
 constexpr int kMatchWindow = 4096;      // right keys staged in LDS per match tile
 constexpr int kRleNT = 1024;
 constexpr int kRleTile = kRleNT * kJoinIPT;
-
-template <class K>
-__device__ __forceinline__ void load_keys16(const K *p, int64_t row0, int64_t cnt, K (&v)[16]) {
-    if (row0 + 16 <= cnt) {
-        if (sizeof(K) == 4) {
-            const int4 *q = reinterpret_cast<const int4 *>(p + row0);
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                int4 x = q[k];
-                v[4 * k + 0] = K(x.x);
-                v[4 * k + 1] = K(x.y);
-                v[4 * k + 2] = K(x.z);
-                v[4 * k + 3] = K(x.w);
-            }
-        } else {
-            const longlong2 *q = reinterpret_cast<const longlong2 *>(p + row0);
-#pragma unroll
-            for (int k = 0; k < 8; k++) {
-                longlong2 x = q[k];
-                v[2 * k + 0] = K(x.x);
-                v[2 * k + 1] = K(x.y);
-            }
-        }
-    } else {
-#pragma unroll
-        for (int r = 0; r < 16; r++) v[r] = row0 + r < cnt ? p[row0 + r] : K(0);
-    }
-}
 
 // Run heads of a sorted column -> (unique key, run start), count in *d_nu.
 // Tiles of 1024 threads x 16 keys: the keys are only 4-8 bytes each, so a

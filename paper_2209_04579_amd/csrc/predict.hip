@@ -232,7 +232,8 @@ TQP_API int tqp_mlp_predict(const tqp_col *feats, int nfeat, const int32_t *rows
             return set_error(TQP_EINVAL, "tqp_mlp_predict: feature %d is invalid or unaligned", k);
         if (!rows && feats[k].len < n)
             return set_error(TQP_EINVAL, "tqp_mlp_predict: feature %d is shorter than n", k);
-        a.feat[k] = feats[k].len > 0 ? feats[k].data : model;   // never read when empty
+        // (a stand-in for an empty column: k_mlp_predict2 reads its first element and takes 0 instead)
+        a.feat[k] = feats[k].len > 0 ? feats[k].data : model;
         a.flen[k] = feats[k].len;
         a.fdt[k] = feats[k].dtype;
     }

@@ -297,7 +297,7 @@ __device__ __forceinline__ void flush_stage(const void *s_stage, const uint32_t 
 // What bounds it: on wide rows the traffic itself (each column read and
 // written once, the writes in runs of about 4096 / bins items); on narrow ones
 // the phases between barriers.  So the kernel is kept to 64
-// registers and 42 KiB of LDS, and two workgroups of 16 waves (all a CU can
+// registers (2 of them in scratch, 6 with int64 keys and a filter) and 42 KiB of LDS, and two workgroups of 16 waves (all a CU can
 // hold) share a CU: one's waits are the other's work.  (512 threads of 8 items
 // take 100 to 128 registers, so half the waves.)  10M rows of 21 bytes: 139 -> 100
 // us (4.2 TB/s); 30M of them: 312 -> 268 (4.7); the filtered first pass of 60M,

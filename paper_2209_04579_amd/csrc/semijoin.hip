@@ -30,9 +30,10 @@
 //     1 int32 set                                      30.3/15.6 33.8/19.7 36.4/24.0
 //     3 int32 sets                                     26.6/19.3 31.6/25.6 38.5/31.9
 //     3 int64 sets                                     36.5/25.9 43.7/37.9 48.7/45.9
-// Slower than that form: three or four int64 sets of tables below 200 MB by up to 16% where most rows are
-// kept (four sets: 200K rows, all kept 22.3/25.4; 4M rows, 14% 59.8/67.9), and four of 60M
-// rows, all kept 925/990.
+// Slower than that form: three or four int64 sets of tables below 200 MB by up to 16%
+// where most rows are kept (four sets: 200K rows, all kept 22.3/25.4; 4M rows, 14%
+// 59.8/67.9), four of 60M rows, all kept 925/990, and tables taken in parts by up to 5%
+// (300M rows, three int32 sets, 0.2% kept 988/1043).
 #include <mutex>
 #include <type_traits>
 
@@ -185,8 +186,8 @@ __device__ __forceinline__ uint32_t sj_test_mem(const SemiArgs &a, int s, const 
     return m;
 }
 
-// Copies the sets that belong in LDS there (see sj_test_lds), the positions below 32 of the smallest ones to
-// small.  COUNT: returns the product of the sets' shares of members, the share of
+// Copies the sets that belong in LDS there (see sj_test_lds), those of less than 32
+// positions also to small.  COUNT: returns the product of the sets' shares of members, the share of
 // rows kept if keys were spread evenly; 0 if a set is not in LDS.
 template <int NS, bool COUNT>
 __device__ __forceinline__ float sj_stage(const SemiArgs &a, uint32_t *s_sets, uint32_t (&small)[NS]) {
@@ -689,8 +690,8 @@ TQP_API size_t tqp_semijoin_workspace_bytes(int64_t n, int dtype) {
     return semi_layout(nullptr, n < 0 ? 0 : n, dtype, true).bytes;
 }
 
-// Validates the arguments and runs both kernels, over the whole table with slabs or,
-// with `part` rows > 0, over parts of that many rows one after another without.
+// Validates the arguments and runs the kernels, over the whole table with slabs (if it is
+// large) or, with `part` rows > 0, over parts of that many rows one after another without.
 static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *sets, int nsets,
                         const tqp_col *keys_out, const tqp_col *pay_in, const tqp_col *pay_out,
                         int npay, int32_t *out_rows, int64_t *d_count, void *ws, size_t ws_bytes,
@@ -838,7 +839,9 @@ TQP_API int tqp_semijoin(const tqp_col *keys, const tqp_keyset *sets, int nsets,
 // the process ends.
 constexpr size_t kSjScratchBytes = size_t(8) << 20;
 static_assert(size_t(kSjPartRows) / 8 < kSjScratchBytes, "a part's keep bits");
-// the longest table with int64 keys (of int32: any)
+// The longest table with int64 keys that is accepted (of int32: any).  The parts would
+// take more; the limit of an earlier layout of the scratch is kept, for callers that rely on
+// what is refused.
 constexpr int64_t kSjMaxRows64 = ((int64_t(1) << 20) - 4) * 1536;
 static __device__ __align__(256) uint64_t scratch[kSjScratchBytes / 8];
 constexpr int kSjMaxDevices = 64;

@@ -1,7 +1,7 @@
 // Internal helpers shared by the libtqp translation units: error reporting,
-// launch checks, wave64 primitives and the decoupled look-back used by every
-// single-pass scan (filter compaction, run-length encoding, join offsets,
-// group-by prefix sums, radix scatter).
+// launch checks, wave64 primitives and the decoupled look-back of the single-pass
+// scans (run-length encoding, the join's matched ranges, the semi-join that keeps
+// many rows).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -46,15 +46,15 @@ struct Carver {
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Grid of a persistent tile loop: at most `per_cu` workgroups per compute
-// unit, never more than there are tiles.  Every tile id comes from one
-// device-wide ticket counter, whose atomic serializes (about 11 ns per ticket
-// on MI355X), so a grid of idle workgroups is not free: size it to the
-// machine, not to the capacity.
+// unit, never more than there are tiles.  A workgroup without a tile is not free:
+// size the grid to the machine, not to the capacity.  Where tiles are dealt by one
+// device-wide ticket counter (the look-back scans), it also takes a ticket, and the
+// counter's atomic serializes (about 11 ns each on MI355X).
 constexpr int kComputeUnits = 256;
 
 // Tuning knobs (set through tqp_tune_set, read at launch time on the host).
 enum TuneKnob {
-    kTuneFilterPerCu = 0,   // workgroups per CU of the filter's persistent grid
+    kTuneFilterPerCu = 0,   // pairs of workgroups per CU of filter_sum's grid
     kTuneSortPerCu,         // 8 workgroups per CU and unit of a radix pass whose count is on the device
     kTuneRlePerCu,          // ... of run-length encoding
     kTuneMatchPerCu,        // ... of the join match
@@ -113,13 +113,6 @@ size_t rle_words(int64_t n);
 int rle_i32(const int32_t *keys, int64_t n, int32_t *ukey, int32_t *ustart, int64_t *d_nu,
             uint64_t *words, hipStream_t s);
 int fill_u32(void *dst, uint32_t value, int64_t count, hipStream_t s);
-// Zeroes the head words before dst, then nsec sections (section k at dst +
-// k * stride words), each over its first ceil(count / per) * width words
-// with count = min(*d_n, n) read on the device (d_n NULL: count = n).  One
-// launch for both.
-int clear_sections(uint32_t *dst, int64_t head, int nsec, int64_t stride, const int64_t *d_n,
-                   int64_t n, int64_t per, int64_t width, hipStream_t s);
-
 // Device-side min / max of a key column over min(*d_n, n) entries, written to
 // out[0] = min, out[1] = max (int64).
 int launch_minmax(const void *key, int dtype, int64_t n, const int64_t *d_n,
@@ -252,14 +245,8 @@ __device__ __forceinline__ T block_excl_scan(T v, T *total, T *lds) {
 
 // ---- agent-scope atomics ------------------------------------------------
 
-template <class T> __device__ __forceinline__ T ld_acquire(const T *p) {
-    return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT);
-}
 template <class T> __device__ __forceinline__ T ld_relaxed(const T *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <class T> __device__ __forceinline__ void st_release(T *p, T v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <class T> __device__ __forceinline__ void st_relaxed(T *p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -377,18 +364,6 @@ __device__ __forceinline__ void store_any(void *p, int dtype, int64_t i, int64_t
     case TQP_INT8: static_cast<int8_t *>(p)[i] = static_cast<int8_t>(v); break;
     case TQP_INT32: static_cast<int32_t *>(p)[i] = static_cast<int32_t>(v); break;
     default: static_cast<int64_t *>(p)[i] = v; break;
-    }
-}
-
-// `v op lit` for a tqp_cmp code, compared as mathematical integers.
-__device__ __forceinline__ bool cmp_holds(int64_t v, int op, int64_t lit) {
-    switch (op) {
-    case TQP_LT: return v < lit;
-    case TQP_LE: return v <= lit;
-    case TQP_GT: return v > lit;
-    case TQP_GE: return v >= lit;
-    case TQP_EQ: return v == lit;
-    default: return v != lit;
     }
 }
 
