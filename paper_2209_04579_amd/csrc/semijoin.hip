@@ -30,9 +30,8 @@
 //     1 int32 set                                      30.3/15.6 33.8/19.7 36.4/24.0
 //     3 int32 sets                                     26.6/19.3 31.6/25.6 38.5/31.9
 //     3 int64 sets                                     36.5/25.9 43.7/37.9 48.7/45.9
-// Slower than that form: three or four int64 sets of tables below 200 MB by up to 16%
-// where most rows are kept (four sets: 200K rows, all kept 22.3/25.4; 4M rows, 14%
-// 59.8/67.9), four of 60M rows, all kept 925/990, and tables taken in parts by up to 5%
+// Slower than that form: four int64 sets of 3M to 6M rows by up to 12% where many rows are
+// kept (4M rows, 14% 59.8/67.9), and of 60M rows with all kept 925/990, and tables taken in parts by up to 5%
 // (300M rows, three int32 sets, 0.2% kept 988/1043).
 #include <mutex>
 #include <type_traits>
@@ -53,7 +52,8 @@ constexpr int kSjLdsWordsPer256 = 9216;
 // us, staged / from L2, of sets of 1M, 100K, 25 and 1000 positions: one int32 set 13.7/12.6 at 1M
 // rows, 15.6/19.8 at 3M; two int64 sets 17.5/15.1 at 400K, 21.2/14.8 at 1M, 27.9/20.5 at 3M; four
 // 27.9/19.3 at 1M, 43.9/35.3 at 3M (at 60% kept 64.5/59.8).  A set of a few words is staged
-// at once: 10K to 200K rows of three int64 sets of 100K, 30K and 10K positions, all kept, 18.0/20.0.
+// at once: 10K to 200K rows of three int64 sets of 100K, 30K and 10K positions, all kept, 18.0/20.0
+// (all with workgroups of 1024).
 static bool sj_staged(int64_t n, int nsets, int64_t words) {
     return words <= 4096 || n >= (nsets == 1 ? 64 : 128) * words;
 }
@@ -781,14 +781,20 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
     hipStream_t s = as_stream(stream);
     out.out_rows = out_rows;
     out.d_count = d_count;
-    // workgroups per CU count 256-thread units: a 1024-thread workgroup takes four
-    const int per_cu = tune(kTuneSemiPerCu) / wg > 0 ? tune(kTuneSemiPerCu) / wg : 1;
-    const int ks = dtype_size(dt), nw = kSjNT * wg / kWave;
+    const int ks = dtype_size(dt);
     int64_t row0 = 0;
     for (int turn = 0; row0 < n || row0 == 0; turn ^= 1) {
         const int64_t rows = sj_part_rows(n, row0, most);
         const SemiLayout L = semi_layout(ws, rows, dt, part == 0);
         a.n = rows;
+        // smaller workgroups where larger ones would leave compute units without one and
+        // the sets leave room (100K rows of four int64 columns, 60% kept: 21.6 -> 17.5 us)
+        int units = wg;                          // 256-thread units per workgroup
+        while (units > 1 && rows < int64_t(kComputeUnits) * kSjChunk * (kSjNT / kWave) * units &&
+               lds_words <= kSjLdsWordsPer256 * (units / 2))
+            units /= 2;
+        const int nw = kSjNT * units / kWave;
+        const int per_cu = tune(kTuneSemiPerCu) / units > 0 ? tune(kTuneSemiPerCu) / units : 1;
         const int per_block = L.keep.steps * kFilterTile / kSjChunk;        // powers of two
         a.lg_block = __builtin_ctz(per_block);
         a.lg_group = __builtin_ctz(per_block > nw ? per_block : nw);
@@ -806,7 +812,7 @@ static int semijoin_run(const char *who, const tqp_col *keys, const tqp_keyset *
         a.pick = sj_picks(ks, nsets) && large ? L.pick : nullptr;
         a.words = reinterpret_cast<uint64_t *>(L.keep.keep);
         a.nwords = 1 + ceil_div(rows, ks == 4 ? sj_direct_tile<int32_t>() : sj_direct_tile<int64_t>());
-        const SemiLaunch l = {per_cu, kSjNT * wg, size_t(lds_words) * 4, vec};
+        const SemiLaunch l = {per_cu, kSjNT * units, size_t(lds_words) * 4, vec};
         const bool whole = sj_whole_chunks(vec, rows);
         const auto run = dt == TQP_INT32 ? (whole ? launch_semijoin<int32_t, true> : launch_semijoin<int32_t, false>)
                                          : (whole ? launch_semijoin<int64_t, true> : launch_semijoin<int64_t, false>);
