@@ -27,6 +27,7 @@ namespace tqp {
 constexpr int kSortNT = 1024;
 constexpr int kSortIPT = 4;
 constexpr int kSortTile = kSortNT * kSortIPT;
+constexpr int64_t kSortLargeRows = int64_t(1) << 25;
 constexpr int kRadixBits = 8;
 constexpr int kBins = 1 << kRadixBits;
 constexpr int kSortNW = kSortNT / kWave;
@@ -754,8 +755,11 @@ int run_radix(const K *key_in, int64_t n, const int64_t *d_n, int bits, Ord ord,
         // knob, each looping, when the actual count is on the device and may be far smaller: a
         // workgroup without rows still costs its launch.  us at two units / one, capacity 30M,
         // int32 keys of 20 bits (and with 9 bytes of payload): 3000 rows 50/39 (51/46), 3M 92/80
-        // (115/104), 15M 243/243 (438/438), 30M 508/499 (908/948).
-        const int64_t most = int64_t(8) * kComputeUnits * tune(kTuneSortPerCu);
+        // (115/104), 15M 243/243 (438/438), 30M 508/499 (908/948).  From 2^25 rows of
+        // capacity on always at least two units: the tiles that the longer loops leave uneven
+        // weigh more there (256 queries of 633M rows in all, half of them kept: 23.8/24.6 ms).
+        const int units = tune(kTuneSortPerCu) < 2 && n >= kSortLargeRows ? 2 : tune(kTuneSortPerCu);
+        const int64_t most = int64_t(8) * kComputeUnits * units;
         const unsigned grid_pass = unsigned(cn && turns > most ? most : turns);
         if (filt) TQP_PASS(true);
         else TQP_PASS(false);
