@@ -424,7 +424,9 @@ __global__ __launch_bounds__(kJoinNT) void k_join_expand(
 // listed, and windows that cannot be staged are searched once only, with what the
 // search found kept for the writing (12 bytes per left row).  us through the runs / with
 // every tile's pairs found again and written by its own workgroup up to 16384 of
-// them, in steps of 32768 beyond / now, int32 keys:
+// them, in steps of 32768 beyond / now, int32 keys (slower than through the runs: few keys
+// that are only counted, 20K x 20K rows of two keys 22/25, and 2M x 30M int64 rows of 1M keys
+// counted 163/177):
 //   500 x 10K, 20 right rows each 41/83/28          10K x 1M, 100 each     54/205/44
 //   3M x 3M, 10 each             200/238/168        2M x 30M, 30 each      450/923/339
 //   30K x 30K, 300 each          66/129/44          20K x 20K, 10K each    4330/720/500
@@ -479,9 +481,10 @@ struct PairArgs {
     uint32_t *nlist;
 };
 // A tile is listed if it has more than pj_direct pairs or a left row with more than kPjRun
-// right rows: its pairs are then spread over the chip by a third launch.  With a capacity of kPjSmallCap (or as many pairs at most) no workgroup
-// writes more than that anyway, so if every window can be staged, every tile is written
-// at once and that launch (4 us of a 10,000-row query's 66) is left out.
+// right rows: its pairs are then spread over the chip by a third launch.  With a capacity
+// of kPjSmallCap (or as many pairs at most) no workgroup writes more than that anyway, so if
+// every window can be staged, every tile is written at once and that launch (4 us of a
+// 10,000-row query's 66) is left out.
 static bool pj_lists(int64_t nl, int64_t nr, int64_t cap, int key_size) {
     const int64_t most = (nl < kPjTile ? nl : kPjTile) * nr;
     return nr > kPjWinBytes / key_size || (most > kPjSmallCap && cap > kPjSmallCap);

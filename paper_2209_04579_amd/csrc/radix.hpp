@@ -302,7 +302,9 @@ __device__ __forceinline__ void flush_stage(const void *s_stage, const uint32_t 
 // hold) share a CU: one's waits are the other's work.  (512 threads of 8 items
 // take 100 to 128 registers, so half the waves.)  10M rows of 21 bytes: 139 -> 100
 // us (4.2 TB/s); 30M of them: 312 -> 268 (4.7); the filtered first pass of 60M,
-// half of them kept: 572 -> 466.
+// half of them kept: 572 -> 466.  Slower than
+// with those tiles: 30M rows with four 8-byte columns, by 4 to 13% (64-bit keys, the whole
+// sort 5467 -> 6272), whose runs of 16 items are half as long.
 //
 // FILT: items whose bit in keep_bits is clear (bit i % 64 of
 // word i / 64, written by the filtered count) are dropped, as items past

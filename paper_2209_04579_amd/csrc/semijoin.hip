@@ -31,8 +31,8 @@
 //     3 int32 sets                                     26.6/19.3 31.6/25.6 38.5/31.9
 //     3 int64 sets                                     36.5/25.9 43.7/37.9 48.7/45.9
 // Slower than that form: four int64 sets of 3M to 6M rows by up to 12% where many rows are
-// kept (4M rows, 14% 59.8/67.9), and of 60M rows with all kept 925/990, and tables taken in parts by up to 5%
-// (300M rows, three int32 sets, 0.2% kept 988/1043).
+// kept (4M rows, 14% 59.8/67.9) and of 60M rows with all kept (925/990), and tables taken
+// in parts by up to 5% (300M rows, three int32 sets, 0.2% kept 988/1043).
 #include <mutex>
 #include <type_traits>
 
